@@ -455,153 +455,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// dK or dV (template flag), the two-launch form kept for head dim 32 (whose 32-row tiles are too small to
-// split over four loading waves in attn_bwd_dkdv_kernel).  Workgroup = 4 waves = 128 keys of one (batch,
-// kv head); wave = 32 keys.  Streams the Q and dO tiles (64 query rows) of every query head of the group,
-// from the last query tile back to the diagonal: dV takes the S and dV^T products, dK the S, dP and dK^T
-// products.
-// ------------------------------------------------------------------------------------------
-template <int DH, bool WANT_DV>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
-    const bf16_t* __restrict__ d_o, const float* __restrict__ lse2, const float* __restrict__ delta,
-    bf16_t* __restrict__ dout, int B, int S, int Hq, int Hkv, float scale, const float* __restrict__ rope_cos,
-    const float* __restrict__ rope_sin, int rope_layout) {
-  using Tile = RowTile<64, DH, 4>;
-  constexpr int STAGE = 2 * Tile::BYTES + 512;  // Q tile, dO tile, lse[64], delta[64]
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int kt, pair;   // low key tiles have the most query tiles: first
-  split_block_id((int)blockIdx.x, B * Hkv, kt, pair);
-  const int G = Hq / Hkv, b = pair / Hkv, hk = pair % Hkv;
-  const int kv0 = kt * 128, kvw = kv0 + wave * 32;
-  const int lk = lane & 31, half = lane >> 5;
-  const int64_t ldq = (int64_t)Hq * DH, ldk = (int64_t)Hkv * DH;
-  const float scale_log2 = scale * kLog2e;
-
-  bf16x8 kf[DH / 16], vf[WANT_DV ? 1 : DH / 16];
-  {
-    const int64_t off = ((int64_t)b * S + kvw + lk) * ldk + (int64_t)hk * DH + half * 8;
-#pragma unroll
-    for (int kk = 0; kk < DH / 16; ++kk) {
-      kf[kk] = *reinterpret_cast<const bf16x8*>(k + off + kk * 16);
-      if constexpr (!WANT_DV) vf[kk] = *reinterpret_cast<const bf16x8*>(v + off + kk * 16);
-    }
-  }
-  f32x16 acc[DH / 32];
-#pragma unroll
-  for (int t = 0; t < DH / 32; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-
-  const int first_qt = kv0 / 64, nq = S / 64 - first_qt, niter = G * nq;
-  const uint32_t q_bytes = (uint32_t)((((int64_t)S - 1) * ldq + DH) * 2);
-  // (query tile, head) of the tile to load next and of the tile being processed, advanced without
-  // divisions.  Every workgroup walks the query tiles from the LAST one down to its diagonal, all G
-  // heads of a tile in turn: workgroups of one pair that start together then read the same Q/dO
-  // tile at the same time, whatever their key tile, and share it in the L2.
-  int ld_g = 0, ld_qt = S / 64 - 1, cur_g = 0, cur_qt = S / 64 - 1;
-  auto issue_tile = [&](int stage) {
-    const int h = hk * G + ld_g, qrow = ld_qt * 64;
-    if (++ld_g == G) { ld_g = 0; --ld_qt; }
-    const int64_t base = ((int64_t)b * S) * ldq + (int64_t)h * DH;
-    const uint32_t skip = (uint32_t)((int64_t)qrow * ldq * 2);
-    char* st = smem + stage * STAGE;
-    Tile::issue(attn_rsrc(q + base + (int64_t)qrow * ldq, q_bytes - skip), st, wave, lane, ldq);
-    Tile::issue(attn_rsrc(d_o + base + (int64_t)qrow * ldq, q_bytes - skip), st + Tile::BYTES, wave, lane, ldq);
-    // the 64 lse2 (and delta) values of the tile take the same asynchronous global -> LDS path, 4 bytes
-    // per lane: a register round trip here would make the wave wait for the tile loads as well
-    const int64_t sidx = ((int64_t)b * Hq + h) * S + qrow;
-    if (wave == 0)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(attn_rsrc(lse2 + sidx, 256), (LDS_PTR(void))(st + 2 * Tile::BYTES), 4,
-                                               (uint32_t)lane * 4, 0, 0, 0);
-    if (!WANT_DV && wave == 1)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(attn_rsrc(delta + sidx, 256), (LDS_PTR(void))(st + 2 * Tile::BYTES + 256),
-                                               4, (uint32_t)lane * 4, 0, 0, 0);
-  };
-  issue_tile(0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  int stage = 0;
-  for (int it = 0; it < niter; ++it) {
-    if (it + 1 < niter) issue_tile(stage ^ 1);
-    const int qrow = cur_qt * 64;
-    if (++cur_g == G) { cur_g = 0; --cur_qt; }
-    const char* tq = smem + stage * STAGE;
-    const char* tdo = tq + Tile::BYTES;
-    const float* stat = reinterpret_cast<const float*>(tq + 2 * Tile::BYTES);
-    // queries before the key are masked: P = 0 for query rows below  kvw + lk - qrow
-    const bool diag = qrow < kvw + 31;
-#pragma unroll
-    for (int qs = 0; qs < 2; ++qs) {
-      // S[q][kv] (and dP[q][kv]) for 32 queries: lane owns key kvw + lk, queries along registers
-      f32x16 s, dp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-      if constexpr (!WANT_DV) {
-        // dP - delta comes out of the product itself: the dP accumulator starts from -delta of its query rows
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(stat + 64 + qs * 32 + g * 8 + half * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dp[g * 4 + e] = d4[e];
-        }
-      }
-#pragma unroll
-      for (int kk = 0; kk < DH / 16; ++kk) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(tq, qs * 32, kk, lane), kf[kk], s, 0, 0, 0);
-        if constexpr (!WANT_DV)
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(tdo, qs * 32, kk, lane), vf[kk], dp, 0, 0, 0);
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int ql = qs * 32 + g * 8 + half * 4;
-        const f32x4 l4 = *reinterpret_cast<const f32x4*>(stat + ql);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = g * 4 + e;
-          const float pv = fast_exp2(__builtin_fmaf(s[r], scale_log2, -l4[e]));
-          if constexpr (WANT_DV) s[r] = pv; else s[r] = pv * dp[r];   // P or dS = P (dP - delta)
-        }
-      }
-      if (diag) {
-        asm volatile("" ::: "memory");
-        const int first_ok = kvw + lk - qrow - (half << 2);   // smallest unmasked row offset for this lane
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (qs * 32 + ((r >> 2) << 3) + (r & 3) < first_ok) s[r] = 0.f;
-      }
-      // dV^T[d][kv] += dO^T[d][q] P[q][kv]   or   dK^T[d][kv] += Q^T[d][q] dS[q][kv]
-      const char* tsrc = WANT_DV ? tdo : tq;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8 pf = pack_slots(s, ks * 8);
-#pragma unroll
-        for (int t2 = 0; t2 < DH / 32; ++t2)
-          acc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_cols(tsrc, t2 * 32, qs * 32 + ks * 16, lane), pf, acc[t2], 0, 0, 0);
-      }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    stage ^= 1;
-  }
-  const float oscale = WANT_DV ? 1.0f : scale;
-  if constexpr (!WANT_DV) {
-    if (rope_cos) rope_unrotate<DH>(acc, rope_cos + (int64_t)(kvw + lk) * (DH / 2), rope_sin + (int64_t)(kvw + lk) * (DH / 2), rope_layout, half);
-  }
-  const int64_t off = ((int64_t)b * S + kvw + lk) * ldk + (int64_t)hk * DH + half * 4;
-#pragma unroll
-  for (int t2 = 0; t2 < DH / 32; ++t2)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 ov;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ov[e] = (bf16_t)(acc[t2][g * 4 + e] * oscale);
-      *reinterpret_cast<bf16x4*>(dout + off + t2 * 32 + g * 8) = ov;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
 // dS handed from the dK/dV pass to the dQ pass (128-wide heads, long sequences), so that dQ is one product per tile
 // instead of three (S and dP are not formed a second time).  Storage, bf16, lower triangle only:
 //   per (batch, query head): query blocks qb of 128 rows, each followed by its 2 (qb + 1) key tiles of 64;
@@ -763,20 +616,28 @@ __global__ __launch_bounds__(256 * NH, 2 / NH) void attn_bwd_dq_from_ds_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// dK and dV in one pass (head dims 64 and 128).  Workgroup = 4 waves = 128 keys of one (batch, kv head),
+// dK and dV in one pass.  Workgroup = 4 waves = 128 keys of one (batch, kv head),
 // wave = 32 keys; it streams 32-row Q / dO tiles of every query head of the group from the last query
 // tile back to the diagonal.  Per tile: S = Q K^T and dP = dO V^T - delta once, P = exp2(..), dS = P dP,
 // then dV^T += dO^T P and dK^T += Q^T dS: 4 products where the two separate kernels run 5, one
 // exponential pass instead of two, and every Q / dO tile crosses L2 -> LDS once instead of twice.
 // To hold both accumulators at two waves per SIMD the wave's V fragments live in LDS (the 128-key V tile
 // stays resident), only its K fragments in registers, and the query tile is 32 rows.
+//
+// `ns` workgroups share a key block (dkdv_splits): number p takes every ns-th (query tile, head) of the
+// walk, so all of them still move over the same query tiles at the same pace and meet in the L2, and leaves
+// its fp32 sums in part[p] for attn_dkdv_reduce_kernel, which adds them in the order of p.  The causal
+// triangle makes a key block's work fall from S/32 tiles per head to 4, and with few KV heads there are
+// fewer blocks than the 512 workgroups the chip holds, so one workgroup per block leaves the launch
+// waiting for the first ones (measurements at dkdv_splits).
 // ------------------------------------------------------------------------------------------
 template <int DH, bool WRITE_DS>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ d_o, const float* __restrict__ lse2, const float* __restrict__ delta,
-    bf16_t* __restrict__ dk_out, bf16_t* __restrict__ dv_out, bf16_t* __restrict__ ds_out, int B, int S, int Hq,
-    int Hkv, float scale, const float* __restrict__ rope_cos, const float* __restrict__ rope_sin, int rope_layout) {
+    bf16_t* __restrict__ dk_out, bf16_t* __restrict__ dv_out, bf16_t* __restrict__ ds_out, float* __restrict__ part,
+    int ns, int B, int S, int Hq, int Hkv, float scale, const float* __restrict__ rope_cos,
+    const float* __restrict__ rope_sin, int rope_layout) {
   using VTile = RowTile<128, DH, 4>;
   using Tile = RowTile<32, DH, 1>;          // addressing of a 32-row tile; loaded by issue32 below
   constexpr int TB = 32 * DH * 2;           // one Q or dO tile
@@ -784,8 +645,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   char* tv = smem + 2 * STAGE;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int kt, pair;   // low key tiles have the most query tiles: first
-  split_block_id((int)blockIdx.x, B * Hkv, kt, pair);
+  int j, pair;   // low key tiles have the most query tiles: first
+  split_block_id((int)blockIdx.x, B * Hkv, j, pair);
+  const int kt = j / ns, piece = j % ns;
   const int G = Hq / Hkv, b = pair / Hkv, hk = pair % Hkv;
   const int kv0 = kt * 128, kvw = kv0 + wave * 32;
   const int lk = lane & 31, half = lane >> 5;
@@ -804,32 +666,41 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
 #pragma unroll
     for (int e = 0; e < 16; ++e) { acc_k[t][e] = 0.f; acc_v[t][e] = 0.f; }
 
-  const int nq = (S - kv0) / 32, niter = G * nq;
+  // number of (query tile, head) pairs this workgroup takes: piece, piece + ns, ... of G * nq
+  const int nq = (S - kv0) / 32, niter = (G * nq - piece + ns - 1) / ns;
+  const int step_qt = ns / G, step_g = ns % G;
   const uint32_t q_bytes = (uint32_t)((((int64_t)S - 1) * ldq + DH) * 2);
-  // 32 rows x DH*2 bytes = 32*DH*2/1024 wave-wide loads per tile, dealt to the four waves
-  constexpr int RPI = 1024 / (DH * 2), NI = 32 / RPI, IPW = NI / 4;
-  static_assert(NI % 4 == 0 && IPW >= 1, "a 32-row tile must split over four waves");
+  // 32 rows x DH*2 bytes = 32*DH*2/1024 wave-wide loads per tile, dealt to the four waves (head dim 32, two
+  // loads: to waves 0 and 1 of the Q tile, to waves 2 and 3 of the dO tile)
+  constexpr int RPI = 1024 / (DH * 2), NI = 32 / RPI, IPW = NI >= 4 ? NI / 4 : 1;
+  static_assert(NI % 4 == 0 || NI == 2, "a 32-row tile must split over the waves");
+  const int lwave = NI >= 4 ? wave : wave & 1;
   auto issue32 = [&](const bf16_t* base, uint32_t bytes, char* dst) {
     const __amdgpu_buffer_rsrc_t rs = attn_rsrc(base, bytes);
     const int r = lane / Tile::LPR, pc = lane % Tile::LPR;
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
-      const int j = wave * IPW + i, row = j * RPI + r;
+      const int j = lwave * IPW + i, row = j * RPI + r;
       const int c = pc ^ Tile::swz(row);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(dst + j * 1024), 16, (uint32_t)(r * ldq * 2 + (c << 4)),
                                                (uint32_t)((int64_t)j * RPI * ldq * 2), 0, 0);
     }
   };
-  int ld_g = 0, ld_qt = S / 32 - 1, cur_g = 0, cur_qt = S / 32 - 1;
+  int ld_g = piece % G, ld_qt = S / 32 - 1 - piece / G, cur_g = ld_g, cur_qt = ld_qt;
+  auto advance = [&](int& g, int& qt) {
+    g += step_g;
+    qt -= step_qt;
+    if (g >= G) { g -= G; --qt; }
+  };
   const uint32_t ds_lane = (uint32_t)(lk * 32 + half * 16);
   auto issue_tile = [&](int stage) {
     const int h = hk * G + ld_g, qrow = ld_qt * 32;
-    if (++ld_g == G) { ld_g = 0; --ld_qt; }
+    advance(ld_g, ld_qt);
     const int64_t base = ((int64_t)b * S) * ldq + (int64_t)h * DH;
     const uint32_t skip = (uint32_t)((int64_t)qrow * ldq * 2);
     char* st = smem + stage * STAGE;
-    issue32(q + base + (int64_t)qrow * ldq, q_bytes - skip, st);
-    issue32(d_o + base + (int64_t)qrow * ldq, q_bytes - skip, st + TB);
+    if (NI >= 4 || wave < 2) issue32(q + base + (int64_t)qrow * ldq, q_bytes - skip, st);
+    if (NI >= 4 || wave >= 2) issue32(d_o + base + (int64_t)qrow * ldq, q_bytes - skip, st + TB);
     // 32 lse2 and 32 -delta values of the tile, 4 bytes per lane, lanes 32..63 out of range (they store zeros into the pad)
     const int64_t sidx = ((int64_t)b * Hq + h) * S + qrow;
     if (wave == 0)
@@ -843,7 +714,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
     const bf16_t* vb = v + ((int64_t)b * S + kv0) * ldk + (int64_t)hk * DH;
     VTile::issue(attn_rsrc(vb, kv_bytes - (uint32_t)((int64_t)kv0 * ldk * 2)), tv, wave, lane, ldk);
   }
-  issue_tile(0);
+  if (niter > 0) issue_tile(0);   // a short key block may have fewer tiles than pieces
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   int stage = 0;
@@ -854,18 +725,19 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
     // before it, every iteration (-7 % on the backward at S = 2048; at S = 8192, where the kernels run
     // at the power limit, the other workgroup's waves cover the stall and nothing changes).  With the
     // pin the spill moves to values whose reload comes after the first two products.
-    static_assert(DH == 128 || DH == 64, "the pin lists the DH / 16 fragments by name");
     if constexpr (DH == 128)
       asm volatile("" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]), "+v"(kf[5]), "+v"(kf[6]), "+v"(kf[7]));
-    else
+    else if constexpr (DH == 64)
       asm volatile("" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]));
+    else
+      asm volatile("" : "+v"(kf[0]), "+v"(kf[1]));
     if (it + 1 < niter) issue_tile(stage ^ 1);
     const int qrow = cur_qt * 32;
     // where this wave's 32 keys x 32 queries of dS go (layout: DsLayout above)
     const char* ds_dst = reinterpret_cast<const char*>(ds_out) +
                          (DsLayout::head_units(S) * ((int64_t)b * Hq + hk * G + cur_g) + DsLayout::block_unit(cur_qt >> 2) + 2 * kt + (wave >> 1)) * DsLayout::UNIT +
                          (cur_qt & 3) * DsLayout::SUB + (wave & 1) * 2048;   // wave-uniform; the lane adds ds_lane
-    if (++cur_g == G) { cur_g = 0; --cur_qt; }
+    advance(cur_g, cur_qt);
     const char* tq = smem + stage * STAGE;
     const char* tdo = tq + TB;
     const float* stat = reinterpret_cast<const float*>(tq + 2 * TB);
@@ -928,8 +800,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
     __syncthreads();
     stage ^= 1;
   }
-  if (rope_cos) rope_unrotate<DH>(acc_k, rope_cos + (int64_t)(kvw + lk) * (DH / 2), rope_sin + (int64_t)(kvw + lk) * (DH / 2), rope_layout, half);
   const int64_t off = ((int64_t)b * S + kvw + lk) * ldk + (int64_t)hk * DH + half * 4;
+  if (ns > 1) {
+    const int64_t n = (int64_t)B * S * ldk;
+    float* pk = part + (int64_t)piece * 2 * n + off;
+#pragma unroll
+    for (int t2 = 0; t2 < DH / 32; ++t2)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 ok, ov;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { ok[e] = acc_k[t2][g * 4 + e]; ov[e] = acc_v[t2][g * 4 + e]; }
+        *reinterpret_cast<f32x4*>(pk + t2 * 32 + g * 8) = ok;
+        *reinterpret_cast<f32x4*>(pk + n + t2 * 32 + g * 8) = ov;
+      }
+    return;
+  }
+  if (rope_cos) rope_unrotate<DH>(acc_k, rope_cos + (int64_t)(kvw + lk) * (DH / 2), rope_sin + (int64_t)(kvw + lk) * (DH / 2), rope_layout, half);
 #pragma unroll
   for (int t2 = 0; t2 < DH / 32; ++t2)
 #pragma unroll
@@ -942,6 +829,69 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
     }
 }
 
+// Adds the ns partial sums of dK and dV that attn_bwd_dkdv_kernel left in part ([ns][dK, dV][B*S][Hkv][DH]
+// fp32), in the order of the pieces, then scales, un-rotates and rounds dK, rounds dV.  A thread owns elements
+// 4c .. 4c+3 and their partners DH/2 further on of one (token, head).  Bound by the reads: 4 ns bytes per element.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_dkdv_reduce_kernel(const float* __restrict__ part, int ns, bf16_t* __restrict__ dk_out,
+                                                               bf16_t* __restrict__ dv_out, int64_t rows, int S, int Hkv, float scale,
+                                                               const float* __restrict__ rope_cos,
+                                                               const float* __restrict__ rope_sin, int rope_layout) {
+  constexpr int CPR = DH / 8;
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t row = idx / CPR;
+  if (row >= rows) return;
+  const int i0 = (int)(idx % CPR) * 4;
+  const int64_t n = rows * DH, off = row * DH + i0;
+  f32x4 a[2][2];   // [dK, dV][half of the head]
+#pragma unroll
+  for (int w = 0; w < 2; ++w)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) a[w][h] = *reinterpret_cast<const f32x4*>(part + w * n + off + h * (DH / 2));
+  for (int p = 1; p < ns; ++p)
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(part + ((int64_t)p * 2 + w) * n + off + h * (DH / 2));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[w][h][e] += x[e];
+      }
+  if (rope_cos) {
+    const int64_t pos = (row / Hkv) % S;
+    const float* cr = rope_cos + pos * (DH / 2);
+    const float* sr = rope_sin + pos * (DH / 2);
+    if (rope_layout == 0) {
+      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cr + i0), s4 = *reinterpret_cast<const f32x4*>(sr + i0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = a[0][0][e], y = a[0][1][e];
+        a[0][0][e] = x * c4[e] + y * s4[e];
+        a[0][1][e] = y * c4[e] - x * s4[e];
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int i2 = (i0 + h * (DH / 2)) >> 1;
+        const f32x2 c2 = *reinterpret_cast<const f32x2*>(cr + i2), s2 = *reinterpret_cast<const f32x2*>(sr + i2);
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          const float x = a[0][h][e], y = a[0][h][e + 1];
+          a[0][h][e] = x * c2[e >> 1] + y * s2[e >> 1];
+          a[0][h][e + 1] = y * c2[e >> 1] - x * s2[e >> 1];
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    bf16x4 ok, ov;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { ok[e] = (bf16_t)(a[0][h][e] * scale); ov[e] = (bf16_t)a[1][h][e]; }
+    *reinterpret_cast<bf16x4*>(dk_out + off + h * (DH / 2)) = ok;
+    *reinterpret_cast<bf16x4*>(dv_out + off + h * (DH / 2)) = ov;
+  }
+}
 
 // ------------------------------------------------------------------------------------------
 template <int DH>
@@ -964,18 +914,74 @@ int launch_attention_fwd(const void* q, const void* k, const void* v, int64_t B,
   return fwd_dh<32>(q, k, v, B, S, Hq, Hkv, o, lse, st);
 }
 
-// -rowsum(dO * O) and lse * log2(e), then (head dims 64 and 128) the dS tiles of DsLayout
+// -rowsum(dO * O) and lse * log2(e), then the dS tiles of DsLayout, then the partial sums of a split dK/dV pass
 static size_t bwd_stats_bytes(int64_t B, int64_t S, int64_t Hq) {
   return (2 * (size_t)B * Hq * S * sizeof(float) + 4095) / 4096 * 4096;
+}
+// Workgroups per key block of the dK/dV pass.  Left whole, the launch takes as long as its longest key block (the
+// first: every query tile of every head of the group), however few blocks there are; every further piece costs
+// a round trip of one more set of fp32 partial sums, and the kernel that adds them a launch.  The estimate weighs
+// the two in microseconds, fitted to sweeps of 1 .. 24 pieces over twelve shapes, and lands within 4 % of the
+// best of every sweep:
+//   tile: a 32-row tile of one head takes a lone workgroup 1.1 / 0.7 / 0.45 us at head dim 128 / 64 / 32, and a second
+//         workgroup on the CU hardly adds to its throughput, so a CU's mean load counts in full;
+//   skew: with no more than three workgroups per two slots a CU's load is what it was dealt at the start, half
+//         a piece off the mean; with more of them the short late blocks even it out;
+//   sums: written and read at 4.2 TB/s.
+// Measured (whole backward, us, unsplit -> split): B2 S2944 16q/4kv x64 339 -> 163 (6 pieces), B1 S4224 24q/8kv x128
+// 549 -> 359 (3), B1 S8192 32q/8kv x128 1885 -> 1616 (2); stays whole: B2 S8192 32q/8kv x128 3116 (3154 with 2),
+// B4 S2048 16q/8kv x128 260 (275 with 2), B8 S1024 12q/12kv x64 79 (104 with 2).
+static int dkdv_splits(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
+  const int64_t n = S / 128;
+  const double longest = (double)(Hq / Hkv * 4 * n), mean = (double)B * Hq * 4 * n * (n + 1) / 2 / 256;   // tiles; per CU
+  const double tile = dh == 128 ? 1.1 : dh == 64 ? 0.7 : 0.45;
+  const double sums = (double)B * S * Hkv * dh * 16 / 4.2e6;
+  int best = 1;
+  double best_us = 0;
+  for (int ns = 1; ns <= 8; ++ns) {
+    const double piece = longest / ns, skew = B * Hkv * n * ns <= 768 ? 0.5 : 0.1;
+    const double load = 1.15 * piece > mean + skew * piece ? 1.15 * piece : mean + skew * piece;
+    const double us = load * tile + (ns > 1 ? 5 + ns * sums : 0);
+    if (ns == 1 || us < best_us) { best = ns; best_us = us; }
+  }
+  return best;
+}
+static size_t dkdv_partial_bytes(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
+  if (Hkv <= 0 || Hq % Hkv) return 0;   // a shape the call itself rejects
+  const int ns = dkdv_splits(B, S, Hq, Hkv, dh);
+  return ns > 1 ? (size_t)ns * 2 * B * S * Hkv * dh * sizeof(float) : 0;
 }
 // Handing dS over costs its HBM round trip (2 bytes per causal score, written and read once) and saves two of
 // the dQ pass's three products, whose cost grows with the head dim: worth it for 128-wide heads once the
 // sequences are long enough for the products to dominate (measured on the backward: -6 % at S = 2048 to
 // 16384 with 128-wide heads; with 64-wide heads +4 % at S = 2048, +11 % at 4096 and +29 % at 8192).
 static bool ds_handoff(int64_t S, int64_t dh) { return dh == 128 && S >= 2048; }
-size_t attention_bwd_workspace(int64_t B, int64_t S, int64_t Hq, int64_t, int64_t dh) {
-  const size_t stats = bwd_stats_bytes(B, S, Hq);
-  return ds_handoff(S, dh) ? stats + (size_t)B * Hq * DsLayout::head_units(S) * DsLayout::UNIT : stats;
+static size_t bwd_ds_bytes(int64_t B, int64_t S, int64_t Hq, int64_t dh) {
+  return ds_handoff(S, dh) ? (size_t)B * Hq * DsLayout::head_units(S) * DsLayout::UNIT : 0;
+}
+size_t attention_bwd_workspace(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
+  return bwd_stats_bytes(B, S, Hq) + bwd_ds_bytes(B, S, Hq, dh) + dkdv_partial_bytes(B, S, Hq, Hkv, dh);
+}
+
+template <int DH, bool WRITE_DS>
+static int launch_dkdv(const void* q, const void* k, const void* v, const void* d_o, const float* lse2, const float* delta,
+                       int64_t B, int64_t S, int64_t Hq, int64_t Hkv, void* dk, void* dv, bf16_t* ds, float* part,
+                       float scale, const float* rope_cos, const float* rope_sin, int rope_layout, hipStream_t st) {
+  const size_t lds = 2 * (2 * (size_t)(32 * DH * 2) + 512) + (size_t)RowTile<128, DH, 4>::BYTES;
+  static std::atomic<unsigned long long> done{0};
+  if (int rc = reserve_lds(attn_bwd_dkdv_kernel<DH, WRITE_DS>, lds, done, "attention_backward")) return rc;
+  const int ns = dkdv_splits(B, S, Hq, Hkv, DH);
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<DH, WRITE_DS>), dim3((unsigned)(S / 128 * Hkv * B * ns)), dim3(256), lds, st,
+                     (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)d_o, lse2, delta, (bf16_t*)dk, (bf16_t*)dv,
+                     ds, part, ns, (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
+  if (int rc = check_launch("attention_backward(dk, dv)")) return rc;
+  if (ns > 1) {
+    const int64_t rows = B * S * Hkv, nthreads = rows * (DH / 8);
+    hipLaunchKernelGGL(attn_dkdv_reduce_kernel<DH>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, st, (const float*)part, ns,
+                       (bf16_t*)dk, (bf16_t*)dv, rows, (int)S, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
+    return check_launch("attention_backward(dk, dv sums)");
+  }
+  return 0;
 }
 
 template <int DH>
@@ -985,61 +991,39 @@ static int bwd_dh(const void* q, const void* k, const void* v, const void* o, co
                   hipStream_t st) {
   float* delta = (float*)workspace;
   float* lse2 = delta + B * Hq * S;
+  char* after_stats = reinterpret_cast<char*>(workspace) + bwd_stats_bytes(B, S, Hq);
+  float* part = reinterpret_cast<float*>(after_stats + bwd_ds_bytes(B, S, Hq, DH));
   const int64_t rows = B * S * Hq;
   const int64_t nthreads = rows * (DH / 8);
   hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, st,
                      (const bf16_t*)o, (const bf16_t*)d_o, lse, delta, lse2, rows, (int)S, (int)Hq);
   if (int rc = check_launch("attention_backward(delta)")) return rc;
   const float scale = (float)(1.0 / sqrt((double)DH));
-  const dim3 kv_grid((unsigned)(S / 128 * Hkv * B)), q_grid((unsigned)(S / 128 * Hq * B));
-  if constexpr (DH >= 64) {
-    const size_t lds_m = 2 * (2 * (size_t)(32 * DH * 2) + 512) + (size_t)RowTile<128, DH, 4>::BYTES;
-    if constexpr (DH == 128) {
-      if (ds_handoff(S, DH)) {
-        bf16_t* ds = reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(workspace) + bwd_stats_bytes(B, S, Hq));
-        static std::atomic<unsigned long long> done_m{0};
-        if (int rc = reserve_lds(attn_bwd_dkdv_kernel<DH, true>, lds_m, done_m, "attention_backward")) return rc;
-        hipLaunchKernelGGL((attn_bwd_dkdv_kernel<DH, true>), kv_grid, dim3(256), lds_m, st, (const bf16_t*)q, (const bf16_t*)k,
-                           (const bf16_t*)v, (const bf16_t*)d_o, (const float*)lse2, (const float*)delta, (bf16_t*)dk, (bf16_t*)dv, ds,
-                           (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
-        if (int rc = check_launch("attention_backward(dk, dv)")) return rc;
-        // two query heads of a KV group per workgroup where the group has an even number of them
-        if ((Hq / Hkv) % 2 == 0) {
-          const size_t lds_q = 2 * (size_t)RowTile<64, DH, 4>::BYTES + 3 * 8 * (size_t)DsLayout::SUB;
-          static std::atomic<unsigned long long> done_q{0};
-          if (int rc = reserve_lds(attn_bwd_dq_from_ds_kernel<DH, 2>, lds_q, done_q, "attention_backward")) return rc;
-          hipLaunchKernelGGL((attn_bwd_dq_from_ds_kernel<DH, 2>), dim3(q_grid.x / 2), dim3(512), lds_q, st, (const bf16_t*)k,
-                             (const bf16_t*)ds, (bf16_t*)dq, (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
-        } else {
-          const size_t lds_q = 2 * (size_t)RowTile<64, DH, 4>::BYTES + 3 * 4 * (size_t)DsLayout::SUB;
-          static std::atomic<unsigned long long> done_q{0};
-          if (int rc = reserve_lds(attn_bwd_dq_from_ds_kernel<DH, 1>, lds_q, done_q, "attention_backward")) return rc;
-          hipLaunchKernelGGL((attn_bwd_dq_from_ds_kernel<DH, 1>), q_grid, dim3(256), lds_q, st, (const bf16_t*)k,
-                             (const bf16_t*)ds, (bf16_t*)dq, (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
-        }
-        return check_launch("attention_backward(dq)");
+  const dim3 q_grid((unsigned)(S / 128 * Hq * B));
+  if constexpr (DH == 128) {
+    if (ds_handoff(S, DH)) {
+      bf16_t* ds = reinterpret_cast<bf16_t*>(after_stats);
+      if (int rc = launch_dkdv<DH, true>(q, k, v, d_o, lse2, delta, B, S, Hq, Hkv, dk, dv, ds, part, scale, rope_cos, rope_sin,
+                                         rope_layout, st)) return rc;
+      // two query heads of a KV group per workgroup where the group has an even number of them
+      if ((Hq / Hkv) % 2 == 0) {
+        const size_t lds_q = 2 * (size_t)RowTile<64, DH, 4>::BYTES + 3 * 8 * (size_t)DsLayout::SUB;
+        static std::atomic<unsigned long long> done_q{0};
+        if (int rc = reserve_lds(attn_bwd_dq_from_ds_kernel<DH, 2>, lds_q, done_q, "attention_backward")) return rc;
+        hipLaunchKernelGGL((attn_bwd_dq_from_ds_kernel<DH, 2>), dim3(q_grid.x / 2), dim3(512), lds_q, st, (const bf16_t*)k,
+                           (const bf16_t*)ds, (bf16_t*)dq, (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
+      } else {
+        const size_t lds_q = 2 * (size_t)RowTile<64, DH, 4>::BYTES + 3 * 4 * (size_t)DsLayout::SUB;
+        static std::atomic<unsigned long long> done_q{0};
+        if (int rc = reserve_lds(attn_bwd_dq_from_ds_kernel<DH, 1>, lds_q, done_q, "attention_backward")) return rc;
+        hipLaunchKernelGGL((attn_bwd_dq_from_ds_kernel<DH, 1>), q_grid, dim3(256), lds_q, st, (const bf16_t*)k,
+                           (const bf16_t*)ds, (bf16_t*)dq, (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
       }
+      return check_launch("attention_backward(dq)");
     }
-    static std::atomic<unsigned long long> done_m{0};
-    if (int rc = reserve_lds(attn_bwd_dkdv_kernel<DH, false>, lds_m, done_m, "attention_backward")) return rc;
-    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<DH, false>), kv_grid, dim3(256), lds_m, st, (const bf16_t*)q, (const bf16_t*)k,
-                       (const bf16_t*)v, (const bf16_t*)d_o, (const float*)lse2, (const float*)delta, (bf16_t*)dk, (bf16_t*)dv,
-                       (bf16_t*)nullptr, (int)B, (int)S, (int)Hq, (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
-    if (int rc = check_launch("attention_backward(dk, dv)")) return rc;
-  } else {
-    const size_t lds_kv = 2 * (2 * (size_t)RowTile<64, DH, 4>::BYTES + 512);
-    static std::atomic<unsigned long long> done_dv{0}, done_dk{0};
-    if (int rc = reserve_lds(attn_bwd_dkv_kernel<DH, true>, lds_kv, done_dv, "attention_backward")) return rc;
-    if (int rc = reserve_lds(attn_bwd_dkv_kernel<DH, false>, lds_kv, done_dk, "attention_backward")) return rc;
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<DH, true>), kv_grid, dim3(256), lds_kv, st, (const bf16_t*)q, (const bf16_t*)k,
-                       (const bf16_t*)v, (const bf16_t*)d_o, (const float*)lse2, (const float*)delta, (bf16_t*)dv, (int)B, (int)S, (int)Hq,
-                       (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
-    if (int rc = check_launch("attention_backward(dv)")) return rc;
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<DH, false>), kv_grid, dim3(256), lds_kv, st, (const bf16_t*)q, (const bf16_t*)k,
-                       (const bf16_t*)v, (const bf16_t*)d_o, (const float*)lse2, (const float*)delta, (bf16_t*)dk, (int)B, (int)S, (int)Hq,
-                       (int)Hkv, scale, rope_cos, rope_sin, rope_layout);
-    if (int rc = check_launch("attention_backward(dk)")) return rc;
   }
+  if (int rc = launch_dkdv<DH, false>(q, k, v, d_o, lse2, delta, B, S, Hq, Hkv, dk, dv, nullptr, part, scale, rope_cos, rope_sin,
+                                      rope_layout, st)) return rc;
   const size_t lds_dq = 2 * 2 * (size_t)RowTile<64, DH, 4>::BYTES;
   static std::atomic<unsigned long long> done_dq{0};
   if (int rc = reserve_lds(attn_bwd_dq_kernel<DH>, lds_dq, done_dq, "attention_backward")) return rc;
