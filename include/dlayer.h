@@ -204,16 +204,14 @@ int qkv_rope_forward(const void* h, const void* wq, const void* wk, const void* 
 
 /* The gated pair of the SwiGLU MLP of the transformer block (Fig. 2; Training Pipeline paragraph):
  * g = x Wg^T, u = x Wu^T, a = silu(g) * u.  x [T, K], w_gate and w_up [F, K], g, u, a [T, F] dense;
- * all bf16.  K % 64 == 0, F % 8 == 0.  Large problems run as one kernel whose epilogue applies the
- * activation to the fp32 sums (a is rounded once); small ones as two products and the activation
- * kernel, which reads g and u as stored.                                                       */
+ * all bf16.  K % 64 == 0, F % 8 == 0.  The activation is applied to the fp32 sums in the product's
+ * epilogue (a is rounded once).                                                                */
 int linear_swiglu_forward(const void* x, const void* w_gate, const void* w_up, int64_t T, int64_t K,
                           int64_t F, void* g, void* u, void* a, void* stream);
 
 /* Backward of y = a W_down^T with a = silu(g) * u, as far as g and u: da = dy W_down, then
- * (dg, du) = swiglu_backward(g, u, da); large problems run as one kernel that applies the gradient to
- * the fp32 sums of da and never stores it, small ones as the product (da rounded to bf16) and the
- * activation-gradient kernel.  dy [T, D], w_down [D, F], g, u, dg, du [T, F] dense; all bf16.
+ * (dg, du) = swiglu_backward(g, u, da); the gradient is applied to the fp32 sums of da in the product's
+ * epilogue, da is never stored.  dy [T, D], w_down [D, F], g, u, dg, du [T, F] dense; all bf16.
  * T, D, F multiples of 64.  workspace (device; receives a transposed copy of w_down):
  * linear_swiglu_backward_workspace_bytes(T, D, F).                                             */
 size_t linear_swiglu_backward_workspace_bytes(int64_t T, int64_t D, int64_t F);

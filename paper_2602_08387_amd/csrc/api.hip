@@ -168,17 +168,6 @@ static int gemm_nt(const void* x, int64_t ldx, const void* w, const void* res, i
   return launch_gemm(nt_args(x, ldx, w, res, T, K, N, y), st);
 }
 
-// g = x Wg^T, u = x Wu^T, a = silu(g) * u (a with leading dimension lda): one fused launch when the
-// problem fills the chip with 256 x 256 tiles, otherwise two products and the activation kernel.
-// Both routes give the same bits (the fused epilogue applies the activation to the rounded g, u).
-static int gate_up_swiglu(const void* x, const void* wg, const void* wu, int64_t T, int64_t K, int64_t F, void* g,
-                          void* u, void* a, int64_t lda, hipStream_t st) {
-  if (gemm_swiglu_applies(T, F)) return launch_gemm_swiglu(x, K, wg, wu, K, T, K, F, g, u, F, a, lda, st);
-  TRY(gemm_nt(x, K, wg, nullptr, T, K, F, g, st));
-  TRY(gemm_nt(x, K, wu, nullptr, T, K, F, u, st));
-  return launch_swiglu_fwd_rows(g, u, T, F, F, a, lda, st);
-}
-
 // dx[T,K] = sum_s dy_s[T,N_s] WT_s[K,N_s]^T with the transposed weights WT_s = W_s^T; ld: leading
 // dimension of every dy_s and WT_s, lddx: that of dx
 static int gemm_dgrad_t(int nseg, const void* const* dy, const void* const* wt, const int64_t* Ns, int64_t ld,
@@ -189,17 +178,6 @@ static int gemm_dgrad_t(int nseg, const void* const* dy, const void* const* wt, 
   g.M = (int)T; g.N = (int)K; g.c = dx; g.ldc = lddx; g.r = nullptr; g.accumulate = 0;
   g.a_kmajor = true; g.b_kmajor = true;
   return launch_gemm(g, st);
-}
-
-// da = dy Wd for the transposed copy wdT [F, D], then (dg, du) = SwiGLU gradient; dg, du with leading
-// dimension ldd.  One fused launch when the problem fills the chip, otherwise the product into dg
-// followed by the activation-gradient kernel in place; same bits either way.
-static int down_dgrad_swiglu(const void* dy, const void* wdT, int64_t T, int64_t D, int64_t F, const void* g,
-                             const void* u, void* dg, void* du, int64_t ldd, hipStream_t st) {
-  if (gemm_swiglu_grad_applies(T, F)) return launch_gemm_swiglu_grad(dy, D, wdT, D, T, D, F, g, u, F, dg, du, ldd, st);
-  const void* dys[1] = {dy}; const void* ws[1] = {wdT}; const int64_t ns[1] = {D};
-  TRY(gemm_dgrad_t(1, dys, ws, ns, 0, T, F, dg, ldd, st));
-  return launch_swiglu_bwd_rows(g, u, dg, T, F, F, ldd, dg, du, st);
 }
 
 // dw[N,K] (+)= dy[T,N]^T x[T,K]; lddy, ldx: leading dimensions of dy and x
@@ -270,7 +248,7 @@ int dlayer_forward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* w
   TRY(gemm_nt(s.o, QD, w->wo, x, T, QD, D, s.y1, st));
   TRY(launch_rmsnorm_fwd(s.y1, w->g_mlp, T, D, cfg->rms_eps, s.h2, s.rstd2, st));
   const int64_t Fp = padded_ff(cfg);
-  TRY(gate_up_swiglu(s.h2, w->w_gate, w->w_up, T, D, F, s.g, s.u, s.a, Fp, st));
+  TRY(launch_gemm_swiglu(s.h2, D, w->w_gate, w->w_up, D, T, D, F, s.g, s.u, F, s.a, Fp, st));
   TRY(gemm_nt(s.a, Fp, w->w_down, s.y1, T, F, D, y, st));
   return DLAYER_OK;
 }
@@ -302,7 +280,7 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
     TRY(launch_transpose_group(jobs, 7, st));
   }
   // y = y1 + a Wd^T
-  TRY(down_dgrad_swiglu(dy, k.wdT, T, D, F, s.g, s.u, k.da_dg, k.du, Fp, st));
+  TRY(launch_gemm_swiglu_grad(dy, D, k.wdT, D, T, D, F, s.g, s.u, F, k.da_dg, k.du, Fp, st));
   {
     const void* dys[2] = {k.da_dg, k.du}; const void* ws[2] = {k.wgT, k.wuT}; const int64_t ns[2] = {F, F};
     TRY(gemm_dgrad_t(2, dys, ws, ns, Fp, T, D, k.dh2, D, st));
@@ -491,7 +469,7 @@ int linear_swiglu_forward(const void* x, const void* w_gate, const void* w_up, i
           "linear_swiglu_forward: an operand reaches 4 GiB");
   REQUIRE_PTR(x); REQUIRE_PTR(w_gate); REQUIRE_PTR(w_up); REQUIRE_PTR(g); REQUIRE_PTR(u); REQUIRE_PTR(a);
   TRY(check_device());
-  return gate_up_swiglu(x, w_gate, w_up, T, K, F, g, u, a, F, (hipStream_t)stream);
+  return launch_gemm_swiglu(x, K, w_gate, w_up, K, T, K, F, g, u, F, a, F, (hipStream_t)stream);
 }
 
 size_t linear_backward_workspace_bytes(int64_t T, int64_t K, int64_t N) {
@@ -533,7 +511,7 @@ int linear_swiglu_backward(const void* dy, const void* w_down, const void* g, co
   TRY(check_device());
   hipStream_t st = (hipStream_t)stream;
   TRY(launch_transpose(w_down, workspace, D, F, D, st));
-  return down_dgrad_swiglu(dy, workspace, T, D, F, g, u, dg, du, F, st);
+  return launch_gemm_swiglu_grad(dy, D, workspace, D, T, D, F, g, u, F, dg, du, F, st);
 }
 
 int linear_wgrad_group(int32_t n, const void* const* dy, const void* const* x, const int64_t* N, const int64_t* K,

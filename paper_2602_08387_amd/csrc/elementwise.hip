@@ -390,8 +390,8 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const bf16x8* g, const 
   }
 }
 
-// Row variants: g, u are [rows, cols] with leading dimension ld_gu, the other arrays with ld_p
-// (the layer keeps a, da/dg and du with padded rows).  One row per workgroup at a time.
+// Row variant: g, u are [rows, cols] with leading dimension ld_gu, a with ld_p (the layer keeps it with padded
+// rows).  One row per workgroup at a time.
 constexpr int SW_U = 4;   // 16-byte vectors per thread in flight
 __device__ __forceinline__ bf16x8 swiglu_vec(bf16x8 gv, bf16x8 uv) {
   bf16x8 o;
@@ -402,16 +402,6 @@ __device__ __forceinline__ bf16x8 swiglu_vec(bf16x8 gv, bf16x8 uv) {
   }
   return o;
 }
-__device__ __forceinline__ void swiglu_grad_vec(bf16x8 gv, bf16x8 uv, bf16x8 dv, bf16x8& og, bf16x8& ou) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float z = (float)gv[e], d = (float)dv[e];
-    const float sg = logistic(z);
-    og[e] = (bf16_t)(d * (float)uv[e] * sg * (1.0f + z * (1.0f - sg)));
-    ou[e] = (bf16_t)(d * z * sg);
-  }
-}
-
 __global__ __launch_bounds__(256) void swiglu_fwd_rows_kernel(const bf16_t* __restrict__ g, const bf16_t* __restrict__ u,
                                                               bf16_t* __restrict__ a, int rows, int cols_vec,
                                                               int64_t ld_gu, int64_t ld_p) {
@@ -430,38 +420,6 @@ __global__ __launch_bounds__(256) void swiglu_fwd_rows_kernel(const bf16_t* __re
       for (int q = 0; q < SW_U; ++q) {
         const int i = i0 + q * 256;
         if (i < cols_vec) ar[i] = swiglu_vec(gv[q], uv[q]);
-      }
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void swiglu_bwd_rows_kernel(const bf16_t* __restrict__ g, const bf16_t* __restrict__ u,
-                                                              const bf16_t* da, bf16_t* dg, bf16_t* __restrict__ du,
-                                                              int rows, int cols_vec, int64_t ld_gu, int64_t ld_p) {
-  for (int r = blockIdx.x; r < rows; r += gridDim.x) {
-    const bf16x8* gr = reinterpret_cast<const bf16x8*>(g + r * ld_gu);
-    const bf16x8* ur = reinterpret_cast<const bf16x8*>(u + r * ld_gu);
-    const bf16x8* dr = reinterpret_cast<const bf16x8*>(da + r * ld_p);
-    bf16x8* ogr = reinterpret_cast<bf16x8*>(dg + r * ld_p);
-    bf16x8* our = reinterpret_cast<bf16x8*>(du + r * ld_p);
-    for (int i0 = threadIdx.x; i0 < cols_vec; i0 += 256 * SW_U) {
-      bf16x8 gv[SW_U], uv[SW_U], dv[SW_U];
-#pragma unroll
-      for (int q = 0; q < SW_U; ++q) {
-        const int i = i0 + q * 256;
-        if (i < cols_vec) {
-          gv[q] = __builtin_nontemporal_load(gr + i); uv[q] = __builtin_nontemporal_load(ur + i); dv[q] = dr[i];
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < SW_U; ++q) {
-        const int i = i0 + q * 256;
-        if (i < cols_vec) {
-          bf16x8 og, ou;
-          swiglu_grad_vec(gv[q], uv[q], dv[q], og, ou);
-          ogr[i] = og;
-          our[i] = ou;
-        }
       }
     }
   }
@@ -490,14 +448,6 @@ int launch_swiglu_fwd_rows(const void* g, const void* u, int64_t rows, int64_t c
                      (const bf16_t*)g, (const bf16_t*)u, (bf16_t*)a, (int)rows, (int)(cols / 8), ld_gu, ld_a);
   return check_launch("swiglu_forward(rows)");
 }
-int launch_swiglu_bwd_rows(const void* g, const void* u, const void* da, int64_t rows, int64_t cols, int64_t ld_gu,
-                           int64_t ld_p, void* dg, void* du, hipStream_t st) {
-  hipLaunchKernelGGL(swiglu_bwd_rows_kernel, dim3((unsigned)(rows < 8192 ? rows : 8192)), dim3(256), 0, st,
-                     (const bf16_t*)g, (const bf16_t*)u, (const bf16_t*)da, (bf16_t*)dg, (bf16_t*)du, (int)rows,
-                     (int)(cols / 8), ld_gu, ld_p);
-  return check_launch("swiglu_backward(rows)");
-}
-
 // ------------------------------------------------------------------------------------------
 // bf16 transpose: out[c][r] = in[r][c], 64x64 tiles through LDS (16-byte global accesses on
 // both sides).  R and C are multiples of 64.

@@ -23,321 +23,18 @@
 // "B" (column index j), so a lane ends up with 4 consecutive n for one m.  The epilogue passes
 // the tile through LDS so that global stores (and residual loads) are 16 bytes per lane along
 // rows of C.
-#include "common.h"
-#include "kernels.h"
-#include <atomic>
-#include <type_traits>
+#include "gemm_core.h"
 
 namespace dl {
-
-// Measured on MI355X (M=16384, K=4096, N=14336, normal data): 2 stages of 64 k-values beat 3, 4 and 5
-// stages of 32 (the K-step is not latency-bound, a deeper ring only adds barriers); 16x16x32 MFMA
-// blocks beat 32x32x16 by 3 % on y = x W^T and 11 % on dx = dy W (half the accumulator traffic per
-// flop); 8 waves of 128x64 beat 4 waves of 128x128 under the compiler's schedule.
-constexpr int BK = 64;   // k-values per pipeline stage
-constexpr int NS = 2;    // ring stages
-constexpr int MI = 16;               // MFMA block edge: 32 (32x32x16) or 16 (16x16x32)
-constexpr int KSTEP = MI == 32 ? 16 : 32;  // k per MFMA
-constexpr int NACC = MI * MI / 64;       // accumulator registers per MFMA block
-typedef float acc_t __attribute__((ext_vector_type(NACC)));
-__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-struct GemmKArgs {
-  const bf16_t* a[3];
-  const bf16_t* b[3];
-  int64_t lda[3], ldb[3];
-  int K[3];
-  int nseg;
-  int M, N;
-  bf16_t* c;
-  int64_t ldc;
-  const bf16_t* r;
-  int accumulate;
-  int tiles_m, tiles_n;
-  int band_rows;   // tile rows per band of the tile sequence (see band_rows_for)
-  // gated-pair products only (see gemm_swiglu_kernel): second weight, second and third output
-  const bf16_t* b2;
-  bf16_t *c2, *c3;
-  int64_t ldc3;
-  // activation-gradient epilogue only (see EPI_SWIGLU_GRAD)
-  const bf16_t *e1, *e2;
-  int64_t lde;
-  // rotary epilogue only (see EPI_ROPE): rotate this problem's output
-  int rope;
-};
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-
-// Loads one operand tile (R rows of the M/N index, BK of k) for K-step origin k0 into LDS.
-template <int R, bool KMAJOR, int NW>
-struct TileLoader {
-  static constexpr int NINSTR = R * BK * 2 / 1024;  // wave-wide 1 KiB loads per tile
-  static constexpr int PER_WAVE = NINSTR / NW;
-  static_assert(NINSTR % NW == 0 && PER_WAVE >= 1, "tile loads must divide across waves");
-  static constexpr int CPRK = BK / 8;               // chunks per row of a k-major tile
-  static constexpr int RPW = 16 / CPRK;             // k-major rows per 256-byte bank window
-  static constexpr int CPR = R / 8;                 // chunks per k-row (mn-major)
-  static constexpr int RPI = KMAJOR ? 1024 / (BK * 2) : 1024 / (R * 2);  // tile rows per instruction
-  // k-major: swizzle variants a lane needs across its instructions (precomputed offsets);
-  // mn-major: the chunk swizzle is applied per instruction from (row part, chunk, k-row in instr).
-  static constexpr int NVAR = KMAJOR ? (RPI >= 16 ? 1 : 16 / RPI) : 1;
-  static_assert(PER_WAVE % NVAR == 0, "swizzle variant must not depend on the wave index");
-  uint32_t voff[NVAR];
-  int pc, kq;
-
-  // chunk XOR of k-row k of an mn-major tile: the rows k..k+3 (bits 2-3) and k+8.. (bit 1) that a
-  // 32-lane transposed read touches fall in 8 different 32-byte bank groups.
-  static __device__ __forceinline__ int mn_swz(int k) {
-    return (((k & 3) << 2) | (((k >> 3) & 1) << 1)) & (CPR - 1);
-  }
-
-  __device__ __forceinline__ void init(int lane, int64_t ld) {
-    if constexpr (KMAJOR) {
-      // instruction j covers rows RPI*j ..; the swizzle depends on (row / RPW) & (CPRK - 1)
-#pragma unroll
-      for (int v = 0; v < NVAR; ++v) {
-        const int row = v * RPI + lane / CPRK;   // row modulo 16
-        const int c = (lane % CPRK) ^ ((row / RPW) & (CPRK - 1));
-        voff[v] = (uint32_t)((lane / CPRK) * ld * 2 + (c << 4));
-      }
-    } else {
-      kq = lane / CPR;
-      pc = lane % CPR;
-      voff[0] = (uint32_t)(kq * ld * 2);
-    }
-  }
-
-  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
-                                        int k0) const {
-    issue_range<0, PER_WAVE>(rs, lds_tile, wave, ld, k0);
-  }
-  // this wave's loads I0 .. I1-1 of the tile
-  template <int I0, int I1>
-  __device__ __forceinline__ void issue_range(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
-                                              int k0) const {
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-      const int j = wave * PER_WAVE + i;
-      const uint32_t soff = KMAJOR ? (uint32_t)(((int64_t)RPI * j * ld + k0) * 2)
-                                   : (uint32_t)(((int64_t)(k0 + j * RPI) * ld) * 2);
-      uint32_t vo;
-      if constexpr (KMAJOR) vo = voff[i % NVAR];
-      else vo = voff[0] + (uint32_t)((pc ^ mn_swz(j * RPI + kq)) << 4);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(lds_tile + j * 1024), 16, vo, soff, 0, 0);
-    }
-  }
-  // Tile of a k-major matrix whose rows are heads of 128 features, loaded so that a wave whose MFMA
-  // tile spans 64 tile rows holds 32 features of a head's first half and, 32 tile rows further, their
-  // rotary partners 64 features on: tile row r <- matrix row
-  // 128 * (r / 128) + 32 * ((r / 64) & 1) + r % 32 + 64 * ((r / 32) & 1).
-  static __device__ __forceinline__ int perm_row(int r) {
-    return ((r >> 7) << 7) + (((r >> 6) & 1) << 5) + (r & 31) + (((r >> 5) & 1) << 6);
-  }
-  template <int I0, int I1>
-  __device__ __forceinline__ void issue_perm_range(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
-                                                   int k0) const {
-    static_assert(KMAJOR && 32 % RPI == 0, "an instruction's rows must lie in one run of 32");
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-      const int j = wave * PER_WAVE + i;
-      const uint32_t soff = (uint32_t)(((int64_t)perm_row(j * RPI) * ld + k0) * 2);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(lds_tile + j * 1024), 16, voff[i % NVAR], soff, 0, 0);
-    }
-  }
-  // Tile of a PAIR of k-major matrices: of every 64 tile rows the first 32 are rows of the first
-  // matrix and the next 32 the SAME rows of the second (tile row r <- matrix (r / 32) & 1, row
-  // (r / 64) * 32 + r % 32), so that a wave whose MFMA tile spans 64 of these rows holds both values
-  // of a column pair.  LDS placement and swizzle are those of the plain tile.
-  template <int I0, int I1>
-  __device__ __forceinline__ void issue_pair_range(__amdgpu_buffer_rsrc_t rs0, __amdgpu_buffer_rsrc_t rs1,
-                                                   char* lds_tile, int wave, int64_t ld, int k0) const {
-    static_assert(KMAJOR && 32 % RPI == 0, "an instruction's rows must lie in one matrix");
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-      const int j = wave * PER_WAVE + i;
-      const int r0 = j * RPI;
-      const int row = (r0 >> 6) * 32 + (r0 & 31);
-      const uint32_t soff = (uint32_t)(((int64_t)row * ld + k0) * 2);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(((r0 >> 5) & 1) ? rs1 : rs0, (LDS_PTR(void))(lds_tile + j * 1024), 16,
-                                               voff[i % NVAR], soff, 0, 0);
-    }
-  }
-};
-
-// MFMA operand fragment for MI rows starting at row0 (tile-local M/N index), k-substep kk (KSTEP k).
-template <int R, bool KMAJOR>
-__device__ __forceinline__ bf16x8 read_frag(const char* tile, int row0, int kk, int lane) {
-  if constexpr (KMAJOR) {
-    constexpr int CPRK = BK / 8, RPW = 16 / CPRK;
-    const int row = row0 + (lane & (MI - 1));
-    const int c = (kk * (KSTEP / 8) + lane / MI) ^ ((row / RPW) & (CPRK - 1));
-    return *reinterpret_cast<const bf16x8*>(tile + row * (BK * 2) + (c << 4));
-  } else {
-    constexpr int CPR = R / 8;
-    const int grp = lane >> 4, s = lane & 15, e = s >> 2, g = s & 3;
-    const int col = MI == 32 ? row0 + ((grp & 1) << 4) + (g << 2) : row0 + (g << 2);
-    const int krow = MI == 32 ? kk * 16 + ((grp >> 1) << 3) + e : kk * 32 + (grp << 3) + e;
-    const int f = (((krow & 3) << 2) | (((krow >> 3) & 1) << 1)) & (CPR - 1);  // same for krow and krow + 4
-    const char* p0 = tile + krow * (R * 2) + ((((col >> 3) ^ f) << 4) | ((col & 7) << 1));
-    // Issued as inline assembly: for the builtin the compiler cannot tell that the read does not
-    // touch the stage the asynchronous global -> LDS loads are filling and puts an s_waitcnt vmcnt(0)
-    // in front of it, which stalls the loading waves for the whole load latency every K-step.  The
-    // price: the compiler does not count these reads in lgkmcnt either, so every consumer must sit
-    // behind wait_frags().
-    bf16x8 v;
-    bf16x4 lo, hi;
-    const uint32_t a0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(p0);
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(a0));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(a0), "n"(4 * R * 2));
-    v.lo = lo;
-    v.hi = hi;
-    return v;
-  }
-}
-
-// f(integral_constant<int, I>) for I = I0 .. N-1: a loop whose index is a compile-time constant
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Waits for every LDS read of this wave and makes the fragments depend on that wait, so that no
-// consumer of a fragment fetched by the inline-assembly transposed read can be scheduled before it.
-template <int FM, int FN>
-__device__ __forceinline__ void wait_frags(bf16x8 (&fa)[FM], bf16x8 (&fb)[FN]) {
-  static_assert(FM == 8 && FN == 4 || FM == 4 && FN == 4, "operand list written out for the two wave tiles in use");
-  if constexpr (FM == 8)
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fa[4]), "+v"(fa[5]), "+v"(fa[6]), "+v"(fa[7]),
-                   "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
-  else
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
-}
-
-// Position of the next tile pair to fetch: segment, k offset, and that segment's descriptors.
-// PAIR: the B tile interleaves two weight matrices (TileLoader::issue_pair_range); n0 and N then
-// count columns of the interleaved product, twice the rows of either matrix.
-// PERM: the B tile takes its rows in the rotary-partner order of TileLoader::issue_perm_range.
-template <int BM, int BN, int NW, bool AK, bool BKM, bool PAIR = false, bool PERM = false>
-struct LoadCursor {
-  TileLoader<BM, AK, NW> la;
-  TileLoader<BN, BKM, NW> lb;
-  __amdgpu_buffer_rsrc_t ra, rb, rb2;
-  int64_t lda, ldb;
-  int seg = 0, k = 0, kend = 0, nseg = 1;   // kend: K of the open segment (kept in a register: no kernarg read per K-step)
-  int left = 0;                             // K-steps of the tile still to fetch; the walk may start anywhere and wraps
-
-  __device__ __forceinline__ void open_raw(const bf16_t* a, const bf16_t* b, int64_t lda_, int64_t ldb_, int K, int M,
-                                           int N, int m0, int n0, int lane) {
-    kend = K;
-    lda = lda_;
-    ldb = ldb_;
-    const bf16_t* ab = AK ? a + (int64_t)m0 * lda : a + m0;
-    const bf16_t* bb = BKM ? b + (int64_t)n0 * ldb : b + n0;
-    const uint32_t a_bytes = AK ? (uint32_t)((((int64_t)(M - m0 - 1)) * lda + K) * 2)
-                                : (uint32_t)((((int64_t)(K - 1)) * lda + (M - m0)) * 2);
-    const uint32_t b_bytes = BKM ? (uint32_t)((((int64_t)(N - n0 - 1)) * ldb + K) * 2)
-                                 : (uint32_t)((((int64_t)(K - 1)) * ldb + (N - n0)) * 2);
-    ra = make_rsrc(ab, a_bytes);
-    rb = make_rsrc(bb, b_bytes);
-    la.init(lane, lda);
-    lb.init(lane, ldb);
-  }
-  __device__ __forceinline__ void open_pair(const bf16_t* a, const bf16_t* b, const bf16_t* b2, int64_t lda_,
-                                            int64_t ldb_, int K, int M, int N, int m0, int n0, int lane) {
-    static_assert(!PAIR || (AK && BKM), "paired weights are k-major");
-    open_raw(a, b, lda_, ldb_, K, M, N / 2, m0, n0 / 2, lane);
-    rb2 = make_rsrc(b2 + (int64_t)(n0 / 2) * ldb_, (uint32_t)((((int64_t)(N / 2 - n0 / 2 - 1)) * ldb_ + K) * 2));
-  }
-  __device__ __forceinline__ void open(const GemmKArgs& p, int s, int m0, int n0, int lane) {
-    open_raw(p.a[s], p.b[s], p.lda[s], p.ldb[s], p.K[s], p.M, p.N, m0, n0, lane);
-  }
-  // The same in NC pieces (piece C of the A loads and of the B loads), so that a wave can spread its
-  // loads between MFMAs; the cursor moves on with the last piece.
-  template <int C, int NC>
-  __device__ __forceinline__ void issue_piece(const GemmKArgs& segs, char* stage, int wave, int m0, int n0, int lane) {
-    constexpr int PA = TileLoader<BM, AK, NW>::PER_WAVE, PB = TileLoader<BN, BKM, NW>::PER_WAVE;
-    if (left > 0) {
-      la.template issue_range<C * PA / NC, (C + 1) * PA / NC>(ra, stage, wave, lda, k);
-      if constexpr (PAIR)
-        lb.template issue_pair_range<C * PB / NC, (C + 1) * PB / NC>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
-      else if constexpr (PERM)
-        lb.template issue_perm_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
-      else
-        lb.template issue_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
-      if constexpr (C + 1 == NC) advance(segs, m0, n0, lane);
-    }
-  }
-  // `segs`: the problem whose further K-segments follow (only read when nseg > 1)
-  __device__ __forceinline__ void issue_next(const GemmKArgs& segs, char* stage, int wave, int m0, int n0, int lane) {
-    if (left > 0) {
-      la.issue(ra, stage, wave, lda, k);
-      if constexpr (PAIR)
-        lb.template issue_pair_range<0, TileLoader<BN, BKM, NW>::PER_WAVE>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
-      else if constexpr (PERM)
-        lb.template issue_perm_range<0, TileLoader<BN, BKM, NW>::PER_WAVE>(rb, stage + BM * BK * 2, wave, ldb, k);
-      else
-        lb.issue(rb, stage + BM * BK * 2, wave, ldb, k);
-      advance(segs, m0, n0, lane);
-    }
-  }
-  // one K-step on: past the end of a segment the walk goes on in the next one, past the last in the first
-  __device__ __forceinline__ void advance(const GemmKArgs& segs, int m0, int n0, int lane) {
-    --left;
-    k += BK;
-    if (k == kend) {
-      k = 0;
-      if (nseg > 1 && left > 0) {
-        seg = seg + 1 == nseg ? 0 : seg + 1;
-        open(segs, seg, m0, n0, lane);
-      }
-    }
-  }
-};
-
-// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: give every XCD a contiguous
-// range of the tile sequence.
-__device__ __forceinline__ int xcd_contiguous(int id, int ntiles) {
-  const int per_xcd = ntiles >> 3;
-  return id < (per_xcd << 3) ? (id & 7) * per_xcd + (id >> 3) : id;
-}
-
-// Several independent problems of one operand layout in one grid: their tile sequences are laid end
-// to end, so the last, partly filled round of one problem runs alongside the first of the next.
-constexpr int MAX_GROUP = 8;
-struct GemmGroupKArgs {
-  GemmKArgs prob[MAX_GROUP];
-  int tile_start[MAX_GROUP + 1];
-  int n;
-  // rotary epilogue only (see EPI_ROPE): cos and sin of the angle of (position, pair), [seq][head_dim/2]
-  const float *rope_cos, *rope_sin;
-  int rope_seq, rope_dh, rope_layout;
-};
 
 // Persistent workgroup: one per CU, walking the tile sequence with stride gridDim.x.  Between two
 // tiles the first two K-steps of the next tile are already on their way into the LDS ring while the
 // epilogue of the current one drains the accumulators through a staging region of its own, and the
 // C stores of a tile complete under the next tile's main loop.
 //
-// The kernel arguments are only ever read with compile-time offsets (a grouped launch picks its
-// problem by comparing against each index in turn): a run-time index into the argument block would
-// make the compiler copy the whole block to scratch memory and read it back through vector loads.
+// The kernel arguments are only read with compile-time offsets: a run-time index into the argument block
+// would make the compiler copy the whole block to scratch memory and read it back through vector loads.  A
+// grouped launch reads its problem through group_problem().
 //
 // EPI_SWIGLU: the gated pair of the MLP in one pass.  B interleaves the rows of two weight matrices
 // (LoadCursor PAIR) so that every wave holds g = x Wg^T and u = x Wu^T for the same 32 columns; the
@@ -405,7 +102,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
     const bf16_t *a0, *b0;
     int64_t lda0, ldb0;
     Tile t;
-    auto take = [&](const GemmKArgs& q) {
+    auto take = [&](const auto& q) {
       tiles_m = q.tiles_m; tiles_n = q.tiles_n; K0 = q.K[0]; GM = q.band_rows > 0 ? q.band_rows : 8;
       a0 = q.a[0]; b0 = q.b[0]; lda0 = q.lda[0]; ldb0 = q.ldb[0];
       t.M = q.M; t.N = q.N; t.accumulate = q.accumulate; t.c = q.c; t.r = q.r; t.ldc = q.ldc;
@@ -413,10 +110,11 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
     };
     if constexpr (GROUPED) {
       // problem index: the number of problems whose first tile is not after pid
-      take(grp.prob[0]);
+      int pi = 0;
 #pragma unroll
       for (int i = 1; i < MAX_GROUP; ++i)
-        if (i < grp.n && pid >= grp.tile_start[i]) { take(grp.prob[i]); start = grp.tile_start[i]; }
+        if (i < grp.n && pid >= grp.tile_start[i]) { pi = i; start = grp.tile_start[i]; }
+      take(group_problem(pi));
       pid -= start;
       cur.nseg = 1;   // grouped problems have a single K-segment (checked on the host)
       t.total = K0 / BK;
@@ -432,14 +130,8 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
     const int in_band = pid - band * GM * tiles_n;
     t.m0 = (first_m + in_band % band_h) * BM;
     t.n0 = (in_band / band_h) * BN;
-    // The contraction of a tile starts (g mod 8) eighths of the way through K and wraps around, g = the
-    // tile's group of 8 tile-rows.  The XCDs work on different groups at any one time, and without this
-    // they would all stream the same k-range of their operands at once: the requests then crowd the
-    // same memory channels (worst with rows a multiple of 4 KiB apart, see the down projection's
-    // weight).  The start depends on the tile's rows only - not on the workgroup, the launch or the band
-    // height - so a product gives the same bits in whatever launch it is computed.
     cur.left = t.total;
-    int first = (((t.m0 / (8 * BM)) & 7) * t.total) >> 3;   // in K-steps from the start of segment 0
+    int first = k_start(t.m0, t.total);   // in K-steps from the start of segment 0
     cur.seg = 0;
     if constexpr (!GROUPED) {
       for (int s2 = 0; s2 + 1 < one.nseg; ++s2)
@@ -874,7 +566,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_group_kernel(const GemmGroup
 }
 
 template <int BM, int BN, int WM, int WN, bool PERM>
-__global__ __launch_bounds__(WM* WN * 64, WM* WN == 4 ? 2 : 1) void gemm_group_rope_kernel(const GemmGroupKArgs g) {
+__global__ __launch_bounds__(WM* WN * 64) void gemm_group_rope_kernel(const GemmGroupKArgs g) {
   gemm_persistent<true, BM, BN, WM, WN, true, true, EPI_ROPE, PERM>(g, g.prob[0]);
 }
 
@@ -889,10 +581,8 @@ static int band_rows_for(bool both_kmajor, int64_t k_total, bool epilogue_reads_
   return both_kmajor && !epilogue_reads_tiles && k_total <= 4096 ? 8 : 4;
 }
 
-// As many workgroups as the LDS lets a CU hold at once (one for the 256 x 256 tile's 160 KB, two for
-// the 128 x 128 tile's 72 KB, which then also gives every SIMD a second wave), fewer if there are fewer
-// tiles.
-static int persistent_grid(int ntiles, size_t lds) {
+// One workgroup per CU (the tile's ring and staging take all of the LDS), fewer if there are fewer tiles.
+static int persistent_grid(int ntiles) {
   static std::atomic<int> cu_count[64];   // per device; 0 = not asked yet
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) return ntiles;
@@ -903,84 +593,165 @@ static int persistent_grid(int ntiles, size_t lds) {
     cus = n > 0 ? n : 256;
     cu_count[dev].store(cus, std::memory_order_relaxed);
   }
-  const int per_cu = lds * 2 <= 160 * 1024 ? 2 : 1;
-  return ntiles < cus * per_cu ? ntiles : cus * per_cu;
+  return ntiles < cus ? ntiles : cus;
 }
 
-template <int BM, int BN>
-static size_t lds_bytes(int nwaves, int wm) {
-  const size_t ring = (size_t)NS * (BM + BN) * BK * 2, staging = (size_t)nwaves * (BM / wm / 4) * 128;
-  return ring + staging;
+constexpr int PM = 256, PN = 256, PWM = 2, PWN = 4;   // the persistent kernels' tile and waves
+constexpr size_t kPersistentLds = (size_t)NS * (PM + PN) * BK * 2 + (size_t)PWM * PWN * (PM / PWM / 4) * 128;
+
+static int64_t k_total(const GemmKArgs& k) {
+  int64_t t = 0;
+  for (int s = 0; s < k.nseg; ++s) t += k.K[s];
+  return t;
+}
+static GemmKArgs persistent_tiling(GemmKArgs k, bool both_kmajor, bool epilogue_reads_tiles) {
+  k.tiles_m = (k.M + PM - 1) / PM;
+  k.tiles_n = (k.N + PN - 1) / PN;
+  k.band_rows = band_rows_for(both_kmajor, k_total(k), epilogue_reads_tiles);
+  return k;
 }
 
-template <int BM, int BN, int WM, int WN>
-static int launch_group_cfg(const GemmKArgs* ks, int n, bool ak, bool bk, const RopeEpilogue* rope, hipStream_t st) {
+#define GEMM_LAUNCH(KERN, NTILES, ARGS, WHAT)                                                                   \
+  do {                                                                                                          \
+    auto kern_ = KERN;                                                                                          \
+    static std::atomic<unsigned long long> lds_done{0};                                                         \
+    if (int rc_ = reserve_lds(kern_, kPersistentLds, lds_done, WHAT)) return rc_;                               \
+    hipLaunchKernelGGL(kern_, dim3((unsigned)persistent_grid(NTILES)), dim3(PWM * PWN * 64), kPersistentLds, st, ARGS); \
+    return check_launch(WHAT);                                                                                  \
+  } while (0)
+
+static int launch_persistent_group(const GemmKArgs* ks, int n, bool ak, bool bk, const RopeEpilogue* rope, hipStream_t st) {
   GemmGroupKArgs g{};
   g.n = n;
   for (int i = 0; i < n; ++i) {
-    g.prob[i] = ks[i];
-    g.prob[i].tiles_m = (ks[i].M + BM - 1) / BM;
-    g.prob[i].band_rows = band_rows_for(ak && bk, ks[i].K[0], false);
-    g.prob[i].tiles_n = (ks[i].N + BN - 1) / BN;
+    g.prob[i] = persistent_tiling(ks[i], ak && bk, false);
     g.tile_start[i + 1] = g.tile_start[i] + g.prob[i].tiles_m * g.prob[i].tiles_n;
   }
-  const size_t lds = lds_bytes<BM, BN>(WM * WN, WM);
-  const dim3 grid((unsigned)persistent_grid(g.tile_start[n], lds)), block(WM * WN * 64);
   if (rope) {
     g.rope_cos = rope->cos; g.rope_sin = rope->sin;
     g.rope_seq = rope->seq; g.rope_dh = rope->head_dim; g.rope_layout = rope->layout;
-    for (int i = 0; i < n; ++i) g.prob[i].rope = (rope->rotate_mask >> i) & 1;
-#define GEMM_ROPE_LAUNCH(PERM_)                                                                  \
-  do {                                                                                           \
-    auto kern = gemm_group_rope_kernel<BM, BN, WM, WN, PERM_>;                                   \
-    static std::atomic<unsigned long long> lds_done{0};                                          \
-    if (int rc_ = reserve_lds(kern, lds, lds_done, "gemm rope")) return rc_;                     \
-    hipLaunchKernelGGL(kern, grid, block, lds, st, g);                                           \
-  } while (0)
-    if (rope->layout == 0 && rope->head_dim == 128) GEMM_ROPE_LAUNCH(true);
-    else GEMM_ROPE_LAUNCH(false);
-#undef GEMM_ROPE_LAUNCH
-    return check_launch("gemm group (rotary epilogue)");
+    for (int i = 0; i < n; ++i) g.prob[i].rope = ks[i].rope;
+    if (rope->layout == 0 && rope->head_dim == 128)
+      GEMM_LAUNCH((gemm_group_rope_kernel<PM, PN, PWM, PWN, true>), g.tile_start[n], g, "gemm group (rotary epilogue)");
+    GEMM_LAUNCH((gemm_group_rope_kernel<PM, PN, PWM, PWN, false>), g.tile_start[n], g, "gemm group (rotary epilogue)");
   }
-#define GEMM_GROUP_LAUNCH(AK_, BK_)                                                              \
-  do {                                                                                           \
-    auto kern = gemm_group_kernel<BM, BN, WM, WN, AK_, BK_>;                                     \
-    static std::atomic<unsigned long long> lds_done{0};                                                      \
-    if (int rc_ = reserve_lds(kern, lds, lds_done, "gemm")) return rc_;                          \
-    hipLaunchKernelGGL(kern, grid, block, lds, st, g);                                           \
-  } while (0)
   // only the layouts in use are instantiated: the weight-gradient products (both operands mn-major)
   // and the forward projections (both k-major)
-  if (!ak && !bk) GEMM_GROUP_LAUNCH(false, false);
-  else if (ak && bk) GEMM_GROUP_LAUNCH(true, true);
-  else return fail(-1, "gemm group: operand layout not built");
-#undef GEMM_GROUP_LAUNCH
-  return check_launch("gemm group");
+  if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<PM, PN, PWM, PWN, false, false>), g.tile_start[n], g, "gemm group");
+  if (ak && bk) GEMM_LAUNCH((gemm_group_kernel<PM, PN, PWM, PWN, true, true>), g.tile_start[n], g, "gemm group");
+  return fail(-1, "gemm group: operand layout not built");
 }
 
-template <int BM, int BN, int WM, int WN>
-static int launch_cfg(const GemmKArgs& k, bool ak, bool bk, hipStream_t st) {
-  GemmKArgs a = k;
-  a.tiles_m = (k.M + BM - 1) / BM;
-  int64_t k_total = 0;
-  for (int s = 0; s < k.nseg; ++s) k_total += k.K[s];
-  a.band_rows = band_rows_for(ak && bk, k_total, false);
-  a.tiles_n = (k.N + BN - 1) / BN;
-  const size_t lds = lds_bytes<BM, BN>(WM * WN, WM);
-  const dim3 grid((unsigned)persistent_grid(a.tiles_m * a.tiles_n, lds)), block(WM * WN * 64);
-#define GEMM_LAUNCH(AK_, BK_)                                                                    \
-  do {                                                                                           \
-    auto kern = gemm_kernel<BM, BN, WM, WN, AK_, BK_>;                                           \
-    static std::atomic<unsigned long long> lds_done{0};                                                      \
-    if (int rc_ = reserve_lds(kern, lds, lds_done, "gemm")) return rc_;                          \
-    hipLaunchKernelGGL(kern, grid, block, lds, st, a);                                           \
-  } while (0)
-  if (ak && bk) GEMM_LAUNCH(true, true);
-  else if (ak && !bk) GEMM_LAUNCH(true, false);
-  else if (!ak && bk) GEMM_LAUNCH(false, true);
-  else GEMM_LAUNCH(false, false);
+static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue epi, hipStream_t st) {
+  const GemmKArgs a = persistent_tiling(k, ak && bk, epi == TileEpilogue::SWIGLU_GRAD);
+  const int ntiles = a.tiles_m * a.tiles_n;
+  if (epi == TileEpilogue::SWIGLU) GEMM_LAUNCH((gemm_swiglu_kernel<PM, PN, PWM, PWN, EPI_SWIGLU>), ntiles, a, "gemm swiglu");
+  if (epi == TileEpilogue::SWIGLU_GRAD) GEMM_LAUNCH((gemm_swiglu_kernel<PM, PN, PWM, PWN, EPI_SWIGLU_GRAD>), ntiles, a, "gemm swiglu grad");
+  if (ak && bk) GEMM_LAUNCH((gemm_kernel<PM, PN, PWM, PWN, true, true>), ntiles, a, "gemm");
+  if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<PM, PN, PWM, PWN, false, false>), ntiles, a, "gemm");
+  return fail(-1, "gemm: operand layout not built");
+}
 #undef GEMM_LAUNCH
-  return check_launch("gemm");
+
+// ------------------------------------------------------------------------------------------
+// Which kernel a product runs on.  A 256 x 256 tile has the cheapest K-step per flop, but a launch costs whole rounds
+// of 256 tiles: 289 tiles take two.  So the time of every candidate is estimated from its rounds -
+//   time = launch + rounds x (K-steps x step + tile), a last round that is filled to f taking step lo + f (hi - lo)
+// (a CU runs faster while others idle: clock, L2) - and the cheapest runs: the persistent kernel, one of the three
+// tile sizes of gemm_tile.hip, or the persistent kernel for its full rounds and a smaller tile, in a second
+// launch, for the rows left over.  All give the same bits.  Microseconds, from sweeps on MI355X
+// (both operands k-major / an operand mn-major); slots: tiles in flight.  The estimates are within 10 % of
+// the measured launches from 15 us up.
+// ------------------------------------------------------------------------------------------
+struct KernelCost { int bm, bn, slots; double lo, hi, tile; };
+constexpr int kPersistent = 3;
+static const KernelCost kCostKK[4] = {
+    {128, 256, 256, 0.62, 0.75, 4.0},   // T = 8192, K = 4096, N = 768 (192 tiles): 50 us against 71 on 96 tiles of 256 x 256
+    {128, 128, 256, 0.38, 0.48, 3.0},   // T = 1920, K = 6272, N = 1152 (135 tiles): 44 us; 67 as 75 tiles of 128 x 256
+    {64, 64, 512, 0.27, 0.56, 2.0},     // T = 1000, K = 2048, N = 1024 (256 tiles): 8 us; 17 as 64 tiles of 128 x 128
+    {256, 256, 256, 0.98, 1.39, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
+static const KernelCost kCostMN[4] = {
+    {128, 256, 256, 0.70, 0.82, 4.0},   // 768 x 768, K = 8192 (18 tiles): 94 us
+    {128, 128, 256, 0.48, 0.56, 3.0},   // the same as 36 tiles: 63 us
+    {64, 64, 512, 0.30, 0.60, 2.0},     // as 144 tiles: 39 us (157 as 9 tiles of 256 x 256)
+    {256, 256, 256, 1.20, 1.45, 5.0}};
+constexpr double kLaunchUs = 3.5;
+
+static double kernel_us(const KernelCost& c, const GemmKArgs* ks, int n) {
+  int64_t tiles = 0, steps = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles += (int64_t)((ks[i].M + c.bm - 1) / c.bm) * ((ks[i].N + c.bn - 1) / c.bn);
+    const int64_t s = k_total(ks[i]) / BK;
+    steps = s > steps ? s : steps;
+  }
+  const int64_t full = tiles / c.slots, rem = tiles % c.slots;
+  double us = kLaunchUs + full * (steps * c.hi + c.tile);
+  if (rem) us += steps * (c.lo + (c.hi - c.lo) * rem / c.slots) + c.tile;
+  return us;
+}
+
+// rows [r0, r0 + rows) of a product
+static GemmKArgs row_part(GemmKArgs k, int r0, int rows, bool a_kmajor) {
+  for (int s = 0; s < k.nseg; ++s) k.a[s] += a_kmajor ? (int64_t)r0 * k.lda[s] : r0;
+  k.c += (int64_t)r0 * k.ldc;
+  if (k.c2) k.c2 += (int64_t)r0 * k.ldc;
+  if (k.c3) k.c3 += (int64_t)r0 * k.ldc3;
+  if (k.r) k.r += (int64_t)r0 * k.ldc;
+  if (k.e1) { k.e1 += (int64_t)r0 * k.lde; k.e2 += (int64_t)r0 * k.lde; }
+  k.M = rows;
+  k.m_base += r0;
+  return k;
+}
+
+static int run_gemm(const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, hipStream_t st) {
+  const KernelCost* cost = ak && bk ? kCostKK : kCostMN;
+  // a 64-column tile does not hold both members of a split pair of a 128-wide head; the persistent kernels are not built
+  // for one k-major and one mn-major operand
+  const bool no64 = rope && rope->layout == 0 && rope->head_dim == 128, persistent = ak == bk;
+  auto best_tile = [&](const GemmKArgs* ps, int m, double& us) {
+    int best = 0;
+    us = kernel_us(cost[0], ps, m);
+    for (int c = 1; c < (no64 ? 2 : 3); ++c) {
+      const double u = kernel_us(cost[c], ps, m);
+      if (u < us) { us = u; best = c; }
+    }
+    return best;
+  };
+  auto run_persistent = [&](const GemmKArgs* ps, int m) {
+    return m > 1 || rope ? launch_persistent_group(ps, m, ak, bk, rope, st) : launch_persistent(ps[0], ak, bk, epi, st);
+  };
+  double tile_us, best_us;
+  const int tile = best_tile(ks, n, tile_us);
+  best_us = persistent ? kernel_us(cost[kPersistent], ks, n) : 1e30;
+  // full rounds of the persistent kernel, the rows behind them on a smaller tile
+  GemmKArgs head[MAX_GROUP], tail[MAX_GROUP];
+  int nh = 0, nt = 0, tail_tile = 0;
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += (int64_t)((ks[i].M + PM - 1) / PM) * ((ks[i].N + PN - 1) / PN);
+  const bool can_split = persistent && tiles > 256 && tiles % 256 != 0;
+  double split_us = 1e30;
+  if (can_split) {
+    int64_t room = tiles / 256 * 256;
+    for (int i = 0; i < n; ++i) {
+      const int tn = (ks[i].N + PN - 1) / PN;
+      const int64_t fit = room / tn * PM;   // rows that still fit
+      const int rows = fit < ks[i].M ? (int)fit : ks[i].M;
+      if (rows > 0) head[nh++] = row_part(ks[i], 0, rows, ak);
+      if (rows < ks[i].M) tail[nt++] = row_part(ks[i], rows, ks[i].M - rows, ak);
+      room -= (int64_t)((rows + PM - 1) / PM) * tn;
+    }
+    if (nh > 0 && nt > 0) {
+      double t_us;
+      tail_tile = best_tile(tail, nt, t_us);
+      split_us = kernel_us(cost[kPersistent], head, nh) + t_us;
+    }
+  }
+  if (split_us < best_us && split_us < tile_us) {
+    if (int rc = run_persistent(head, nh)) return rc;
+    return launch_gemm_tile((TileSize)tail_tile, tail, nt, ak, bk, epi, rope, st);
+  }
+  if (best_us <= tile_us) return run_persistent(ks, n);
+  return launch_gemm_tile((TileSize)tile, ks, n, ak, bk, epi, rope, st);
 }
 
 static GemmKArgs kernel_args(const GemmArgs& g) {
@@ -1004,40 +775,13 @@ static GemmKArgs kernel_args(const GemmArgs& g) {
 
 int launch_gemm(const GemmArgs& g, hipStream_t st) {
   const GemmKArgs k = kernel_args(g);
-  // Large problems: 256x256 tiles, 8 waves (2 per SIMD), 128x64 per wave.  Small ones: 128x128
-  // tiles so that the grid still covers the 256 CUs.
-  const int64_t tiles256 = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  if (tiles256 >= 192) return launch_cfg<256, 256, 2, 4>(k, g.a_kmajor, g.b_kmajor, st);
-  return launch_cfg<128, 128, 2, 2>(k, g.a_kmajor, g.b_kmajor, st);
-}
-
-bool gemm_swiglu_applies(int64_t T, int64_t F) {
-  return F % 8 == 0 && ((T + 255) / 256) * ((2 * F + 255) / 256) >= 192;
-}
-bool gemm_swiglu_grad_applies(int64_t T, int64_t F) {
-  return F % 8 == 0 && ((T + 255) / 256) * ((F + 255) / 256) >= 192;
-}
-
-template <int EPI>
-static int launch_fused(GemmKArgs k, const char* what, hipStream_t st) {
-  constexpr int BM = 256, BN = 256, WM = 2, WN = 4;
-  k.nseg = 1;
-  k.tiles_m = (k.M + BM - 1) / BM;
-  k.band_rows = band_rows_for(true, k.K[0], EPI == EPI_SWIGLU_GRAD);
-  k.tiles_n = (k.N + BN - 1) / BN;
-  const size_t lds = lds_bytes<BM, BN>(WM * WN, WM);
-  const dim3 grid((unsigned)persistent_grid(k.tiles_m * k.tiles_n, lds)), block(WM * WN * 64);
-  auto kern = gemm_swiglu_kernel<BM, BN, WM, WN, EPI>;
-  static std::atomic<unsigned long long> lds_done{0};
-  if (int rc = reserve_lds(kern, lds, lds_done, what)) return rc;
-  hipLaunchKernelGGL(kern, grid, block, lds, st, k);
-  return check_launch(what);
+  return run_gemm(&k, 1, g.a_kmajor, g.b_kmajor, TileEpilogue::PLAIN, nullptr, st);
 }
 
 int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* wu, int64_t ldw, int64_t T, int64_t K,
                        int64_t F, void* g, void* u, int64_t ldgu, void* a, int64_t lda, hipStream_t st) {
-  if (!gemm_swiglu_applies(T, F)) return fail(-1, "gemm swiglu: shape T=%lld F=%lld not served by the fused kernel", (long long)T, (long long)F);
   GemmKArgs k{};
+  k.nseg = 1;
   k.a[0] = (const bf16_t*)x;
   k.b[0] = (const bf16_t*)wg;
   k.b2 = (const bf16_t*)wu;
@@ -1051,14 +795,14 @@ int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* w
   k.ldc = ldgu;
   k.c3 = (bf16_t*)a;
   k.ldc3 = lda;
-  return launch_fused<EPI_SWIGLU>(k, "gemm swiglu", st);
+  return run_gemm(&k, 1, true, true, TileEpilogue::SWIGLU, nullptr, st);
 }
 
 int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* wt, int64_t ldw, int64_t T, int64_t K, int64_t F,
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
                             hipStream_t st) {
-  if (!gemm_swiglu_grad_applies(T, F)) return fail(-1, "gemm swiglu grad: shape T=%lld F=%lld not served by the fused kernel", (long long)T, (long long)F);
   GemmKArgs k{};
+  k.nseg = 1;
   k.a[0] = (const bf16_t*)dy;
   k.b[0] = (const bf16_t*)wt;
   k.lda[0] = lddy;
@@ -1072,7 +816,7 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* wt, int64_
   k.e1 = (const bf16_t*)g;
   k.e2 = (const bf16_t*)u;
   k.lde = ldgu;
-  return launch_fused<EPI_SWIGLU_GRAD>(k, "gemm swiglu grad", st);
+  return run_gemm(&k, 1, true, true, TileEpilogue::SWIGLU_GRAD, nullptr, st);
 }
 
 int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st) { return launch_gemm_group_rope(gs, n, nullptr, st); }
@@ -1080,13 +824,12 @@ int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st) { return launch
 int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, hipStream_t st) {
   if (n < 1 || n > MAX_GROUP) return fail(-1, "gemm group: 1..%d problems, got %d", MAX_GROUP, n);
   GemmKArgs ks[MAX_GROUP];
-  int64_t tiles256 = 0;
   for (int i = 0; i < n; ++i) {
     if (gs[i].a_kmajor != gs[0].a_kmajor || gs[i].b_kmajor != gs[0].b_kmajor)
       return fail(-1, "gemm group: all problems must share one operand layout");
     if (gs[i].nseg != 1) return fail(-1, "gemm group: problems must have a single K-segment");
     ks[i] = kernel_args(gs[i]);
-    tiles256 += (int64_t)((gs[i].M + 255) / 256) * ((gs[i].N + 255) / 256);
+    if (rope) ks[i].rope = (rope->rotate_mask >> i) & 1;
   }
   if (rope) {
     if (!gs[0].a_kmajor || !gs[0].b_kmajor) return fail(-1, "gemm group: the rotary epilogue needs k-major operands");
@@ -1095,8 +838,7 @@ int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, 
       if (gs[i].r || gs[i].accumulate || gs[i].N % rope->head_dim || gs[i].ldc % 8)
         return fail(-1, "gemm group: rotary epilogue on a product with residual, accumulation or partial heads");
   }
-  if (tiles256 >= 192) return launch_group_cfg<256, 256, 2, 4>(ks, n, gs[0].a_kmajor, gs[0].b_kmajor, rope, st);
-  return launch_group_cfg<128, 128, 2, 2>(ks, n, gs[0].a_kmajor, gs[0].b_kmajor, rope, st);
+  return run_gemm(ks, n, gs[0].a_kmajor, gs[0].b_kmajor, TileEpilogue::PLAIN, rope, st);
 }
 
 }  // namespace dl

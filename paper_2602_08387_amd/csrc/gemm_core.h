@@ -1,0 +1,336 @@
+// Pieces shared by the GEMM kernels (gemm.hip, gemm_tile.hip): kernel arguments, the asynchronous global -> LDS
+// tile loads, operand fragments and the load cursor.  The layouts are described at the top of gemm.hip.
+#pragma once
+#include "common.h"
+#include "kernels.h"
+#include <atomic>
+#include <type_traits>
+
+namespace dl {
+
+// Measured on MI355X (M=16384, K=4096, N=14336, normal data): 2 stages of 64 k-values beat 3, 4 and 5
+// stages of 32 (the K-step is not latency-bound, a deeper ring only adds barriers); 16x16x32 MFMA
+// blocks beat 32x32x16 by 3 % on y = x W^T and 11 % on dx = dy W (half the accumulator traffic per
+// flop); 8 waves of 128x64 beat 4 waves of 128x128 under the compiler's schedule.
+constexpr int BK = 64;   // k-values per pipeline stage
+constexpr int NS = 2;    // ring stages
+constexpr int MI = 16;               // MFMA block edge: 32 (32x32x16) or 16 (16x16x32)
+constexpr int KSTEP = MI == 32 ? 16 : 32;  // k per MFMA
+constexpr int NACC = MI * MI / 64;       // accumulator registers per MFMA block
+typedef float acc_t __attribute__((ext_vector_type(NACC)));
+__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+struct GemmKArgs {
+  const bf16_t* a[3];
+  const bf16_t* b[3];
+  int64_t lda[3], ldb[3];
+  int K[3];
+  int nseg;
+  int M, N;
+  int m_base;      // rows of the whole product above this part of it (the second launch of a product in two parts)
+  bf16_t* c;
+  int64_t ldc;
+  const bf16_t* r;
+  int accumulate;
+  int tiles_m, tiles_n;
+  int band_rows;   // tile rows per band of the tile sequence (see band_rows_for)
+  // gated-pair products only (see gemm_swiglu_kernel): second weight, second and third output
+  const bf16_t* b2;
+  bf16_t *c2, *c3;
+  int64_t ldc3;
+  // activation-gradient epilogue only (see EPI_SWIGLU_GRAD)
+  const bf16_t *e1, *e2;
+  int64_t lde;
+  // rotary epilogue only (see EPI_ROPE): rotate this problem's output
+  int rope;
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Loads one operand tile (R rows of the M/N index, BK of k) for K-step origin k0 into LDS.
+template <int R, bool KMAJOR, int NW>
+struct TileLoader {
+  static constexpr int NINSTR = R * BK * 2 / 1024;  // wave-wide 1 KiB loads per tile
+  static constexpr int PER_WAVE = NINSTR / NW;
+  static_assert(NINSTR % NW == 0 && PER_WAVE >= 1, "tile loads must divide across waves");
+  static constexpr int CPRK = BK / 8;               // chunks per row of a k-major tile
+  static constexpr int RPW = 16 / CPRK;             // k-major rows per 256-byte bank window
+  static constexpr int CPR = R / 8;                 // chunks per k-row (mn-major)
+  static constexpr int RPI = KMAJOR ? 1024 / (BK * 2) : 1024 / (R * 2);  // tile rows per instruction
+  // k-major: swizzle variants a lane needs across its instructions (precomputed offsets);
+  // mn-major: the chunk swizzle is applied per instruction from (row part, chunk, k-row in instr).
+  static constexpr int NVAR = KMAJOR ? (RPI >= 16 ? 1 : 16 / RPI) : 1;
+  static_assert(PER_WAVE % NVAR == 0, "swizzle variant must not depend on the wave index");
+  uint32_t voff[NVAR];
+  int pc, kq;
+
+  // chunk XOR of k-row k of an mn-major tile: the rows k..k+3 (bits 2-3) and k+8.. (bit 1) that a
+  // 32-lane transposed read touches fall in 8 different 32-byte bank groups.
+  // A 64-wide tile has 128-byte rows: two rows share a bank window, rows k, k + 2 are told apart by bit 2.
+  static __device__ __forceinline__ int mn_swz(int k) {
+    if constexpr (CPR == 8) return (((k >> 1) & 1) << 2) | (((k >> 3) & 1) << 1);
+    return (((k & 3) << 2) | (((k >> 3) & 1) << 1)) & (CPR - 1);
+  }
+
+  __device__ __forceinline__ void init(int lane, int64_t ld) {
+    if constexpr (KMAJOR) {
+      // instruction j covers rows RPI*j ..; the swizzle depends on (row / RPW) & (CPRK - 1)
+#pragma unroll
+      for (int v = 0; v < NVAR; ++v) {
+        const int row = v * RPI + lane / CPRK;   // row modulo 16
+        const int c = (lane % CPRK) ^ ((row / RPW) & (CPRK - 1));
+        voff[v] = (uint32_t)((lane / CPRK) * ld * 2 + (c << 4));
+      }
+    } else {
+      kq = lane / CPR;
+      pc = lane % CPR;
+      voff[0] = (uint32_t)(kq * ld * 2);
+    }
+  }
+
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
+                                        int k0) const {
+    issue_range<0, PER_WAVE>(rs, lds_tile, wave, ld, k0);
+  }
+  // this wave's loads I0 .. I1-1 of the tile
+  template <int I0, int I1>
+  __device__ __forceinline__ void issue_range(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
+                                              int k0) const {
+#pragma unroll
+    for (int i = I0; i < I1; ++i) {
+      const int j = wave * PER_WAVE + i;
+      const uint32_t soff = KMAJOR ? (uint32_t)(((int64_t)RPI * j * ld + k0) * 2)
+                                   : (uint32_t)(((int64_t)(k0 + j * RPI) * ld) * 2);
+      uint32_t vo;
+      if constexpr (KMAJOR) vo = voff[i % NVAR];
+      else vo = voff[0] + (uint32_t)((pc ^ mn_swz(j * RPI + kq)) << 4);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(lds_tile + j * 1024), 16, vo, soff, 0, 0);
+    }
+  }
+  // Tile of a k-major matrix whose rows are heads of 128 features, loaded so that a wave whose MFMA
+  // tile spans 64 tile rows holds 32 features of a head's first half and, 32 tile rows further, their
+  // rotary partners 64 features on: tile row r <- matrix row
+  // 128 * (r / 128) + 32 * ((r / 64) & 1) + r % 32 + 64 * ((r / 32) & 1).
+  static __device__ __forceinline__ int perm_row(int r) {
+    return ((r >> 7) << 7) + (((r >> 6) & 1) << 5) + (r & 31) + (((r >> 5) & 1) << 6);
+  }
+  template <int I0, int I1>
+  __device__ __forceinline__ void issue_perm_range(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
+                                                   int k0) const {
+    static_assert(KMAJOR && 32 % RPI == 0, "an instruction's rows must lie in one run of 32");
+#pragma unroll
+    for (int i = I0; i < I1; ++i) {
+      const int j = wave * PER_WAVE + i;
+      const uint32_t soff = (uint32_t)(((int64_t)perm_row(j * RPI) * ld + k0) * 2);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(lds_tile + j * 1024), 16, voff[i % NVAR], soff, 0, 0);
+    }
+  }
+  // Tile of a PAIR of k-major matrices: of every 64 tile rows the first 32 are rows of the first
+  // matrix and the next 32 the SAME rows of the second (tile row r <- matrix (r / 32) & 1, row
+  // (r / 64) * 32 + r % 32), so that a wave whose MFMA tile spans 64 of these rows holds both values
+  // of a column pair.  LDS placement and swizzle are those of the plain tile.
+  template <int I0, int I1>
+  __device__ __forceinline__ void issue_pair_range(__amdgpu_buffer_rsrc_t rs0, __amdgpu_buffer_rsrc_t rs1,
+                                                   char* lds_tile, int wave, int64_t ld, int k0) const {
+    static_assert(KMAJOR && 32 % RPI == 0, "an instruction's rows must lie in one matrix");
+#pragma unroll
+    for (int i = I0; i < I1; ++i) {
+      const int j = wave * PER_WAVE + i;
+      const int r0 = j * RPI;
+      const int row = (r0 >> 6) * 32 + (r0 & 31);
+      const uint32_t soff = (uint32_t)(((int64_t)row * ld + k0) * 2);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(((r0 >> 5) & 1) ? rs1 : rs0, (LDS_PTR(void))(lds_tile + j * 1024), 16,
+                                               voff[i % NVAR], soff, 0, 0);
+    }
+  }
+};
+
+// MFMA operand fragment for MI rows starting at row0 (tile-local M/N index), k-substep kk (KSTEP k).
+template <int R, bool KMAJOR>
+__device__ __forceinline__ bf16x8 read_frag(const char* tile, int row0, int kk, int lane) {
+  if constexpr (KMAJOR) {
+    constexpr int CPRK = BK / 8, RPW = 16 / CPRK;
+    const int row = row0 + (lane & (MI - 1));
+    const int c = (kk * (KSTEP / 8) + lane / MI) ^ ((row / RPW) & (CPRK - 1));
+    return *reinterpret_cast<const bf16x8*>(tile + row * (BK * 2) + (c << 4));
+  } else {
+    constexpr int CPR = R / 8;
+    const int grp = lane >> 4, s = lane & 15, e = s >> 2, g = s & 3;
+    const int col = MI == 32 ? row0 + ((grp & 1) << 4) + (g << 2) : row0 + (g << 2);
+    const int krow = MI == 32 ? kk * 16 + ((grp >> 1) << 3) + e : kk * 32 + (grp << 3) + e;
+    const int f = (((krow & 3) << 2) | (((krow >> 3) & 1) << 1)) & (CPR - 1);  // same for krow and krow + 4
+    const char* p0 = tile + krow * (R * 2) + ((((col >> 3) ^ f) << 4) | ((col & 7) << 1));
+    // Issued as inline assembly: for the builtin the compiler cannot tell that the read does not
+    // touch the stage the asynchronous global -> LDS loads are filling and puts an s_waitcnt vmcnt(0)
+    // in front of it, which stalls the loading waves for the whole load latency every K-step.  The
+    // price: the compiler does not count these reads in lgkmcnt either, so every consumer must sit
+    // behind wait_frags().
+    bf16x8 v;
+    bf16x4 lo, hi;
+    const uint32_t a0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(p0);
+    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(a0));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(a0), "n"(4 * R * 2));
+    v.lo = lo;
+    v.hi = hi;
+    return v;
+  }
+}
+
+// f(integral_constant<int, I>) for I = I0 .. N-1: a loop whose index is a compile-time constant
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Start of a tile's contraction, in K-steps: (g mod 8) eighths of the way through K (the walk wraps around),
+// g = the tile's group of 2048 rows, whatever the tile height.  Tiles that run at the same time belong to
+// different groups, and without this all of them stream the same k-range of their operands at once: the requests
+// then crowd the same memory channels (worst with rows a multiple of 4 KiB apart).  The start depends on the
+// row group only - not on the workgroup, the launch, the tile size or the band height - so a product gives the
+// same bits in whatever launch it is computed.
+__device__ __forceinline__ int k_start(int m0, int total) { return (((m0 >> 11) & 7) * total) >> 3; }
+
+// Waits for every LDS read of this wave and makes the fragments depend on that wait, so that no
+// consumer of a fragment fetched by the inline-assembly transposed read can be scheduled before it.
+template <int FM, int FN>
+__device__ __forceinline__ void wait_frags(bf16x8 (&fa)[FM], bf16x8 (&fb)[FN]) {
+  static_assert(FM == 8 && FN == 4 || FM == 4 && FN == 4, "operand list written out for the two wave tiles in use");
+  if constexpr (FM == 8)
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fa[4]), "+v"(fa[5]), "+v"(fa[6]), "+v"(fa[7]),
+                   "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
+  else
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
+}
+
+// Position of the next tile pair to fetch: segment, k offset, and that segment's descriptors.
+// PAIR: the B tile interleaves two weight matrices (TileLoader::issue_pair_range); n0 and N then
+// count columns of the interleaved product, twice the rows of either matrix.
+// PERM: the B tile takes its rows in the rotary-partner order of TileLoader::issue_perm_range.
+template <int BM, int BN, int NW, bool AK, bool BKM, bool PAIR = false, bool PERM = false>
+struct LoadCursor {
+  TileLoader<BM, AK, NW> la;
+  TileLoader<BN, BKM, NW> lb;
+  __amdgpu_buffer_rsrc_t ra, rb, rb2;
+  int64_t lda, ldb;
+  int seg = 0, k = 0, kend = 0, nseg = 1;   // kend: K of the open segment (kept in a register: no kernarg read per K-step)
+  int left = 0;                             // K-steps of the tile still to fetch; the walk may start anywhere and wraps
+
+  __device__ __forceinline__ void open_raw(const bf16_t* a, const bf16_t* b, int64_t lda_, int64_t ldb_, int K, int M,
+                                           int N, int m0, int n0, int lane) {
+    kend = K;
+    lda = lda_;
+    ldb = ldb_;
+    const bf16_t* ab = AK ? a + (int64_t)m0 * lda : a + m0;
+    const bf16_t* bb = BKM ? b + (int64_t)n0 * ldb : b + n0;
+    const uint32_t a_bytes = AK ? (uint32_t)((((int64_t)(M - m0 - 1)) * lda + K) * 2)
+                                : (uint32_t)((((int64_t)(K - 1)) * lda + (M - m0)) * 2);
+    const uint32_t b_bytes = BKM ? (uint32_t)((((int64_t)(N - n0 - 1)) * ldb + K) * 2)
+                                 : (uint32_t)((((int64_t)(K - 1)) * ldb + (N - n0)) * 2);
+    ra = make_rsrc(ab, a_bytes);
+    rb = make_rsrc(bb, b_bytes);
+    la.init(lane, lda);
+    lb.init(lane, ldb);
+  }
+  __device__ __forceinline__ void open_pair(const bf16_t* a, const bf16_t* b, const bf16_t* b2, int64_t lda_,
+                                            int64_t ldb_, int K, int M, int N, int m0, int n0, int lane) {
+    static_assert(!PAIR || (AK && BKM), "paired weights are k-major");
+    open_raw(a, b, lda_, ldb_, K, M, N / 2, m0, n0 / 2, lane);
+    rb2 = make_rsrc(b2 + (int64_t)(n0 / 2) * ldb_, (uint32_t)((((int64_t)(N / 2 - n0 / 2 - 1)) * ldb_ + K) * 2));
+  }
+  __device__ __forceinline__ void open(const GemmKArgs& p, int s, int m0, int n0, int lane) {
+    open_raw(p.a[s], p.b[s], p.lda[s], p.ldb[s], p.K[s], p.M, p.N, m0, n0, lane);
+  }
+  // The same in NC pieces (piece C of the A loads and of the B loads), so that a wave can spread its
+  // loads between MFMAs; the cursor moves on with the last piece.
+  template <int C, int NC>
+  __device__ __forceinline__ void issue_piece(const GemmKArgs& segs, char* stage, int wave, int m0, int n0, int lane) {
+    constexpr int PA = TileLoader<BM, AK, NW>::PER_WAVE, PB = TileLoader<BN, BKM, NW>::PER_WAVE;
+    if (left > 0) {
+      la.template issue_range<C * PA / NC, (C + 1) * PA / NC>(ra, stage, wave, lda, k);
+      if constexpr (PAIR)
+        lb.template issue_pair_range<C * PB / NC, (C + 1) * PB / NC>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
+      else if constexpr (PERM)
+        lb.template issue_perm_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
+      else
+        lb.template issue_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
+      if constexpr (C + 1 == NC) advance(segs, m0, n0, lane);
+    }
+  }
+  // `segs`: the problem whose further K-segments follow (only read when nseg > 1)
+  __device__ __forceinline__ void issue_next(const GemmKArgs& segs, char* stage, int wave, int m0, int n0, int lane) {
+    if (left > 0) {
+      la.issue(ra, stage, wave, lda, k);
+      if constexpr (PAIR)
+        lb.template issue_pair_range<0, TileLoader<BN, BKM, NW>::PER_WAVE>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
+      else if constexpr (PERM)
+        lb.template issue_perm_range<0, TileLoader<BN, BKM, NW>::PER_WAVE>(rb, stage + BM * BK * 2, wave, ldb, k);
+      else
+        lb.issue(rb, stage + BM * BK * 2, wave, ldb, k);
+      advance(segs, m0, n0, lane);
+    }
+  }
+  // one K-step on: past the end of a segment the walk goes on in the next one, past the last in the first
+  __device__ __forceinline__ void advance(const GemmKArgs& segs, int m0, int n0, int lane) {
+    --left;
+    k += BK;
+    if (k == kend) {
+      k = 0;
+      if (nseg > 1 && left > 0) {
+        seg = seg + 1 == nseg ? 0 : seg + 1;
+        open(segs, seg, m0, n0, lane);
+      }
+    }
+  }
+};
+
+// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: give every XCD a contiguous
+// range of the tile sequence.
+__device__ __forceinline__ int xcd_contiguous(int id, int ntiles) {
+  const int per_xcd = ntiles >> 3;
+  return id < (per_xcd << 3) ? (id & 7) * per_xcd + (id >> 3) : id;
+}
+
+// Several independent problems of one operand layout in one grid: their tile sequences are laid end
+// to end, so the last, partly filled round of one problem runs alongside the first of the next.
+constexpr int MAX_GROUP = 8;
+struct GemmGroupKArgs {
+  GemmKArgs prob[MAX_GROUP];
+  int tile_start[MAX_GROUP + 1];
+  int n;
+  // rotary epilogue only (see EPI_ROPE): cos and sin of the angle of (position, pair), [seq][head_dim/2]
+  const float *rope_cos, *rope_sin;
+  int rope_seq, rope_dh, rope_layout;
+};
+// Problem i of a grouped launch, whose GemmGroupKArgs is the kernel's only argument: a reference into the constant
+// kernel-argument segment, so that a wave-uniform run-time index becomes scalar loads of the one problem (selecting
+// among all of them by compile-time index held eight problems in scalar registers and spilled two hundred).
+typedef const __attribute__((address_space(4))) GemmGroupKArgs ConstGroupKArgs;
+__device__ __forceinline__ const __attribute__((address_space(4))) GemmKArgs& group_problem(int i) {
+  static_assert(std::is_trivially_copyable<GemmGroupKArgs>::value, "read in place");
+  return ((ConstGroupKArgs*)__builtin_amdgcn_kernarg_segment_ptr())->prob[__builtin_amdgcn_readfirstlane(i)];
+}
+
+// Kernels of gemm_tile.hip: one tile per workgroup.
+enum class TileSize { T128x256, T128, T64 };
+enum class TileEpilogue { PLAIN, SWIGLU, SWIGLU_GRAD };
+int launch_gemm_tile(TileSize size, const GemmKArgs* ks, int n, bool a_kmajor, bool b_kmajor, TileEpilogue epi, const RopeEpilogue* rope,
+                     hipStream_t st);
+
+}  // namespace dl

@@ -26,11 +26,9 @@ int launch_rope_table(float* cos, float* sin, int64_t seq, int64_t head_dim, flo
 int launch_swiglu_fwd(const void* g, const void* u, int64_t n, void* a, hipStream_t st);
 int launch_swiglu_bwd(const void* g, const void* u, const void* da, int64_t n, void* dg, void* du,
                       hipStream_t st);
-// g, u: [rows, cols] with leading dimension ld_gu; a / da / dg / du with their own (padded) one
+// g, u: [rows, cols] with leading dimension ld_gu; a with its own (padded) one
 int launch_swiglu_fwd_rows(const void* g, const void* u, int64_t rows, int64_t cols, int64_t ld_gu, void* a,
                            int64_t ld_a, hipStream_t st);
-int launch_swiglu_bwd_rows(const void* g, const void* u, const void* da, int64_t rows, int64_t cols, int64_t ld_gu,
-                           int64_t ld_p, void* dg, void* du, hipStream_t st);
 // out[c][r] = in[r][c]; out has leading dimension ld_out >= R
 int launch_transpose(const void* in, void* out, int64_t R, int64_t C, int64_t ld_out, hipStream_t st);
 // up to 8 transposes (each R, C multiples of 64) in one launch
@@ -73,15 +71,12 @@ int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st);
 // cos, sin: [seq][head_dim / 2] fp32 (launch_rope_table); position of a row = row % seq.
 struct RopeEpilogue { const float *cos, *sin; int seq, head_dim, layout; unsigned rotate_mask; };
 int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, hipStream_t st);
-// g = x Wg^T, u = x Wu^T and a = silu(g) * u (from the rounded g, u) in one launch.  x [T, K] with
-// leading dimension ldx, wg and wu [F, K] with ldw, g and u with ldgu, a with lda.  Only shapes
-// gemm_swiglu_applies() accepts (enough 256 x 256 tiles to fill the chip).
-bool gemm_swiglu_applies(int64_t T, int64_t F);
+// g = x Wg^T, u = x Wu^T and a = silu(g) * u (from the fp32 sums) in one launch.  x [T, K] with
+// leading dimension ldx, wg and wu [F, K] with ldw, g and u with ldgu, a with lda.  F % 8 == 0.
 int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* wu, int64_t ldw, int64_t T, int64_t K,
                        int64_t F, void* g, void* u, int64_t ldgu, void* a, int64_t lda, hipStream_t st);
 // da = dy W^T for dy [T, K] (lddy) and wt = W [F, K] (ldw), then (dg, du) = gradient of silu(g) * u for
-// the rounded da, without da ever being stored.  g, u with ldgu; dg, du with ldd.
-bool gemm_swiglu_grad_applies(int64_t T, int64_t F);
+// the fp32 da, which is never stored.  g, u with ldgu; dg, du with ldd.
 int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* wt, int64_t ldw, int64_t T, int64_t K, int64_t F,
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
                             hipStream_t st);

@@ -78,3 +78,97 @@ def test_layer_with_split_key_blocks(K, override):
     g.backward()
     torch.cuda.synchronize()
     _check_layer(g, f, r, "split")
+
+
+# ------------------------------------------------------------------ products on every tile size and on two launches
+# rounding the fp32 sum to bf16 is off by 2^-9 of an element at most; 5 % more for the order of the fp32 sums
+ONE_ROUNDING = 1.05 * 2.0 ** -9
+
+
+@pytest.mark.parametrize("T,Kd,N,res", [
+    (1, 64, 8, False),            # one row, one K-step, one vector of columns
+    (65, 192, 136, True),         # 64 x 64 tiles, remainders on every side, fewer K-steps than ring stages
+    (1000, 1024, 1024, True),
+    (1920, 576, 1160, True),      # 128 x 128 tiles, ragged columns
+    (8192, 320, 768, False),      # 128 x 256 tiles
+    (4160, 448, 4288, True),      # full rounds of 256 x 256 tiles and a launch of small ones for the last rows
+    (16640, 128, 1096, False),    # the same, several row groups: the contraction starts elsewhere in each
+])
+def test_linear_forward_on_every_tile_size(K, T, Kd, N, res):
+    rng = np.random.default_rng(T + N)
+    xb, wb, rb = _rand_bits(rng, (T, Kd)), _rand_bits(rng, (N, Kd), 0.05), _rand_bits(rng, (T, N))
+    x, w, r = map(si.bf16_bits_to_f64, (xb, wb, rb))
+    xd, wd, rd = map(dev_bf16, (xb, wb, rb))
+    y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    K.linear_forward(xd, wd, rd if res else None, T, Kd, N, y)
+    assert _norm_err(y, x @ w.T + (r if res else 0.0)) <= ONE_ROUNDING
+    # a product has the same bits whatever kernel the number of rows selects
+    for rows in (T // 2, 1):
+        part = torch.full((max(rows, 1), N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        K.linear_forward(xd[:max(rows, 1)].contiguous(), wd, rd[:max(rows, 1)].contiguous() if res else None, max(rows, 1), Kd, N, part)
+        assert torch.equal(part.view(torch.int16), y[:max(rows, 1)].view(torch.int16)), rows
+
+
+@pytest.mark.parametrize("T,shapes", [
+    (64, [(64, 64)]),                                        # one tile, one K-step
+    (320, [(64, 192), (320, 64), (128, 128)]),               # 64 x 64 tiles, grouped
+    (1024, [(1152, 1152), (384, 1152), (1152, 3136)]),       # larger tiles
+    (192, [(4160, 4416), (64, 4288), (4416, 320)]),          # more than one round of 256 x 256 tiles: two launches
+])
+def test_weight_gradients_on_every_tile_size(K, T, shapes):
+    rng = np.random.default_rng(T + len(shapes))
+    dyb, xb = [_rand_bits(rng, (T, n)) for n, _ in shapes], [_rand_bits(rng, (T, k)) for _, k in shapes]
+    dyd, xd = [dev_bf16(b) for b in dyb], [dev_bf16(b) for b in xb]
+    dws = [torch.full((n, k), float("nan"), dtype=torch.bfloat16, device="cuda") for n, k in shapes]
+    K.linear_wgrad_group(dyd, xd, [n for n, _ in shapes], [k for _, k in shapes], T, dws, 0)
+    for i, (n, k) in enumerate(shapes):
+        assert _norm_err(dws[i], si.bf16_bits_to_f64(dyb[i]).T @ si.bf16_bits_to_f64(xb[i])) <= ONE_ROUNDING, i
+        one = torch.empty_like(dws[i])
+        K.linear_backward(xd[i], xd[i], dyd[i], T, k, n, None, one, 0, None)
+        assert torch.equal(one.view(torch.int16), dws[i].view(torch.int16)), f"grouped dw[{i}] differs from the single launch"
+
+
+@pytest.mark.parametrize("T,Kd,F", [(64, 64, 64), (200, 192, 104), (1920, 1152, 200), (1000, 64, 1608), (4160, 192, 2176)])
+def test_gated_pair_on_every_tile_size(K, T, Kd, F):
+    rng = np.random.default_rng(T + F)
+    xb, wgb, wub = _rand_bits(rng, (T, Kd)), _rand_bits(rng, (F, Kd), 0.1), _rand_bits(rng, (F, Kd), 0.1)
+    x, wg, wu = map(si.bf16_bits_to_f64, (xb, wgb, wub))
+    out = [torch.full((T, F), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    K.linear_swiglu_forward(dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub), T, Kd, F, *out)
+    g, u = x @ wg.T, x @ wu.T
+    for name, got, ref in zip("gua", out, (g, u, odl.swiglu_fwd(g, u))):
+        assert _norm_err(got, ref) <= ONE_ROUNDING, name
+
+
+@pytest.mark.parametrize("T,D,F", [(64, 64, 64), (192, 128, 320), (1920, 192, 1152), (4160, 64, 4288)])
+def test_activation_gradient_on_every_tile_size(K, T, D, F):
+    rng = np.random.default_rng(T + F)
+    dyb, wb, gb, ub = _rand_bits(rng, (T, D)), _rand_bits(rng, (D, F), 0.1), _rand_bits(rng, (T, F)), _rand_bits(rng, (T, F))
+    dy, w, g, u = map(si.bf16_bits_to_f64, (dyb, wb, gb, ub))
+    dg, du = (torch.full((T, F), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    K.linear_swiglu_backward(dev_bf16(dyb), dev_bf16(wb), dev_bf16(gb), dev_bf16(ub), T, D, F, dg, du,
+                             _poisoned(K.linear_swiglu_backward_workspace_bytes(T, D, F)))
+    for name, got, ref in zip(("dg", "du"), (dg, du), odl.swiglu_bwd(g, u, dy @ w)):
+        assert _norm_err(got, ref) <= ONE_ROUNDING, name
+
+
+@pytest.mark.parametrize("B,S,D,Hq,Hkv,dh,layout", [
+    (1, 128, 64, 2, 1, 64, 0),       # 64 x 64 tiles: a head per tile
+    (1, 192, 64, 4, 2, 32, 0),       # two heads per tile
+    (3, 320, 128, 3, 1, 128, 1),     # adjacent pairs: a 128-wide head spans two 64-column tiles
+    (5, 384, 192, 9, 9, 128, 0),     # 128 x 128 tiles: split pairs of 128-wide heads
+    (3, 2816, 64, 12, 12, 64, 0),    # full rounds of 256 x 256 tiles, then small ones: positions go on across the cut
+])
+def test_rotary_projections_on_every_tile_size(K, B, S, D, Hq, Hkv, dh, layout):
+    rng = np.random.default_rng(S + dh)
+    T, QD, KD = B * S, Hq * dh, Hkv * dh
+    hb, wqb, wkb, wvb = (_rand_bits(rng, s, std) for s, std in (((T, D), 1.0), ((QD, D), 0.1), ((KD, D), 0.1), ((KD, D), 0.1)))
+    h, wq, wk, wv = map(si.bf16_bits_to_f64, (hb, wqb, wkb, wvb))
+    phi = odl.rope_angles(S, dh, 1e4)
+    refs = (odl.rope_rotate((h @ wq.T).reshape(B, S, Hq, dh), phi, layout=layout),
+            odl.rope_rotate((h @ wk.T).reshape(B, S, Hkv, dh), phi, layout=layout), h @ wv.T)
+    out = [torch.full((T, n), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (QD, KD, KD)]
+    K.qkv_rope_forward(*map(dev_bf16, (hb, wqb, wkb, wvb)), B, S, D, Hq, Hkv, dh, 1e4, layout, *out,
+                       _poisoned(K.qkv_rope_workspace_bytes(S, dh)))
+    for name, got, ref in zip("qkv", out, refs):
+        assert _norm_err(got, ref) <= ONE_ROUNDING, name
