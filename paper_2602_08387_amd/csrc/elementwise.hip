@@ -68,189 +68,191 @@ int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, f
 }
 
 // ------------------------------------------------------------------------------------------
-// RMSNorm backward.  Each wavefront walks rows with a grid stride, writes dx for its rows and
-// keeps the gain-gradient partial sums of its columns in registers; the block then folds its
-// waves through LDS and writes one fp32 partial row; a second kernel sums the partial rows.
+// RMSNorm backward.  TPR threads share a row, one 16-byte vector each (two beyond 8192 columns); a workgroup of RG such
+// groups walks rows with a grid stride, two at a time (one beyond 8192 columns), writes dx and keeps the gain-gradient sums of its columns in
+// registers, folds its groups through LDS and writes one fp32 partial row; a second kernel sums the partial
+// rows.  Bound by HBM (8 bytes per element with the residual gradient).  A thread that holds one vector of a row
+// needs 60 registers where a wave that holds the whole row needs 160, and the residual row is asked for together with
+// the others, so four times the loads are in flight; rows of any width are read once.
 // ------------------------------------------------------------------------------------------
-constexpr int kRmsBwdWaves = 8;
-constexpr int kRmsBwdChunk = 4096;   // columns a wave keeps gain-gradient sums for (8 vectors of 8 per lane)
-
-// mean_d(dh * gamma * xhat) per row, for rows wider than one chunk: one wave per row at a time
-__global__ __launch_bounds__(256) void rms_dot_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
-                                                      const float* __restrict__ rstd, const bf16_t* __restrict__ dh,
-                                                      float* __restrict__ dot, int64_t T, int D) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nvec = D >> 3;
-  for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < T; row += (int64_t)gridDim.x * 4) {
-    const bf16x8* xr = reinterpret_cast<const bf16x8*>(x + row * D);
-    const bf16x8* dr = reinterpret_cast<const bf16x8*>(dh + row * D);
-    const bf16x8* gr = reinterpret_cast<const bf16x8*>(gamma);
-    const float r = rstd[row];
-    float s = 0.f;
-    for (int c = lane; c < nvec; c += 64) {
-      const bf16x8 xv = xr[c], dv = dr[c], gv = gr[c];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += (float)dv[e] * (float)gv[e] * ((float)xv[e] * r);
-    }
-    s = wave_sum(s);
-    if (lane == 0) dot[row] = s / (float)D;
-  }
-}
-
-template <int NV>
-__global__ __launch_bounds__(64 * kRmsBwdWaves) void rmsnorm_bwd_kernel(
+template <int TPR, int NV>
+__global__ __launch_bounds__(TPR < 256 ? 256 : TPR) void rmsnorm_bwd_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma, const float* __restrict__ rstd,
-    const bf16_t* __restrict__ dh, const bf16_t* dres, bf16_t* dx, float* __restrict__ partial,
-    int64_t T, int D, const float* __restrict__ dot_in) {
-  // Rows wider than 4096 are handled in column chunks of 4096, one per blockIdx.y, with the row's
-  // mean_d(dxhat * xhat) taken from dot_in (a kernel of its own computes it first); gridDim.y == 1 and
-  // dot_in == nullptr is the one-pass case.
-  extern __shared__ float red[];  // [kRmsBwdWaves][Dc]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int base = blockIdx.y * kRmsBwdChunk;
-  const int Dc = gridDim.y == 1 ? D : min(kRmsBwdChunk, D - base);
-  x += base; dh += base; dx += base; gamma += base;
-  if (dres) dres += base;
-  const int nvec = Dc >> 3;
-  float dg[NV][8];
-  bf16x8 gv[NV];
+    const bf16_t* __restrict__ dh, const bf16_t* dres, bf16_t* dx, float* __restrict__ partial, int64_t T, int D) {
+  constexpr int RG = TPR < 256 ? 256 / TPR : 1, WPR = TPR / 64, U = NV == 1 ? 2 : 1;
+  __shared__ float red[2][RG][U][WPR];
+  __shared__ float fold[RG > 1 ? RG * TPR * NV * 8 : 1];
+  const int rg = threadIdx.x / TPR, tr = threadIdx.x % TPR, lane = threadIdx.x & 63, wave = tr >> 6;
+  const int nvec = D >> 3;
+  float dg[NV][8], gv[NV][8];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int c = i * 64 + lane;
-    if (c < nvec) gv[i] = reinterpret_cast<const bf16x8*>(gamma)[c];
+    const int c = i * TPR + tr;
+    bf16x8 g = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (c < nvec) g = reinterpret_cast<const bf16x8*>(gamma)[c];
+    unpack8(g, gv[i]);
 #pragma unroll
     for (int e = 0; e < 8; ++e) dg[i][e] = 0.f;
   }
-  const int64_t wstride = (int64_t)gridDim.x * kRmsBwdWaves;
-  for (int64_t row = (int64_t)blockIdx.x * kRmsBwdWaves + wave; row < T; row += wstride) {
-    const bf16x8* xr = reinterpret_cast<const bf16x8*>(x + row * D);
-    const bf16x8* dr = reinterpret_cast<const bf16x8*>(dh + row * D);
-    const float r = rstd[row];
-    bf16x8 xv[NV], dv[NV];
-    float dot = 0.f;
+  const float inv_d = 1.0f / (float)D;
+  const int64_t stride = (int64_t)gridDim.x * RG;
+  int par = 0;
+  for (int64_t base = (int64_t)blockIdx.x * RG; base < T; base += U * stride, par ^= 1) {
+    bf16x8 xv[U][NV], dv[U][NV], rv[U][NV];
+    float r[U], dot[U];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int c = i * 64 + lane;
-      if (c < nvec) {
-        xv[i] = xr[c];
-        dv[i] = dr[c];
+    for (int u = 0; u < U; ++u) {
+      const int64_t row = base + u * stride + rg;
+      const bool row_ok = row < T;
+      r[u] = row_ok ? rstd[row] : 0.f;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = i * TPR + tr;
+        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+        xv[u][i] = dv[u][i] = rv[u][i] = zero;
+        if (row_ok && c < nvec) {
+          xv[u][i] = reinterpret_cast<const bf16x8*>(x + row * D)[c];
+          dv[u][i] = reinterpret_cast<const bf16x8*>(dh + row * D)[c];
+          if (dres) rv[u][i] = reinterpret_cast<const bf16x8*>(dres + row * D)[c];
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      dot[u] = 0.f;
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float xh = (float)xv[i][e] * r, d = (float)dv[i][e];
+          const float xh = (float)xv[u][i][e] * r[u], d = (float)dv[u][i][e];
           dg[i][e] += d * xh;
-          dot += d * (float)gv[i][e] * xh;
+          dot[u] += d * gv[i][e] * xh;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int u = 0; u < U; ++u) dot[u] += __shfl_xor(dot[u], o, 64);
+    if constexpr (WPR > 1) {
+      // two sets of slots in turn: a wave writes a set again only after a barrier that every reader of it has passed
+      if (lane == 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) red[par][rg][u][wave] = dot[u];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        dot[u] = red[par][rg][u][0];
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) dot[u] += red[par][rg][u][w];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t row = base + u * stride + rg;
+      if (row >= T) continue;
+      const float mean = dot[u] * inv_d;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = i * TPR + tr;
+        if (c < nvec) {
+          bf16x8 o;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float xh = (float)xv[u][i][e] * r[u];
+            o[e] = (bf16_t)(r[u] * ((float)dv[u][i][e] * gv[i][e] - xh * mean) + (float)rv[u][i][e]);
+          }
+          reinterpret_cast<bf16x8*>(dx + row * D)[c] = o;
         }
       }
     }
-    dot = dot_in ? dot_in[row] : wave_sum(dot) / (float)D;
-    bf16x8* oxr = reinterpret_cast<bf16x8*>(dx + row * D);
-    const bf16x8* rr = dres ? reinterpret_cast<const bf16x8*>(dres + row * D) : nullptr;
+  }
+  if constexpr (RG > 1) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) fold[(rg * NV + i) * TPR * 8 + tr * 8 + e] = dg[i][e];
+    __syncthreads();
+    for (int c = threadIdx.x; c < D; c += 256) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < RG; ++w) s += fold[w * NV * TPR * 8 + c];
+      partial[(int64_t)blockIdx.x * D + c] = s;
+    }
+  } else {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int c = i * 64 + lane;
+      const int c = i * TPR + tr;
       if (c < nvec) {
-        bf16x8 o, rs;
-        if (rr) rs = rr[c];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float xh = (float)xv[i][e] * r;
-          float g = r * ((float)dv[i][e] * (float)gv[i][e] - xh * dot);
-          if (rr) g += (float)rs[e];
-          o[e] = (bf16_t)g;
-        }
-        oxr[c] = o;
+        f32x4* p = reinterpret_cast<f32x4*>(partial + (int64_t)blockIdx.x * D) + c * 2;
+        p[0] = f32x4{dg[i][0], dg[i][1], dg[i][2], dg[i][3]};
+        p[1] = f32x4{dg[i][4], dg[i][5], dg[i][6], dg[i][7]};
       }
     }
-  }
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int c = i * 64 + lane;
-    if (c < nvec) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) red[wave * Dc + c * 8 + e] = dg[i][e];
-    }
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < Dc; c += blockDim.x) {
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < kRmsBwdWaves; ++w) s += red[w * Dc + c];
-    partial[(int64_t)blockIdx.x * D + base + c] = s;
   }
 }
 
-// Column sums of the per-block partial rows: 256 threads = 32 columns x 8 row groups, folded through LDS.
-__global__ __launch_bounds__(256) void colsum_partials_kernel(const float* __restrict__ partial, int nrows, int D,
-                                                              bf16_t* out, int accumulate) {
-  __shared__ float red[8][33];
+// Column sums of the per-block partial rows: 1024 threads = 32 columns x 32 row groups, folded through LDS.  Four loads in
+// flight per thread and 32 groups: the kernel is a chain of load latencies (512 rows: 7 us with 8 groups).
+__global__ __launch_bounds__(1024) void colsum_partials_kernel(const float* __restrict__ partial, int nrows, int D,
+                                                               bf16_t* out, int accumulate) {
+  __shared__ float red[32][33];
   const int cl = threadIdx.x & 31, rg = threadIdx.x >> 5;
   const int c = blockIdx.x * 32 + cl;
-  // four loads in flight per thread: the loop is latency-bound otherwise (20 us for 512 rows)
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   if (c < D) {
     int r = rg;
-    for (; r + 24 < nrows; r += 32) {
+    for (; r + 96 < nrows; r += 128) {
       s0 += partial[(int64_t)r * D + c];
-      s1 += partial[(int64_t)(r + 8) * D + c];
-      s2 += partial[(int64_t)(r + 16) * D + c];
-      s3 += partial[(int64_t)(r + 24) * D + c];
+      s1 += partial[(int64_t)(r + 32) * D + c];
+      s2 += partial[(int64_t)(r + 64) * D + c];
+      s3 += partial[(int64_t)(r + 96) * D + c];
     }
-    for (; r < nrows; r += 8) s0 += partial[(int64_t)r * D + c];
+    for (; r < nrows; r += 32) s0 += partial[(int64_t)r * D + c];
   }
   red[rg][cl] = (s0 + s1) + (s2 + s3);
   __syncthreads();
   if (rg == 0 && c < D) {
     float t = 0.f;
 #pragma unroll
-    for (int g = 0; g < 8; ++g) t += red[g][cl];
+    for (int g = 0; g < 32; ++g) t += red[g][cl];
     if (accumulate) t += (float)out[c];
     out[c] = (bf16_t)t;
   }
 }
 
-static int rms_bwd_blocks(int64_t T) {
-  int64_t b = (T + kRmsBwdWaves - 1) / kRmsBwdWaves;
-  return (int)(b < 512 ? b : 512);
+// threads per row, and workgroups (= partial rows): enough of them for every CU's registers, few enough that the partial
+// rows stay small next to the tensors
+static int rms_bwd_tpr(int64_t D) { return D <= 512 ? 64 : D <= 1024 ? 128 : D <= 2048 ? 256 : D <= 4096 ? 512 : 1024; }
+static int rms_bwd_blocks(int64_t T, int64_t D) {
+  const int tpr = rms_bwd_tpr(D), rg = tpr < 256 ? 256 / tpr : 1;
+  const int64_t b = (T + rg - 1) / rg, most = tpr <= 256 ? 1024 : 512;
+  return (int)(b < most ? b : most);
 }
-size_t rmsnorm_bwd_workspace(int64_t T, int64_t D) {
-  return (size_t)rms_bwd_blocks(T) * D * sizeof(float) + (D > kRmsBwdChunk ? (size_t)T * sizeof(float) : 0);
-}
+size_t rmsnorm_bwd_workspace(int64_t T, int64_t D) { return (size_t)rms_bwd_blocks(T, D) * D * sizeof(float); }
 
 int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,
                        const void* dres, int64_t T, int64_t D, void* dx, void* dgamma,
                        int accumulate, void* workspace, hipStream_t st) {
-  const int nchunk = (int)((D + kRmsBwdChunk - 1) / kRmsBwdChunk);
-  const int64_t Dc = nchunk == 1 ? D : kRmsBwdChunk;       // widest chunk
-  const int nv = (int)((Dc / 8 + 63) / 64);
-  const int nb = rms_bwd_blocks(T);
-  const size_t lds = (size_t)kRmsBwdWaves * Dc * sizeof(float);
+  const int nb = rms_bwd_blocks(T, D);
   float* partial = (float*)workspace;
-  float* dot = nullptr;
-  if (nchunk > 1) {
-    dot = partial + (size_t)nb * D;
-    hipLaunchKernelGGL(rms_dot_kernel, dim3((unsigned)(T < 4096 ? (T + 3) / 4 : 1024)), dim3(256), 0, st, (const bf16_t*)x,
-                       (const bf16_t*)gamma, rstd, (const bf16_t*)dh, dot, T, (int)D);
-    if (int rc = check_launch("rmsnorm_backward(dot)")) return rc;
+#define RMS_BWD(TPR, NV)                                                                                     \
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<TPR, NV>), dim3(nb), dim3(TPR < 256 ? 256 : TPR), 0, st, (const bf16_t*)x, \
+                     (const bf16_t*)gamma, rstd, (const bf16_t*)dh, (const bf16_t*)dres, (bf16_t*)dx, partial, T, (int)D)
+  switch (rms_bwd_tpr(D)) {
+    case 64: RMS_BWD(64, 1); break;
+    case 128: RMS_BWD(128, 1); break;
+    case 256: RMS_BWD(256, 1); break;
+    case 512: RMS_BWD(512, 1); break;
+    default:
+      if (D <= 8192) RMS_BWD(1024, 1);
+      else RMS_BWD(1024, 2);
   }
-  dim3 grid(nb, nchunk), block(64 * kRmsBwdWaves);
-#define RMS_BWD(NV)                                                                             \
-  do {                                                                                          \
-    static std::atomic<unsigned long long> lds_done{0};                                                     \
-    if (int rc_ = reserve_lds(rmsnorm_bwd_kernel<NV>, (size_t)kRmsBwdWaves * NV * 512 * sizeof(float), lds_done,        \
-                              "rmsnorm_backward")) return rc_;                                  \
-    hipLaunchKernelGGL(rmsnorm_bwd_kernel<NV>, grid, block, lds, st, (const bf16_t*)x,          \
-                       (const bf16_t*)gamma, rstd, (const bf16_t*)dh, (const bf16_t*)dres,      \
-                       (bf16_t*)dx, partial, T, (int)D, (const float*)dot);                     \
-  } while (0)
-  if (nv <= 1) RMS_BWD(1);
-  else if (nv <= 2) RMS_BWD(2);
-  else if (nv <= 4) RMS_BWD(4);
-  else RMS_BWD(8);
 #undef RMS_BWD
   int rc = check_launch("rmsnorm_backward");
   if (rc) return rc;
-  hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)((D + 31) / 32)), dim3(256), 0, st,
-                     (const float*)workspace, nb, (int)D, (bf16_t*)dgamma, accumulate);
+  hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)((D + 31) / 32)), dim3(1024), 0, st, (const float*)partial, nb, (int)D,
+                     (bf16_t*)dgamma, accumulate);
   return check_launch("rmsnorm_backward(dgamma)");
 }
 
