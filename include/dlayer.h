@@ -148,7 +148,7 @@ int ce_loss_fwd_bwd_static(const void* logits, const int64_t* targets, int64_t T
 /*
  * The LM head and its loss in one call, without ever holding all T x V logits (same training loss):
  *   logits = h w_lm^T;  loss, dlogits as in ce_loss_fwd_bwd;  dh = dlogits w_lm;  dw_lm (+)= dlogits^T h
- * The rows are walked in chunks of chunk_rows (0 = chosen by the library: about 1 GiB of logits):
+ * The rows are walked in chunks of chunk_rows (0 = chosen by the library: about 2 GiB of logits):
  * each chunk's logits are formed, turned into their gradient in place and consumed by the two
  * gradient products before the next chunk overwrites them.  dw_lm is accumulated in bf16 from chunk
  * to chunk (fp32 within a chunk), so it is rounded once per chunk instead of once.

@@ -350,10 +350,10 @@ int ce_loss_fwd_bwd_static(const void* logits, const int64_t* targets, int64_t T
 static int64_t lm_head_chunk(int64_t T, int64_t V, int64_t chunk_rows) {
   int64_t c = chunk_rows;
   if (c <= 0) {
-    // about 1 GiB of logits: at V = 128256 that is 4096 rows, where the call costs what the unchunked
-    // route does (21 ms at T = 8192, D = 4096); with 2048 rows it is 20 % slower, the weight gradient
-    // being re-read and re-rounded once per chunk and its products having a shorter contraction
-    c = (((int64_t)1 << 30) / (V * 2)) / 256 * 256;
+    // about 2 GiB of logits: every chunk re-reads and re-rounds the weight gradient and gives the products fewer tiles, so
+    // a chunk is as large as one buffer descriptor and 288 GB allow without a second thought.  T = 8192, V = 128256:
+    // D = 2048 11.7 ms in two chunks of 4096 rows, 10.7 ms in one of 8192.
+    c = (((int64_t)1 << 31) / (V * 2)) / 256 * 256;
     if (c < 256) c = 256;
   }
   return c < T ? c : T;
