@@ -276,9 +276,9 @@ int embed_forward(const void* table, const int64_t* ids, int64_t T, int64_t V, i
 /* dtable[v, :] = sum over t with ids[t] == v of dx0[t, :] (rows of absent ids are zero; ids outside
  * [0, V) are skipped).  Deterministic: the tokens of an id are listed, sorted and summed in fp32 in
  * ascending token order (interleaved partial sums, combined in a fixed order), bf16 result; no
- * floating-point atomics, bitwise reproducible.  An id with more than four tokens is summed by one
+ * floating-point atomics, bitwise reproducible.  An id with more than 64 tokens is summed by one
  * workgroup per 128 columns, whatever its frequency.  dtable [V, D] bf16 is overwritten.
- * workspace (device): embed_backward_workspace_bytes(T, V), about (3 V + 2.2 T) ints.         */
+ * workspace (device): embed_backward_workspace_bytes(T, V), about (2 V + 2.2 T) ints.         */
 size_t embed_backward_workspace_bytes(int64_t T, int64_t V);
 int embed_backward(const void* dx0, const int64_t* ids, int64_t T, int64_t V, int64_t D,
                    void* dtable, void* workspace, void* stream);

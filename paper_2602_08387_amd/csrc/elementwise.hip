@@ -555,64 +555,213 @@ int launch_embed_fwd(const void* table, const int64_t* ids, int64_t T, int64_t V
 // Embedding gradient dtable[v] = sum of the rows dx0[t] with ids[t] == v, deterministic and without
 // floating-point atomics.  The tokens of every id are gathered into a list (integer atomics: which slot
 // a token gets depends on scheduling, the SET of tokens in a list does not), the list is sorted, and
-// the rows are summed in ascending token order by a fixed assignment of rows to partial sums.  So the
-// result is bitwise reproducible.  Ids with up to four tokens (one workgroup each) and ids with more (a
-// sorting pass, then one workgroup per 128 columns) take different kernels; which one depends on the
-// count alone.
-//   count[v]   tokens with id v                       (embed_count_kernel)
-//   start[v]   first slot of id v's segment of list   (embed_segments_kernel)
-//   list[...]  token indices grouped by id, slot[t] = position of t in list    (embed_fill_kernel)
-//   owner of an id = the token that drew the first slot of its group: its workgroups sum the rows
+// the rows are summed by a fixed assignment of ranks to partial sums.  So the result is bitwise
+// reproducible.
+//   count[v]   tokens with id v; slot[t] = the token's place among them      (embed_count_kernel)
+//   start[v]   first slot of id v's segment of list                          (embed_segments_kernel)
+//   list[...]  token indices grouped by id, slot[t] = position of t in list  (embed_fill_kernel)
+// Then one launch sums the rows with tokens, ids with few, with some and with many of them on workgroups of their own
+// (T = 8192, V = 128256, D = 4096, Zipf ids: 53 us where three launches took 109), and another zeroes the rows
+// without (0.97 of 1.05 GB, 165 us, 6.3 TB/s: the floor of the whole; both in one launch, side by side, take longer
+// than one after the other).  The hot counters - the commonest word's, the cursor - take one atomic per wavefront or
+// workgroup, not one per token: same-address atomics are served one after the other and cost 16 to 20 us in each of
+// three kernels at that shape, 5 us now.
 // ------------------------------------------------------------------------------------------
-constexpr int kEmbSortMax = 8192;   // tokens of one id that are sorted in LDS (ids beyond that are walked)
-constexpr int kEmbVecPerBlock = 16; // 16-byte column vectors per workgroup (128 columns) of the heavy kernel
-constexpr int kEmbLight = 4;        // ids with at most this many tokens: one workgroup sums the whole row, no LDS
+constexpr int kEmbThreads = 512;
+constexpr int kEmbVecs = 16;        // 16-byte column vectors per workgroup (128 columns) of a heavy id
+constexpr int kEmbGroups = kEmbThreads / kEmbVecs;   // partial sums of a heavy id: the row of rank r goes to sum r % 32
+constexpr int kEmbLight = 4;        // ids with at most this many tokens: one wavefront sums the row, tokens sorted in registers
+constexpr int kEmbMedium = 64;      // up to here one workgroup sums the row; beyond, one per 128 columns
+constexpr int kEmbListMax = 4096;   // sorted tokens held in LDS at a time
+constexpr int kEmbWordsMax = 4096;  // 32-bit words of the sorting bitmap: 131072 tokens at a time
+constexpr int kEmbSegIds = 4096;    // ids per workgroup of embed_segments_kernel
 
 __global__ __launch_bounds__(256) void embed_zero_ints_kernel(int* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
 }
 
-__global__ __launch_bounds__(256) void embed_count_kernel(const int64_t* __restrict__ ids, int T, int64_t V, int* count) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const int64_t id = ids[t];
-  if (id >= 0 && id < V) atomicAdd(&count[id], 1);
+// One atomic per distinct id of a wavefront: its first lane with the id adds their number, the others take their
+// place behind its answer.
+__global__ __launch_bounds__(256) void embed_count_kernel(const int64_t* __restrict__ ids, int T, int64_t V, int* count,
+                                                          int* __restrict__ slot) {
+  const int t = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+  const int64_t id64 = t < T ? ids[t] : -1;
+  const bool ok = id64 >= 0 && id64 < V;
+  const int id = ok ? (int)id64 : -1;
+  unsigned long long left = __ballot(ok);
+  unsigned long long mine = 0;
+  while (left) {
+    const int first = __builtin_ctzll(left);
+    const unsigned long long same = __ballot(ok && id == __builtin_amdgcn_readlane(id, first));
+    if ((same >> lane) & 1) mine = same;
+    left &= ~same;
+  }
+  // all leaders' atomics go out together
+  const int leader = mine ? __builtin_ctzll(mine) : lane;
+  int base = 0;
+  if (ok && lane == leader) base = atomicAdd(&count[id], __builtin_popcountll(mine));
+  base = __shfl(base, leader, 64);
+  if (t < T) slot[t] = ok ? base + __builtin_popcountll(mine & ((1ull << lane) - 1)) : -1;
 }
 
-// start[v] = first slot of id v's segment of `list`.  The segments only have to be disjoint, not in id
-// order, so they are handed out from a running cursor: one atomic per wavefront (the lanes' counts are
-// prefix-summed with shuffles).  Where a segment lands depends on scheduling; what it holds does not.
-__global__ __launch_bounds__(256) void embed_segments_kernel(const int* __restrict__ count, int* __restrict__ start, int V,
-                                                             int* cursor) {
-  const int v = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
-  const int c = v < V ? count[v] : 0;
-  int incl = c;
+// Sum of v over the lanes before this one; total of the wavefront in `total`.
+__device__ __forceinline__ int wave_prefix(int v, int lane, int& total) {
+  int incl = v;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const int x = __shfl_up(incl, off, 64);
     if (lane >= off) incl += x;
   }
-  const int total = __shfl(incl, 63, 64);
-  int base = 0;
-  if (lane == 63 && total > 0) base = atomicAdd(cursor, total);
-  base = __shfl(base, 63, 64);
-  if (v < V) start[v] = base + incl - c;
+  total = __shfl(incl, 63, 64);
+  return incl - v;
 }
 
-__global__ __launch_bounds__(256) void embed_fill_kernel(const int64_t* __restrict__ ids, int T, int64_t V,
-                                                         const int* __restrict__ count, const int* __restrict__ start, int* fill,
-                                                         int* __restrict__ list, int* __restrict__ slot, int* heavy,
-                                                         int* n_heavy) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const int64_t id = ids[t];
-  if (id < 0 || id >= V) { slot[t] = -1; return; }
-  const int first = start[id], s = first + atomicAdd(&fill[id], 1);
-  list[s] = t;
-  slot[t] = s;
-  // ids with more than kEmbLight tokens are summed by the heavy kernel; the order of this list does not
-  // matter (every entry is worked on independently)
-  if (s == first && count[id] > kEmbLight) heavy[atomicAdd(n_heavy, 1)] = (int)id;
+// start[v] = first slot of id v's segment of `list`.  The segments only have to be disjoint, not in id
+// order, so they are handed out from a running cursor: one atomic per workgroup.  Where a segment lands depends on
+// scheduling; what it holds does not.
+__global__ __launch_bounds__(1024) void embed_segments_kernel(const int* __restrict__ count, int* __restrict__ start, int V,
+                                                              int* cursor) {
+  __shared__ int wsum[16], wbase[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int v0 = blockIdx.x * kEmbSegIds + threadIdx.x * 4;
+  int c[4], mine = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { c[i] = v0 + i < V ? count[v0 + i] : 0; mine += c[i]; }
+  int total;
+  int off = wave_prefix(mine, lane, total);
+  if (lane == 0) wsum[wave] = total;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int run = 0;
+    for (int w = 0; w < 16; ++w) { wbase[w] = run; run += wsum[w]; }
+    const int base = run > 0 ? atomicAdd(cursor, run) : 0;
+    for (int w = 0; w < 16; ++w) wbase[w] += base;
+  }
+  __syncthreads();
+  off += wbase[wave];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (v0 + i < V) start[v0 + i] = off;
+    off += c[i];
+  }
+}
+
+__global__ __launch_bounds__(256) void embed_fill_kernel(const int64_t* __restrict__ ids, int T, const int* __restrict__ count,
+                                                         const int* __restrict__ start, int* __restrict__ list,
+                                                         int* __restrict__ slot, int* __restrict__ many, int most, int* n_many) {
+  const int t = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+  const int place = t < T ? slot[t] : -1;   // -1: an id outside the table
+  int cls = -1, id = 0;
+  if (place >= 0) {
+    id = (int)ids[t];
+    const int s = start[id] + place;
+    list[s] = t;
+    slot[t] = s;
+    if (place == 0) cls = count[id] > kEmbMedium ? 1 : count[id] > kEmbLight ? 0 : -1;
+  }
+  // ids with more than kEmbLight tokens: the medium ones from the front of `many`, the heavy ones from its back; the order
+  // does not matter (the entries are independent)
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const unsigned long long m = __ballot(cls == k);
+    if (!m) continue;
+    int base = 0;
+    if (lane == __builtin_ctzll(m)) base = atomicAdd(n_many + k, __builtin_popcountll(m));
+    base = __shfl(base, __builtin_ctzll(m), 64) + __builtin_popcountll(m & ((1ull << lane) - 1));
+    if (cls == k) many[k == 0 ? base : most - 1 - base] = id;
+  }
+}
+
+// Rows of an id with more than kEmbMedium tokens, 128 columns per workgroup.  Its tokens are brought into ascending order
+// in LDS - up to 512 by counting the smaller ones, more through a bitmap of the tokens whose words are prefix-summed
+// - a piece of the token range at a time, so that a piece holds at most kEmbListMax of them.
+__device__ __forceinline__ void embed_sum_heavy(const bf16_t* __restrict__ dx0, const int* __restrict__ count,
+                                                const int* __restrict__ start, const int* __restrict__ list, int64_t id, int split,
+                                                bf16_t* __restrict__ dtable, int T, int D, char* lds) {
+  int* lst = reinterpret_cast<int*>(lds);
+  unsigned* bits = reinterpret_cast<unsigned*>(lst + kEmbListMax);
+  float(*part)[kEmbVecs][8] = reinterpret_cast<float(*)[kEmbVecs][8]>(bits);   // after the last use of the bitmap
+  __shared__ int wsum[kEmbThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int vec = tid % kEmbVecs, grp = tid / kEmbVecs;
+  const int cvec = split * kEmbVecs + vec;
+  const bool col_ok = cvec < (D >> 3);
+  const bf16_t* col = dx0 + (col_ok ? cvec * 8 : 0);
+  const int first = start[id], L = count[id];
+  const int piece = L <= kEmbListMax ? kEmbWordsMax * 32 : kEmbListMax;
+  float a[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] = 0.f;
+  for (int lo = 0; lo < T; lo += piece) {
+    int n = 0;
+    __syncthreads();   // the list and the partial sums of the piece or id before have been read
+    if (L <= kEmbThreads) {
+      // one pass, whatever the token range
+      const int mine = tid < L ? list[first + tid] : 0;
+      if (tid < L) reinterpret_cast<int*>(bits)[tid] = mine;
+      __syncthreads();
+      if (tid < L) {
+        int rank = 0;
+        for (int j = 0; j < L; ++j) rank += reinterpret_cast<const int*>(bits)[j] < mine;
+        lst[rank] = mine;
+      }
+      n = L;
+    } else {
+      const int hi = lo + piece < T ? lo + piece : T, words = (hi - lo + 31) >> 5;
+      for (int w = tid; w < words; w += kEmbThreads) bits[w] = 0u;
+      __syncthreads();
+      for (int i = tid; i < L; i += kEmbThreads) {
+        const int t = list[first + i] - lo;
+        if (t >= 0 && t < hi - lo) atomicOr(&bits[t >> 5], 1u << (t & 31));
+      }
+      __syncthreads();
+      const int per = (words + kEmbThreads - 1) / kEmbThreads, w0 = tid * per, w1 = w0 + per < words ? w0 + per : words;
+      int mine = 0, total;
+      for (int w = w0; w < w1; ++w) mine += __builtin_popcount(bits[w]);
+      int o = wave_prefix(mine, lane, total);
+      if (lane == 0) wsum[wave] = total;
+      __syncthreads();
+      for (int w = 0; w < kEmbThreads / 64; ++w) { if (w < wave) o += wsum[w]; n += wsum[w]; }
+      for (int w = w0; w < w1; ++w) {
+        unsigned m = bits[w];
+        while (m) { lst[o++] = lo + w * 32 + __builtin_ctz(m); m &= m - 1; }
+      }
+    }
+    __syncthreads();
+    if (col_ok) {
+      int j = grp;
+      for (; j + 7 * kEmbGroups < n; j += 8 * kEmbGroups) {   // eight rows in flight
+        bf16x8 r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = *reinterpret_cast<const bf16x8*>(col + (int64_t)lst[j + q * kEmbGroups] * D);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) a[e] += (float)r[q][e];
+      }
+      for (; j < n; j += kEmbGroups) {
+        const bf16x8 r0 = *reinterpret_cast<const bf16x8*>(col + (int64_t)lst[j] * D);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] += (float)r0[e];
+      }
+    }
+    if (L <= kEmbThreads) break;
+  }
+  __syncthreads();   // the bitmap (or the unsorted list in its place) has been read
+#pragma unroll
+  for (int e = 0; e < 8; ++e) part[grp][vec][e] = a[e];
+  __syncthreads();
+  // pairwise in a fixed order, one thread per column
+  if (tid < kEmbVecs * 8 && split * kEmbVecs * 8 + tid < D) {
+    float q[kEmbGroups];
+#pragma unroll
+    for (int g = 0; g < kEmbGroups; ++g) q[g] = part[g][tid >> 3][tid & 7];
+#pragma unroll
+    for (int w = 1; w < kEmbGroups; w <<= 1)
+#pragma unroll
+      for (int g = 0; g < kEmbGroups; g += 2 * w) q[g] += q[g + w];
+    dtable[id * D + split * kEmbVecs * 8 + tid] = (bf16_t)q[0];
+  }
 }
 
 // rows of dtable no token points at
@@ -626,201 +775,139 @@ __global__ __launch_bounds__(256) void embed_zero_rows_kernel(const int* __restr
   }
 }
 
-// Ids with at most kEmbLight tokens (nearly all of them unless the ids are very skewed).  One workgroup
-// per token; the token that owns its id sorts the id's few tokens in registers and sums their rows with the
-// same rule as the heavy kernel: row of rank r to partial sum r % 4, then (s0 + s1) + (s2 + s3).
-__global__ __launch_bounds__(256) void embed_sum_light_kernel(const bf16_t* __restrict__ dx0, const int64_t* __restrict__ ids,
-                                                              const int* __restrict__ count, const int* __restrict__ start,
-                                                              const int* __restrict__ list, const int* __restrict__ slot,
-                                                              bf16_t* __restrict__ dtable, int T, int64_t V, int D) {
-  const int t = blockIdx.x;
+// The rows with tokens.  Workgroups [0, n_hb * n_cs): the heavy ids, column split by column split; n_mb: the medium ids;
+// the rest: ids of up to kEmbLight tokens, a wavefront per token (the first of its id does the work).
+__global__ __launch_bounds__(kEmbThreads, 8) void embed_grad_kernel(
+    const bf16_t* __restrict__ dx0, const int64_t* __restrict__ ids, const int* __restrict__ count,
+    const int* __restrict__ start, const int* __restrict__ list, const int* __restrict__ slot, const int* __restrict__ many,
+    int most, const int* __restrict__ n_many, bf16_t* __restrict__ dtable, int T, int D, int n_hb, int n_cs, int n_mb) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int nvec = D >> 3, tid = threadIdx.x;
+  int b = blockIdx.x;
+  if (b < n_hb * n_cs) {
+    const int nh = n_many[1];
+    for (int hi = b / n_cs; hi < nh; hi += n_hb) embed_sum_heavy(dx0, count, start, list, many[most - 1 - hi], b % n_cs, dtable, T, D, lds);
+    return;
+  }
+  b -= n_hb * n_cs;
+  if (b < n_mb) {
+    int* tmp = reinterpret_cast<int*>(lds);
+    int* lst = tmp + kEmbMedium;
+    const int nm = n_many[0];
+    for (int mi = b; mi < nm; mi += n_mb) {
+      const int64_t id = many[mi];
+      const int first = start[id], L = count[id];
+      __syncthreads();   // the list of the id before has been read
+      const int mine = tid < L ? list[first + tid] : 0;
+      if (tid < L) tmp[tid] = mine;
+      __syncthreads();
+      if (tid < L) {
+        int rank = 0;
+        for (int j = 0; j < L; ++j) rank += tmp[j] < mine;
+        lst[rank] = mine;
+      }
+      __syncthreads();
+      for (int c = tid; c < nvec; c += kEmbThreads) {
+        const bf16_t* col = dx0 + c * 8;
+        float a[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] = 0.f;
+        int j = 0;
+        for (; j + 8 <= L; j += 8) {
+          bf16x8 r[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) r[q] = *reinterpret_cast<const bf16x8*>(col + (int64_t)lst[j + q] * D);
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[e] += (float)r[q][e];
+        }
+        for (; j < L; ++j) {
+          const bf16x8 r0 = *reinterpret_cast<const bf16x8*>(col + (int64_t)lst[j] * D);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) a[e] += (float)r0[e];
+        }
+        *reinterpret_cast<bf16x8*>(dtable + id * D + c * 8) = pack8(a);
+      }
+    }
+    return;
+  }
+  b -= n_mb;
+  constexpr int WPB = kEmbThreads / 64;
+  const int t = b * WPB + __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (t >= T) return;
+  // The tokens, sorted in registers, go to partial sum rank % 4, then (s0 + s1) + (s2 + s3).
+  const int s = slot[t];
+  if (s < 0) return;
   const int64_t id = ids[t];
-  if (id < 0 || id >= V) return;
-  const int first = start[id], L = count[id];
-  if (slot[t] != first || L > kEmbLight) return;
+  const int L = count[id];
+  if (L > kEmbLight || s != start[id]) return;
   int r[kEmbLight];
 #pragma unroll
-  for (int i = 0; i < kEmbLight; ++i) r[i] = i < L ? list[first + i] : T;
+  for (int i = 0; i < kEmbLight; ++i) r[i] = i < L ? list[s + i] : T;
 #pragma unroll
   for (int i = 0; i < kEmbLight; ++i)       // sorting network for four keys (padding sorts last)
 #pragma unroll
     for (int j = 0; j + 1 < kEmbLight - i; ++j)
       if (r[j] > r[j + 1]) { const int x = r[j]; r[j] = r[j + 1]; r[j + 1] = x; }
   static_assert(kEmbLight == 4, "one row per partial sum");
-  for (int c = threadIdx.x; c < (D >> 3); c += 256) {
-    float a[4][8];
+#pragma unroll 2
+  for (int c = lane; c < nvec; c += 64) {
+    bf16x8 v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      bf16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (i < L) v = *reinterpret_cast<const bf16x8*>(dx0 + (int64_t)r[i] * D + c * 8);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) a[i][e] = (float)v[e];
+      const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+      v[i] = zero;
+      if (i < L) v[i] = *reinterpret_cast<const bf16x8*>(dx0 + (int64_t)r[i] * D + c * 8);
     }
     bf16x8 o;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((a[0][e] + a[1][e]) + (a[2][e] + a[3][e]));
+    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)(((float)v[0][e] + (float)v[1][e]) + ((float)v[2][e] + (float)v[3][e]));
     *reinterpret_cast<bf16x8*>(dtable + id * D + c * 8) = o;
   }
 }
 
-// Sorts the token list of every id on the heavy list, in place: one workgroup per id at a time.  Lists
-// of up to kEmbSortMax tokens go through a bitonic network in LDS; a longer one is rebuilt in order by
-// walking all ids (a bitmap per piece of kEmbSortMax tokens, positions from prefix sums of its words).
-__global__ __launch_bounds__(1024) void embed_sort_kernel(const int64_t* __restrict__ ids, const int* __restrict__ count,
-                                                         const int* __restrict__ start, int* list,
-                                                         const int* __restrict__ heavy, const int* __restrict__ n_heavy, int T) {
-  __shared__ int lst[kEmbSortMax];
-  __shared__ unsigned bits[kEmbSortMax / 32];
-  __shared__ int wpre[kEmbSortMax / 32 + 1];
-  const int nh = *n_heavy;
-  for (int hi = blockIdx.x; hi < nh; hi += gridDim.x) {
-    const int64_t id = heavy[hi];
-    const int first = start[id], L = count[id];
-    __syncthreads();   // the previous id's list has been written back
-    if (L <= kEmbSortMax) {
-      int n2 = 1;
-      while (n2 < L) n2 <<= 1;
-      for (int i = threadIdx.x; i < n2; i += 1024) lst[i] = i < L ? list[first + i] : T;
-      __syncthreads();
-      for (int k = 2; k <= n2; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-          for (int i = threadIdx.x; i < n2; i += 1024) {
-            const int p = i ^ j;
-            if (p > i) {
-              const int x = lst[i], y = lst[p];
-              const bool up = (i & k) == 0;
-              if ((x > y) == up) { lst[i] = y; lst[p] = x; }
-            }
-          }
-          __syncthreads();
-        }
-      for (int i = threadIdx.x; i < L; i += 1024) list[first + i] = lst[i];
-    } else {
-      int rank = 0;
-      for (int base = 0; base < T; base += kEmbSortMax) {
-        __syncthreads();
-        for (int w = threadIdx.x; w < kEmbSortMax / 32; w += 1024) bits[w] = 0u;
-        __syncthreads();
-        for (int k = threadIdx.x; k < kEmbSortMax; k += 1024)
-          if (base + k < T && ids[base + k] == id) atomicOr(&bits[k >> 5], 1u << (k & 31));
-        __syncthreads();
-        if (threadIdx.x == 0) {
-          int run = 0;
-          for (int w = 0; w < kEmbSortMax / 32; ++w) { wpre[w] = run; run += __builtin_popcount(bits[w]); }
-          wpre[kEmbSortMax / 32] = run;
-        }
-        __syncthreads();
-        for (int w = threadIdx.x; w < kEmbSortMax / 32; w += 1024) {
-          unsigned m = bits[w];
-          int o = first + rank + wpre[w];
-          while (m) { list[o++] = base + w * 32 + __builtin_ctz(m); m &= m - 1; }
-        }
-        rank += wpre[kEmbSortMax / 32];
-      }
-    }
-  }
-}
-
-// Sums the rows of every id on the heavy list, whose token lists are sorted by now.  grid (workgroups,
-// column splits of 128 columns); a workgroup is 16 column vectors x 16 row groups: the row of rank r goes
-// to partial sum r % 16 (each summed in ascending token order), and the 16 partial sums are combined
-// pairwise in a fixed order.
-__global__ __launch_bounds__(256) void embed_sum_kernel(const bf16_t* __restrict__ dx0, const int* __restrict__ count,
-                                                        const int* __restrict__ start, const int* __restrict__ list,
-                                                        const int* __restrict__ heavy, const int* __restrict__ n_heavy,
-                                                        bf16_t* __restrict__ dtable, int D) {
-  __shared__ float part[16][kEmbVecPerBlock][8];
-  const int vec = threadIdx.x & (kEmbVecPerBlock - 1), grp = threadIdx.x / kEmbVecPerBlock;
-  const int cvec = blockIdx.y * kEmbVecPerBlock + vec;
-  const bool col_ok = cvec < (D >> 3);
-  const int nh = *n_heavy;
-  for (int hi = blockIdx.x; hi < nh; hi += gridDim.x) {
-    const int64_t id = heavy[hi];
-    const int* lst = list + start[id];
-    const int L = count[id];
-    float a[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) a[e] = 0.f;
-    if (col_ok) {
-      const bf16_t* col = dx0 + cvec * 8;
-      int j = grp;
-      for (; j + 112 < L; j += 128) {   // eight rows in flight
-        bf16x8 r[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) r[q] = *reinterpret_cast<const bf16x8*>(col + (int64_t)lst[j + 16 * q] * D);
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) a[e] += (float)r[q][e];
-      }
-      for (; j < L; j += 16) {
-        const bf16x8 r0 = *reinterpret_cast<const bf16x8*>(col + (int64_t)lst[j] * D);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[e] += (float)r0[e];
-      }
-    }
-    __syncthreads();   // the previous id's partial sums have been read
-#pragma unroll
-    for (int e = 0; e < 8; ++e) part[grp][vec][e] = a[e];
-    __syncthreads();
-    if (grp == 0 && col_ok) {
-      bf16x8 o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float q[16];
-#pragma unroll
-        for (int g = 0; g < 16; ++g) q[g] = part[g][vec][e];
-#pragma unroll
-        for (int w = 1; w < 16; w <<= 1)
-#pragma unroll
-          for (int g = 0; g < 16; g += 2 * w) q[g] += q[g + w];
-        o[e] = (bf16_t)q[0];
-      }
-      *reinterpret_cast<bf16x8*>(dtable + id * D + cvec * 8) = o;
-    }
-  }
-}
-
-// count[V], fill[V], the heavy-id counter and the segment cursor (padded to 4 ints), start[V], list[T], slot[T],
-// heavy[T / 5 + 1]
-size_t embed_bwd_workspace(int64_t T, int64_t V) { return (size_t)(3 * V + 4 + 2 * T + T / (kEmbLight + 1) + 1) * sizeof(int); }
+// count[V], the counters of medium and heavy ids and the segment cursor (padded to 4 ints), start[V], list[T], slot[T],
+// many[T / 5 + 1]
+size_t embed_bwd_workspace(int64_t T, int64_t V) { return (size_t)(2 * V + 4 + 2 * T + T / (kEmbLight + 1) + 1) * sizeof(int); }
 
 int launch_embed_bwd(const void* dx0, const int64_t* ids, int64_t T, int64_t V, int64_t D,
                      void* dtable, void* workspace, hipStream_t st) {
   int* count = (int*)workspace;
-  int* fill = count + V;
-  int* n_heavy = fill + V;
-  int* start = n_heavy + 4;
+  int* n_many = count + V;
+  int* start = n_many + 4;
   int* list = start + V;
   int* slot = list + T;
-  int* heavy = slot + T;
+  int* many = slot + T;
+  const int64_t most = T / (kEmbLight + 1) + 1;
   const unsigned tb = (unsigned)((T + 255) / 256);
-  const int64_t zn = 2 * V + 4, zb = (zn + 255) / 256;
+  const int64_t zn = V + 4, zb = (zn + 255) / 256;
   hipLaunchKernelGGL(embed_zero_ints_kernel, dim3((unsigned)(zb < 2048 ? zb : 2048)), dim3(256), 0, st, count, zn);
   if (int rc = check_launch("embed_backward(clear)")) return rc;
-  hipLaunchKernelGGL(embed_count_kernel, dim3(tb), dim3(256), 0, st, ids, (int)T, V, count);
+  hipLaunchKernelGGL(embed_count_kernel, dim3(tb), dim3(256), 0, st, ids, (int)T, V, count, slot);
   if (int rc = check_launch("embed_backward(count)")) return rc;
-  hipLaunchKernelGGL(embed_segments_kernel, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, (const int*)count, start, (int)V,
-                     n_heavy + 1);
+  hipLaunchKernelGGL(embed_segments_kernel, dim3((unsigned)((V + kEmbSegIds - 1) / kEmbSegIds)), dim3(1024), 0, st, (const int*)count,
+                     start, (int)V, n_many + 2);
   if (int rc = check_launch("embed_backward(segments)")) return rc;
-  hipLaunchKernelGGL(embed_fill_kernel, dim3(tb), dim3(256), 0, st, ids, (int)T, V, (const int*)count, (const int*)start, fill,
-                     list, slot, heavy, n_heavy);
+  hipLaunchKernelGGL(embed_fill_kernel, dim3(tb), dim3(256), 0, st, ids, (int)T, (const int*)count, (const int*)start, list, slot,
+                     many, (int)most, n_many);
   if (int rc = check_launch("embed_backward(fill)")) return rc;
+  // Half of the chip's 1024 workgroup slots for the heavy ids, as many for the medium ones; a workgroup that finds no id
+  // ends at once.
+  const int64_t cs = (D / 8 + kEmbVecs - 1) / kEmbVecs, max_heavy = T / (kEmbMedium + 1);
+  int64_t hb = 512 / cs > 0 ? 512 / cs : 1, mb = most < 512 ? most : 512;
+  if (hb > max_heavy) hb = max_heavy;
+  const int64_t lb = (T + kEmbThreads / 64 - 1) / (kEmbThreads / 64);
+  constexpr size_t lds = kEmbListMax * sizeof(int) + (kEmbWordsMax > kEmbThreads * 8 ? kEmbWordsMax : kEmbThreads * 8) * 4;
+  static std::atomic<unsigned long long> lds_done{0};
+  if (int rc = reserve_lds(embed_grad_kernel, lds, lds_done, "embed_backward")) return rc;
+  hipLaunchKernelGGL(embed_grad_kernel, dim3((unsigned)(hb * cs + mb + lb)), dim3(kEmbThreads), lds, st, (const bf16_t*)dx0, ids,
+                     (const int*)count, (const int*)start, (const int*)list, (const int*)slot, (const int*)many, (int)most,
+                     (const int*)n_many, (bf16_t*)dtable, (int)T, (int)D, (int)hb, (int)cs, (int)mb);
+  if (int rc = check_launch("embed_backward")) return rc;
   hipLaunchKernelGGL(embed_zero_rows_kernel, dim3((unsigned)(V < 16384 ? V : 16384)), dim3(256), 0, st, (const int*)count,
                      (u32x4*)dtable, V, (int)(D / 8));
-  if (int rc = check_launch("embed_backward(zero)")) return rc;
-  hipLaunchKernelGGL(embed_sum_light_kernel, dim3((unsigned)T), dim3(256), 0, st, (const bf16_t*)dx0, ids, (const int*)count,
-                     (const int*)start, (const int*)list, (const int*)slot, (bf16_t*)dtable, (int)T, V, (int)D);
-  if (int rc = check_launch("embed_backward(light)")) return rc;
-  const unsigned cs = (unsigned)((D / 8 + kEmbVecPerBlock - 1) / kEmbVecPerBlock);
-  const int64_t max_heavy = T / (kEmbLight + 1) + 1;
-  hipLaunchKernelGGL(embed_sort_kernel, dim3((unsigned)(max_heavy < 1024 ? max_heavy : 1024)), dim3(1024), 0, st, ids,
-                     (const int*)count, (const int*)start, list, (const int*)heavy, (const int*)n_heavy, (int)T);
-  if (int rc = check_launch("embed_backward(sort)")) return rc;
-  hipLaunchKernelGGL(embed_sum_kernel, dim3((unsigned)(max_heavy < 256 ? max_heavy : 256), cs), dim3(256), 0, st,
-                     (const bf16_t*)dx0, (const int*)count, (const int*)start, (const int*)list, (const int*)heavy,
-                     (const int*)n_heavy, (bf16_t*)dtable, (int)D);
-  return check_launch("embed_backward");
+  return check_launch("embed_backward(zero)");
 }
 
 }  // namespace dl

@@ -195,3 +195,32 @@ def test_rmsnorm_backward_on_every_row_split(K, T, D):
     K.rmsnorm_backward(xd, gd, rstdd, dhd, dresd, T, D, dresd, dg, 1, ws)     # in place over dres, gain gradient accumulated
     assert _norm_err(dresd, dx_ref + dres) <= ONE_ROUNDING
     assert _norm_err(dg, host_f64(first) + dg_ref) <= ONE_ROUNDING
+
+
+# ------------------------------------------------------------------ embedding gradient: light, medium and heavy ids, pieces
+@pytest.mark.parametrize("V,D,T,counts", [
+    (3, 8, 1, [1]),                              # one token
+    (70, 72, 1000, [4, 5, 63, 64, 65, 512, 200]),# both sides of every class, ids without tokens
+    (9, 1032, 1200, [513, 600]),                 # the bitmap; nine column splits, the last one partly filled
+    (4, 16, 6000, [4096, 1800]),                 # a full list
+    (4, 16, 9000, [4097, 4800]),                 # more tokens than the list holds: walked in pieces
+    (5, 8, 140000, [3000, 65, 4]),               # tokens beyond one bitmap (131072)
+])
+def test_embedding_gradient_by_token_counts(K, V, D, T, counts):
+    rng = np.random.default_rng(T + V)
+    ids = np.full(T, -1, dtype=np.int64)         # ids outside the table are skipped
+    at = rng.permutation(T)[:sum(counts)]
+    ids[at] = np.repeat(np.arange(len(counts)) % V, counts)
+    db = _rand_bits(rng, (T, D))
+    d = si.bf16_bits_to_f64(db)
+    ref = np.zeros((V, D))
+    np.add.at(ref, ids[at], d[at])
+    dd, idd = dev_bf16(db), torch.from_numpy(ids).cuda()
+    runs = []
+    for _ in range(2):
+        got = torch.full((V, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+        K.embed_backward(dd, idd, T, V, D, got, _poisoned(K.embed_backward_workspace_bytes(T, V)))
+        runs.append(got)
+    assert _norm_err(runs[0], ref) <= ONE_ROUNDING
+    assert not host_f64(runs[0])[ref.any(axis=1) == False].any()   # noqa: E712
+    assert torch.equal(runs[0].view(torch.int16), runs[1].view(torch.int16))
