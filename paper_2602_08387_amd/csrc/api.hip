@@ -123,7 +123,7 @@ static Saved carve_saved(const dlayer_cfg* c, void* p) {
 }
 
 struct Work {
-  void *da_dg, *du, *dh2, *dy1, *d_o, *dq, *dk, *dv, *dh1, *attn_ws, *rms_ws;
+  void *da_dg, *du, *dh2, *dy1, *d_o, *dq, *dk, *dv, *dh1, *attn_ws, *rms_ws1, *rms_ws2;
   void *h1, *h2, *a;   // the activations a recomputing configuration does not keep in `saved` (null otherwise)
   void *wqT, *wkT, *wvT, *woT, *wgT, *wuT, *wdT;   // W^T copies: the input-gradient products then read both operands k-major
   size_t bytes;
@@ -143,7 +143,8 @@ static Work carve_work(const dlayer_cfg* c, void* p) {
   w.dv = cv.take(T * KD * 2);
   w.dh1 = cv.take(T * D * 2);
   w.attn_ws = cv.take(attention_bwd_workspace(c->batch, c->seq, c->n_q_heads, c->n_kv_heads, c->head_dim));
-  w.rms_ws = cv.take(rmsnorm_bwd_workspace(T, D));
+  w.rms_ws1 = cv.take(rmsnorm_bwd_workspace(T, D));
+  w.rms_ws2 = cv.take(rmsnorm_bwd_workspace(T, D));
   w.wqT = cv.take(QD * D * 2); w.wkT = cv.take(KD * D * 2); w.wvT = cv.take(KD * D * 2); w.woT = cv.take(D * QD * 2);
   w.wgT = cv.take(D * padded_ff(c) * 2); w.wuT = cv.take(D * padded_ff(c) * 2); w.wdT = cv.take(D * F * 2);
   w.h1 = (c->recompute & DLAYER_RECOMPUTE_NORMS) ? cv.take(T * D * 2) : nullptr;
@@ -234,8 +235,7 @@ int dlayer_forward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* w
     if (!s.h1) { s.h1 = k.h1; s.h2 = k.h2; }
     if (!s.a) s.a = k.a;
   }
-  TRY(launch_rmsnorm_fwd(x, w->g_attn, T, D, cfg->rms_eps, s.h1, s.rstd1, st));
-  TRY(launch_rope_table(s.rope_cos, s.rope_sin, S, dh, cfg->rope_base, st));
+  TRY(launch_rmsnorm_fwd_rope_table(x, w->g_attn, T, D, cfg->rms_eps, s.h1, s.rstd1, s.rope_cos, s.rope_sin, S, dh, cfg->rope_base, st));
   {
     // q, k and v in one launch: their tile sequences run end to end (k and v alone do not fill the chip
     // for small layers); q and k leave the epilogue rotated, from the fp32 sums
@@ -285,7 +285,7 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
     const void* dys[2] = {k.da_dg, k.du}; const void* ws[2] = {k.wgT, k.wuT}; const int64_t ns[2] = {F, F};
     TRY(gemm_dgrad_t(2, dys, ws, ns, Fp, T, D, k.dh2, D, st));
   }
-  TRY(launch_rmsnorm_bwd(s.y1, w->g_mlp, s.rstd2, k.dh2, dy, T, D, k.dy1, dw->g_mlp, acc, k.rms_ws, st));
+  TRY(launch_rmsnorm_bwd_rows(s.y1, w->g_mlp, s.rstd2, k.dh2, dy, T, D, k.dy1, k.rms_ws2, st));
   // y1 = x + o Wo^T
   {
     const void* dys[1] = {k.dy1}; const void* ws[1] = {k.woT}; const int64_t ns[1] = {D};
@@ -299,13 +299,13 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
     const int64_t ns[3] = {QD, KD, KD};
     TRY(gemm_dgrad_t(3, dys, ws, ns, 0, T, D, k.dh1, D, st));
   }
-  TRY(launch_rmsnorm_bwd(x, w->g_attn, s.rstd1, k.dh1, k.dy1, T, D, dx, dw->g_attn, acc, k.rms_ws, st));
+  TRY(launch_rmsnorm_bwd_rows(x, w->g_attn, s.rstd1, k.dh1, k.dy1, T, D, dx, k.rms_ws1, st));
+  TRY(launch_rmsnorm_bwd_gain(k.rms_ws1, dw->g_attn, k.rms_ws2, dw->g_mlp, T, D, acc, st));
   // Recomputing configurations: the normalised activations and the SwiGLU output are only operands of
   // the weight gradients; they are rebuilt here from x, y1 (with the saved statistics) and from g, u.
   if (!s.h1) {
     s.h1 = k.h1; s.h2 = k.h2;
-    TRY(launch_rmsnorm_fwd(x, w->g_attn, T, D, cfg->rms_eps, s.h1, s.rstd1, st));
-    TRY(launch_rmsnorm_fwd(s.y1, w->g_mlp, T, D, cfg->rms_eps, s.h2, s.rstd2, st));
+    TRY(launch_rmsnorm_fwd_pair(x, w->g_attn, s.h1, s.rstd1, s.y1, w->g_mlp, s.h2, s.rstd2, T, D, cfg->rms_eps, st));
   }
   if (!s.a) {
     s.a = k.a;

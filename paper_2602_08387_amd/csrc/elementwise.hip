@@ -9,16 +9,43 @@
 namespace dl {
 
 // ------------------------------------------------------------------------------------------
-// RMSNorm forward: one wavefront per token row, the row stays in registers.
+// RMSNorm forward: one wavefront per token row, the row stays in registers.  A launch takes one or two norms of the
+// same shape, and may carry the rotary table (the angles as cos and sin for the kernels that rotate inside another
+// pass, the q/k projection epilogue and the attention backward stores) on workgroups of its own behind them: for
+// small layers a launch costs more than its work (5 us each for the table and for the second norm at T = 1920).
 // ------------------------------------------------------------------------------------------
-template <int NV>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restrict__ x,
-                                                          const bf16_t* __restrict__ gamma,
-                                                          bf16_t* __restrict__ h,
-                                                          float* __restrict__ rstd, int64_t T,
-                                                          int D, float eps) {
+struct RmsFwdJob { const bf16_t *x, *gamma; bf16_t* h; float* rstd; };
+struct RopeTableJob { float *cs, *sn; int seq, half; double log2_base; };
+
+// angle p * base^(-i / half) of (position p, pair i) in fp64, stored as fp32 [seq][half]
+__device__ __forceinline__ void rope_table_entry(const RopeTableJob& r, int idx) {
+  if (idx >= r.seq * r.half) return;
+  const int p = idx / r.half, i = idx % r.half;
+  const double theta = exp2(-(double)i / (double)r.half * r.log2_base);
+  double s, c;
+  sincos((double)p * theta, &s, &c);
+  r.cs[idx] = (float)c;
+  r.sn[idx] = (float)s;
+}
+
+template <int NV, bool ROPE>
+__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const RmsFwdJob ja, const RmsFwdJob jb, int blocks, int norms, int64_t T,
+                                                          int D, float eps, const RopeTableJob rope) {
+  int b = blockIdx.x;
+  if constexpr (ROPE) {
+    if (b >= blocks * norms) {
+      rope_table_entry(rope, (b - blocks * norms) * 256 + (int)threadIdx.x);
+      return;
+    }
+  }
+  const bool second = b >= blocks;
+  if (second) b -= blocks;
+  const bf16_t* x = second ? jb.x : ja.x;
+  const bf16_t* gamma = second ? jb.gamma : ja.gamma;
+  bf16_t* h = second ? jb.h : ja.h;
+  float* rstd = second ? jb.rstd : ja.rstd;
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)b * 4 + (threadIdx.x >> 6);
   if (row >= T) return;
   const int nvec = D >> 3;
   const bf16x8* xr = reinterpret_cast<const bf16x8*>(x + row * D);
@@ -50,13 +77,13 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* __restri
   }
 }
 
-int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h,
-                       float* rstd, hipStream_t st) {
+template <bool ROPE>
+static int launch_rms_jobs(const RmsFwdJob& ja, const RmsFwdJob& jb, int norms, int64_t T, int64_t D, float eps,
+                           const RopeTableJob& rope, hipStream_t st) {
   const int nv = (int)((D / 8 + 63) / 64);
-  dim3 grid((unsigned)((T + 3) / 4)), block(256);
-#define RMS_FWD(NV)                                                                             \
-  hipLaunchKernelGGL(rmsnorm_fwd_kernel<NV>, grid, block, 0, st, (const bf16_t*)x,              \
-                     (const bf16_t*)gamma, (bf16_t*)h, rstd, T, (int)D, eps)
+  const int64_t blocks = (T + 3) / 4, table = ROPE ? ((int64_t)rope.seq * rope.half + 255) / 256 : 0;
+  dim3 grid((unsigned)(blocks * norms + table)), block(256);
+#define RMS_FWD(NV) hipLaunchKernelGGL((rmsnorm_fwd_kernel<NV, ROPE>), grid, block, 0, st, ja, jb, (int)blocks, norms, T, (int)D, eps, rope)
   if (nv <= 1) RMS_FWD(1);
   else if (nv <= 2) RMS_FWD(2);
   else if (nv <= 4) RMS_FWD(4);
@@ -65,6 +92,22 @@ int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, f
   else RMS_FWD(32);
 #undef RMS_FWD
   return check_launch("rmsnorm_forward");
+}
+
+int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h,
+                       float* rstd, hipStream_t st) {
+  const RmsFwdJob j{(const bf16_t*)x, (const bf16_t*)gamma, (bf16_t*)h, rstd};
+  return launch_rms_jobs<false>(j, j, 1, T, D, eps, RopeTableJob{}, st);
+}
+int launch_rmsnorm_fwd_pair(const void* xa, const void* ga, void* ha, float* ra, const void* xb, const void* gb, void* hb, float* rb,
+                            int64_t T, int64_t D, float eps, hipStream_t st) {
+  const RmsFwdJob ja{(const bf16_t*)xa, (const bf16_t*)ga, (bf16_t*)ha, ra}, jb{(const bf16_t*)xb, (const bf16_t*)gb, (bf16_t*)hb, rb};
+  return launch_rms_jobs<false>(ja, jb, 2, T, D, eps, RopeTableJob{}, st);
+}
+int launch_rmsnorm_fwd_rope_table(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h, float* rstd, float* cos,
+                                  float* sin, int64_t seq, int64_t head_dim, float base, hipStream_t st) {
+  const RmsFwdJob j{(const bf16_t*)x, (const bf16_t*)gamma, (bf16_t*)h, rstd};
+  return launch_rms_jobs<true>(j, j, 1, T, D, eps, RopeTableJob{cos, sin, (int)seq, (int)(head_dim / 2), log2((double)base)}, st);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -192,11 +235,14 @@ __global__ __launch_bounds__(TPR < 256 ? 256 : TPR) void rmsnorm_bwd_kernel(
   }
 }
 
-// Column sums of the per-block partial rows: 1024 threads = 32 columns x 32 row groups, folded through LDS.  Four loads in
-// flight per thread and 32 groups: the kernel is a chain of load latencies (512 rows: 7 us with 8 groups).
-__global__ __launch_bounds__(1024) void colsum_partials_kernel(const float* __restrict__ partial, int nrows, int D,
-                                                               bf16_t* out, int accumulate) {
+// Column sums of the per-block partial rows, of one or two norms (blockIdx.y): 1024 threads = 32 columns x 32 row
+// groups, folded through LDS.  Four loads in flight per thread and 32 groups: the kernel is a chain of load latencies
+// (512 rows: 7 us with 8 groups, 5 us with 32).
+__global__ __launch_bounds__(1024) void colsum_partials_kernel(const float* __restrict__ pa, const float* __restrict__ pb, int nrows,
+                                                               int D, bf16_t* outa, bf16_t* outb, int accumulate) {
   __shared__ float red[32][33];
+  const float* partial = blockIdx.y ? pb : pa;
+  bf16_t* out = blockIdx.y ? outb : outa;
   const int cl = threadIdx.x & 31, rg = threadIdx.x >> 5;
   const int c = blockIdx.x * 32 + cl;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
@@ -231,9 +277,8 @@ static int rms_bwd_blocks(int64_t T, int64_t D) {
 }
 size_t rmsnorm_bwd_workspace(int64_t T, int64_t D) { return (size_t)rms_bwd_blocks(T, D) * D * sizeof(float); }
 
-int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,
-                       const void* dres, int64_t T, int64_t D, void* dx, void* dgamma,
-                       int accumulate, void* workspace, hipStream_t st) {
+int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd, const void* dh,
+                            const void* dres, int64_t T, int64_t D, void* dx, void* workspace, hipStream_t st) {
   const int nb = rms_bwd_blocks(T, D);
   float* partial = (float*)workspace;
 #define RMS_BWD(TPR, NV)                                                                                     \
@@ -249,11 +294,21 @@ int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, cons
       else RMS_BWD(1024, 2);
   }
 #undef RMS_BWD
-  int rc = check_launch("rmsnorm_backward");
-  if (rc) return rc;
-  hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)((D + 31) / 32)), dim3(1024), 0, st, (const float*)partial, nb, (int)D,
-                     (bf16_t*)dgamma, accumulate);
+  return check_launch("rmsnorm_backward");
+}
+
+int launch_rmsnorm_bwd_gain(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D,
+                            int accumulate, hipStream_t st) {
+  hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)((D + 31) / 32), dgamma_b ? 2 : 1), dim3(1024), 0, st, (const float*)ws_a,
+                     (const float*)ws_b, rms_bwd_blocks(T, D), (int)D, (bf16_t*)dgamma_a, (bf16_t*)dgamma_b, accumulate);
   return check_launch("rmsnorm_backward(dgamma)");
+}
+
+int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,
+                       const void* dres, int64_t T, int64_t D, void* dx, void* dgamma,
+                       int accumulate, void* workspace, hipStream_t st) {
+  if (int rc = launch_rmsnorm_bwd_rows(x, gamma, rstd, dh, dres, T, D, dx, workspace, st)) return rc;
+  return launch_rmsnorm_bwd_gain(workspace, dgamma, nullptr, nullptr, T, D, accumulate, st);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -301,10 +356,8 @@ __device__ __forceinline__ void rope_rotate_row(bf16_t* zt, const float* cs, con
   }
 }
 
-// z2 (n_heads2 heads per token) is an optional second tensor rotated by the same angles: q and k of
-// a layer in one launch, with the fp64 trigonometry done once.
-__global__ __launch_bounds__(256) void rope_kernel(bf16_t* z, bf16_t* z2, int seq, int n_heads, int n_heads2,
-                                                   int head_dim, double log2_base, int layout, int inverse) {
+__global__ __launch_bounds__(256) void rope_kernel(bf16_t* z, int seq, int n_heads, int head_dim, double log2_base, int layout,
+                                                   int inverse) {
   __shared__ float cs[64], sn[64];
   const int64_t tok = blockIdx.x;
   const int p = (int)(tok % seq);
@@ -318,41 +371,22 @@ __global__ __launch_bounds__(256) void rope_kernel(bf16_t* z, bf16_t* z2, int se
   }
   __syncthreads();
   rope_rotate_row(z + tok * (int64_t)n_heads * head_dim, cs, sn, n_heads, head_dim, layout);
-  if (z2) rope_rotate_row(z2 + tok * (int64_t)n_heads2 * head_dim, cs, sn, n_heads2, head_dim, layout);
 }
 
 int launch_rope(void* z, int64_t batch, int64_t seq, int64_t n_heads, int64_t head_dim,
                 float base, int layout, int inverse, hipStream_t st) {
-  hipLaunchKernelGGL(rope_kernel, dim3((unsigned)(batch * seq)), dim3(256), 0, st, (bf16_t*)z, (bf16_t*)nullptr,
-                     (int)seq, (int)n_heads, 0, (int)head_dim, log2((double)base), layout, inverse);
+  hipLaunchKernelGGL(rope_kernel, dim3((unsigned)(batch * seq)), dim3(256), 0, st, (bf16_t*)z, (int)seq,
+                     (int)n_heads, (int)head_dim, log2((double)base), layout, inverse);
   return check_launch("rope_apply");
 }
 
-int launch_rope_pair(void* q, void* k, int64_t batch, int64_t seq, int64_t n_q_heads, int64_t n_kv_heads,
-                     int64_t head_dim, float base, int layout, int inverse, hipStream_t st) {
-  hipLaunchKernelGGL(rope_kernel, dim3((unsigned)(batch * seq)), dim3(256), 0, st, (bf16_t*)q, (bf16_t*)k, (int)seq,
-                     (int)n_q_heads, (int)n_kv_heads, (int)head_dim, log2((double)base), layout, inverse);
-  return check_launch("rope_apply(q, k)");
-}
-
-// The angles as a table for the kernels that rotate inside another pass (the q/k projection epilogue,
-// the attention backward stores): one thread per (position, pair).
-__global__ __launch_bounds__(256) void rope_table_kernel(float* __restrict__ cs, float* __restrict__ sn, int seq, int half,
-                                                         double log2_base) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= seq * half) return;
-  const int p = idx / half, i = idx % half;
-  const double theta = exp2(-(double)i / (double)half * log2_base);
-  double s, c;
-  sincos((double)p * theta, &s, &c);
-  cs[idx] = (float)c;
-  sn[idx] = (float)s;
-}
+// The angles as a table, one thread per (position, pair).
+__global__ __launch_bounds__(256) void rope_table_kernel(const RopeTableJob r) { rope_table_entry(r, blockIdx.x * 256 + threadIdx.x); }
 
 int launch_rope_table(float* cos, float* sin, int64_t seq, int64_t head_dim, float base, hipStream_t st) {
   const int64_t n = seq * (head_dim / 2);
-  hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, cos, sin, (int)seq,
-                     (int)(head_dim / 2), log2((double)base));
+  hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                     (RopeTableJob{cos, sin, (int)seq, (int)(head_dim / 2), log2((double)base)}));
   return check_launch("rope table");
 }
 

@@ -11,15 +11,24 @@ namespace dl {
 // ---- elementwise.hip
 int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h,
                        float* rstd, hipStream_t st);
+// two norms of one shape in one launch
+int launch_rmsnorm_fwd_pair(const void* xa, const void* ga, void* ha, float* ra, const void* xb, const void* gb, void* hb, float* rb,
+                            int64_t T, int64_t D, float eps, hipStream_t st);
+// a norm and the rotary table (launch_rope_table) in one launch
+int launch_rmsnorm_fwd_rope_table(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h, float* rstd, float* cos,
+                                  float* sin, int64_t seq, int64_t head_dim, float base, hipStream_t st);
 size_t rmsnorm_bwd_workspace(int64_t T, int64_t D);
+// the two halves of launch_rmsnorm_bwd: dx and the partial rows in `workspace`; then dgamma from them, of one norm or
+// (ws_b, dgamma_b not null) two of the same shape
+int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd, const void* dh,
+                            const void* dres, int64_t T, int64_t D, void* dx, void* workspace, hipStream_t st);
+int launch_rmsnorm_bwd_gain(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D,
+                            int accumulate, hipStream_t st);
 int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,
                        const void* dres, int64_t T, int64_t D, void* dx, void* dgamma,
                        int accumulate, void* workspace, hipStream_t st);
 int launch_rope(void* z, int64_t batch, int64_t seq, int64_t n_heads, int64_t head_dim, float base,
                 int layout, int inverse, hipStream_t st);
-// q and k of a layer in one launch (same positions and angles)
-int launch_rope_pair(void* q, void* k, int64_t batch, int64_t seq, int64_t n_q_heads, int64_t n_kv_heads,
-                     int64_t head_dim, float base, int layout, int inverse, hipStream_t st);
 // cos and sin of angle(p, i) = p * base^(-2 i / head_dim) for p < seq, i < head_dim / 2, evaluated in
 // fp64 and stored as fp32 [seq][head_dim / 2]
 int launch_rope_table(float* cos, float* sin, int64_t seq, int64_t head_dim, float base, hipStream_t st);
