@@ -938,6 +938,7 @@ static size_t bwd_stats_bytes(int64_t B, int64_t S, int64_t Hq) {
 //   skew: with no more than three workgroups per two slots a CU's load is what it was dealt at the start, half
 //         a piece off the mean; with more of them the short late blocks even it out;
 //   sums: written and read at 4.2 TB/s.
+// A split has to promise 5 %: B1 S5760 13q/13kv x128 was promised 3 % and lost 1.
 // Measured (whole backward, us, unsplit -> split): B2 S2944 16q/4kv x64 339 -> 163 (6 pieces), B1 S4224 24q/8kv x128
 // 549 -> 359 (3), B1 S8192 32q/8kv x128 1885 -> 1616 (2); stays whole: B2 S8192 32q/8kv x128 3116 (3154 with 2),
 // B4 S2048 16q/8kv x128 260 (275 with 2), B8 S1024 12q/12kv x64 79 (104 with 2).
@@ -947,12 +948,13 @@ static int dkdv_splits(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh
   const double tile = dh == 128 ? 1.1 : dh == 64 ? 0.7 : 0.45;
   const double sums = (double)B * S * Hkv * dh * 16 / 4.2e6;
   int best = 1;
-  double best_us = 0;
+  double best_us = 0, whole_us = 0;
   for (int ns = 1; ns <= 8; ++ns) {
     const double piece = longest / ns, skew = B * Hkv * n * ns <= 768 ? 0.5 : 0.1;
     const double load = 1.15 * piece > mean + skew * piece ? 1.15 * piece : mean + skew * piece;
     const double us = load * tile + (ns > 1 ? 5 + ns * sums : 0);
-    if (ns == 1 || us < best_us) { best = ns; best_us = us; }
+    if (ns == 1) whole_us = best_us = us;
+    else if (us < best_us && us < 0.95 * whole_us) { best = ns; best_us = us; }
   }
   return best;
 }
