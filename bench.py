@@ -25,16 +25,17 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 # HBM bytes per launch of the dominant kernel (mean over the replayed launches of the seven projection
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
 # run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
-# counters were taken on: reported as null when gemm.hip has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_hip_sha256": "f94e8db7edcbef10e1afe77c4e421204cea0725d8f7e95c0786bbaca67d9b716",
+# counters were taken on: reported as null when gemm.hip or gemm_core.h has changed since.
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "7818f0e22c28cd7e8d5cbace1aea747b2f791cb2ade9003a09efbac286f3a0ba",
                 "fetch_bytes": 1.496e+09, "write_bytes": 2.013e+08}
 
 
 def _gemm_traffic(config_name):
     import hashlib
-    src = os.path.join(ROOT, "paper_2602_08387_amd", "csrc", "gemm.hip")
+    src = os.path.join(ROOT, "paper_2602_08387_amd", "csrc")
     try:
-        same = hashlib.sha256(open(src, "rb").read()).hexdigest() == GEMM_TRAFFIC["gemm_hip_sha256"]
+        both = b"".join(open(os.path.join(src, n), "rb").read() for n in ("gemm.hip", "gemm_core.h"))
+        same = hashlib.sha256(both).hexdigest() == GEMM_TRAFFIC["gemm_sha256"]
     except OSError:
         same = False
     if not same or config_name != GEMM_TRAFFIC["config"]:

@@ -1,4 +1,4 @@
-// bf16 GEMM for gfx950: C[M,N] = sum_s opA_s[M,K_s] * opB_s[K_s,N] (+R) with fp32 accumulation
+// bf16 GEMM for gfx950 (products that fill the chip; gemm_tile.hip has the others): C[M,N] = sum_s opA_s[M,K_s] * opB_s[K_s,N] (+R) with fp32 accumulation
 // on v_mfma_f32_16x16x32_bf16.  One kernel template serves the three products of a linear
 // layer (y = x W^T, dx = dy W, dW = dy^T x): each operand may be stored with the contraction
 // index contiguous ("k-major") or with its M/N index contiguous ("mn-major").
@@ -38,12 +38,12 @@ namespace dl {
 //
 // EPI_SWIGLU: the gated pair of the MLP in one pass.  B interleaves the rows of two weight matrices
 // (LoadCursor PAIR) so that every wave holds g = x Wg^T and u = x Wu^T for the same 32 columns; the
-// epilogue stores g to c, u to c2 and silu(g) * u, taken from the ROUNDED g and u like the separate
-// activation kernel would, to c3.  M x N is the interleaved product: N = twice the columns of g.
+// epilogue stores g to c, u to c2 and silu(g) * u, taken from the fp32 sums, to c3.  M x N is the interleaved
+// product: N = twice the columns of g.
 //
 // EPI_SWIGLU_GRAD: the product is da, the gradient arriving at a = silu(g) * u; the epilogue reads the
-// g and u tiles (e1, e2, leading dimension lde) and stores dg to c and du to c2 instead of da,
-// again from the rounded da like the separate kernel.
+// g and u tiles (e1, e2, leading dimension lde) and stores dg to c and du to c2, from the fp32 sums of da, instead
+// of da.
 //
 // EPI_ROPE (grouped launch of head projections): problems flagged `rope` have the rotary embedding
 // applied to their output in the epilogue, on the fp32 accumulators, so that q and k are rounded to

@@ -1,13 +1,15 @@
-// bf16 GEMM for problems that do not fill the chip with 256 x 256 tiles: one 128 x 128 or 64 x 64 tile per
-// workgroup, a deep ring of K-steps in LDS.  Same operand layouts, same MFMA, same order of summation as the
-// persistent kernel (gemm.hip): a product has the same bits on either.
+// bf16 GEMM for problems that do not fill the chip with 256 x 256 tiles: one 128 x 256, 128 x 128 or 64 x 64 tile per
+// workgroup.  Same operand layouts, same MFMA, same order of summation as the persistent kernel (gemm.hip): a
+// product has the same bits on either.
 //
-// What bounds it: with few tiles a CU works on one or two of them and the K loop is a chain of load latencies, one
-// per ring depth.  The persistent kernel's two-stage ring paid about 0.8 us per K-step of 64 at T = 1000,
-// K = 2048, N = 1024 (25 us); a K-step's MFMAs take 0.25 us for a 128 x 128 tile.  So the ring is four stages deep
-// (loads run three K-steps ahead, the wait counts them), which the small tile's LDS leaves room for, and there is
-// one barrier per K-step.  From 256 x 256 tiles on the address unit (16 cycles per 1 KiB load, as many as
-// the MFMAs of a 128 x 128 x 64 step take) makes the small tile the slower one.
+// What bounds it: a CU works on one or two tiles, so nothing covers what a K-step serialises.  With four waves, a
+// two-stage ring and its loads and fragment reads in bunches around the barrier a 128 x 128 tile paid 0.77 us per K-step
+// of 64 (T = 1920, K = 6272, N = 1152: 68 us), of which its MFMAs are 0.21 us and its loads, 16 cycles each at the
+// address unit, 0.22.  Measured on the way: a four-stage ring alone changes nothing; eight waves of 64 x 32 0.48;
+// reads and loads between the rows of MFMAs, half a K-step ahead, 0.40 (44 us).  A 64 x 64 tile takes 0.25 us, four
+// times the tiles to fill the chip with (T = 1000, K = 2048, N = 1024: 25 -> 9 us); a 128 x 256 tile 0.62 to 0.75
+// (T = 8192, K = 4096, N = 768: 64 -> 50 us).  Full rounds of 256 x 256 tiles stay on the persistent kernel: a quarter
+// fewer loads per flop, and its epilogue under the next tile's main loop.
 //
 // The epilogue passes the fp32 sums through LDS (the ring is free by then), so every fused epilogue is an
 // element-wise function of rows: residual or accumulation, rotary embedding (both members of a pair lie in the
@@ -17,10 +19,9 @@
 namespace dl {
 
 // Operand fragments of one wave from an LDS tile: F blocks of 16 rows (the M/N index) from row0 on, k-substep kk.
-// The reads are inline assembly, see read_frag; consumers sit behind a counted wait.
+// The reads are inline assembly, see read_frag; consumers sit behind wait_reads().
 template <int R, bool KMAJOR, int F>
 struct FragReader {
-  static constexpr int READS = KMAJOR ? F : 2 * F;   // LDS instructions per k-substep
   uint32_t at[KMAJOR ? 2 : F];
   __device__ __forceinline__ void init(const char* tile, int row0, int lane) {
     const uint32_t base = (uint32_t)(uintptr_t)(LDS_PTR(char))(const_cast<char*>(tile));
