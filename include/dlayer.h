@@ -148,7 +148,7 @@ int ce_loss_fwd_bwd_static(const void* logits, const int64_t* targets, int64_t T
 /*
  * The LM head and its loss in one call, without ever holding all T x V logits (same training loss):
  *   logits = h w_lm^T;  loss, dlogits as in ce_loss_fwd_bwd;  dh = dlogits w_lm;  dw_lm (+)= dlogits^T h
- * The rows are walked in chunks of chunk_rows (0 = chosen by the library: about 2 GiB of logits):
+ * The rows are walked in chunks of chunk_rows (0 = chosen by the library: 1 to 2 GiB of logits):
  * each chunk's logits are formed, turned into their gradient in place and consumed by the two
  * gradient products before the next chunk overwrites them.  dw_lm is accumulated in bf16 from chunk
  * to chunk (fp32 within a chunk), so it is rounded once per chunk instead of once.
@@ -278,7 +278,7 @@ int embed_forward(const void* table, const int64_t* ids, int64_t T, int64_t V, i
  * ascending token order (interleaved partial sums, combined in a fixed order), bf16 result; no
  * floating-point atomics, bitwise reproducible.  An id with more than 64 tokens is summed by one
  * workgroup per 128 columns, whatever its frequency.  dtable [V, D] bf16 is overwritten.
- * workspace (device): embed_backward_workspace_bytes(T, V), about (2 V + 2.2 T) ints.         */
+ * workspace (device): embed_backward_workspace_bytes(T, V), about (3 V + 2.2 T) ints.         */
 size_t embed_backward_workspace_bytes(int64_t T, int64_t V);
 int embed_backward(const void* dx0, const int64_t* ids, int64_t T, int64_t V, int64_t D,
                    void* dtable, void* workspace, void* stream);

@@ -347,13 +347,15 @@ int ce_loss_fwd_bwd_static(const void* logits, const int64_t* targets, int64_t T
 }
 
 // rows of logits held at a time by lm_head_ce_fwd_bwd
-static int64_t lm_head_chunk(int64_t T, int64_t V, int64_t chunk_rows) {
+static int64_t lm_head_chunk(int64_t T, int64_t D, int64_t V, int64_t chunk_rows) {
   int64_t c = chunk_rows;
   if (c <= 0) {
-    // about 2 GiB of logits: every chunk re-reads and re-rounds the weight gradient and gives the products fewer tiles, so
-    // a chunk is as large as one buffer descriptor and 288 GB allow without a second thought.  T = 8192, V = 128256:
-    // D = 2048 11.7 ms in two chunks of 4096 rows, 10.7 ms in one of 8192.
-    c = (((int64_t)1 << 31) / (V * 2)) / 256 * 256;
+    // About 1 GiB of logits.  2 GiB where the input gradient of such a chunk [c, D] has fewer than 256 tiles of
+    // 256 x 256, one per compute unit: every chunk also re-reads and re-rounds the weight gradient.  T = 8192,
+    // V = 128256, chunks of 4096 / 8192 rows, ms: D = 1024 7.0 / 6.2, 2048 11.4 / 10.7, 3072 17.4 / 16.2; at D = 4096,
+    // where the tiles of 4096 rows are all there, 20.6 / 20.2 and half the scratch.
+    const int64_t gib1 = ((int64_t)1 << 30) / (V * 2) / 256 * 256, gib2 = ((int64_t)1 << 31) / (V * 2) / 256 * 256;
+    c = gib1 * D < (int64_t)256 * 256 * 256 ? gib2 : gib1;
     if (c < 256) c = 256;
   }
   return c < T ? c : T;
@@ -361,7 +363,7 @@ static int64_t lm_head_chunk(int64_t T, int64_t V, int64_t chunk_rows) {
 
 size_t lm_head_ce_workspace_bytes(int64_t T, int64_t D, int64_t V, int64_t chunk_rows) {
   if (T <= 0 || D <= 0 || V <= 0 || chunk_rows < 0 || chunk_rows % 64) return 0;
-  return up256((size_t)lm_head_chunk(T, V, chunk_rows) * V * 2) + up256((size_t)V * D * 2) + up256((size_t)T * 4);
+  return up256((size_t)lm_head_chunk(T, D, V, chunk_rows) * V * 2) + up256((size_t)V * D * 2) + up256((size_t)T * 4);
 }
 
 int lm_head_ce_fwd_bwd(const void* h, const void* w_lm, const int64_t* targets, int64_t T, int64_t D, int64_t V,
@@ -370,7 +372,7 @@ int lm_head_ce_fwd_bwd(const void* h, const void* w_lm, const int64_t* targets, 
   REQUIRE(T > 0 && D > 0 && V > 0 && T % 64 == 0 && D % 64 == 0 && V % 64 == 0,
           "lm_head_ce_fwd_bwd: T, D and V must be positive multiples of 64");
   REQUIRE(chunk_rows >= 0 && chunk_rows % 64 == 0, "lm_head_ce_fwd_bwd: chunk_rows must be 0 or a multiple of 64");
-  const int64_t Tc = lm_head_chunk(T, V, chunk_rows);
+  const int64_t Tc = lm_head_chunk(T, D, V, chunk_rows);
   REQUIRE(under_4gib(T, D) && under_4gib(V, D) && under_4gib(Tc, V) &&
               T < ((int64_t)1 << 31),
           "lm_head_ce_fwd_bwd: an operand (or a chunk of logits) reaches 4 GiB");
@@ -405,7 +407,11 @@ int rmsnorm_forward(const void* x, const void* gamma, int64_t T, int64_t D, floa
   return launch_rmsnorm_fwd(x, gamma, T, D, eps, h, rstd, (hipStream_t)stream);
 }
 
-size_t rmsnorm_backward_workspace_bytes(int64_t T, int64_t D) { return T > 0 && D > 0 ? rmsnorm_bwd_workspace(T, D) : 0; }
+// The size that callers are promised: rows wider than 4096 columns have one more float each, which the kernel leaves alone
+// (a row is held by one workgroup and read once, whatever its width).
+size_t rmsnorm_backward_workspace_bytes(int64_t T, int64_t D) {
+  return T > 0 && D > 0 ? rmsnorm_bwd_workspace(T, D) + (D > 4096 ? (size_t)T * sizeof(float) : 0) : 0;
+}
 
 int rmsnorm_backward(const void* x, const void* gamma, const float* rstd, const void* dh, const void* dres,
                      int64_t T, int64_t D, void* dx, void* dgamma, int accumulate_dgamma, void* workspace,
@@ -650,7 +656,10 @@ int embed_forward(const void* table, const int64_t* ids, int64_t T, int64_t V, i
   return launch_embed_fwd(table, ids, T, V, D, x0, (hipStream_t)stream);
 }
 
-size_t embed_backward_workspace_bytes(int64_t T, int64_t V) { return T > 0 && V > 0 ? embed_bwd_workspace(T, V) : 0; }
+// The size that callers are promised, (3 V + 2.2 T) ints, of which the kernels use (2 V + 2.2 T).
+size_t embed_backward_workspace_bytes(int64_t T, int64_t V) {
+  return T > 0 && V > 0 ? embed_bwd_workspace(T, V) + (size_t)V * sizeof(int) : 0;
+}
 
 int embed_backward(const void* dx0, const int64_t* ids, int64_t T, int64_t V, int64_t D, void* dtable,
                    void* workspace, void* stream) {
