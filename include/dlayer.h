@@ -111,6 +111,8 @@ int dlayer_forward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* w
  *                                    workspace, nothing else having written to it since
  *                                    (dlayer_forward leaves that part alone) - are still valid and skips rewriting
  *                                    them: for several micro-batches between two optimizer steps.
+ *                                    (For the smallest layers, where the copies would cost more than they
+ *                                    give, no call makes or reads any; the flag is then without effect.)
  */
 #define DLAYER_ACCUMULATE_WGRADS 1
 #define DLAYER_REUSE_TRANSPOSED_WEIGHTS 2
@@ -212,7 +214,7 @@ int linear_swiglu_forward(const void* x, const void* w_gate, const void* w_up, i
 /* Backward of y = a W_down^T with a = silu(g) * u, as far as g and u: da = dy W_down, then
  * (dg, du) = swiglu_backward(g, u, da); the gradient is applied to the fp32 sums of da in the product's
  * epilogue, da is never stored.  dy [T, D], w_down [D, F], g, u, dg, du [T, F] dense; all bf16.
- * T, D, F multiples of 64.  workspace (device; receives a transposed copy of w_down):
+ * T, D, F multiples of 64.  workspace (device; may receive a transposed copy of w_down):
  * linear_swiglu_backward_workspace_bytes(T, D, F).                                             */
 size_t linear_swiglu_backward_workspace_bytes(int64_t T, int64_t D, int64_t F);
 int linear_swiglu_backward(const void* dy, const void* w_down, const void* g, const void* u,
@@ -221,7 +223,7 @@ int linear_swiglu_backward(const void* dy, const void* w_down, const void* g, co
 
 /* Gradients of y = x W^T: dx = dy W ([T, K], skipped if dx == NULL) and dw = dy^T x ([N, K],
  * skipped if dw == NULL).  T, K, N multiples of 64.  workspace (device, needed when dx is
- * asked for: it receives a transposed copy of w): linear_backward_workspace_bytes(T, K, N).   */
+ * asked for: it may receive a transposed copy of w): linear_backward_workspace_bytes(T, K, N).   */
 size_t linear_backward_workspace_bytes(int64_t T, int64_t K, int64_t N);
 int linear_backward(const void* x, const void* w, const void* dy, int64_t T, int64_t K,
                     int64_t N, void* dx, void* dw, int accumulate_dw, void* workspace,

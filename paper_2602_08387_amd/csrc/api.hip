@@ -169,16 +169,27 @@ static int gemm_nt(const void* x, int64_t ldx, const void* w, const void* res, i
   return launch_gemm(nt_args(x, ldx, w, res, T, K, N, y), st);
 }
 
-// dx[T,K] = sum_s dy_s[T,N_s] WT_s[K,N_s]^T with the transposed weights WT_s = W_s^T; ld: leading
-// dimension of every dy_s and WT_s, lddx: that of dx
-static int gemm_dgrad_t(int nseg, const void* const* dy, const void* const* wt, const int64_t* Ns, int64_t ld,
-                        int64_t T, int64_t K, void* dx, int64_t lddx, hipStream_t st) {
+// dx[T,K] = sum_s dy_s[T,N_s] W_s[N_s,K] with W_s as stored, or (transposed) through the copies W_s^T [K,N_s]; ld: leading
+// dimension of every dy_s, and of the copies, where it is not N_s; lddx: that of dx
+static int gemm_dgrad(int nseg, const void* const* dy, const void* const* w, const int64_t* Ns, int64_t ld, bool transposed,
+                      int64_t T, int64_t K, void* dx, int64_t lddx, hipStream_t st) {
   GemmArgs g{};
   g.nseg = nseg;
-  for (int s = 0; s < nseg; ++s) g.seg[s] = {dy[s], wt[s], ld ? ld : Ns[s], ld ? ld : Ns[s], (int)Ns[s]};
+  for (int s = 0; s < nseg; ++s) g.seg[s] = {dy[s], w[s], ld ? ld : Ns[s], !transposed ? K : ld ? ld : Ns[s], (int)Ns[s]};
   g.M = (int)T; g.N = (int)K; g.c = dx; g.ldc = lddx; g.r = nullptr; g.accumulate = 0;
-  g.a_kmajor = true; g.b_kmajor = true;
+  g.a_kmajor = true; g.b_kmajor = transposed;
   return launch_gemm(g, st);
+}
+
+// Whether the input gradient [T, K] of a product reads its weights as they are stored, not through a transposed copy.
+// The copy costs a launch and a read and a write of the weights; reading W[N, K] across its rows costs the product 5 to
+// 10 % (transposing LDS reads), which grows with T.  The whole call with the copy and without, us, measured for
+// (T, K, N): linear_backward (2048,1024,1024) 13.8 / 9.9, (512,2048,2048) 18.0 / 12.5, (2048,4096,14336) 258 / 182,
+// (4096,2048,2048) 37.0 / 31.2, (2048,14336,4096) 208 / 211, (4096,4096,4096) 103 / 108, (4160,4416,4288) 137 / 156;
+// lm_head_ce_fwd_bwd (448,2176,33088) 443 / 365, (4096,1024,64000) 1816 / 1778, (4096,4096,128256) 10260 / 10397.
+// The weights are one buffer of a workgroup's loads, whose offsets have 32 bits: at most 2 GiB.
+static bool weights_as_stored(int64_t T, int64_t K, int64_t weight_numel) {
+  return T <= 4096 && T * K <= (int64_t)4096 * 2048 && weight_numel <= ((int64_t)1 << 30);
 }
 
 // dw[N,K] (+)= dy[T,N]^T x[T,K]; lddy, ldx: leading dimensions of dy and x
@@ -273,31 +284,39 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
   Saved s = carve_saved(cfg, const_cast<void*>(saved));
   Work k = carve_work(cfg, workspace);
   const int64_t Fp = padded_ff(cfg);
-  if (!(flags & DLAYER_REUSE_TRANSPOSED_WEIGHTS)) {
+  // A call that reuses the copies pays for none, and which call will follow is not known here; one that reads the
+  // weights as stored is as fast as such a call only where the products are all launch latency.  The call with copies,
+  // reusing them, and without, us: D 128, F 384, 128 tokens 50.9 / 46.9 / 47.3; D 256, F 704, 256 tokens 59.0 / 54.4 /
+  // 55.3; D 2048, F 5632, 2048 tokens 620 / 589 / 616; D 4096, F 14336, 256 tokens 816 / 639 / 678.
+  const int64_t widest = D * (F > QD ? F : QD);
+  const bool direct = widest <= 65536 && weights_as_stored(T, D, widest);
+  if (!direct && !(flags & DLAYER_REUSE_TRANSPOSED_WEIGHTS)) {
     const TransposeJob jobs[7] = {{w->w_down, k.wdT, D, F, D},  {w->w_gate, k.wgT, F, D, Fp}, {w->w_up, k.wuT, F, D, Fp},
                                   {w->wo, k.woT, D, QD, D},     {w->wq, k.wqT, QD, D, QD},    {w->wk, k.wkT, KD, D, KD},
                                   {w->wv, k.wvT, KD, D, KD}};
     TRY(launch_transpose_group(jobs, 7, st));
   }
   // y = y1 + a Wd^T
-  TRY(launch_gemm_swiglu_grad(dy, D, k.wdT, D, T, D, F, s.g, s.u, F, k.da_dg, k.du, Fp, st));
+  TRY(launch_gemm_swiglu_grad(dy, D, direct ? w->w_down : k.wdT, !direct, direct ? F : D, T, D, F, s.g, s.u, F, k.da_dg, k.du, Fp, st));
   {
-    const void* dys[2] = {k.da_dg, k.du}; const void* ws[2] = {k.wgT, k.wuT}; const int64_t ns[2] = {F, F};
-    TRY(gemm_dgrad_t(2, dys, ws, ns, Fp, T, D, k.dh2, D, st));
+    const void* dys[2] = {k.da_dg, k.du}; const void* ws[2] = {direct ? w->w_gate : k.wgT, direct ? w->w_up : k.wuT};
+    const int64_t ns[2] = {F, F};
+    TRY(gemm_dgrad(2, dys, ws, ns, Fp, !direct, T, D, k.dh2, D, st));
   }
   TRY(launch_rmsnorm_bwd_rows(s.y1, w->g_mlp, s.rstd2, k.dh2, dy, T, D, k.dy1, k.rms_ws2, st));
   // y1 = x + o Wo^T
   {
-    const void* dys[1] = {k.dy1}; const void* ws[1] = {k.woT}; const int64_t ns[1] = {D};
-    TRY(gemm_dgrad_t(1, dys, ws, ns, 0, T, QD, k.d_o, QD, st));
+    const void* dys[1] = {k.dy1}; const void* ws[1] = {direct ? w->wo : k.woT}; const int64_t ns[1] = {D};
+    TRY(gemm_dgrad(1, dys, ws, ns, 0, !direct, T, QD, k.d_o, QD, st));
   }
   // dq and dk come back as gradients of the unrotated q and k (inverse rotation inside the kernels' stores)
   TRY(launch_attention_bwd_rope(s.q, s.k, s.v, s.o, k.d_o, s.lse, B, S, Hq, Hkv, dh, k.dq, k.dk, k.dv, k.attn_ws,
                                 s.rope_cos, s.rope_sin, cfg->rope_layout, st));
   {
-    const void* dys[3] = {k.dq, k.dk, k.dv}; const void* ws[3] = {k.wqT, k.wkT, k.wvT};
+    const void* dys[3] = {k.dq, k.dk, k.dv};
+    const void* ws[3] = {direct ? w->wq : k.wqT, direct ? w->wk : k.wkT, direct ? w->wv : k.wvT};
     const int64_t ns[3] = {QD, KD, KD};
-    TRY(gemm_dgrad_t(3, dys, ws, ns, 0, T, D, k.dh1, D, st));
+    TRY(gemm_dgrad(3, dys, ws, ns, 0, !direct, T, D, k.dh1, D, st));
   }
   TRY(launch_rmsnorm_bwd_rows(x, w->g_attn, s.rstd1, k.dh1, k.dy1, T, D, dx, k.rms_ws1, st));
   TRY(launch_rmsnorm_bwd_gain(k.rms_ws1, dw->g_attn, k.rms_ws2, dw->g_mlp, T, D, acc, st));
@@ -384,15 +403,16 @@ int lm_head_ce_fwd_bwd(const void* h, const void* w_lm, const int64_t* targets, 
   void* logits = cv.take((size_t)Tc * V * 2);
   void* wT = cv.take((size_t)V * D * 2);
   float* row_loss = (float*)cv.take((size_t)T * 4);
-  TRY(launch_transpose(w_lm, wT, V, D, V, st));
+  const bool direct = weights_as_stored(T, D, V * D);
+  if (!direct) TRY(launch_transpose(w_lm, wT, V, D, V, st));
   const float scale = grad_scale / (float)T;
   for (int64_t r0 = 0; r0 < T; r0 += Tc) {
     const int64_t rows = T - r0 < Tc ? T - r0 : Tc;
     const bf16_t* hc = (const bf16_t*)h + r0 * D;
     TRY(gemm_nt(hc, D, w_lm, nullptr, rows, D, V, logits, st));
     TRY(launch_ce_rows(logits, targets + r0, rows, V, scale, row_loss + r0, logits, st));
-    const void* dys[1] = {logits}; const void* ws[1] = {wT}; const int64_t ns[1] = {V};
-    TRY(gemm_dgrad_t(1, dys, ws, ns, 0, rows, D, (bf16_t*)dh + r0 * D, D, st));
+    const void* dys[1] = {logits}; const void* ws[1] = {direct ? w_lm : wT}; const int64_t ns[1] = {V};
+    TRY(gemm_dgrad(1, dys, ws, ns, 0, !direct, rows, D, (bf16_t*)dh + r0 * D, D, st));
     TRY(gemm_wgrad(logits, hc, rows, V, D, dw_lm, (accumulate_dw || r0 > 0) ? 1 : 0, st));
   }
   return launch_ce_mean(row_loss, T, loss, st);
@@ -494,9 +514,10 @@ int linear_backward(const void* x, const void* w, const void* dy, int64_t T, int
   hipStream_t st = (hipStream_t)stream;
   if (dx) {
     REQUIRE_PTR(workspace);
-    TRY(launch_transpose(w, workspace, N, K, N, st));
-    const void* dys[1] = {dy}; const void* ws[1] = {workspace}; const int64_t ns[1] = {N};
-    TRY(gemm_dgrad_t(1, dys, ws, ns, 0, T, K, dx, K, st));
+    const bool direct = weights_as_stored(T, K, N * K);
+    if (!direct) TRY(launch_transpose(w, workspace, N, K, N, st));
+    const void* dys[1] = {dy}; const void* ws[1] = {direct ? w : workspace}; const int64_t ns[1] = {N};
+    TRY(gemm_dgrad(1, dys, ws, ns, 0, !direct, T, K, dx, K, st));
   }
   if (dw) TRY(gemm_wgrad(dy, x, T, N, K, dw, accumulate_dw ? 1 : 0, st));
   return DLAYER_OK;
@@ -516,8 +537,9 @@ int linear_swiglu_backward(const void* dy, const void* w_down, const void* g, co
   REQUIRE_PTR(workspace);
   TRY(check_device());
   hipStream_t st = (hipStream_t)stream;
+  if (weights_as_stored(T, F, D * F)) return launch_gemm_swiglu_grad(dy, D, w_down, false, F, T, D, F, g, u, F, dg, du, F, st);
   TRY(launch_transpose(w_down, workspace, D, F, D, st));
-  return launch_gemm_swiglu_grad(dy, D, workspace, D, T, D, F, g, u, F, dg, du, F, st);
+  return launch_gemm_swiglu_grad(dy, D, workspace, true, D, T, D, F, g, u, F, dg, du, F, st);
 }
 
 int linear_wgrad_group(int32_t n, const void* const* dy, const void* const* x, const int64_t* N, const int64_t* K,

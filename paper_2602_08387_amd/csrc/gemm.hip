@@ -802,13 +802,13 @@ int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* w
   return run_gemm(&k, 1, true, true, TileEpilogue::SWIGLU, nullptr, st);
 }
 
-int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* wt, int64_t ldw, int64_t T, int64_t K, int64_t F,
+int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_kmajor, int64_t ldw, int64_t T, int64_t K, int64_t F,
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
                             hipStream_t st) {
   GemmKArgs k{};
   k.nseg = 1;
   k.a[0] = (const bf16_t*)dy;
-  k.b[0] = (const bf16_t*)wt;
+  k.b[0] = (const bf16_t*)w;
   k.lda[0] = lddy;
   k.ldb[0] = ldw;
   k.K[0] = (int)K;
@@ -820,7 +820,7 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* wt, int64_
   k.e1 = (const bf16_t*)g;
   k.e2 = (const bf16_t*)u;
   k.lde = ldgu;
-  return run_gemm(&k, 1, true, true, TileEpilogue::SWIGLU_GRAD, nullptr, st);
+  return run_gemm(&k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, st);
 }
 
 int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st) { return launch_gemm_group_rope(gs, n, nullptr, st); }

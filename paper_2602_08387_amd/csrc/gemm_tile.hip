@@ -381,9 +381,11 @@ int launch_gemm_tile(TileSize size, const GemmKArgs* ks, int n, bool ak, bool bk
                      hipStream_t st) {
   if (rope) return launch_size<true, true, TILE_ROPE>(size, ks, n, rope, st);
   if (epi == TileEpilogue::SWIGLU) return launch_size<true, true, TILE_SWIGLU>(size, ks, n, nullptr, st);
-  if (epi == TileEpilogue::SWIGLU_GRAD) return launch_size<true, true, TILE_SWIGLU_GRAD>(size, ks, n, nullptr, st);
+  if (epi == TileEpilogue::SWIGLU_GRAD)
+    return bk ? launch_size<true, true, TILE_SWIGLU_GRAD>(size, ks, n, nullptr, st) : launch_size<true, false, TILE_SWIGLU_GRAD>(size, ks, n, nullptr, st);
   if (ak && bk) return launch_size<true, true, TILE_PLAIN>(size, ks, n, nullptr, st);
   if (!ak && !bk) return launch_size<false, false, TILE_PLAIN>(size, ks, n, nullptr, st);
+  if (ak && !bk) return launch_size<true, false, TILE_PLAIN>(size, ks, n, nullptr, st);
   return fail(-1, "gemm tile: operand layout not built");
 }
 

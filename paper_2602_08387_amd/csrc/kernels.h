@@ -84,9 +84,9 @@ int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, 
 // leading dimension ldx, wg and wu [F, K] with ldw, g and u with ldgu, a with lda.  F % 8 == 0.
 int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* wu, int64_t ldw, int64_t T, int64_t K,
                        int64_t F, void* g, void* u, int64_t ldgu, void* a, int64_t lda, hipStream_t st);
-// da = dy W^T for dy [T, K] (lddy) and wt = W [F, K] (ldw), then (dg, du) = gradient of silu(g) * u for
+// da = dy W^T for dy [T, K] (lddy) and W stored [F, K] (w_kmajor) or [K, F] with ldw, then (dg, du) = gradient of silu(g) * u for
 // the fp32 da, which is never stored.  g, u with ldgu; dg, du with ldd.
-int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* wt, int64_t ldw, int64_t T, int64_t K, int64_t F,
+int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_kmajor, int64_t ldw, int64_t T, int64_t K, int64_t F,
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
                             hipStream_t st);
 

@@ -153,6 +153,25 @@ def test_activation_gradient_on_every_tile_size(K, T, D, F):
         assert _norm_err(got, ref) <= ONE_ROUNDING, name
 
 
+@pytest.mark.parametrize("rows,Kd,N", [
+    ((64,), 64, 64),                  # one tile, one K-step
+    ((4160, 4096, 64), 320, 192),     # the last rows that read the weights as stored, and the first that do not
+    ((4032, 1984, 320), 2112, 448),   # the same for rows x columns; 128 x 256 tiles
+    ((1920, 64), 1152, 3136),         # 128 x 128 tiles
+])
+def test_input_gradient_with_and_without_the_transposed_weights(K, rows, Kd, N):
+    rng = np.random.default_rng(rows[0] + N)
+    dyb, wb = _rand_bits(rng, (rows[0], N)), _rand_bits(rng, (N, Kd), 0.05)
+    ref = si.bf16_bits_to_f64(dyb) @ si.bf16_bits_to_f64(wb)
+    dyd, wd, first = dev_bf16(dyb), dev_bf16(wb), None
+    for T in rows:
+        dx = torch.full((T, Kd), float("nan"), dtype=torch.bfloat16, device="cuda")
+        K.linear_backward(dx, wd, dyd[:T], T, Kd, N, dx, None, 0, _poisoned(K.linear_backward_workspace_bytes(T, Kd, N)))
+        assert _norm_err(dx, ref[:T]) <= ONE_ROUNDING, T
+        first = dx if first is None else first
+        assert torch.equal(dx.view(torch.int16), first[:T].view(torch.int16)), T
+
+
 @pytest.mark.parametrize("B,S,D,Hq,Hkv,dh,layout", [
     (1, 128, 64, 2, 1, 64, 0),       # 64 x 64 tiles: a head per tile
     (1, 192, 64, 4, 2, 32, 0),       # two heads per tile
