@@ -640,7 +640,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
     const float* __restrict__ rope_sin, int rope_layout, bf16_t* __restrict__ dq) {
   // Where dQ forms S and dP itself it depends on neither dK nor dV, and its workgroups follow in the same launch: they
   // start as the key blocks run out, and a short sequence's launch ends once instead of twice (B8 S1024
-  // 12q/12kv x64: 84 -> 68 us for the two passes).
+  // 12q/12kv x64: 84 -> 68 us for the two passes).  With ns == 0 a launch holds dQ workgroups only.
   if constexpr (!WRITE_DS) {
     const int n_kv = S / 128 * Hkv * B * ns;
     if ((int)blockIdx.x >= n_kv) {
@@ -994,6 +994,12 @@ static int launch_dkdv_sums(const AttnBwdArgs& a, hipStream_t st) {
   return check_launch("attention_backward(dk, dv sums)");
 }
 
+// whether two buffers of n bytes share any of them
+static bool overlap(const void* a, const void* b, int64_t n) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return (x < y ? y - x : x - y) < (uintptr_t)n;
+}
+
 template <int DH>
 static int bwd_dh(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                   const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv, void* dq, void* dk,
@@ -1047,10 +1053,17 @@ static int bwd_dh(const void* q, const void* k, const void* v, const void* o, co
   const size_t lds_q = 2 * 2 * (size_t)RowTile<64, DH, 4>::BYTES, lds = lds_kv > lds_q ? lds_kv : lds_q;
   static std::atomic<unsigned long long> done{0};
   if (int rc = reserve_lds(attn_bwd_dkdv_kernel<DH, false>, lds, done, "attention_backward")) return rc;
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<DH, false>), dim3(kv_blocks + q_blocks), dim3(256), lds, st, a.q, a.k, a.v, a.d_o, a.lse2,
-                     a.delta, a.dk, a.dv, (bf16_t*)nullptr, a.part, a.ns, a.B, a.S, a.Hq, a.Hkv, a.scale, rope_cos, rope_sin,
-                     rope_layout, a.dq);
-  if (int rc = check_launch("attention_backward(dk, dv, dq)")) return rc;
+  // One launch for both passes, unless dq is to replace q or dO: every key block reads those, so the dQ workgroups, which
+  // only read the rows they write, then follow in a launch of their own (no pieces, hence no key blocks before them).
+  auto launch = [&](unsigned blocks, int ns) {
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<DH, false>), dim3(blocks), dim3(256), lds, st, a.q, a.k, a.v, a.d_o, a.lse2, a.delta, a.dk,
+                       a.dv, (bf16_t*)nullptr, a.part, ns, a.B, a.S, a.Hq, a.Hkv, a.scale, rope_cos, rope_sin, rope_layout, a.dq);
+    return check_launch("attention_backward(dk, dv, dq)");
+  };
+  const bool in_place = overlap(dq, q, rows * DH * 2) || overlap(dq, d_o, rows * DH * 2);
+  if (int rc = launch(in_place ? kv_blocks : kv_blocks + q_blocks, a.ns)) return rc;
+  if (in_place)
+    if (int rc = launch(q_blocks, 0)) return rc;
   return launch_dkdv_sums<DH>(a, st);
 }
 

@@ -63,6 +63,34 @@ def test_attention_backward_with_split_key_blocks(K, B, S, Hq, Hkv, dh):
         assert torch.equal(got.view(torch.int16), again.view(torch.int16)), f"{name} is not reproducible"
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,dh", [
+    (2, 1024, 4, 4, 64),     # one workgroup per key block; the dQ workgroups follow in the same launch where dq is a buffer of its own
+    (1, 640, 6, 2, 64),      # split key blocks
+    (1, 256, 4, 2, 32),
+    (1, 640, 3, 1, 128),
+    (1, 2048, 2, 1, 128),    # with the dS hand-over: two launches anyway
+])
+def test_attention_backward_with_dq_in_place(K, B, S, Hq, Hkv, dh):
+    """Every key block reads q and dO, so dq may only replace one of them once the dK/dV pass is over."""
+    rng = np.random.default_rng(S + dh)
+    q, do = (dev_bf16(_rand_bits(rng, (B, S, Hq, dh))) for _ in range(2))
+    k, v = (dev_bf16(_rand_bits(rng, (B, S, Hkv, dh))) for _ in range(2))
+    o, lse = torch.empty_like(q), torch.empty(B, Hq, S, dtype=torch.float32, device="cuda")
+    K.attention_forward(q, k, v, B, S, Hq, Hkv, dh, o, lse)
+
+    def backward(q, do, dq):
+        dk, dv = torch.full_like(k, float("nan")), torch.full_like(v, float("nan"))
+        K.attention_backward(q, k, v, o, do, lse, B, S, Hq, Hkv, dh, dq, dk, dv,
+                             _poisoned(K.attention_backward_workspace_bytes(B, S, Hq, Hkv, dh)))
+        return dq, dk, dv
+
+    want = backward(q, do, torch.full_like(q, float("nan")))
+    over_q, over_do = q.clone(), do.clone()
+    for what, got in (("q", backward(over_q, do, over_q)), ("dO", backward(q, over_do, over_do))):
+        for name, g, w in zip(("dq", "dk", "dv"), got, want):
+            assert torch.equal(g.view(torch.int16), w.view(torch.int16)), f"{name} with dq over {what}"
+
+
 @pytest.mark.parametrize("override", [
     {"seq": 640, "d_model": 192, "n_q_heads": 6, "n_kv_heads": 2, "head_dim": 64, "d_ff": 320, "rope_layout": 1},
     {"seq": 512, "d_model": 256, "n_q_heads": 4, "n_kv_heads": 1, "head_dim": 128, "d_ff": 320},
