@@ -939,9 +939,14 @@ static size_t bwd_stats_bytes(int64_t B, int64_t S, int64_t Hq) {
 //         a piece off the mean; with more of them the short late blocks even it out;
 //   sums: written and read at 4.2 TB/s.
 // A split has to promise 5 %: B1 S5760 13q/13kv x128 was promised 3 % and lost 1.
+// All pieces together are at most kMostPieces workgroups, three to a slot, which bounds the scratch (see
+// dkdv_partial_bytes); where the estimate asks for more (groups of 16 heads from 2816 positions on, others from longer
+// ones) it promises less than 2 %.
 // Measured (whole backward, us, unsplit -> split): B2 S2944 16q/4kv x64 339 -> 163 (6 pieces), B1 S4224 24q/8kv x128
 // 549 -> 359 (3), B1 S8192 32q/8kv x128 1885 -> 1616 (2); stays whole: B2 S8192 32q/8kv x128 3116 (3154 with 2),
 // B4 S2048 16q/8kv x128 260 (275 with 2), B8 S1024 12q/12kv x64 79 (104 with 2).
+constexpr int kMostPerBlock = 8;
+constexpr int64_t kMostPieces = 1536;
 static int dkdv_splits(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
   const int64_t n = S / 128;
   const double longest = (double)(Hq / Hkv * 4 * n), mean = (double)B * Hq * 4 * n * (n + 1) / 2 / 256;   // tiles; per CU
@@ -949,7 +954,7 @@ static int dkdv_splits(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh
   const double sums = (double)B * S * Hkv * dh * 16 / 4.2e6;
   int best = 1;
   double best_us = 0, whole_us = 0;
-  for (int ns = 1; ns <= 8; ++ns) {
+  for (int ns = 1; ns <= kMostPerBlock && (ns == 1 || ns * B * Hkv * n <= kMostPieces); ++ns) {
     const double piece = longest / ns, skew = B * Hkv * n * ns <= 768 ? 0.5 : 0.1;
     const double load = 1.15 * piece > mean + skew * piece ? 1.15 * piece : mean + skew * piece;
     const double us = load * tile + (ns > 1 ? 5 + ns * sums : 0);
@@ -958,10 +963,13 @@ static int dkdv_splits(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh
   }
   return best;
 }
-static size_t dkdv_partial_bytes(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
-  if (Hkv <= 0 || Hq % Hkv) return 0;   // a shape the call itself rejects
-  const int ns = dkdv_splits(B, S, Hq, Hkv, dh);
-  return ns > 1 ? (size_t)ns * 2 * B * S * Hkv * dh * sizeof(float) : 0;
+// Room for the partial sums, one fp32 tile of dK and one of dV per piece.  Reserved for the most pieces that a call with no
+// more key blocks may be split into and not for this call's own: how often a block is split falls as the batch grows,
+// and a buffer that was taken for a large batch has to serve a smaller one.
+static size_t dkdv_partial_bytes(int64_t B, int64_t S, int64_t Hkv, int64_t dh) {
+  if (Hkv <= 0) return 0;   // a shape the call itself rejects
+  const double most = (double)kMostPerBlock * (double)B * (double)Hkv * (double)(S / 128);
+  return (size_t)(most < kMostPieces ? most : kMostPieces) * 2 * 128 * (size_t)dh * sizeof(float);
 }
 // Handing dS over costs its HBM round trip (2 bytes per causal score, written and read once) and saves two of
 // the dQ pass's three products, whose cost grows with the head dim: worth it for 128-wide heads once the
@@ -972,7 +980,7 @@ static size_t bwd_ds_bytes(int64_t B, int64_t S, int64_t Hq, int64_t dh) {
   return ds_handoff(S, dh) ? (size_t)B * Hq * DsLayout::head_units(S) * DsLayout::UNIT : 0;
 }
 size_t attention_bwd_workspace(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
-  return bwd_stats_bytes(B, S, Hq) + bwd_ds_bytes(B, S, Hq, dh) + dkdv_partial_bytes(B, S, Hq, Hkv, dh);
+  return bwd_stats_bytes(B, S, Hq) + bwd_ds_bytes(B, S, Hq, dh) + dkdv_partial_bytes(B, S, Hkv, dh);
 }
 
 struct AttnBwdArgs {
