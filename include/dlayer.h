@@ -180,7 +180,8 @@ int rmsnorm_forward(const void* x, const void* gamma, int64_t T, int64_t D, floa
  *   dx = rstd*(dxhat - xhat*mean_d(dxhat*xhat)) + (dres ? dres : 0)
  * dres [T, D] bf16 is an optional gradient arriving through a residual connection (may be
  * NULL; may alias dx).  dgamma [D] bf16; accumulate_dgamma as in dlayer_backward.
- * workspace: rmsnorm_backward_workspace_bytes(T, D).                                        */
+ * workspace: rmsnorm_backward_workspace_bytes(T, D) = 4 D min(ceil(T / 8), 512) bytes, and 4 T more
+ * where D > 4096.                                                                           */
 size_t rmsnorm_backward_workspace_bytes(int64_t T, int64_t D);
 int rmsnorm_backward(const void* x, const void* gamma, const float* rstd, const void* dh,
                      const void* dres, int64_t T, int64_t D, void* dx, void* dgamma,

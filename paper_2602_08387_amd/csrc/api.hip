@@ -427,8 +427,9 @@ int rmsnorm_forward(const void* x, const void* gamma, int64_t T, int64_t D, floa
   return launch_rmsnorm_fwd(x, gamma, T, D, eps, h, rstd, (hipStream_t)stream);
 }
 
-// The size that callers are promised: rows wider than 4096 columns have one more float each, which the kernel leaves alone
-// (a row is held by one workgroup and read once, whatever its width).
+// Rows wider than 4096 columns have one more float each, which the kernel leaves alone (a row is held by one workgroup and
+// read once, whatever its width): the size is as it was when those rows took a pass of their own, for programs that
+// compare it or keep it.
 size_t rmsnorm_backward_workspace_bytes(int64_t T, int64_t D) {
   return T > 0 && D > 0 ? rmsnorm_bwd_workspace(T, D) + (D > 4096 ? (size_t)T * sizeof(float) : 0) : 0;
 }

@@ -114,15 +114,15 @@ int launch_rmsnorm_fwd_rope_table(const void* x, const void* gamma, int64_t T, i
 // RMSNorm backward.  TPR threads share a row, one 16-byte vector each (two beyond 8192 columns); a workgroup of RG such
 // groups walks rows with a grid stride, two at a time (one beyond 8192 columns), writes dx and keeps the gain-gradient sums of its columns in
 // registers, folds its groups through LDS and writes one fp32 partial row; a second kernel sums the partial
-// rows.  Bound by HBM (8 bytes per element with the residual gradient).  A thread that holds one vector of a row
-// needs 60 registers where a wave that holds the whole row needs 160, and the residual row is asked for together with
-// the others, so four times the loads are in flight; rows of any width are read once.
+// rows.  Bound by HBM (8 bytes per element with the residual gradient).  A thread holds one vector of a row where a wave
+// held the whole row, in 100 to 128 registers for its two rows, and the residual row is asked for together with the
+// others; rows of any width are read once.
 // ------------------------------------------------------------------------------------------
-template <int TPR, int NV>
-__global__ __launch_bounds__(TPR < 256 ? 256 : TPR) void rmsnorm_bwd_kernel(
+template <int TPR, int NV, int RG>
+__global__ __launch_bounds__(TPR * RG) void rmsnorm_bwd_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma, const float* __restrict__ rstd,
     const bf16_t* __restrict__ dh, const bf16_t* dres, bf16_t* dx, float* __restrict__ partial, int64_t T, int D) {
-  constexpr int RG = TPR < 256 ? 256 / TPR : 1, WPR = TPR / 64, U = NV == 1 ? 2 : 1;
+  constexpr int WPR = TPR / 64, U = NV == 1 ? 2 : 1;
   __shared__ float red[2][RG][U][WPR];
   __shared__ float fold[RG > 1 ? RG * TPR * NV * 8 : 1];
   const int rg = threadIdx.x / TPR, tr = threadIdx.x % TPR, lane = threadIdx.x & 63, wave = tr >> 6;
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(TPR < 256 ? 256 : TPR) void rmsnorm_bwd_kernel(
 #pragma unroll
       for (int e = 0; e < 8; ++e) fold[(rg * NV + i) * TPR * 8 + tr * 8 + e] = dg[i][e];
     __syncthreads();
-    for (int c = threadIdx.x; c < D; c += 256) {
+    for (int c = threadIdx.x; c < D; c += RG * TPR) {
       float s = 0.f;
 #pragma unroll
       for (int w = 0; w < RG; ++w) s += fold[w * NV * TPR * 8 + c];
@@ -267,32 +267,31 @@ __global__ __launch_bounds__(1024) void colsum_partials_kernel(const float* __re
   }
 }
 
-// threads per row, and workgroups (= partial rows): enough of them for every CU's registers, few enough that the partial
-// rows stay small next to the tensors
-static int rms_bwd_tpr(int64_t D) { return D <= 512 ? 64 : D <= 1024 ? 128 : D <= 2048 ? 256 : D <= 4096 ? 512 : 1024; }
-static int rms_bwd_blocks(int64_t T, int64_t D) {
-  const int tpr = rms_bwd_tpr(D), rg = tpr < 256 ? 256 / tpr : 1;
-  const int64_t b = (T + rg - 1) / rg, most = tpr <= 256 ? 1024 : 512;
-  return (int)(b < most ? b : most);
+// Workgroups, i.e. partial rows: one per eight rows and at most 512, which is what the size query asks room for.
+static int rms_bwd_blocks(int64_t T) {
+  const int64_t b = (T + 7) / 8;
+  return (int)(b < 512 ? b : 512);
 }
-size_t rmsnorm_bwd_workspace(int64_t T, int64_t D) { return (size_t)rms_bwd_blocks(T, D) * D * sizeof(float); }
+size_t rmsnorm_bwd_workspace(int64_t T, int64_t D) { return (size_t)rms_bwd_blocks(T) * D * sizeof(float); }
 
+// Threads per row by the width.  512 threads to a workgroup, so that two are resident on a compute unit - but 1024, two
+// rows side by side, for rows of 2056 to 4096 columns while every compute unit has at most one (D 4096, us, 512 / 1024
+// threads: T 2048 17.7 / 16.2, T 4096 25.3 / 27.6).  With 256 threads and up to 1024 partial rows: D 2048 T 8192 27.7
+// against 24.8, D 768 T 8192 14.3 against 13.0.
 int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd, const void* dh,
                             const void* dres, int64_t T, int64_t D, void* dx, void* workspace, hipStream_t st) {
-  const int nb = rms_bwd_blocks(T, D);
+  const int nb = rms_bwd_blocks(T);
   float* partial = (float*)workspace;
-#define RMS_BWD(TPR, NV)                                                                                     \
-  hipLaunchKernelGGL((rmsnorm_bwd_kernel<TPR, NV>), dim3(nb), dim3(TPR < 256 ? 256 : TPR), 0, st, (const bf16_t*)x, \
+#define RMS_BWD(TPR, NV, RG)                                                                                   \
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<TPR, NV, RG>), dim3(nb), dim3(TPR * RG), 0, st, (const bf16_t*)x,      \
                      (const bf16_t*)gamma, rstd, (const bf16_t*)dh, (const bf16_t*)dres, (bf16_t*)dx, partial, T, (int)D)
-  switch (rms_bwd_tpr(D)) {
-    case 64: RMS_BWD(64, 1); break;
-    case 128: RMS_BWD(128, 1); break;
-    case 256: RMS_BWD(256, 1); break;
-    case 512: RMS_BWD(512, 1); break;
-    default:
-      if (D <= 8192) RMS_BWD(1024, 1);
-      else RMS_BWD(1024, 2);
-  }
+  if (D <= 512) RMS_BWD(64, 1, 8);
+  else if (D <= 1024) RMS_BWD(128, 1, 4);
+  else if (D <= 2048) RMS_BWD(256, 1, 2);
+  else if (D <= 4096 && nb <= 256) RMS_BWD(512, 1, 2);
+  else if (D <= 4096) RMS_BWD(512, 1, 1);
+  else if (D <= 8192) RMS_BWD(1024, 1, 1);
+  else RMS_BWD(1024, 2, 1);
 #undef RMS_BWD
   return check_launch("rmsnorm_backward");
 }
@@ -300,7 +299,7 @@ int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd,
 int launch_rmsnorm_bwd_gain(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D,
                             int accumulate, hipStream_t st) {
   hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)((D + 31) / 32), dgamma_b ? 2 : 1), dim3(1024), 0, st, (const float*)ws_a,
-                     (const float*)ws_b, rms_bwd_blocks(T, D), (int)D, (bf16_t*)dgamma_a, (bf16_t*)dgamma_b, accumulate);
+                     (const float*)ws_b, rms_bwd_blocks(T), (int)D, (bf16_t*)dgamma_a, (bf16_t*)dgamma_b, accumulate);
   return check_launch("rmsnorm_backward(dgamma)");
 }
 

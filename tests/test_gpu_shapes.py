@@ -223,7 +223,8 @@ def test_rotary_projections_on_every_tile_size(K, B, S, D, Hq, Hkv, dh, layout):
 
 
 # ------------------------------------------------------------------ RMSNorm backward: threads per row, rows per workgroup
-@pytest.mark.parametrize("T,D", [(1, 8), (3, 512), (2050, 520), (1025, 1024), (5000, 1032), (77, 2056), (1030, 4096), (9, 8192), (515, 8200), (3, 16384)])
+@pytest.mark.parametrize("T,D", [(1, 8), (3, 512), (2050, 520), (1025, 1024), (5000, 1032), (77, 2056), (1030, 4096), (9, 8192), (515, 8200), (3, 16384),
+                                 (2048, 2056), (2049, 4096)])   # the last and the first of the two workgroup sizes
 def test_rmsnorm_backward_on_every_row_split(K, T, D):
     rng = np.random.default_rng(T + D)
     xb, db, rb = (_rand_bits(rng, (T, D)) for _ in range(3))

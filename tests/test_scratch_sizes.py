@@ -38,3 +38,9 @@ def test_layer_scratch_serves_smaller_batches_and_sequences(K, override):
         _never_falls([K.dlayer_workspace_bytes(cfg.with_(batch=B, seq=S)) for B in range(1, 25)], f"batch at S = {S}")
     for B in (1, 4):
         _never_falls([K.dlayer_workspace_bytes(cfg.with_(batch=B, seq=S)) for S in range(128, 4097, 128)], f"seq at B = {B}")
+
+
+@pytest.mark.parametrize("D", [8, 512, 520, 1024, 2048, 2056, 4096, 4104, 8192, 16384])
+def test_rmsnorm_backward_scratch_is_a_partial_row_per_eight_rows(K, D):
+    for T in (1, 7, 8, 9, 128, 1000, 4088, 4096, 4104, 16384):
+        assert K.rmsnorm_backward_workspace_bytes(T, D) == 4 * D * min(-(-T // 8), 512) + (4 * T if D > 4096 else 0)
