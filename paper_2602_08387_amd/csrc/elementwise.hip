@@ -593,6 +593,7 @@ int launch_embed_fwd(const void* table, const int64_t* ids, int64_t T, int64_t V
 //   count[v]   tokens with id v; slot[t] = the token's place among them      (embed_count_kernel)
 //   start[v]   first slot of id v's segment of list                          (embed_segments_kernel)
 //   list[...]  token indices grouped by id, slot[t] = position of t in list  (embed_fill_kernel)
+//   the segments of more than 512 tokens brought into order, beyond 131072 tokens only  (embed_sort_kernel)
 // Then one launch sums the rows with tokens, ids with few, with some and with many of them on workgroups of their own
 // (T = 8192, V = 128256, D = 4096, Zipf ids: 53 us where three launches took 109), and another zeroes the rows
 // without (0.97 of 1.05 GB, 165 us, 6.3 TB/s: the floor of the whole; both in one launch, side by side, take longer
@@ -607,6 +608,7 @@ constexpr int kEmbLight = 4;        // ids with at most this many tokens: one wa
 constexpr int kEmbMedium = 64;      // up to here one workgroup sums the row; beyond, one per 128 columns
 constexpr int kEmbListMax = 4096;   // sorted tokens held in LDS at a time
 constexpr int kEmbWordsMax = 4096;  // 32-bit words of the sorting bitmap: 131072 tokens at a time
+constexpr int kEmbBitmapTokens = kEmbWordsMax * 32;
 constexpr int kEmbSegIds = 4096;    // ids per workgroup of embed_segments_kernel
 
 __global__ __launch_bounds__(256) void embed_zero_ints_kernel(int* p, int64_t n) {
@@ -705,31 +707,125 @@ __global__ __launch_bounds__(256) void embed_fill_kernel(const int64_t* __restri
   }
 }
 
-// Rows of an id with more than kEmbMedium tokens, 128 columns per workgroup.  Its tokens are brought into ascending order
-// in LDS - up to 512 by counting the smaller ones, more through a bitmap of the tokens whose words are prefix-summed
-// - a piece of the token range at a time, so that a piece holds at most kEmbListMax of them.
-__device__ __forceinline__ void embed_sum_heavy(const bf16_t* __restrict__ dx0, const int* __restrict__ count,
-                                                const int* __restrict__ start, const int* __restrict__ list, int64_t id, int split,
-                                                bf16_t* __restrict__ dtable, int T, int D, char* lds) {
+// Bits of the tokens [lo, lo + 32 words) with this id, from the ids themselves; eight loads per thread in flight.  Every
+// thread of the workgroup calls it.
+template <int NT>
+__device__ __forceinline__ void embed_mark_tokens(const int64_t* __restrict__ ids, int64_t id, int lo, int T, int words, unsigned* bits) {
+  const int lane = threadIdx.x & 63;
+  for (int i0 = 0; i0 < words * 32; i0 += 8 * NT) {
+    int64_t v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int t = lo + i0 + q * NT + (int)threadIdx.x;
+      v[q] = t < T ? ids[t] : -1;   // an id that is looked for is never negative
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int i = i0 + q * NT + (int)threadIdx.x;
+      const unsigned long long m = __ballot(v[q] == id);
+      if ((lane & 31) == 0 && i < words * 32) bits[i >> 5] = (unsigned)(lane ? m >> 32 : m);
+    }
+  }
+}
+
+// Writes base + the index of every set bit, in ascending order, to out; returns their number.  The bits and, at the return,
+// the list are the workgroup's: the caller puts a barrier on either side.  wsum: a word per wavefront.
+template <int NT>
+__device__ __forceinline__ int embed_list_bits(const unsigned* bits, int words, int base, int* out, int* wsum) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (words + NT - 1) / NT, w0 = tid * per, w1 = w0 + per < words ? w0 + per : words;
+  int mine = 0, total, n = 0;
+  for (int w = w0; w < w1; ++w) mine += __builtin_popcount(bits[w]);
+  int o = wave_prefix(mine, lane, total);
+  if (lane == 0) wsum[wave] = total;
+  __syncthreads();
+  for (int w = 0; w < NT / 64; ++w) { if (w < wave) o += wsum[w]; n += wsum[w]; }
+  for (int w = w0; w < w1; ++w) {
+    unsigned m = bits[w];
+    while (m) { out[o++] = base + w * 32 + __builtin_ctz(m); m &= m - 1; }
+  }
+  return n;
+}
+
+// Brings the token lists of more than kEmbThreads tokens into ascending order, in place, one workgroup per id, so that the
+// column splits of the summing kernel need not each sort them.  Only for batches that one bitmap does not span: up to there
+// the summing kernel's own bitmap costs less than this launch.  Lists of up to kEmbSortMax tokens go through a bitonic
+// network in LDS, whatever the number of tokens in the batch; a longer one is rebuilt from one walk over the ids.
+constexpr int kEmbSortMax = 8192;
+__global__ __launch_bounds__(1024) void embed_sort_kernel(const int64_t* __restrict__ ids, const int* __restrict__ count,
+                                                          const int* __restrict__ start, int* list, const int* __restrict__ many,
+                                                          int most, const int* __restrict__ n_many, int T) {
+  __shared__ int lst[kEmbSortMax];
+  __shared__ int wsum[16];
+  const int nh = n_many[1], tid = threadIdx.x;
+  for (int hi = blockIdx.x; hi < nh; hi += gridDim.x) {
+    const int64_t id = many[most - 1 - hi];
+    const int first = start[id], L = count[id];
+    if (L <= kEmbThreads) continue;
+    __syncthreads();   // the list of the id before has been read
+    if (L <= kEmbSortMax) {
+      int n2 = 1;
+      while (n2 < L) n2 <<= 1;
+      for (int i = tid; i < n2; i += 1024) lst[i] = i < L ? list[first + i] : T;
+      __syncthreads();
+      for (int k = 2; k <= n2; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+          for (int i = tid; i < n2; i += 1024) {
+            const int p = i ^ j;
+            if (p > i) {
+              const int x = lst[i], y = lst[p];
+              if ((x > y) == ((i & k) == 0)) { lst[i] = y; lst[p] = x; }
+            }
+          }
+          __syncthreads();
+        }
+      for (int i = tid; i < L; i += 1024) list[first + i] = lst[i];
+    } else {
+      unsigned* bits = reinterpret_cast<unsigned*>(lst);
+      static_assert(kEmbWordsMax <= kEmbSortMax, "the bitmap takes the list's place");
+      int done = 0;
+      for (int lo = 0; lo < T; lo += kEmbBitmapTokens) {
+        const int left = T - lo, words = (left < kEmbBitmapTokens ? left + 31 : kEmbBitmapTokens) >> 5;
+        embed_mark_tokens<1024>(ids, id, lo, T, words, bits);
+        __syncthreads();
+        done += embed_list_bits<1024>(bits, words, lo, list + first + done, wsum);
+        __syncthreads();   // the bits and the wavefronts' sums have been read
+      }
+    }
+  }
+}
+
+// Rows of an id with more than kEmbMedium tokens, 128 columns per workgroup: the row of rank r in ascending token order goes
+// to partial sum r % 32, whichever way the order is found.  Up to 512 tokens are ranked in LDS by counting the smaller ones.
+// More come from a bitmap of the batch where one spans it: filled from the id's list, or, where there are more of them
+// than the list in LDS holds, from the ids, a piece of 4096 tokens at a time (scanning the id's list anew for every
+// piece took time that grew with the square of T; half of the batch one id, V 128256, us, that way and this: T 65536
+// D 4096 972 / 828).  Beyond that size embed_sort_kernel has sorted the list (T 262144 D 1024 4706 / 2471; Zipf ids 1094 / 688).
+__device__ __forceinline__ void embed_sum_heavy(const bf16_t* __restrict__ dx0, const int64_t* __restrict__ ids,
+                                                const int* __restrict__ count, const int* __restrict__ start,
+                                                const int* __restrict__ list, int64_t id, int split, bf16_t* __restrict__ dtable, int T,
+                                                int D, char* lds) {
   int* lst = reinterpret_cast<int*>(lds);
   unsigned* bits = reinterpret_cast<unsigned*>(lst + kEmbListMax);
   float(*part)[kEmbVecs][8] = reinterpret_cast<float(*)[kEmbVecs][8]>(bits);   // after the last use of the bitmap
   __shared__ int wsum[kEmbThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   const int vec = tid % kEmbVecs, grp = tid / kEmbVecs;
   const int cvec = split * kEmbVecs + vec;
   const bool col_ok = cvec < (D >> 3);
   const bf16_t* col = dx0 + (col_ok ? cvec * 8 : 0);
   const int first = start[id], L = count[id];
-  const int piece = L <= kEmbListMax ? kEmbWordsMax * 32 : kEmbListMax;
+  const bool few = L <= kEmbThreads, sorted = !few && T > kEmbBitmapTokens;
+  // the walk: over ranks of a sorted list, else over tokens
+  const int end = few ? 1 : sorted ? L : T, step = few ? 1 : sorted || L > kEmbListMax ? kEmbListMax : T;
   float a[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) a[e] = 0.f;
-  for (int lo = 0; lo < T; lo += piece) {
+  int done = 0;      // rows of the steps before
+  for (int lo = 0; lo < end; lo += step) {
     int n = 0;
-    __syncthreads();   // the list and the partial sums of the piece or id before have been read
-    if (L <= kEmbThreads) {
-      // one pass, whatever the token range
+    __syncthreads();   // the list and the partial sums of the step or id before have been read
+    if (few) {
       const int mine = tid < L ? list[first + tid] : 0;
       if (tid < L) reinterpret_cast<int*>(bits)[tid] = mine;
       __syncthreads();
@@ -739,30 +835,27 @@ __device__ __forceinline__ void embed_sum_heavy(const bf16_t* __restrict__ dx0, 
         lst[rank] = mine;
       }
       n = L;
+    } else if (sorted) {
+      n = L - lo < kEmbListMax ? L - lo : kEmbListMax;
+      for (int i = tid; i < n; i += kEmbThreads) lst[i] = list[first + lo + i];
     } else {
-      const int hi = lo + piece < T ? lo + piece : T, words = (hi - lo + 31) >> 5;
-      for (int w = tid; w < words; w += kEmbThreads) bits[w] = 0u;
-      __syncthreads();
-      for (int i = tid; i < L; i += kEmbThreads) {
-        const int t = list[first + i] - lo;
-        if (t >= 0 && t < hi - lo) atomicOr(&bits[t >> 5], 1u << (t & 31));
+      const int left = T - lo, words = (left < step ? left + 31 : step + 31) >> 5;
+      if (L > kEmbListMax) {
+        embed_mark_tokens<kEmbThreads>(ids, id, lo, T, words, bits);
+      } else {
+        for (int w = tid; w < words; w += kEmbThreads) bits[w] = 0u;
+        __syncthreads();
+        for (int i = tid; i < L; i += kEmbThreads) {
+          const int t = list[first + i];
+          atomicOr(&bits[t >> 5], 1u << (t & 31));
+        }
       }
       __syncthreads();
-      const int per = (words + kEmbThreads - 1) / kEmbThreads, w0 = tid * per, w1 = w0 + per < words ? w0 + per : words;
-      int mine = 0, total;
-      for (int w = w0; w < w1; ++w) mine += __builtin_popcount(bits[w]);
-      int o = wave_prefix(mine, lane, total);
-      if (lane == 0) wsum[wave] = total;
-      __syncthreads();
-      for (int w = 0; w < kEmbThreads / 64; ++w) { if (w < wave) o += wsum[w]; n += wsum[w]; }
-      for (int w = w0; w < w1; ++w) {
-        unsigned m = bits[w];
-        while (m) { lst[o++] = lo + w * 32 + __builtin_ctz(m); m &= m - 1; }
-      }
+      n = embed_list_bits<kEmbThreads>(bits, words, lo, lst, wsum);
     }
     __syncthreads();
     if (col_ok) {
-      int j = grp;
+      int j = (grp - done) & (kEmbGroups - 1);
       for (; j + 7 * kEmbGroups < n; j += 8 * kEmbGroups) {   // eight rows in flight
         bf16x8 r[8];
 #pragma unroll
@@ -778,7 +871,7 @@ __device__ __forceinline__ void embed_sum_heavy(const bf16_t* __restrict__ dx0, 
         for (int e = 0; e < 8; ++e) a[e] += (float)r0[e];
       }
     }
-    if (L <= kEmbThreads) break;
+    done += n;
   }
   __syncthreads();   // the bitmap (or the unsorted list in its place) has been read
 #pragma unroll
@@ -819,7 +912,7 @@ __global__ __launch_bounds__(kEmbThreads, 8) void embed_grad_kernel(
   int b = blockIdx.x;
   if (b < n_hb * n_cs) {
     const int nh = n_many[1];
-    for (int hi = b / n_cs; hi < nh; hi += n_hb) embed_sum_heavy(dx0, count, start, list, many[most - 1 - hi], b % n_cs, dtable, T, D, lds);
+    for (int hi = b / n_cs; hi < nh; hi += n_hb) embed_sum_heavy(dx0, ids, count, start, list, many[most - 1 - hi], b % n_cs, dtable, T, D, lds);
     return;
   }
   b -= n_hb * n_cs;
@@ -925,6 +1018,12 @@ int launch_embed_bwd(const void* dx0, const int64_t* ids, int64_t T, int64_t V, 
   hipLaunchKernelGGL(embed_fill_kernel, dim3(tb), dim3(256), 0, st, ids, (int)T, (const int*)count, (const int*)start, list, slot,
                      many, (int)most, n_many);
   if (int rc = check_launch("embed_backward(fill)")) return rc;
+  if (T > kEmbBitmapTokens) {
+    const int64_t lists = T / (kEmbThreads + 1);
+    hipLaunchKernelGGL(embed_sort_kernel, dim3((unsigned)(lists < 1024 ? lists : 1024)), dim3(1024), 0, st, ids, (const int*)count,
+                       (const int*)start, list, (const int*)many, (int)most, (const int*)n_many, (int)T);
+    if (int rc = check_launch("embed_backward(sort)")) return rc;
+  }
   // Half of the chip's 1024 workgroup slots for the heavy ids, as many for the medium ones; a workgroup that finds no id
   // ends at once.
   const int64_t cs = (D / 8 + kEmbVecs - 1) / kEmbVecs, max_heavy = T / (kEmbMedium + 1);

@@ -252,7 +252,9 @@ def test_rmsnorm_backward_on_every_row_split(K, T, D):
     (9, 1032, 1200, [513, 600]),                 # the bitmap; nine column splits, the last one partly filled
     (4, 16, 6000, [4096, 1800]),                 # a full list
     (4, 16, 9000, [4097, 4800]),                 # more tokens than the list holds: walked in pieces
-    (5, 8, 140000, [3000, 65, 4]),               # tokens beyond one bitmap (131072)
+    (3, 264, 131072, [4096, 20000, 9001]),       # the largest batch that one bitmap spans, three column splits
+    (5, 8, 140000, [3000, 65, 4]),               # tokens beyond one bitmap: lists of more than 512 sorted beforehand,
+    (6, 136, 140033, [512, 513, 8192, 8193, 40000, 70]),   # up to 8192 in LDS, longer ones from the ids
 ])
 def test_embedding_gradient_by_token_counts(K, V, D, T, counts):
     rng = np.random.default_rng(T + V)
@@ -272,3 +274,25 @@ def test_embedding_gradient_by_token_counts(K, V, D, T, counts):
     assert _norm_err(runs[0], ref) <= ONE_ROUNDING
     assert not host_f64(runs[0])[ref.any(axis=1) == False].any()   # noqa: E712
     assert torch.equal(runs[0].view(torch.int16), runs[1].view(torch.int16))
+
+
+def test_embedding_gradient_time_grows_with_the_tokens(K):
+    """Half of the batch is one id (a padding token): four times the tokens may take four times as long, not sixteen."""
+    def best_ms(T):
+        rng = np.random.default_rng(T)
+        ids = rng.integers(0, 1000, T)
+        ids[rng.permutation(T)[:T // 2]] = 7
+        idd, dd = torch.from_numpy(ids).cuda(), torch.zeros(T, 8, dtype=torch.bfloat16, device="cuda")
+        out, ws = torch.empty(1000, 8, dtype=torch.bfloat16, device="cuda"), _poisoned(K.embed_backward_workspace_bytes(T, 1000))
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            K.embed_backward(dd, idd, T, 1000, 8, out, ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    small, large = best_ms(1 << 18), best_ms(1 << 20)
+    print(f"{small:.3f} ms, {large:.3f} ms")
+    assert large <= 8 * small
