@@ -340,6 +340,26 @@ int adamw_step(int32_t n, void* const* params, const void* const* grads, float* 
  * synchronises with the stream.                                                                   */
 int issue_rate_probe(int family, int variant, int waves_per_simd, double* result, void* stream);
 
+/* How the library would run a call, on the host: nothing is launched.  For tests and for reading profiles; the
+ * answers follow rules fitted to measurements and may change.  compute_units: of the device in question (0: the
+ * current device's, 256 where there is none).
+ *
+ * gemm_route: a product C[M, N] with contraction K (or n of them in one launch: weight gradients or rotary
+ * projections).
+ *   operands  0 both stored along K (y = x W^T), 1 the second along N (dx = dy W, W as stored),
+ *             2 both along M or N (dW = dy^T x)
+ *   epilogue  0 none, residual or accumulation, 1 gated pair (N = columns of each half), 2 its gradient,
+ *             3 rotary embedding with split pairs, 4 with adjacent pairs (head_dim: else ignored)
+ * route (3 ints): tile of the first launch (0 128x256, 1 128x128, 2 64x64, one tile per workgroup;
+ * 3 256x256, persistent workgroups), tile of the second launch or -1, rows (of all n together) in the first.
+ *
+ * attention_backward_pieces: workgroups that share the work of 128 keys in the dK/dV pass of attention_backward (0: a shape
+ * it rejects).                                                                                       */
+int gemm_route(int32_t operands, int32_t epilogue, int32_t head_dim, int32_t compute_units, int32_t n,
+               const int64_t* M, const int64_t* N, const int64_t* K, int32_t* route);
+int attention_backward_pieces(int64_t batch, int64_t seq, int64_t n_q_heads, int64_t n_kv_heads,
+                              int64_t head_dim, int32_t compute_units);
+
 #ifdef __cplusplus
 }
 #endif

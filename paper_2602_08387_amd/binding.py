@@ -18,7 +18,7 @@ EXPORTED_SYMBOLS = (
     "linear_swiglu_backward", "linear_backward_workspace_bytes", "linear_backward", "linear_wgrad_group", "rope_apply",
     "attention_forward", "attention_backward_workspace_bytes", "attention_backward",
     "swiglu_forward", "swiglu_backward", "embed_forward", "embed_backward_workspace_bytes", "embed_backward",
-    "grad_sq_norm_workspace_bytes", "grad_sq_norm", "adamw_step", "issue_rate_probe",
+    "grad_sq_norm_workspace_bytes", "grad_sq_norm", "adamw_step", "issue_rate_probe", "gemm_route", "attention_backward_pieces",
 )
 
 
@@ -97,6 +97,8 @@ def _load():
         "grad_sq_norm": (C.c_int, [i32, vp, vp, vp, C.c_int, vp, vp]),
         "adamw_step": (C.c_int, [i32, vp, vp, vp, vp, vp, i64, f32, f32, f32, f32, f32, f32, vp, vp]),
         "issue_rate_probe": (C.c_int, [C.c_int, C.c_int, C.c_int, vp, vp]),
+        "gemm_route": (C.c_int, [i32, i32, i32, i32, i32, vp, vp, vp, vp]),
+        "attention_backward_pieces": (C.c_int, [i64, i64, i64, i64, i64, i32]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(l, name)
@@ -331,3 +333,17 @@ def issue_rate_probe(family, variant, waves_per_simd=2, stream=None):
     out = (C.c_double * 4)()
     _check(lib.issue_rate_probe(family, variant, waves_per_simd, out, _stream(stream)), "issue_rate_probe")
     return tuple(out)
+
+
+def gemm_route(operands, epilogue, Ms, Ns, Ks, head_dim=0, compute_units=0):
+    """(tile of the first launch, tile of the second or -1, rows in the first)"""
+    n = len(Ms)
+    assert len(Ns) == len(Ks) == n
+    i64s = lambda vs: (C.c_int64 * n)(*[int(v) for v in vs])
+    route = (C.c_int32 * 3)()
+    _check(lib.gemm_route(operands, epilogue, head_dim, compute_units, n, i64s(Ms), i64s(Ns), i64s(Ks), route), "gemm_route")
+    return tuple(route)
+
+
+def attention_backward_pieces(batch, seq, n_q_heads, n_kv_heads, head_dim, compute_units=0) -> int:
+    return lib.attention_backward_pieces(batch, seq, n_q_heads, n_kv_heads, head_dim, compute_units)

@@ -694,6 +694,29 @@ int embed_backward(const void* dx0, const int64_t* ids, int64_t T, int64_t V, in
   return launch_embed_bwd(dx0, ids, T, V, D, dtable, workspace, (hipStream_t)stream);
 }
 
+int gemm_route(int32_t operands, int32_t epilogue, int32_t head_dim, int32_t compute_units, int32_t n, const int64_t* M,
+               const int64_t* N, const int64_t* K, int32_t* route) {
+  REQUIRE(operands >= GEMM_ROUTE_K_K && operands <= GEMM_ROUTE_MN_MN && epilogue >= GEMM_ROUTE_PLAIN && epilogue <= GEMM_ROUTE_ROTARY_ADJACENT,
+          "gemm_route: operands 0..2, epilogue 0..4");
+  const bool rotary = epilogue >= GEMM_ROUTE_ROTARY_SPLIT;
+  REQUIRE(epilogue == GEMM_ROUTE_PLAIN || operands == GEMM_ROUTE_K_K || (epilogue == GEMM_ROUTE_GATED_GRADIENT && operands == GEMM_ROUTE_K_MN),
+          "gemm_route: no product has this epilogue with these operands");
+  REQUIRE(!rotary || head_dim == 32 || head_dim == 64 || head_dim == 128, "gemm_route: head_dim must be 32, 64 or 128");
+  REQUIRE(n >= 1 && n <= 8 && (n == 1 || rotary || operands == GEMM_ROUTE_MN_MN), "gemm_route: 1 product, or up to 8 weight gradients or rotary projections");
+  REQUIRE(M && N && K && route && compute_units >= 0, "gemm_route: null argument or negative number of compute units");
+  for (int i = 0; i < n; ++i)
+    REQUIRE(M[i] > 0 && N[i] > 0 && K[i] > 0 && M[i] < (1 << 30) && N[i] < (1 << 30) && K[i] < (1 << 30) && K[i] % 64 == 0,
+            "gemm_route: sizes must be positive and below 2^30, K a multiple of 64");
+  query_gemm_route(operands, epilogue, head_dim, compute_units, n, M, N, K, route);
+  return DLAYER_OK;
+}
+
+int attention_backward_pieces(int64_t batch, int64_t seq, int64_t n_q_heads, int64_t n_kv_heads, int64_t head_dim,
+                              int32_t compute_units) {
+  if (attn_shape_ok(batch, seq, n_q_heads, n_kv_heads, head_dim, "attention_backward_pieces")) return 0;
+  return attention_bwd_pieces(batch, seq, n_q_heads, n_kv_heads, head_dim, compute_units > 0 ? compute_units : dl::compute_units());
+}
+
 int issue_rate_probe(int family, int variant, int waves_per_simd, double* result, void* stream) {
   REQUIRE(result != nullptr, "issue_rate_probe: result is null");
   REQUIRE(family >= 0 && family <= 3 && variant >= 0 && variant <= 3, "issue_rate_probe: family 0..3, variant 0..3");

@@ -624,12 +624,12 @@ __global__ __launch_bounds__(256 * NH, 2 / NH) void attn_bwd_dq_from_ds_kernel(
 // To hold both accumulators at two waves per SIMD the wave's V fragments live in LDS (the 128-key V tile
 // stays resident), only its K fragments in registers, and the query tile is 32 rows.
 //
-// `ns` workgroups share a key block (dkdv_splits): number p takes every ns-th (query tile, head) of the
+// `ns` workgroups share a key block (attention_bwd_pieces): number p takes every ns-th (query tile, head) of the
 // walk, so all of them still move over the same query tiles at the same pace and meet in the L2, and leaves
 // its fp32 sums in part[p] for attn_dkdv_reduce_kernel, which adds them in the order of p.  The causal
 // triangle makes a key block's work fall from S/32 tiles per head to 4, and with few KV heads there are
 // fewer blocks than the 512 workgroups the chip holds, so one workgroup per block leaves the launch
-// waiting for the first ones (measurements at dkdv_splits).
+// waiting for the first ones (measurements at attention_bwd_pieces).
 // ------------------------------------------------------------------------------------------
 template <int DH, bool WRITE_DS>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(
@@ -947,15 +947,15 @@ static size_t bwd_stats_bytes(int64_t B, int64_t S, int64_t Hq) {
 // B4 S2048 16q/8kv x128 260 (275 with 2), B8 S1024 12q/12kv x64 79 (104 with 2).
 constexpr int kMostPerBlock = 8;
 constexpr int64_t kMostPieces = 1536;
-static int dkdv_splits(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh) {
+int attention_bwd_pieces(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh, int cus) {
   const int64_t n = S / 128;
-  const double longest = (double)(Hq / Hkv * 4 * n), mean = (double)B * Hq * 4 * n * (n + 1) / 2 / 256;   // tiles; per CU
+  const double longest = (double)(Hq / Hkv * 4 * n), mean = (double)B * Hq * 4 * n * (n + 1) / 2 / cus;   // tiles; per CU
   const double tile = dh == 128 ? 1.1 : dh == 64 ? 0.7 : 0.45;
   const double sums = (double)B * S * Hkv * dh * 16 / 4.2e6;
   int best = 1;
   double best_us = 0, whole_us = 0;
   for (int ns = 1; ns <= kMostPerBlock && (ns == 1 || ns * B * Hkv * n <= kMostPieces); ++ns) {
-    const double piece = longest / ns, skew = B * Hkv * n * ns <= 768 ? 0.5 : 0.1;
+    const double piece = longest / ns, skew = B * Hkv * n * ns <= 3 * cus ? 0.5 : 0.1;
     const double load = 1.15 * piece > mean + skew * piece ? 1.15 * piece : mean + skew * piece;
     const double us = load * tile + (ns > 1 ? 5 + ns * sums : 0);
     if (ns == 1) whole_us = best_us = us;
@@ -1022,7 +1022,7 @@ static int bwd_dh(const void* q, const void* k, const void* v, const void* o, co
   a.dq = (bf16_t*)dq; a.dk = (bf16_t*)dk; a.dv = (bf16_t*)dv;
   a.ds = reinterpret_cast<bf16_t*>(after_stats);
   a.part = reinterpret_cast<float*>(after_stats + bwd_ds_bytes(B, S, Hq, DH));
-  a.ns = dkdv_splits(B, S, Hq, Hkv, DH);
+  a.ns = attention_bwd_pieces(B, S, Hq, Hkv, DH, compute_units());
   a.B = (int)B; a.S = (int)S; a.Hq = (int)Hq; a.Hkv = (int)Hkv;
   a.scale = (float)(1.0 / sqrt((double)DH));
   a.rope_cos = rope_cos; a.rope_sin = rope_sin; a.rope_layout = rope_layout;

@@ -581,18 +581,22 @@ static int band_rows_for(bool both_kmajor, int64_t k_total, bool epilogue_reads_
   return both_kmajor && !epilogue_reads_tiles && k_total <= 4096 ? 8 : 4;
 }
 
-// One workgroup per CU (the tile's ring and staging take all of the LDS), fewer if there are fewer tiles.
-static int persistent_grid(int ntiles) {
+int compute_units() {
   static std::atomic<int> cu_count[64];   // per device; 0 = not asked yet
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) return ntiles;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) return 256;
   int cus = cu_count[dev].load(std::memory_order_relaxed);
   if (cus == 0) {
     int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return ntiles;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 256;
     cus = n > 0 ? n : 256;
     cu_count[dev].store(cus, std::memory_order_relaxed);
   }
+  return cus;
+}
+// One workgroup per CU (the tile's ring and staging take all of the LDS), fewer if there are fewer tiles.
+static int persistent_grid(int ntiles) {
+  const int cus = compute_units();
   return ntiles < cus ? ntiles : cus;
 }
 
@@ -660,33 +664,33 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
 // (a CU runs faster while others idle: clock, L2) - and the cheapest runs: the persistent kernel, one of the three
 // tile sizes of gemm_tile.hip, or the persistent kernel for its full rounds and a smaller tile, in a second
 // launch, for the rows left over.  All give the same bits.  Microseconds, from sweeps on MI355X
-// (both operands k-major / an operand mn-major); slots: tiles in flight.  The estimates are within 10 % of
-// the measured launches from 15 us up.
+// (both operands k-major / an operand mn-major); per_cu: tiles of a compute unit in flight.  The estimates are within 10 % of
+// the measured launches from 15 us up (256 compute units).
 // ------------------------------------------------------------------------------------------
-struct KernelCost { int bm, bn, slots; double lo, hi, tile; };
+struct KernelCost { int bm, bn, per_cu; double lo, hi, tile; };
 constexpr int kPersistent = 3;
 static const KernelCost kCostKK[4] = {
-    {128, 256, 256, 0.62, 0.75, 4.0},   // T = 8192, K = 4096, N = 768 (192 tiles): 50 us against 71 on 96 tiles of 256 x 256
-    {128, 128, 256, 0.38, 0.48, 3.0},   // T = 1920, K = 6272, N = 1152 (135 tiles): 44 us; 67 as 75 tiles of 128 x 256
-    {64, 64, 512, 0.25, 0.33, 2.0},     // T = 2048, K = 2816, N = 1024 (512 tiles): 20 us; 23 as 128 tiles of 128 x 128
-    {256, 256, 256, 0.98, 1.39, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
+    {128, 256, 1, 0.62, 0.75, 4.0},   // T = 8192, K = 4096, N = 768 (192 tiles): 50 us against 71 on 96 tiles of 256 x 256
+    {128, 128, 1, 0.38, 0.48, 3.0},   // T = 1920, K = 6272, N = 1152 (135 tiles): 44 us; 67 as 75 tiles of 128 x 256
+    {64, 64, 2, 0.25, 0.33, 2.0},     // T = 2048, K = 2816, N = 1024 (512 tiles): 20 us; 23 as 128 tiles of 128 x 128
+    {256, 256, 1, 0.98, 1.39, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
 static const KernelCost kCostMN[4] = {
-    {128, 256, 256, 0.70, 0.82, 4.0},   // 768 x 768, K = 8192 (18 tiles): 94 us
-    {128, 128, 256, 0.48, 0.56, 3.0},   // the same as 36 tiles: 63 us
-    {64, 64, 512, 0.28, 0.39, 2.0},     // as 144 tiles: 39 us (157 as 9 tiles of 256 x 256)
-    {256, 256, 256, 1.20, 1.45, 5.0}};
+    {128, 256, 1, 0.70, 0.82, 4.0},   // 768 x 768, K = 8192 (18 tiles): 94 us
+    {128, 128, 1, 0.48, 0.56, 3.0},   // the same as 36 tiles: 63 us
+    {64, 64, 2, 0.28, 0.39, 2.0},     // as 144 tiles: 39 us (157 as 9 tiles of 256 x 256)
+    {256, 256, 1, 1.20, 1.45, 5.0}};
 constexpr double kLaunchUs = 3.5;
 
-static double kernel_us(const KernelCost& c, const GemmKArgs* ks, int n) {
+static double kernel_us(const KernelCost& c, int cus, const GemmKArgs* ks, int n) {
   int64_t tiles = 0, steps = 0;
   for (int i = 0; i < n; ++i) {
     tiles += (int64_t)((ks[i].M + c.bm - 1) / c.bm) * ((ks[i].N + c.bn - 1) / c.bn);
     const int64_t s = k_total(ks[i]) / BK;
     steps = s > steps ? s : steps;
   }
-  const int64_t full = tiles / c.slots, rem = tiles % c.slots;
+  const int64_t slots = (int64_t)c.per_cu * cus, full = tiles / slots, rem = tiles % slots;
   double us = kLaunchUs + full * (steps * c.hi + c.tile);
-  if (rem) us += steps * (c.lo + (c.hi - c.lo) * rem / c.slots) + c.tile;
+  if (rem) us += steps * (c.lo + (c.hi - c.lo) * rem / slots) + c.tile;
   return us;
 }
 
@@ -703,59 +707,98 @@ static GemmKArgs row_part(GemmKArgs k, int r0, int rows, bool a_kmajor) {
   return k;
 }
 
-static int run_gemm(const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, hipStream_t st) {
+// What a product, or a group of them, runs as: `first` takes all of it, or rows of it that `second`, in a launch of its own,
+// does not (head and tail: the products, or their rows, of the two).
+struct GemmPlan {
+  int first, second = -1;   // index into the cost tables
+  int nh = 0, nt = 0;
+  GemmKArgs head[MAX_GROUP], tail[MAX_GROUP];
+};
+
+static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, int cus) {
   const KernelCost* cost = ak && bk ? kCostKK : kCostMN;
   // a 64-column tile does not hold both members of a split pair of a 128-wide head; the persistent kernels are not built
   // for one k-major and one mn-major operand
   const bool no64 = rope && rope->layout == 0 && rope->head_dim == 128, persistent = ak == bk;
   auto best_tile = [&](const GemmKArgs* ps, int m, double& us) {
     int best = 0;
-    us = kernel_us(cost[0], ps, m);
+    us = kernel_us(cost[0], cus, ps, m);
     for (int c = 1; c < (no64 ? 2 : 3); ++c) {
-      const double u = kernel_us(cost[c], ps, m);
+      const double u = kernel_us(cost[c], cus, ps, m);
       if (u < us) { us = u; best = c; }
     }
     return best;
   };
-  auto run_persistent = [&](const GemmKArgs* ps, int m) {
-    return m > 1 || rope ? launch_persistent_group(ps, m, ak, bk, rope, st) : launch_persistent(ps[0], ak, bk, epi, st);
-  };
-  double tile_us, best_us;
+  double tile_us;
   const int tile = best_tile(ks, n, tile_us);
-  best_us = persistent ? kernel_us(cost[kPersistent], ks, n) : 1e30;
+  const double whole_us = persistent ? kernel_us(cost[kPersistent], cus, ks, n) : 1e30;
   // full rounds of the persistent kernel, the rows behind them on a smaller tile
-  GemmKArgs head[MAX_GROUP], tail[MAX_GROUP];
-  int nh = 0, nt = 0, tail_tile = 0;
   int64_t tiles = 0;
   for (int i = 0; i < n; ++i) tiles += (int64_t)((ks[i].M + PM - 1) / PM) * ((ks[i].N + PN - 1) / PN);
-  const bool can_split = persistent && tiles > 256 && tiles % 256 != 0;
-  double split_us = 1e30;
-  if (can_split) {
-    int64_t room = tiles / 256 * 256;
+  if (persistent && tiles > cus && tiles % cus != 0) {
+    int64_t room = tiles / cus * cus;
     for (int i = 0; i < n; ++i) {
       const int tn = (ks[i].N + PN - 1) / PN;
       const int64_t fit = room / tn * PM;   // rows that still fit
       const int rows = fit < ks[i].M ? (int)fit : ks[i].M;
-      if (rows > 0) head[nh++] = row_part(ks[i], 0, rows, ak);
-      if (rows < ks[i].M) tail[nt++] = row_part(ks[i], rows, ks[i].M - rows, ak);
+      if (rows > 0) p.head[p.nh++] = row_part(ks[i], 0, rows, ak);
+      if (rows < ks[i].M) p.tail[p.nt++] = row_part(ks[i], rows, ks[i].M - rows, ak);
       room -= (int64_t)((rows + PM - 1) / PM) * tn;
     }
-    if (nh > 0 && nt > 0) {
-      double t_us;
-      tail_tile = best_tile(tail, nt, t_us);
-      split_us = kernel_us(cost[kPersistent], head, nh) + t_us;
+    if (p.nh > 0 && p.nt > 0) {
+      double tail_us;
+      const int tail_tile = best_tile(p.tail, p.nt, tail_us);
+      const double split_us = kernel_us(cost[kPersistent], cus, p.head, p.nh) + tail_us;
+      // The second launch drains the chip once more, which the estimate of a launch leaves out: 3 %, and 10 % for the gated
+      // pair, whose three outputs the persistent kernel stores under its next main loop (T = 2048, K = 4096,
+      // F = 14336: 413 us in two launches, 406 in one, 7 % apart the other way in the estimate).
+      const double margin = epi == TileEpilogue::SWIGLU ? 0.9 : 0.97;
+      if (split_us < margin * whole_us && split_us < tile_us) {
+        p.first = kPersistent;
+        p.second = tail_tile;
+        return;
+      }
     }
   }
-  // The second launch drains the chip once more, which the estimate of a launch leaves out: 3 %, and 10 % for the gated
-  // pair, whose three outputs the persistent kernel stores under its next main loop (T = 2048, K = 4096,
-  // F = 14336: 413 us in two launches, 406 in one, 7 % apart the other way in the estimate).
-  const double margin = epi == TileEpilogue::SWIGLU ? 0.9 : 0.97;
-  if (split_us < margin * best_us && split_us < tile_us) {
-    if (int rc = run_persistent(head, nh)) return rc;
-    return launch_gemm_tile((TileSize)tail_tile, tail, nt, ak, bk, epi, rope, st);
+  p.nh = n;
+  p.nt = 0;
+  for (int i = 0; i < n; ++i) p.head[i] = ks[i];
+  p.first = whole_us <= tile_us ? kPersistent : tile;
+}
+
+static int run_gemm(const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, hipStream_t st) {
+  GemmPlan p;
+  plan_gemm(p, ks, n, ak, bk, epi, rope, compute_units());
+  if (p.first != kPersistent) return launch_gemm_tile((TileSize)p.first, p.head, p.nh, ak, bk, epi, rope, st);
+  const int rc = p.nh > 1 || rope ? launch_persistent_group(p.head, p.nh, ak, bk, rope, st) : launch_persistent(p.head[0], ak, bk, epi, st);
+  if (rc || p.second < 0) return rc;
+  return launch_gemm_tile((TileSize)p.second, p.tail, p.nt, ak, bk, epi, rope, st);
+}
+
+void query_gemm_route(int operands, int epilogue, int head_dim, int cus, int n, const int64_t* M, const int64_t* N, const int64_t* K,
+                      int32_t* route) {
+  GemmKArgs ks[MAX_GROUP] = {};
+  for (int i = 0; i < n; ++i) {
+    ks[i].nseg = 1;
+    ks[i].M = (int)M[i];
+    ks[i].N = (int)(epilogue == GEMM_ROUTE_GATED_PAIR ? 2 * N[i] : N[i]);
+    ks[i].K[0] = (int)K[i];
   }
-  if (best_us <= tile_us) return run_persistent(ks, n);
-  return launch_gemm_tile((TileSize)tile, ks, n, ak, bk, epi, rope, st);
+  RopeEpilogue rope{};
+  rope.head_dim = head_dim;
+  rope.layout = epilogue == GEMM_ROUTE_ROTARY_ADJACENT;
+  const bool rotary = epilogue == GEMM_ROUTE_ROTARY_SPLIT || epilogue == GEMM_ROUTE_ROTARY_ADJACENT;
+  const TileEpilogue epi = epilogue == GEMM_ROUTE_GATED_PAIR      ? TileEpilogue::SWIGLU
+                           : epilogue == GEMM_ROUTE_GATED_GRADIENT ? TileEpilogue::SWIGLU_GRAD
+                                                                   : TileEpilogue::PLAIN;
+  GemmPlan p;
+  plan_gemm(p, ks, n, operands != GEMM_ROUTE_MN_MN, operands == GEMM_ROUTE_K_K, epi, rotary ? &rope : nullptr,
+            cus > 0 ? cus : compute_units());
+  int64_t rows = 0;
+  for (int i = 0; i < p.nh; ++i) rows += p.head[i].M;
+  route[0] = p.first;
+  route[1] = p.second;
+  route[2] = (int32_t)rows;
 }
 
 static GemmKArgs kernel_args(const GemmArgs& g) {

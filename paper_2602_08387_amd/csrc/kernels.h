@@ -51,6 +51,9 @@ int launch_embed_bwd(const void* dx0, const int64_t* ids, int64_t T, int64_t V, 
                      void* dtable, void* workspace, hipStream_t st);
 
 // ---- gemm.hip
+// Compute units of the current device: 256 on a whole MI355X, fewer on a partition of one.  256 where there is no device to
+// ask (a plan made on the host).
+int compute_units();
 // C[M,N] (bf16, row-major, leading dimension ldc) = sum over segments s of opA_s * opB_s
 //        (+ R[M,N] if R) (+ C if accumulate), fp32 accumulation.
 // Segment operands are bf16 row-major.  a_kmajor: A_s is [M, K_s] (lda >= K_s) else [K_s, M]
@@ -90,7 +93,15 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
                             hipStream_t st);
 
+// Which kernels a product, or a group, of these sizes runs on: see gemm_route in dlayer.h.  Nothing is launched.
+enum { GEMM_ROUTE_K_K = 0, GEMM_ROUTE_K_MN = 1, GEMM_ROUTE_MN_MN = 2 };
+enum { GEMM_ROUTE_PLAIN = 0, GEMM_ROUTE_GATED_PAIR = 1, GEMM_ROUTE_GATED_GRADIENT = 2, GEMM_ROUTE_ROTARY_SPLIT = 3, GEMM_ROUTE_ROTARY_ADJACENT = 4 };
+void query_gemm_route(int operands, int epilogue, int head_dim, int cus, int n, const int64_t* M, const int64_t* N, const int64_t* K,
+                      int32_t* route);
+
 // ---- attention.hip
+// workgroups that share the work of 128 keys in the dK/dV pass, on a device of `cus` compute units
+int attention_bwd_pieces(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh, int cus);
 int launch_attention_fwd(const void* q, const void* k, const void* v, int64_t B, int64_t S,
                          int64_t Hq, int64_t Hkv, int64_t dh, void* o, float* lse, hipStream_t st);
 size_t attention_bwd_workspace(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh);
