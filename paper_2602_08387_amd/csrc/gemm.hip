@@ -491,8 +491,8 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                       const float fa = a[e], fb = b[e];
-                      a[e] = fa * c4[e] - fb * s4[e];
-                      b[e] = fa * s4[e] + fb * c4[e];
+                      a[e] = rotated_first(fa, fb, c4[e], s4[e]);
+                      b[e] = rotated_second(fa, fb, c4[e], s4[e]);
                     }
                   };
                   if (narrow) rot(acc[2 * t][j], acc[2 * t + 1][j]);
@@ -507,8 +507,8 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
                   for (int e = 0; e < 4; e += 2) {
                     const float fa = acc[i][j][e], fb = acc[i][j][e + 1];
-                    acc[i][j][e] = fa * c2[e >> 1] - fb * s2[e >> 1];
-                    acc[i][j][e + 1] = fa * s2[e >> 1] + fb * c2[e >> 1];
+                    acc[i][j][e] = rotated_first(fa, fb, c2[e >> 1], s2[e >> 1]);
+                    acc[i][j][e + 1] = rotated_second(fa, fb, c2[e >> 1], s2[e >> 1]);
                   }
                 }
               }

@@ -183,6 +183,11 @@ __device__ __forceinline__ bf16x8 read_frag(const char* tile, int row0, int kk, 
   }
 }
 
+// Rotation of the pair (a, b) by the angle with cosine c and sine s.  The fused operations are written out: left to the
+// compiler, every kernel rounds another one of the two products, and a head has other bits on another tile.
+__device__ __forceinline__ float rotated_first(float a, float b, float c, float s) { return __builtin_fmaf(a, c, -(b * s)); }
+__device__ __forceinline__ float rotated_second(float a, float b, float c, float s) { return __builtin_fmaf(b, c, a * s); }
+
 // f(integral_constant<int, I>) for I = I0 .. N-1: a loop whose index is a compile-time constant
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {

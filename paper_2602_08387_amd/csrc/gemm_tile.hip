@@ -295,14 +295,14 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               const float c = cr[idx + e], s = sr[idx + e];
-              f[e] = lowh ? f[e] * c - p[e] * s : p[e] * s + f[e] * c;
+              f[e] = lowh ? rotated_first(f[e], p[e], c, s) : rotated_second(p[e], f[e], c, s);
             }
           } else {
 #pragma unroll
             for (int e = 0; e < 8; e += 2) {
               const float c = cr[(o + e) >> 1], s = sr[(o + e) >> 1], x = f[e], y = f[e + 1];
-              f[e] = x * c - y * s;
-              f[e + 1] = x * s + y * c;
+              f[e] = rotated_first(x, y, c, s);
+              f[e + 1] = rotated_second(x, y, c, s);
             }
           }
         }

@@ -114,6 +114,15 @@ def test_layer_with_split_key_blocks(K, override):
 ONE_ROUNDING = 1.05 * 2.0 ** -8
 
 
+# Tiles as gemm_route names them.  Every shape below states the tile of its launch, or of its two: full rounds of 256 x 256
+# tiles and a smaller tile for the rows behind them.
+T128X256, T128, T64, PERSISTENT = 0, 1, 2, 3
+
+
+def _same_bits(a, b, what):
+    assert torch.equal(a.contiguous().view(torch.int16), b.contiguous().view(torch.int16)), what
+
+
 @pytest.mark.parametrize("T,Kd,N,res", [
     (1, 64, 8, False),            # one row, one K-step, one vector of columns
     (65, 192, 136, True),         # 64 x 64 tiles, remainders on every side, fewer K-steps than ring stages
@@ -200,26 +209,47 @@ def test_input_gradient_with_and_without_the_transposed_weights(K, rows, Kd, N):
         assert torch.equal(dx.view(torch.int16), first[:T].view(torch.int16)), T
 
 
-@pytest.mark.parametrize("B,S,D,Hq,Hkv,dh,layout", [
-    (1, 128, 64, 2, 1, 64, 0),       # 64 x 64 tiles: a head per tile
-    (1, 192, 64, 4, 2, 32, 0),       # two heads per tile
-    (3, 320, 128, 3, 1, 128, 1),     # adjacent pairs: a 128-wide head spans two 64-column tiles
-    (5, 384, 192, 9, 9, 128, 0),     # 128 x 128 tiles: split pairs of 128-wide heads
-    (3, 2816, 64, 12, 12, 64, 0),    # full rounds of 256 x 256 tiles, then small ones: positions go on across the cut
-])
-def test_rotary_projections_on_every_tile_size(K, B, S, D, Hq, Hkv, dh, layout):
-    rng = np.random.default_rng(S + dh)
+# batch, seq, width, query heads, KV heads, head width, layout (0 split pairs, 1 adjacent)
+ROTARY = [
+    ((1, 128, 64, 2, 1, 64, 0), (T64, -1)),           # a head per tile
+    ((1, 192, 64, 4, 2, 32, 0), (T64, -1)),           # two heads per tile
+    ((3, 320, 128, 3, 1, 128, 1), (T64, -1)),         # adjacent pairs: a 128-wide head spans two 64-column tiles
+    ((2, 384, 192, 4, 2, 128, 0), (T128, -1)),        # split pairs of 128-wide heads
+    ((1, 1216, 64, 9, 9, 64, 1), (T128, -1)),
+    ((5, 384, 192, 9, 9, 128, 0), (T128X256, -1)),
+    ((3, 2816, 64, 12, 12, 64, 0), (PERSISTENT, -1)), # more than one round, in one launch
+    ((5, 1728, 256, 30, 2, 64, 0), (PERSISTENT, T128)),     # cut in q, in the middle of a sequence: positions go on across it
+    ((5, 1664, 256, 15, 1, 128, 0), (PERSISTENT, T128)),    # the same, weight tiles of the full rounds in partner order
+    ((5, 1664, 256, 15, 1, 128, 1), (PERSISTENT, T128)),
+]
+
+
+@pytest.mark.parametrize("shape,route", ROTARY)
+def test_rotary_projections_on_every_tile_size(K, shape, route):
+    B, S, D, Hq, Hkv, dh, layout = shape
     T, QD, KD = B * S, Hq * dh, Hkv * dh
+    *tiles, first_rows = K.gemm_route(0, 3 + layout, [T] * 3, [QD, KD, KD], [D] * 3, head_dim=dh)
+    assert tuple(tiles) == route and (route[1] == -1 or first_rows < T and first_rows % S)
+    rng = np.random.default_rng(S + dh)
     hb, wqb, wkb, wvb = (_rand_bits(rng, s, std) for s, std in (((T, D), 1.0), ((QD, D), 0.1), ((KD, D), 0.1), ((KD, D), 0.1)))
     h, wq, wk, wv = map(si.bf16_bits_to_f64, (hb, wqb, wkb, wvb))
+    hd, wqd, wkd, wvd = map(dev_bf16, (hb, wqb, wkb, wvb))
     phi = odl.rope_angles(S, dh, 1e4)
     refs = (odl.rope_rotate((h @ wq.T).reshape(B, S, Hq, dh), phi, layout=layout),
             odl.rope_rotate((h @ wk.T).reshape(B, S, Hkv, dh), phi, layout=layout), h @ wv.T)
-    out = [torch.full((T, n), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (QD, KD, KD)]
-    K.qkv_rope_forward(*map(dev_bf16, (hb, wqb, wkb, wvb)), B, S, D, Hq, Hkv, dh, 1e4, layout, *out,
-                       _poisoned(K.qkv_rope_workspace_bytes(S, dh)))
+
+    def project(heads, kv_heads):
+        out = [torch.full((T, n * dh), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (heads, kv_heads, kv_heads)]
+        K.qkv_rope_forward(hd, wqd[:heads * dh], wkd[:kv_heads * dh], wvd[:kv_heads * dh], B, S, D, heads, kv_heads, dh, 1e4, layout, *out,
+                           _poisoned(K.qkv_rope_workspace_bytes(S, dh)))
+        return out
+
+    out = project(Hq, Hkv)
     for name, got, ref in zip("qkv", out, refs):
         assert _norm_err(got, ref) <= ONE_ROUNDING, name
+    assert K.gemm_route(0, 3 + layout, [T] * 3, [dh] * 3, [D] * 3, head_dim=dh)[1] == -1
+    for name, got, one in zip("qkv", out, project(1, 1)):
+        _same_bits(one, got[:, :dh], f"{name} of one head")
 
 
 # ------------------------------------------------------------------ RMSNorm backward: threads per row, rows per workgroup
