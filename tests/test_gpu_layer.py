@@ -131,7 +131,7 @@ def test_backward_can_reuse_the_transposed_weights(K):
 def test_recomputing_configurations_match_the_oracle_and_keep_less(K, name, override):
     """recompute = norms | swiglu: h1, h2 and a are not kept in `saved`; the backward rebuilds them.  Same
     bar against the oracle; outputs and every gradient but the down projection's equal the keeping
-    configuration's bit for bit (its operand a is rebuilt from the stored g and u when the fused kernel ran)."""
+    configuration's bit for bit (its operand a is rebuilt from the stored g and u; the forward takes it from the fp32 sums)."""
     cfg = si.CONFIGS[name].with_(**override)
     rc = cfg.with_(recompute=3)
     inp = si.make_layer_inputs(cfg, seed=4)
@@ -296,7 +296,7 @@ def test_8b_width_steps_against_the_storage_emulation(K):
     result rounded to bf16 except where the fp32 sum lands on the other side of a rounding boundary,
     i.e. be bit-identical almost everywhere and never more than one bf16 step away.  This separates the
     rounding floor of bf16 storage from any defect of a kernel."""
-    cfg = si.CONFIGS["8b"].with_(batch=1, seq=512)   # 512 rows: enough tiles for the fused gate/up kernel
+    cfg = si.CONFIGS["8b"].with_(batch=1, seq=512)
     inp = si.make_layer_inputs(cfg, seed=0)
     w = {k: si.bf16_bits_to_f64(inp[k]) for k in si.WEIGHT_NAMES}
     wd = {k: dev_bf16(inp[k]) for k in si.WEIGHT_NAMES}

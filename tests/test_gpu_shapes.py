@@ -32,14 +32,21 @@ def _poisoned(nbytes):
 
 
 # ------------------------------------------------------------------ dK/dV pass with several workgroups per key block
-@pytest.mark.parametrize("B,S,Hq,Hkv,dh", [
-    (1, 128, 4, 1, 32),      # one key block, two pieces
-    (1, 640, 6, 2, 64),      # eight pieces, a group of three heads
-    (1, 1792, 1, 1, 64),     # one head: the last key block has four tiles for eight pieces
-    (2, 384, 8, 1, 128),     # a group as wide as the number of pieces
-    (1, 2048, 3, 1, 128),    # with the dS hand-over
-])
-def test_attention_backward_with_split_key_blocks(K, B, S, Hq, Hkv, dh):
+# (batch, seq, query heads, KV heads, head width), pieces of a key block
+SPLIT_ATTENTION = [
+    ((1, 128, 4, 1, 32), 8),      # one key block of sixteen tiles
+    ((1, 640, 6, 2, 64), 8),      # a group of three heads
+    ((1, 1792, 1, 1, 64), 8),     # one head: the last key block has four tiles for eight pieces
+    ((2, 384, 8, 1, 128), 8),     # a group as wide as the number of pieces
+    ((2, 1408, 16, 4, 64), 5),    # pieces that neither divide the group nor are a multiple of it
+    ((1, 2048, 3, 1, 128), 8),    # with the dS hand-over
+]
+
+
+@pytest.mark.parametrize("shape,pieces", SPLIT_ATTENTION)
+def test_attention_backward_with_split_key_blocks(K, shape, pieces):
+    B, S, Hq, Hkv, dh = shape
+    assert K.attention_backward_pieces(*shape) == pieces
     rng = np.random.default_rng(S + dh + Hq)
     qb, kb = _rand_bits(rng, (B, S, Hq, dh)), _rand_bits(rng, (B, S, Hkv, dh))
     vb, dob = _rand_bits(rng, (B, S, Hkv, dh)), _rand_bits(rng, (B, S, Hq, dh))
@@ -63,15 +70,20 @@ def test_attention_backward_with_split_key_blocks(K, B, S, Hq, Hkv, dh):
         assert torch.equal(got.view(torch.int16), again.view(torch.int16)), f"{name} is not reproducible"
 
 
-@pytest.mark.parametrize("B,S,Hq,Hkv,dh", [
-    (2, 1024, 4, 4, 64),     # one workgroup per key block; the dQ workgroups follow in the same launch where dq is a buffer of its own
-    (1, 640, 6, 2, 64),      # split key blocks
-    (1, 256, 4, 2, 32),
-    (1, 640, 3, 1, 128),
-    (1, 2048, 2, 1, 128),    # with the dS hand-over: two launches anyway
-])
-def test_attention_backward_with_dq_in_place(K, B, S, Hq, Hkv, dh):
+IN_PLACE_ATTENTION = [
+    ((8, 512, 12, 12, 64), 1),    # one workgroup per key block; dQ in the same launch where dq is a buffer of its own
+    ((1, 640, 6, 2, 64), 8),
+    ((1, 256, 4, 2, 32), 8),
+    ((1, 640, 3, 1, 128), 8),
+    ((1, 2048, 2, 1, 128), 8),    # with the dS hand-over: two launches anyway
+]
+
+
+@pytest.mark.parametrize("shape,pieces", IN_PLACE_ATTENTION)
+def test_attention_backward_with_dq_in_place(K, shape, pieces):
     """Every key block reads q and dO, so dq may only replace one of them once the dK/dV pass is over."""
+    B, S, Hq, Hkv, dh = shape
+    assert K.attention_backward_pieces(*shape) == pieces
     rng = np.random.default_rng(S + dh)
     q, do = (dev_bf16(_rand_bits(rng, (B, S, Hq, dh))) for _ in range(2))
     k, v = (dev_bf16(_rand_bits(rng, (B, S, Hkv, dh))) for _ in range(2))
@@ -112,8 +124,6 @@ def test_layer_with_split_key_blocks(K, override):
 # rounding the fp32 sum to bf16 is off by 2^-8 of an element at most (1.7e-3 in the 2-norm of many); 5 % more for the
 # order of the fp32 sums
 ONE_ROUNDING = 1.05 * 2.0 ** -8
-
-
 # Tiles as gemm_route names them.  Every shape below states the tile of its launch, or of its two: full rounds of 256 x 256
 # tiles and a smaller tile for the rows behind them.
 T128X256, T128, T64, PERSISTENT = 0, 1, 2, 3
@@ -123,16 +133,23 @@ def _same_bits(a, b, what):
     assert torch.equal(a.contiguous().view(torch.int16), b.contiguous().view(torch.int16)), what
 
 
-@pytest.mark.parametrize("T,Kd,N,res", [
-    (1, 64, 8, False),            # one row, one K-step, one vector of columns
-    (65, 192, 136, True),         # 64 x 64 tiles, remainders on every side, fewer K-steps than ring stages
-    (1000, 1024, 1024, True),
-    (1920, 576, 1160, True),      # 128 x 128 tiles, ragged columns
-    (8192, 320, 768, False),      # 128 x 256 tiles
-    (4160, 448, 4288, True),      # full rounds of 256 x 256 tiles and a launch of small ones for the last rows
-    (16640, 128, 1096, False),    # the same, several row groups: the contraction starts elsewhere in each
-])
-def test_linear_forward_on_every_tile_size(K, T, Kd, N, res):
+LINEAR = [
+    ((1, 64, 8), False, (T64, -1)),                   # one row, one K-step, one vector of columns
+    ((65, 192, 136), True, (T64, -1)),                # remainders on every side, fewer K-steps than ring stages
+    ((1000, 1024, 1024), True, (T64, -1)),
+    ((1920, 576, 1160), True, (T128, -1)),            # ragged columns
+    ((8192, 320, 768), False, (T128X256, -1)),
+    ((16640, 128, 1096), False, (PERSISTENT, -1)),    # more than one round, in one launch
+    ((4160, 448, 4288), True, (PERSISTENT, T64)),     # cut at row 3840: the rows behind it lie in two groups of 2048
+    ((16640, 512, 1096), True, (PERSISTENT, T128)),
+    ((10560, 576, 1856), False, (PERSISTENT, T128X256)),
+]
+
+
+@pytest.mark.parametrize("shape,res,route", LINEAR)
+def test_linear_forward_on_every_tile_size(K, shape, res, route):
+    T, Kd, N = shape
+    assert K.gemm_route(0, 0, [T], [N], [Kd])[:2] == route
     rng = np.random.default_rng(T + N)
     xb, wb, rb = _rand_bits(rng, (T, Kd)), _rand_bits(rng, (N, Kd), 0.05), _rand_bits(rng, (T, N))
     x, w, r = map(si.bf16_bits_to_f64, (xb, wb, rb))
@@ -140,20 +157,35 @@ def test_linear_forward_on_every_tile_size(K, T, Kd, N, res):
     y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
     K.linear_forward(xd, wd, rd if res else None, T, Kd, N, y)
     assert _norm_err(y, x @ w.T + (r if res else 0.0)) <= ONE_ROUNDING
-    # a product has the same bits whatever kernel the number of rows selects
-    for rows in (T // 2, 1):
-        part = torch.full((max(rows, 1), N), float("nan"), dtype=torch.bfloat16, device="cuda")
-        K.linear_forward(xd[:max(rows, 1)].contiguous(), wd, rd[:max(rows, 1)].contiguous() if res else None, max(rows, 1), Kd, N, part)
-        assert torch.equal(part.view(torch.int16), y[:max(rows, 1)].view(torch.int16)), rows
+
+    def part(rows, cols):
+        out = torch.full((rows, cols), float("nan"), dtype=torch.bfloat16, device="cuda")
+        K.linear_forward(xd[:rows], wd[:cols], rd[:rows, :cols].contiguous() if res else None, rows, Kd, cols, out)
+        return out
+
+    # a product has the same bits whatever kernel its size selects: fewer rows, and all of them with fewer columns
+    for rows in (max(T // 2, 1), 1):
+        _same_bits(part(rows, N), y[:rows], f"{rows} rows")
+    for cols in (72, 136, 264):
+        if cols < N:
+            assert K.gemm_route(0, 0, [T], [cols], [Kd])[1] == -1
+            _same_bits(part(T, cols), y[:, :cols], f"{cols} columns")
 
 
-@pytest.mark.parametrize("T,shapes", [
-    (64, [(64, 64)]),                                        # one tile, one K-step
-    (320, [(64, 192), (320, 64), (128, 128)]),               # 64 x 64 tiles, grouped
-    (1024, [(1152, 1152), (384, 1152), (1152, 3136)]),       # larger tiles
-    (192, [(4160, 4416), (64, 4288), (4416, 320)]),          # more than one round of 256 x 256 tiles: two launches
-])
-def test_weight_gradients_on_every_tile_size(K, T, shapes):
+WEIGHT_GRADIENTS = [
+    (64, [(64, 64)], (T64, -1)),                                                  # one tile, one K-step
+    (320, [(64, 192), (320, 64), (128, 128)], (T64, -1)),
+    (64, [(512, 3072), (960, 576)], (T128, -1)),
+    (1024, [(1152, 1152), (384, 1152), (1152, 3136)], (T128X256, -1)),
+    (192, [(4160, 4416), (64, 4288), (4416, 320)], (PERSISTENT, -1)),             # more than one round, in one launch
+    (576, [(4160, 4416), (64, 4288), (4416, 320)], (PERSISTENT, T64)),            # the cut falls into the first product
+    (128, [(768, 512), (4608, 832), (3520, 3136)], (PERSISTENT, T64)),            # into the last: two products lie before it
+]
+
+
+@pytest.mark.parametrize("T,shapes,route", WEIGHT_GRADIENTS)
+def test_weight_gradients_on_every_tile_size(K, T, shapes, route):
+    assert K.gemm_route(2, 0, [n for n, _ in shapes], [k for _, k in shapes], [T] * len(shapes))[:2] == route
     rng = np.random.default_rng(T + len(shapes))
     dyb, xb = [_rand_bits(rng, (T, n)) for n, _ in shapes], [_rand_bits(rng, (T, k)) for _, k in shapes]
     dyd, xd = [dev_bf16(b) for b in dyb], [dev_bf16(b) for b in xb]
@@ -163,45 +195,97 @@ def test_weight_gradients_on_every_tile_size(K, T, shapes):
         assert _norm_err(dws[i], si.bf16_bits_to_f64(dyb[i]).T @ si.bf16_bits_to_f64(xb[i])) <= ONE_ROUNDING, i
         one = torch.empty_like(dws[i])
         K.linear_backward(xd[i], xd[i], dyd[i], T, k, n, None, one, 0, None)
-        assert torch.equal(one.view(torch.int16), dws[i].view(torch.int16)), f"grouped dw[{i}] differs from the single launch"
+        _same_bits(one, dws[i], f"grouped dw[{i}] differs from the single launch")
+        narrow = torch.empty(n, 64, dtype=torch.bfloat16, device="cuda")
+        assert K.gemm_route(2, 0, [n], [64], [T])[1] == -1
+        K.linear_backward(xd[i][:, :64].contiguous(), xd[i], dyd[i], T, 64, n, None, narrow, 0, None)
+        _same_bits(narrow, dws[i][:, :64], f"dw[{i}] of 64 columns")
 
 
-@pytest.mark.parametrize("T,Kd,F", [(64, 64, 64), (200, 192, 104), (1920, 1152, 200), (1000, 64, 1608), (4160, 192, 2176)])
-def test_gated_pair_on_every_tile_size(K, T, Kd, F):
+GATED_PAIRS = [
+    ((64, 64, 64), (T64, -1)),
+    ((200, 192, 104), (T64, -1)),
+    ((1920, 1152, 200), (T64, -1)),
+    ((1000, 64, 1608), (T128, -1)),
+    ((1920, 1152, 1096), (T128X256, -1)),
+    ((4160, 192, 2176), (PERSISTENT, -1)),
+    ((4160, 1024, 2176), (PERSISTENT, T64)),
+    ((2048, 512, 4224), (PERSISTENT, T128)),
+]
+
+
+@pytest.mark.parametrize("shape,route", GATED_PAIRS)
+def test_gated_pair_on_every_tile_size(K, shape, route):
+    T, Kd, F = shape
+    assert K.gemm_route(0, 1, [T], [F], [Kd])[:2] == route
     rng = np.random.default_rng(T + F)
     xb, wgb, wub = _rand_bits(rng, (T, Kd)), _rand_bits(rng, (F, Kd), 0.1), _rand_bits(rng, (F, Kd), 0.1)
     x, wg, wu = map(si.bf16_bits_to_f64, (xb, wgb, wub))
+    xd, wgd, wud = map(dev_bf16, (xb, wgb, wub))
     out = [torch.full((T, F), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
-    K.linear_swiglu_forward(dev_bf16(xb), dev_bf16(wgb), dev_bf16(wub), T, Kd, F, *out)
+    K.linear_swiglu_forward(xd, wgd, wud, T, Kd, F, *out)
     g, u = x @ wg.T, x @ wu.T
     for name, got, ref in zip("gua", out, (g, u, odl.swiglu_fwd(g, u))):
         assert _norm_err(got, ref) <= ONE_ROUNDING, name
+    narrow = [torch.full((T, 64), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    assert K.gemm_route(0, 1, [T], [64], [Kd])[1] == -1
+    K.linear_swiglu_forward(xd, wgd[:64], wud[:64], T, Kd, 64, *narrow)
+    for name, got, few in zip("gua", out, narrow):
+        _same_bits(few, got[:, :64], f"{name} of 64 columns")
 
 
-@pytest.mark.parametrize("T,D,F", [(64, 64, 64), (192, 128, 320), (1920, 192, 1152), (4160, 64, 4288)])
-def test_activation_gradient_on_every_tile_size(K, T, D, F):
+# tokens, width, d_ff; whether the weights are read as stored (up to 4096 tokens and 8M elements of da)
+ACTIVATION_GRADIENTS = [
+    ((64, 64, 64), True, (T64, -1)),
+    ((192, 128, 320), True, (T64, -1)),
+    ((1920, 192, 1152), True, (T128, -1)),
+    ((3200, 512, 2496), True, (T128X256, -1)),
+    ((4160, 512, 1152), False, (T128X256, -1)),
+    ((4160, 64, 4288), False, (PERSISTENT, -1)),
+    ((4160, 512, 4288), False, (PERSISTENT, T64)),
+    ((7360, 256, 2368), False, (PERSISTENT, T128)),
+]
+
+
+@pytest.mark.parametrize("shape,stored,route", ACTIVATION_GRADIENTS)
+def test_activation_gradient_on_every_tile_size(K, shape, stored, route):
+    T, D, F = shape
+    assert K.gemm_route(1 if stored else 0, 2, [T], [F], [D])[:2] == route
     rng = np.random.default_rng(T + F)
     dyb, wb, gb, ub = _rand_bits(rng, (T, D)), _rand_bits(rng, (D, F), 0.1), _rand_bits(rng, (T, F)), _rand_bits(rng, (T, F))
     dy, w, g, u = map(si.bf16_bits_to_f64, (dyb, wb, gb, ub))
-    dg, du = (torch.full((T, F), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
-    K.linear_swiglu_backward(dev_bf16(dyb), dev_bf16(wb), dev_bf16(gb), dev_bf16(ub), T, D, F, dg, du,
-                             _poisoned(K.linear_swiglu_backward_workspace_bytes(T, D, F)))
-    for name, got, ref in zip(("dg", "du"), (dg, du), odl.swiglu_bwd(g, u, dy @ w)):
-        assert _norm_err(got, ref) <= ONE_ROUNDING, name
+    dyd, wd, gd, ud = map(dev_bf16, (dyb, wb, gb, ub))
+
+    def backward(cols):
+        dg, du = (torch.full((T, cols), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        K.linear_swiglu_backward(dyd, wd[:, :cols].contiguous(), gd[:, :cols].contiguous(), ud[:, :cols].contiguous(), T, D, cols, dg, du,
+                                 _poisoned(K.linear_swiglu_backward_workspace_bytes(T, D, cols)))
+        return dg, du
+
+    got = backward(F)
+    for name, d, ref in zip(("dg", "du"), got, odl.swiglu_bwd(g, u, dy @ w)):
+        assert _norm_err(d, ref) <= ONE_ROUNDING, name
+    assert K.gemm_route(1 if T <= 4096 else 0, 2, [T], [64], [D])[1] == -1
+    for name, d, few in zip(("dg", "du"), got, backward(64)):
+        _same_bits(few, d[:, :64], f"{name} of 64 columns")
 
 
-@pytest.mark.parametrize("rows,Kd,N", [
-    ((64,), 64, 64),                  # one tile, one K-step
-    ((4160, 4096, 64), 320, 192),     # the last rows that read the weights as stored, and the first that do not
-    ((4032, 1984, 320), 2112, 448),   # the same for rows x columns; 128 x 256 tiles
-    ((1920, 64), 1152, 3136),         # 128 x 128 tiles
-])
-def test_input_gradient_with_and_without_the_transposed_weights(K, rows, Kd, N):
+INPUT_GRADIENTS = [
+    ((64,), 64, 64, (T64,)),                                    # one tile, one K-step
+    ((4160, 4096, 64), 320, 192, (T64, T64, T64)),              # the last rows that read the weights as stored, and the first that do not
+    ((4032, 1984, 320), 2112, 448, (PERSISTENT, T128X256, T64)),   # the same for rows x columns
+    ((1920, 64), 1152, 3136, (T128, T64)),
+]
+
+
+@pytest.mark.parametrize("rows,Kd,N,tiles", INPUT_GRADIENTS)
+def test_input_gradient_with_and_without_the_transposed_weights(K, rows, Kd, N, tiles):
     rng = np.random.default_rng(rows[0] + N)
     dyb, wb = _rand_bits(rng, (rows[0], N)), _rand_bits(rng, (N, Kd), 0.05)
     ref = si.bf16_bits_to_f64(dyb) @ si.bf16_bits_to_f64(wb)
     dyd, wd, first = dev_bf16(dyb), dev_bf16(wb), None
-    for T in rows:
+    for T, tile in zip(rows, tiles):
+        assert K.gemm_route(1 if T <= 4096 and T * Kd <= 4096 * 2048 else 0, 0, [T], [Kd], [N])[:2] == (tile, -1)
         dx = torch.full((T, Kd), float("nan"), dtype=torch.bfloat16, device="cuda")
         K.linear_backward(dx, wd, dyd[:T], T, Kd, N, dx, None, 0, _poisoned(K.linear_backward_workspace_bytes(T, Kd, N)))
         assert _norm_err(dx, ref[:T]) <= ONE_ROUNDING, T

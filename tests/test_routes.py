@@ -34,3 +34,28 @@ def test_route_query_rejects_what_no_call_runs(K):
                 (0, 3, [64], [64], [64]), (0, 0, [64, 64], [64, 64], [64, 64]), (0, 0, [0], [64], [64]), (0, 0, [64], [64], [65])):
         with pytest.raises(K.DLayerError):
             K.gemm_route(*bad)
+
+
+def test_the_shapes_of_the_gpu_tests_reach_the_paths_they_name(K):
+    """The constants of the choice were fitted and may be fitted again: the shapes then have to follow."""
+    from tests import test_gpu_shapes as shapes
+    for (T, Kd, N), _, route in shapes.LINEAR:
+        assert K.gemm_route(0, 0, [T], [N], [Kd], compute_units=256)[:2] == route, ("linear", T, Kd, N)
+    for T, products, route in shapes.WEIGHT_GRADIENTS:
+        assert K.gemm_route(2, 0, [n for n, _ in products], [k for _, k in products], [T] * len(products),
+                            compute_units=256)[:2] == route, ("weight gradients", T, products)
+    for (T, Kd, F), route in shapes.GATED_PAIRS:
+        assert K.gemm_route(0, 1, [T], [F], [Kd], compute_units=256)[:2] == route, ("gated pair", T, Kd, F)
+    for (T, D, F), stored, route in shapes.ACTIVATION_GRADIENTS:
+        assert K.gemm_route(1 if stored else 0, 2, [T], [F], [D], compute_units=256)[:2] == route, ("activation gradient", T, D, F)
+    for (B, S, D, Hq, Hkv, dh, layout), route in shapes.ROTARY:
+        assert K.gemm_route(0, 3 + layout, [B * S] * 3, [Hq * dh, Hkv * dh, Hkv * dh], [D] * 3, head_dim=dh,
+                            compute_units=256)[:2] == route, ("rotary", B, S, D, Hq, Hkv, dh, layout)
+    for shape, pieces in shapes.SPLIT_ATTENTION + shapes.IN_PLACE_ATTENTION:
+        assert K.attention_backward_pieces(*shape, compute_units=256) == pieces, ("attention", shape)
+    # between them every epilogue runs on every tile, alone and behind a cut
+    for rows, second in ((shapes.LINEAR, {T64, T128, T128X256}), (shapes.WEIGHT_GRADIENTS, {T64}), (shapes.GATED_PAIRS, {T64, T128}),
+                         (shapes.ACTIVATION_GRADIENTS, {T64, T128}), (shapes.ROTARY, {T128})):
+        routes = [r[-1] for r in rows]
+        assert {a for a, b in routes if b == -1} == {T64, T128, T128X256, PERSISTENT}
+        assert {b for a, b in routes if b != -1} == second and all(a == PERSISTENT for a, b in routes if b != -1)
