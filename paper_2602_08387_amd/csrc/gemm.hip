@@ -190,7 +190,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
       for (int i = 0; i < FN; ++i) fb[0][i] = read_frag<BN, BKM>(tb, wave_n * TN + i * MI, 0, lane);
     }
-    if constexpr (!(AK && BKM)) wait_frags<FM, FN>(fa[0], fb[0]);
+    if constexpr (!(AK && BKM)) wait_frags(fa[0], fb[0]);
     for (int t = 0; t < total; ++t) {
       // Every load of this tile is out once its last but one K-step begins.  The cursor moves on to the
       // workgroup's next tile there, and that tile's first two K-steps go out at this tile's last two
@@ -283,7 +283,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
           });
           // the fragments fetched above are complete once this wait has passed; the next group's MFMAs
           // depend on it
-          wait_frags<FM, FN>(fa[nb], fb[nb]);
+          wait_frags(fa[nb], fb[nb]);
         }
       });
     }
@@ -639,10 +639,8 @@ static int launch_persistent_group(const GemmKArgs* ks, int n, bool ak, bool bk,
       GEMM_LAUNCH((gemm_group_rope_kernel<PM, PN, PWM, PWN, true>), g.tile_start[n], g, "gemm group (rotary epilogue)");
     GEMM_LAUNCH((gemm_group_rope_kernel<PM, PN, PWM, PWN, false>), g.tile_start[n], g, "gemm group (rotary epilogue)");
   }
-  // only the layouts in use are instantiated: the weight-gradient products (both operands mn-major)
-  // and the forward projections (both k-major)
+  // only the layout in use is instantiated: the weight-gradient products (both operands mn-major)
   if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<PM, PN, PWM, PWN, false, false>), g.tile_start[n], g, "gemm group");
-  if (ak && bk) GEMM_LAUNCH((gemm_group_kernel<PM, PN, PWM, PWN, true, true>), g.tile_start[n], g, "gemm group");
   return fail(-1, "gemm group: operand layout not built");
 }
 

@@ -212,16 +212,10 @@ __device__ __forceinline__ int k_start(int m0, int total) { return (((m0 >> 11) 
 
 // Waits for every LDS read of this wave and makes the fragments depend on that wait, so that no
 // consumer of a fragment fetched by the inline-assembly transposed read can be scheduled before it.
-template <int FM, int FN>
-__device__ __forceinline__ void wait_frags(bf16x8 (&fa)[FM], bf16x8 (&fb)[FN]) {
-  static_assert(FM == 8 && FN == 4 || FM == 4 && FN == 4, "operand list written out for the two wave tiles in use");
-  if constexpr (FM == 8)
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fa[4]), "+v"(fa[5]), "+v"(fa[6]), "+v"(fa[7]),
-                   "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
-  else
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
+__device__ __forceinline__ void wait_frags(bf16x8 (&fa)[8], bf16x8 (&fb)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fa[4]), "+v"(fa[5]), "+v"(fa[6]), "+v"(fa[7]),
+                 "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
 }
 
 // Position of the next tile pair to fetch: segment, k offset, and that segment's descriptors.

@@ -346,7 +346,7 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hi
     }
   }
   // several products: the weight gradients (both operands mn-major) and the head projections
-  if constexpr (EPI == TILE_ROPE || (EPI == TILE_PLAIN && AK == BKM)) {
+  if constexpr (EPI == TILE_ROPE || (EPI == TILE_PLAIN && !AK && !BKM)) {
     auto kern = gemm_tile_group_kernel<BM, BN, WM, WN, AK, BKM, NST, EPI>;
     static std::atomic<unsigned long long> lds_done_group{0};
     if (int rc = reserve_lds(kern, lds, lds_done_group, "gemm tile group")) return rc;

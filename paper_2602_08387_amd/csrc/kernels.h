@@ -75,8 +75,7 @@ struct GemmArgs {
   bool a_kmajor, b_kmajor;
 };
 int launch_gemm(const GemmArgs& g, hipStream_t st);
-// Up to 8 independent problems with the same a_kmajor/b_kmajor in one launch (built for both operands
-// mn-major, the weight-gradient products, and both k-major, the forward projections).
+// Up to 8 independent problems in one launch, both operands mn-major (the weight-gradient products).
 int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st);
 // The same for k-major products whose outputs are [tokens][heads][head_dim], with the rotary embedding
 // applied in the epilogue (on the fp32 accumulators) to the problems whose bit is set in rotate_mask.
