@@ -679,7 +679,7 @@ int embed_forward(const void* table, const int64_t* ids, int64_t T, int64_t V, i
   return launch_embed_fwd(table, ids, T, V, D, x0, (hipStream_t)stream);
 }
 
-// The size that callers are promised, (3 V + 2.2 T) ints, of which the kernels use (2 V + 2.2 T).
+// What the header states, (3 V + 2.2 T) ints; the kernels use (2 V + 2.2 T) of them.
 size_t embed_backward_workspace_bytes(int64_t T, int64_t V) {
   return T > 0 && V > 0 ? embed_bwd_workspace(T, V) + (size_t)V * sizeof(int) : 0;
 }

@@ -942,7 +942,7 @@ static size_t bwd_stats_bytes(int64_t B, int64_t S, int64_t Hq) {
 // All pieces together are at most kMostPieces workgroups, three to a slot, which bounds the scratch (see
 // dkdv_partial_bytes); where the estimate asks for more (groups of 16 heads from 2816 positions on, others from longer
 // ones) it promises less than 2 %.
-// Measured (whole backward, us, unsplit -> split): B2 S2944 16q/4kv x64 339 -> 163 (6 pieces), B1 S4224 24q/8kv x128
+// Measured (whole backward, us, unsplit -> split): B2 S2944 16q/4kv x64 339 -> 163 (5 pieces), B1 S4224 24q/8kv x128
 // 549 -> 359 (3), B1 S8192 32q/8kv x128 1885 -> 1616 (2); stays whole: B2 S8192 32q/8kv x128 3116 (3154 with 2),
 // B4 S2048 16q/8kv x128 260 (275 with 2), B8 S1024 12q/12kv x64 79 (104 with 2).
 constexpr int kMostPerBlock = 8;

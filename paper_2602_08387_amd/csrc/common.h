@@ -34,7 +34,7 @@ __device__ __forceinline__ float wave_max(float v) {
 // bf16 afterwards).  Written as a division it compiles to the correctly rounded sequence of some ten
 // instructions per element, which the SwiGLU epilogues of the GEMMs (64 or 128 elements per lane and
 // tile, the matrix pipe idle meanwhile) pay for in full.  Every SwiGLU kernel uses this one function,
-// so the fused and the stand-alone paths give the same bits.
+// so the fused and the stand-alone paths differ by the rounding of their operands only.
 __device__ __forceinline__ float logistic(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 
 __device__ __forceinline__ void unpack8(const bf16x8& v, float (&f)[8]) {

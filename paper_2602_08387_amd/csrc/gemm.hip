@@ -672,11 +672,13 @@ static const KernelCost kCostKK[4] = {
     {128, 128, 1, 0.38, 0.48, 3.0},   // T = 1920, K = 6272, N = 1152 (135 tiles): 44 us; 67 as 75 tiles of 128 x 256
     {64, 64, 2, 0.25, 0.33, 2.0},     // T = 2048, K = 2816, N = 1024 (512 tiles): 20 us; 23 as 128 tiles of 128 x 128
     {256, 256, 1, 0.98, 1.39, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
+// The fixed part per tile counts where the contraction is short (a weight gradient over few tokens), and there the 256 x 256
+// tile's is large: its two-stage ring starts and its accumulators drain with nothing beside them.
 static const KernelCost kCostMN[4] = {
-    {128, 256, 1, 0.70, 0.82, 4.0},   // 768 x 768, K = 8192 (18 tiles): 94 us
-    {128, 128, 1, 0.48, 0.56, 3.0},   // the same as 36 tiles: 63 us
-    {64, 64, 2, 0.28, 0.39, 2.0},     // as 144 tiles: 39 us (157 as 9 tiles of 256 x 256)
-    {256, 256, 1, 1.20, 1.45, 5.0}};
+    {128, 256, 1, 0.70, 0.85, 3.8},   // 4096 x 4096, K = 64 (512 tiles): 13.2 us; 768 x 768, K = 8192 (18 tiles): 94 us
+    {128, 128, 1, 0.48, 0.56, 2.2},   // the first as 1024 tiles: 14.8 us; the second as 36: 63 us
+    {64, 64, 2, 0.28, 0.39, 1.3},     // as 4096 tiles: 17.2 us; as 144: 39 us
+    {256, 256, 1, 1.20, 1.45, 8.5}};  // as 256 tiles: 15.6 us; as 9: 157 us
 constexpr double kLaunchUs = 3.5;
 
 static double kernel_us(const KernelCost& c, int cus, const GemmKArgs* ks, int n) {
@@ -709,8 +711,9 @@ static GemmKArgs row_part(GemmKArgs k, int r0, int rows, bool a_kmajor) {
 // does not (head and tail: the products, or their rows, of the two).
 struct GemmPlan {
   int first, second = -1;   // index into the cost tables
+  const GemmKArgs *head, *tail;   // the caller's products, or parts
   int nh = 0, nt = 0;
-  GemmKArgs head[MAX_GROUP], tail[MAX_GROUP];
+  GemmKArgs parts[2][MAX_GROUP];
 };
 
 static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, int cus) {
@@ -739,10 +742,12 @@ static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk,
       const int tn = (ks[i].N + PN - 1) / PN;
       const int64_t fit = room / tn * PM;   // rows that still fit
       const int rows = fit < ks[i].M ? (int)fit : ks[i].M;
-      if (rows > 0) p.head[p.nh++] = row_part(ks[i], 0, rows, ak);
-      if (rows < ks[i].M) p.tail[p.nt++] = row_part(ks[i], rows, ks[i].M - rows, ak);
+      if (rows > 0) p.parts[0][p.nh++] = row_part(ks[i], 0, rows, ak);
+      if (rows < ks[i].M) p.parts[1][p.nt++] = row_part(ks[i], rows, ks[i].M - rows, ak);
       room -= (int64_t)((rows + PM - 1) / PM) * tn;
     }
+    p.head = p.parts[0];
+    p.tail = p.parts[1];
     if (p.nh > 0 && p.nt > 0) {
       double tail_us;
       const int tail_tile = best_tile(p.tail, p.nt, tail_us);
@@ -758,9 +763,9 @@ static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk,
       }
     }
   }
+  p.head = ks;
   p.nh = n;
   p.nt = 0;
-  for (int i = 0; i < n; ++i) p.head[i] = ks[i];
   p.first = whole_us <= tile_us ? kPersistent : tile;
 }
 

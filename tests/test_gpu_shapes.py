@@ -177,9 +177,9 @@ WEIGHT_GRADIENTS = [
     (320, [(64, 192), (320, 64), (128, 128)], (T64, -1)),
     (64, [(512, 3072), (960, 576)], (T128, -1)),
     (1024, [(1152, 1152), (384, 1152), (1152, 3136)], (T128X256, -1)),
-    (192, [(4160, 4416), (64, 4288), (4416, 320)], (PERSISTENT, -1)),             # more than one round, in one launch
-    (576, [(4160, 4416), (64, 4288), (4416, 320)], (PERSISTENT, T64)),            # the cut falls into the first product
-    (128, [(768, 512), (4608, 832), (3520, 3136)], (PERSISTENT, T64)),            # into the last: two products lie before it
+    (256, [(4160, 832), (4608, 1600), (5120, 192)], (PERSISTENT, -1)),            # less than a round
+    (192, [(4032, 4224), (576, 448)], (PERSISTENT, T64)),                         # the cut falls into the first product
+    (384, [(1792, 576), (3328, 3136), (4480, 1344)], (PERSISTENT, T128)),         # into the last: two products lie before it
 ]
 
 

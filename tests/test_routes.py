@@ -22,6 +22,12 @@ def test_the_choice_of_a_product_goes_by_the_compute_units_there_are(K, cus):
     assert K.gemm_route(0, 0, [256 * cus // 4], [256], [4096], compute_units=cus)[0] != PERSISTENT
 
 
+@pytest.mark.parametrize("T,Kd,N", [(128, 3392, 3136), (192, 960, 8896), (192, 11136, 832), (320, 2624, 3392)])
+def test_weight_gradients_over_few_tokens_take_a_smaller_tile(K, T, Kd, N):
+    """Up to a round of 256 x 256 tiles that are all fill and drain: slower than any other tile (most where dW accumulates)."""
+    assert K.gemm_route(2, 0, [N], [Kd], [T], compute_units=256)[0] in (T128, T128X256, T64)
+
+
 def test_key_blocks_are_split_for_the_compute_units_there_are(K):
     shape = (2, 2944, 16, 4, 64)
     assert K.attention_backward_pieces(*shape, compute_units=256) > 1
@@ -54,7 +60,7 @@ def test_the_shapes_of_the_gpu_tests_reach_the_paths_they_name(K):
     for shape, pieces in shapes.SPLIT_ATTENTION + shapes.IN_PLACE_ATTENTION:
         assert K.attention_backward_pieces(*shape, compute_units=256) == pieces, ("attention", shape)
     # between them every epilogue runs on every tile, alone and behind a cut
-    for rows, second in ((shapes.LINEAR, {T64, T128, T128X256}), (shapes.WEIGHT_GRADIENTS, {T64}), (shapes.GATED_PAIRS, {T64, T128}),
+    for rows, second in ((shapes.LINEAR, {T64, T128, T128X256}), (shapes.WEIGHT_GRADIENTS, {T64, T128}), (shapes.GATED_PAIRS, {T64, T128}),
                          (shapes.ACTIVATION_GRADIENTS, {T64, T128}), (shapes.ROTARY, {T128})):
         routes = [r[-1] for r in rows]
         assert {a for a, b in routes if b == -1} == {T64, T128, T128X256, PERSISTENT}
