@@ -150,7 +150,8 @@ int ce_loss_fwd_bwd_static(const void* logits, const int64_t* targets, int64_t T
 /*
  * The LM head and its loss in one call, without ever holding all T x V logits (same training loss):
  *   logits = h w_lm^T;  loss, dlogits as in ce_loss_fwd_bwd;  dh = dlogits w_lm;  dw_lm (+)= dlogits^T h
- * The rows are walked in chunks of chunk_rows (0 = chosen by the library: 1 to 2 GiB of logits):
+ * The rows are walked in chunks of chunk_rows (0 = chosen by the library: 1 GiB of logits, a multiple
+ * of 256 rows, or 2 GiB where rows(1 GiB) * D < 2^24, that is below D = 4096 at V = 128256):
  * each chunk's logits are formed, turned into their gradient in place and consumed by the two
  * gradient products before the next chunk overwrites them.  dw_lm is accumulated in bf16 from chunk
  * to chunk (fp32 within a chunk), so it is rounded once per chunk instead of once.
@@ -158,7 +159,8 @@ int ce_loss_fwd_bwd_static(const void* logits, const int64_t* targets, int64_t T
  * 64; chunk_rows 0 or a multiple of 64; one chunk of logits and every operand below 4 GiB (T * V
  * itself may exceed it).  accumulate_dw as in dlayer_backward.
  * workspace: lm_head_ce_workspace_bytes(T, D, V, chunk_rows) - one chunk of logits, a transposed
- * copy of w_lm and T floats.
+ * copy of w_lm and T floats.  By default a chunk shrinks where D reaches the bound above, and with it
+ * the workspace: ask for every D, or pass chunk_rows.
  */
 size_t lm_head_ce_workspace_bytes(int64_t T, int64_t D, int64_t V, int64_t chunk_rows);
 int lm_head_ce_fwd_bwd(const void* h, const void* w_lm, const int64_t* targets, int64_t T, int64_t D,
