@@ -273,7 +273,8 @@ def test_activation_gradient_on_every_tile_size(K, shape, stored, route):
 INPUT_GRADIENTS = [
     ((64,), 64, 64, (T64,)),                                    # one tile, one K-step
     ((4160, 4096, 64), 320, 192, (T64, T64, T64)),              # the last rows that read the weights as stored, and the first that do not
-    ((4032, 1984, 320), 2112, 448, (PERSISTENT, T128X256, T64)),   # the same for rows x columns
+    ((4032, 1984, 320), 2112, 448, (PERSISTENT, T64, T64)),     # the same for rows x columns
+    ((1600, 576), 2624, 448, (T128X256, T64)),
     ((1920, 64), 1152, 3136, (T128, T64)),
 ]
 

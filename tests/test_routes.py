@@ -54,6 +54,11 @@ def test_the_shapes_of_the_gpu_tests_reach_the_paths_they_name(K):
         assert K.gemm_route(0, 1, [T], [F], [Kd], compute_units=256)[:2] == route, ("gated pair", T, Kd, F)
     for (T, D, F), stored, route in shapes.ACTIVATION_GRADIENTS:
         assert K.gemm_route(1 if stored else 0, 2, [T], [F], [D], compute_units=256)[:2] == route, ("activation gradient", T, D, F)
+    for rows, Kd, N, tiles in shapes.INPUT_GRADIENTS:
+        for T, tile in zip(rows, tiles):
+            stored = T <= 4096 and T * Kd <= 4096 * 2048
+            assert K.gemm_route(1 if stored else 0, 0, [T], [Kd], [N], compute_units=256)[:2] == (tile, -1), ("input gradient", T, Kd, N)
+    assert {t for *_, tiles in shapes.INPUT_GRADIENTS for t in tiles} == {T64, T128, T128X256, PERSISTENT}
     for (B, S, D, Hq, Hkv, dh, layout), route in shapes.ROTARY:
         assert K.gemm_route(0, 3 + layout, [B * S] * 3, [Hq * dh, Hkv * dh, Hkv * dh], [D] * 3, head_dim=dh,
                             compute_units=256)[:2] == route, ("rotary", B, S, D, Hq, Hkv, dh, layout)
