@@ -82,7 +82,8 @@ const char* dlayer_last_error(void);
 
 /* Bytes of the `saved` buffer that carries activations from dlayer_forward to
  * dlayer_backward, and of the scratch `workspace` either call needs.  Return 0 for a
- * configuration the library rejects (see shape granularity above).                          */
+ * configuration the library rejects (see shape granularity above).  Neither falls as batch or seq
+ * grows: buffers for the largest batch serve a smaller one.                                 */
 size_t dlayer_saved_bytes(const dlayer_cfg* cfg);
 size_t dlayer_workspace_bytes(const dlayer_cfg* cfg);
 

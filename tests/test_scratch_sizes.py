@@ -34,10 +34,11 @@ def test_attention_backward_scratch_serves_smaller_batches_and_sequences(K, Hq, 
 ])
 def test_layer_scratch_serves_smaller_batches_and_sequences(K, override):
     cfg = si.CONFIGS["tiny"].with_(**override)
-    for S in (128, 512, 2048):
-        _never_falls([K.dlayer_workspace_bytes(cfg.with_(batch=B, seq=S)) for B in range(1, 25)], f"batch at S = {S}")
-    for B in (1, 4):
-        _never_falls([K.dlayer_workspace_bytes(cfg.with_(batch=B, seq=S)) for S in range(128, 4097, 128)], f"seq at B = {B}")
+    for query in (K.dlayer_workspace_bytes, K.dlayer_saved_bytes):
+        for S in (128, 512, 2048):
+            _never_falls([query(cfg.with_(batch=B, seq=S)) for B in range(1, 25)], f"batch at S = {S}")
+        for B in (1, 4):
+            _never_falls([query(cfg.with_(batch=B, seq=S)) for S in range(128, 4097, 128)], f"seq at B = {B}")
 
 
 @pytest.mark.parametrize("D", [8, 512, 520, 1024, 2048, 2056, 4096, 4104, 8192, 16384])
