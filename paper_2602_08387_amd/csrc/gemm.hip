@@ -3,22 +3,27 @@
 // layer (y = x W^T, dx = dy W, dW = dy^T x): each operand may be stored with the contraction
 // index contiguous ("k-major") or with its M/N index contiguous ("mn-major").
 //
-// Data path: global --buffer_load ... lds (16 B per lane, no VGPR staging)--> LDS ring of NS
-// stages, BK k-values each --ds_read_b128 (k-major) or ds_read_b64_tr_b16 (mn-major)--> MFMA
-// operands.  Loads run NS-1 K-steps ahead of the MFMAs.  The buffer descriptor's range check
-// zero-fills rows past the end of a matrix, so M and N need not be tile multiples; K_s must be a
-// multiple of 64.
+// Data path: global --buffer_load ... lds (16 B per lane, no VGPR staging)--> LDS ring of two
+// stages of 64 k --ds_read_b128 (k-major) or ds_read_b64_tr_b16 (mn-major)--> MFMA operands.  The
+// buffer descriptor's range check zero-fills rows past the end of a matrix, so M and N need not be
+// tile multiples; K_s must be a multiple of 64.
+//
+// What bounds it: the power limit.  At 8192 x 8192 x 8192 the matrix pipes are busy 83 % of the cycles, at 1.8 GHz, and the
+// two trade against each other: what a kernel gains is what it saves in energy per product.  Measured on working copies,
+// as busy share x GHz: this loop 1.47; without its global loads 1.68; without its LDS reads 1.73; with all loads hitting the L2
+// 1.50.  Hence: few instructions beside the MFMAs, and MFMAs in an order that changes few operand bits (mfma_quadrant).
+// One loop of both waves of a SIMD in step, half a K-step of loads by four of the eight waves, as it was before:
+// 8192 x 8192 x 8192 729 us, now 714; 16384 x 14336 x 4096 (streams an operand of 470 MB) 1436, now 1256; weight gradients of
+// 16384 tokens, 14336 x 4096 1465, now 1378; of 8192 tokens, 2048 x 5632 171, now 157; gated pair at T 8192, K 2048, F 5632 303, now 296.
 //
 // LDS layouts (the async load puts lane l's 16 bytes at chunk l of a 1 KiB span, so swizzles
 // are applied on the global-address side).  The LDS serves 256 B of banks per clock: a 16-byte
 // read is done 16 lanes at a time, an 8-byte transposed read 32 lanes at a time.
-//   k-major tile  [rows][BK k]   : BK*2 bytes per row = CPR chunks; chunk c of row r sits at
-//                                  c ^ ((r / (16/CPR)) & (CPR-1)), so 16 consecutive rows reading
-//                                  one logical chunk touch 16 different 16-byte bank groups.
-//   mn-major tile [BK k][R mn]   : R/8 chunks per k-row; chunk c of k-row k sits at
-//                                  c ^ ((((k & 3) << 2) | (((k >> 3) & 1) << 1)) & (R/8 - 1)): the
-//                                  8 k-rows x 32 B that 32 lanes of a transposed read touch fall in
-//                                  8 different 32-byte bank groups.
+//   k-major tile  [256 rows][64 k]  : 128 bytes per row = 8 chunks; chunk c of row r sits at c ^ ((r / 2) & 7), so 16
+//                                     consecutive rows reading one logical chunk touch 16 different 16-byte bank groups.
+//   mn-major half [64 k][128 mn]    : 16 chunks per k-row; chunk c of k-row k sits at c ^ (((k & 3) << 2) | (((k >> 3) & 1) << 1)):
+//                                     the 8 k-rows x 32 B that 32 lanes of a transposed read touch fall in 8 different
+//                                     32-byte bank groups.
 // MFMA roles: the N-side operand feeds MFMA "A" (row index i), the M-side operand feeds MFMA
 // "B" (column index j), so a lane ends up with 4 consecutive n for one m.  The epilogue passes
 // the tile through LDS so that global stores (and residual loads) are 16 bytes per lane along
@@ -27,17 +32,20 @@
 
 namespace dl {
 
-// Persistent workgroup: one per CU, walking the tile sequence with stride gridDim.x.  Between two
+// Persistent workgroup: one per CU (the ring and the staging take the whole LDS), walking the tile sequence with stride
+// gridDim.x; wave w owns 128 rows (M) x 64 columns (N) of the 256 x 256 tile.  Main loop: see kstep below.  Between two
 // tiles the first two K-steps of the next tile are already on their way into the LDS ring while the
 // epilogue of the current one drains the accumulators through a staging region of its own, and the
-// C stores of a tile complete under the next tile's main loop.
+// C stores of a tile complete under the next tile's main loop.  Vector memory operations complete in order, so
+// nothing between two tiles may wait for a load of its own (a spilled register, a table) behind the tile's loads:
+// the gated pair took 346 us instead of 296 with twenty registers spilled around its epilogue.
 //
 // The kernel arguments are only read with compile-time offsets: a run-time index into the argument block
 // would make the compiler copy the whole block to scratch memory and read it back through vector loads.  A
 // grouped launch reads its problem through group_problem().
 //
 // EPI_SWIGLU: the gated pair of the MLP in one pass.  B interleaves the rows of two weight matrices
-// (LoadCursor PAIR) so that every wave holds g = x Wg^T and u = x Wu^T for the same 32 columns; the
+// (LoadStream PAIR) so that every wave holds g = x Wg^T and u = x Wu^T for the same 32 columns; the
 // epilogue stores g to c, u to c2 and silu(g) * u, taken from the fp32 sums, to c3.  M x N is the interleaved
 // product: N = twice the columns of g.
 //
@@ -53,28 +61,190 @@ namespace dl {
 // of one, and for 128-wide heads the B tile is loaded in partner order (PERM, every problem of the
 // launch) and the epilogue stores the two 32-column runs of a wave where they belong.
 enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_GRAD = 2, EPI_ROPE = 3 };
-template <bool GROUPED, int BM, int BN, int WM, int WN, bool AK, bool BKM, int EPI = EPI_PLAIN, bool PERM = false>
+
+constexpr int PM = 256, PN = 256, PWM = 2, PWN = 4;   // tile and waves
+constexpr int STAGE = (PM + PN) * BK * 2, HALF = STAGE / 4, NS = 2;
+
+// acc[i][j] += A[i] B[j] over two k-substeps, for 2 x 4 blocks: cIJ is block (i, j), aKI and bKJ the operands of substep K.
+// As assembly, in place: left to itself the compiler lets accumulators wander from one set of registers to another and
+// runs out of them.  The B operand stays for two MFMAs and the blocks are taken four at a time: the fewer operand bits
+// change from one MFMA to the next, the less power it draws (16384 x 4096 x 14336: A held for four MFMAs while B changes
+// 1288 us, this order 1268; B held for four gains no more).  The s_nop covers a VALU write of an operand right in front; the
+// accumulators may not be read otherwise before mfma_drain().
+__device__ __forceinline__ void mfma_quadrant(f32x4& c00, f32x4& c10, f32x4& c01, f32x4& c11, f32x4& c02, f32x4& c12, f32x4& c03, f32x4& c13,
+                                              bf16x8 a00, bf16x8 a01, bf16x8 a10, bf16x8 a11, bf16x8 b00, bf16x8 b01, bf16x8 b02, bf16x8 b03,
+                                              bf16x8 b10, bf16x8 b11, bf16x8 b12, bf16x8 b13) {
+#define MFMA(C, A, B) "v_mfma_f32_16x16x32_bf16 %" #C ", %" #A ", %" #B ", %" #C "\n\t"
+  asm volatile("s_nop 1\n\t"
+               MFMA(0, 8, 12) MFMA(1, 9, 12) MFMA(2, 8, 13) MFMA(3, 9, 13) MFMA(0, 10, 16) MFMA(1, 11, 16) MFMA(2, 10, 17) MFMA(3, 11, 17)
+               MFMA(4, 8, 14) MFMA(5, 9, 14) MFMA(6, 8, 15) MFMA(7, 9, 15) MFMA(4, 10, 18) MFMA(5, 11, 18) MFMA(6, 10, 19) MFMA(7, 11, 19)
+               : "+v"(c00), "+v"(c10), "+v"(c01), "+v"(c11), "+v"(c02), "+v"(c12), "+v"(c03), "+v"(c13)
+               : "v"(a00), "v"(a01), "v"(a10), "v"(a11), "v"(b00), "v"(b01), "v"(b02), "v"(b03), "v"(b10), "v"(b11), "v"(b12), "v"(b13));
+#undef MFMA
+}
+// waits until the last MFMA has written its block
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 3" ::: "memory"); }
+
+// 16 bytes per lane from LDS address `at` + OFF, or the transposed 2 x 8 of k-rows r and r + 4 of a 256-byte row tile.  As
+// assembly: for the builtins the compiler cannot tell that a read stays clear of the stage the asynchronous loads are filling
+// and waits for those in front of it.  It does not count these reads either, so every fragment passes through arrived().
+template <int OFF>
+__device__ __forceinline__ void lds_read(bf16x8& v, uint32_t at) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(at), "n"(OFF));
+}
+template <int OFF>
+__device__ __forceinline__ void lds_read_tr(bf16x8& v, uint32_t at) {
+  bf16x4 lo, hi;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(at), "n"(OFF));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(at), "n"(OFF + 1024));
+  v.lo = lo;
+  v.hi = hi;
+}
+
+// The lane number, anew.  What the compiler computes from one that it knows is lifted out of the tile loop and spilled across the
+// main loop, and its reload (counted in order behind the next tile's loads) then waits for all of those.
+__device__ __forceinline__ int lane_anew() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+// Where a tile's loads begin: prepared while the tile before it is being stored, taken up by LoadStream::begin.
+struct StreamStart {
+  const bf16_t *a, *b, *b2;
+  uint32_t a_bytes, b_bytes, b2_bytes, lda2, ldb2;   // sizes from the tile's first element on, bytes of a row
+  int k, kend, seg, m0, n0;                          // where in K, end of the segment, segment; the tile
+  bool pad;                                          // one K-step, walked as two: the second is all zeros
+};
+
+// Load cursor.  A K-step is fetched in four halves of 16 KiB, two loads per wave each: A half h is 64 of the 128 rows (M index)
+// of either wave row, B half h 32 of the 64 columns (N index) of each wave column.  Next to a load stands no more than
+// an addition: the instructions of a load phase are on the critical path of the wave group that loads.
+//   KM (both k-major): eight rows of 64 k per load, swizzled as TileLoader's tiles.  PAIR: the B halves are rows of two matrices,
+//      the same rows of either.  PERM: the rows of a B half lie as the rotary partners of 128-wide heads do, half 1 holding the
+//      features 64 beyond those of half 0.
+//   else (both mn-major): four k-rows of 128 M (N) values per load.  A half h: columns 64 h .. of either wave row's 128; B half h: columns
+//      128 h .. of the tile, so that a load reads 256 contiguous bytes (and a wave owns columns 32 w .. and 128 + 32 w ..).
+template <bool KM, bool PAIR, bool PERM, bool SEGS>
+struct LoadStream {
+  __amdgpu_buffer_rsrc_t ra, rb, rb2;
+  uint32_t va, vb;                          // lane offsets
+  uint32_t sa, sb, sa0, sb0, lda2, ldb2;    // wave's offset at the present k and at k = 0; bytes of a row
+  int k, kend, seg, left, m0, n0;
+  bool pad;
+
+  __device__ __forceinline__ void begin(const StreamStart& s, int total, int wave) {
+    const int lane = lane_anew();
+    ra = make_rsrc(s.a, s.a_bytes);
+    rb = make_rsrc(s.b, s.b_bytes);
+    if constexpr (PAIR) rb2 = make_rsrc(s.b2, s.b2_bytes);
+    k = s.k; kend = s.kend; seg = s.seg; left = total; pad = s.pad;
+    if constexpr (SEGS) { m0 = s.m0; n0 = s.n0; }
+    lda2 = s.lda2;
+    ldb2 = s.ldb2;
+    if constexpr (KM) {
+      const int row = lane >> 3, c = (lane & 7) ^ (((wave & 1) * 4 + (row >> 1)) & 7);
+      va = row * lda2 + (c << 4);
+      vb = row * ldb2 + (c << 4);
+      const int w = wave >> 1, rows = PAIR ? w * 32 : PERM ? (w >> 1) * 128 + (w & 1) * 32 : w * 64;
+      sa0 = ((wave >> 2) * 128 + (wave & 3) * 8) * lda2;
+      sb0 = (rows + (wave & 1) * 8) * ldb2;
+      sa = sa0 + k * 2;
+      sb = sb0 + k * 2;
+    } else {
+      const int row = lane >> 4, c = (lane & 15) ^ ((row << 2) | (((wave >> 1) & 1) << 1));
+      va = row * lda2 + (c >> 3) * 256 + (c & 7) * 16;
+      vb = row * ldb2 + c * 16;
+      sa0 = wave * 4 * lda2;
+      sb0 = wave * 4 * ldb2;
+      sa = sa0 + k * lda2;
+      sb = sb0 + k * ldb2;
+    }
+  }
+  // nothing more to fetch: loads go on and bring zeros, so that the main loop counts them as ever
+  __device__ __forceinline__ void close() {
+    ra = rb = make_rsrc(nullptr, 0);
+    if constexpr (PAIR) rb2 = ra;
+    left = 1 << 30;
+    pad = false;
+  }
+  static __device__ __forceinline__ int a_part(int wave) { return KM ? (wave >> 2) * 16384 + (wave & 3) * 1024 : wave * 1024; }
+  static __device__ __forceinline__ int b_part(int wave) { return 2 * HALF + (KM ? (wave >> 1) * 8192 + (wave & 1) * 1024 : wave * 1024); }
+  // half H of A or B; `dst`: this wave's part of the stage
+  template <bool A, int H>
+  __device__ __forceinline__ void issue(char* dst) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const __amdgpu_buffer_rsrc_t rs = A ? ra : PAIR && H ? rb2 : rb;
+      uint32_t so;
+      int at;
+      if constexpr (KM) {
+        at = A ? H * 8192 + i * 4096 : H * 4096 + i * 2048;
+        so = A ? sa + (H * 64 + i * 32) * lda2 : sb + ((PAIR ? 0 : PERM ? H * 64 : H * 32) + i * 16) * ldb2;
+      } else {
+        at = H * HALF + i * 8192;
+        so = A ? sa + H * 128 + i * 32 * lda2 : sb + H * 256 + i * 32 * ldb2;
+      }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(dst + at), 16, A ? va : vb, so, 0, 0);
+    }
+  }
+  // One K-step on.  The walk may start anywhere in K; past the end of a segment it goes on in the next one, past the last in the first.
+  __device__ __forceinline__ void advance(const GemmKArgs& p, int wave) {
+    --left;
+    k += BK;
+    sa += KM ? BK * 2 : BK * lda2;
+    sb += KM ? BK * 2 : BK * ldb2;
+    if (k == kend) {
+      k = 0;
+      sa = sa0;
+      sb = sb0;
+      if constexpr (SEGS) {
+        if (p.nseg > 1 && left > 0) {
+          StreamStart s;
+          s.seg = seg + 1 == p.nseg ? 0 : seg + 1;
+          open_segment(s, p, m0, n0);
+          begin(s, left, wave);
+        }
+      }
+      if (pad) {
+        ra = rb = make_rsrc(nullptr, 0);
+        if constexpr (PAIR) rb2 = ra;
+      }
+    }
+  }
+  // s from its segment's beginning
+  static __device__ __forceinline__ void open_segment(StreamStart& s, const GemmKArgs& p, int m0, int n0) {
+    open(s, p.a[s.seg], p.b[s.seg], p.lda[s.seg], p.ldb[s.seg], p.K[s.seg], p.M, p.N, m0, n0);
+    s.k = 0;
+    s.pad = false;
+  }
+  static __device__ __forceinline__ void open(StreamStart& s, const bf16_t* a, const bf16_t* b, int64_t lda, int64_t ldb, int K, int M, int N,
+                                              int m0, int n0) {
+    s.kend = K;
+    s.m0 = m0;
+    s.n0 = n0;
+    s.lda2 = (uint32_t)(lda * 2);
+    s.ldb2 = (uint32_t)(ldb * 2);
+    // byte offsets and sizes below 4 GiB, as every tensor is
+    s.a = KM ? reinterpret_cast<const bf16_t*>(reinterpret_cast<const char*>(a) + (uint32_t)m0 * s.lda2) : a + m0;
+    s.b = KM ? reinterpret_cast<const bf16_t*>(reinterpret_cast<const char*>(b) + (uint32_t)n0 * s.ldb2) : b + n0;
+    s.a_bytes = KM ? (uint32_t)(M - m0 - 1) * s.lda2 + K * 2 : (uint32_t)(K - 1) * s.lda2 + (M - m0) * 2;
+    s.b_bytes = KM ? (uint32_t)(N - n0 - 1) * s.ldb2 + K * 2 : (uint32_t)(K - 1) * s.ldb2 + (N - n0) * 2;
+  }
+};
+
+template <bool GROUPED, bool KM, int EPI = EPI_PLAIN, bool PERM = false>
 __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const GemmKArgs& one) {
-  constexpr int NW = WM * WN;
-  constexpr int TM = BM / WM, TN = BN / WN;
-  constexpr int FM = TM / MI, FN = TN / MI;
-  constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
-  // Only one wave per SIMD issues the global -> LDS loads.  The address unit takes 16 cycles per
-  // wave-wide 16-byte load (1024 cycles per K-step for a 256x256x64 tile pair) and a wave blocks
-  // while its loads queue up; if both waves of a SIMD do that at the same time the matrix pipe
-  // starves, whereas a loading wave next to a computing wave keeps it fed (+3..6 % measured).
-  constexpr int NL = NW < 4 ? NW : 4;
-  using LoadA = TileLoader<BM, AK, NL>;
-  using LoadB = TileLoader<BN, BKM, NL>;
-  constexpr int LPW = LoadA::PER_WAVE + LoadB::PER_WAVE;   // loads per wave per stage
-  static_assert(NS == 2, "the stage hand-over below is written for a two-stage ring");
-  static_assert(TN % 64 == 0 && FM % 4 == 0, "staging layout: 128-byte rows, four row quarters");
+  constexpr int TM = PM / PWM, TN = PN / PWN, FM = TM / MI, FN = TN / MI;
+  constexpr bool SWIGLU = EPI == EPI_SWIGLU;
+  static_assert(TM == 128 && TN == 64, "halves, quadrants and staging are laid out for 128 x 64 per wave");
+  static_assert(EPI == EPI_PLAIN || KM, "fused epilogues: k-major operands");
+  static_assert(EPI == EPI_PLAIN || GROUPED == (EPI == EPI_ROPE), "the rotary epilogue is the grouped launch's, the others are not");
+  static_assert(!PERM || EPI == EPI_ROPE, "partner-order tiles: rotary epilogue only");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wave_m = wave % WM, wave_n = wave / WM;
-  const bool loader = wave < NL;
+  const int wave_m = wave % PWM, wave_n = wave / PWM;
   int ntiles;
   if constexpr (GROUPED) {
     ntiles = grp.tile_start[1];
@@ -84,26 +254,24 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
     ntiles = one.tiles_m * one.tiles_n;
   }
 
-  // What the epilogue needs of a tile's problem, by value (the next tile's cursor is opened before the
-  // current tile's epilogue runs).
+  // What the epilogue needs of a tile's problem, by value.
   struct Tile { int m0, n0, total, M, N, accumulate, rope; bf16_t* c; const bf16_t* r; int64_t ldc; };
-  constexpr bool SWIGLU = EPI == EPI_SWIGLU;
-  LoadCursor<BM, BN, NL, AK, BKM, SWIGLU, PERM> cur;
-  static_assert(EPI == EPI_PLAIN || (TN == 64 && MI == 16), "fused epilogues: one 64-column strip per wave");
-  static_assert(EPI == EPI_PLAIN || GROUPED == (EPI == EPI_ROPE), "the rotary epilogue is the grouped launch's, the others are not");
-  static_assert(!PERM || (EPI == EPI_ROPE && AK && BKM && BN % 128 == 0), "partner-order tiles: rotary epilogue only");
+  constexpr bool SEGS = KM && !GROUPED && EPI == EPI_PLAIN;   // fused input gradients: several K-segments
+  using Stream = LoadStream<KM, SWIGLU, PERM, SEGS>;
+  Stream cur;
 
-  // tile id -> tile origin, and the load cursor opened on the tile's first K-segment.  The tile
-  // sequence of a problem runs in bands of band_rows (8 or 4) tile-rows, so that the ~32 consecutive
-  // tiles an XCD holds at a time share A and B panels.
-  auto locate = [&](int id) {
+  // tile id -> tile, and where its loads begin.  The tile sequence of a problem runs in bands of 2^band_shift (8 or 4) tile
+  // rows, so that the ~32 consecutive tiles an XCD holds at a time share A and B panels.
+  auto locate = [&](int id, StreamStart& s) {
     int pid = xcd_contiguous(id, ntiles);
-    int tiles_m, tiles_n, K0, GM, start = 0;
+    int tiles_m, K0, shift, band_tiles, start = 0;
+    uint32_t recip;
     const bf16_t *a0, *b0;
     int64_t lda0, ldb0;
     Tile t;
     auto take = [&](const auto& q) {
-      tiles_m = q.tiles_m; tiles_n = q.tiles_n; K0 = q.K[0]; GM = q.band_rows > 0 ? q.band_rows : 8;
+      tiles_m = q.tiles_m; band_tiles = q.band_tiles; recip = q.band_recip; K0 = q.K[0]; shift = q.band_rows == 4 ? 2 : 3;
+      t.total = q.ksteps;
       a0 = q.a[0]; b0 = q.b[0]; lda0 = q.lda[0]; ldb0 = q.ldb[0];
       t.M = q.M; t.N = q.N; t.accumulate = q.accumulate; t.c = q.c; t.r = q.r; t.ldc = q.ldc;
       t.rope = EPI == EPI_ROPE ? q.rope : 0;
@@ -114,207 +282,215 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
       for (int i = 1; i < MAX_GROUP; ++i)
         if (i < grp.n && pid >= grp.tile_start[i]) { pi = i; start = grp.tile_start[i]; }
-      take(group_problem(pi));
+      take(group_problem(pi));   // a single K-segment (checked on the host)
       pid -= start;
-      cur.nseg = 1;   // grouped problems have a single K-segment (checked on the host)
-      t.total = K0 / BK;
     } else {
       take(one);
-      cur.nseg = one.nseg;
-      t.total = 0;
-      for (int s2 = 0; s2 < one.nseg; ++s2) t.total += one.K[s2] / BK;
     }
-    const int band = pid / (GM * tiles_n);
-    const int first_m = band * GM;
-    const int band_h = min(tiles_m - first_m, GM);
-    const int in_band = pid - band * GM * tiles_n;
-    t.m0 = (first_m + in_band % band_h) * BM;
-    t.n0 = (in_band / band_h) * BN;
-    cur.left = t.total;
+    int band = (int)__umulhi((uint32_t)pid, recip);   // at most one too many
+    if (band * band_tiles > pid) --band;
+    const int first_m = band << shift, in_band = pid - band * band_tiles;
+    const int band_h = tiles_m - first_m;
+    if (band_h >> shift) {
+      t.m0 = (first_m + (in_band & ((1 << shift) - 1))) * PM;
+      t.n0 = (in_band >> shift) * PN;
+    } else {   // the last band, of fewer rows
+      t.m0 = (first_m + in_band % band_h) * PM;
+      t.n0 = (in_band / band_h) * PN;
+    }
     int first = k_start(t.m0, t.total);   // in K-steps from the start of segment 0
-    cur.seg = 0;
-    if constexpr (!GROUPED) {
+    s.seg = 0;
+    if constexpr (SEGS) {
       for (int s2 = 0; s2 + 1 < one.nseg; ++s2)
-        if (cur.seg == s2 && first >= one.K[s2] / BK) { first -= one.K[s2] / BK; cur.seg = s2 + 1; }
+        if (s.seg == s2 && first >= one.K[s2] / BK) { first -= one.K[s2] / BK; s.seg = s2 + 1; }
     }
-    cur.k = first * BK;
-    if (cur.seg == 0) {
-      if constexpr (SWIGLU) cur.open_pair(a0, b0, one.b2, lda0, ldb0, K0, t.M, t.N, t.m0, t.n0, lane);
-      else cur.open_raw(a0, b0, lda0, ldb0, K0, t.M, t.N, t.m0, t.n0, lane);
+    if (!SEGS || s.seg == 0) {
+      Stream::open(s, a0, b0, lda0, ldb0, K0, t.M, SWIGLU ? t.N / 2 : t.N, t.m0, SWIGLU ? t.n0 / 2 : t.n0);
+      if constexpr (SWIGLU) {
+        s.b2 = one.b2 + (int64_t)(t.n0 / 2) * ldb0;
+        s.b2_bytes = s.b_bytes;
+      }
     } else {
-      cur.open(one, cur.seg, t.m0, t.n0, lane);
+      Stream::open_segment(s, one, t.m0, t.n0);
     }
+    s.k = first * BK;
+    s.pad = t.total == 1;
+    t.total = max(t.total, 2);
     return t;
   };
 
-  // Load cursor: runs two K-steps ahead of the compute cursor, across segment boundaries.
+  const int step = (int)gridDim.x;
   int id = blockIdx.x;
   if (id >= ntiles) return;
-  Tile tl = locate(id);
-  if (loader) {
-    cur.issue_next(one, smem, wave, tl.m0, tl.n0, lane);
-    cur.issue_next(one, smem + STAGE, wave, tl.m0, tl.n0, lane);
+  StreamStart start;
+  Tile tl = locate(id, start), next = tl;
+  cur.begin(start, tl.total, wave);
+  const int pa = Stream::a_part(wave), pb = Stream::b_part(wave);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    cur.template issue<true, 0>(smem + t * STAGE + pa);
+    cur.template issue<false, 0>(smem + t * STAGE + pb);
+    cur.template issue<false, 1>(smem + t * STAGE + pb);
+    cur.template issue<true, 1>(smem + t * STAGE + pa);
+    cur.advance(one, wave);
   }
-  if (tl.total >= 2) wait_vmcnt<LPW>(); else wait_vmcnt<0>();
+  bool more = id + step < ntiles;
+  if (more) next = locate(id + step, start);
 
-  // K-step s of a tile lives in ring stage (s + par) & 1: the K-steps of successive tiles form one
-  // stream through the ring, so `par` moves on by the tile's number of K-steps.
-  int par = 0;
+  // The tile's first K-step has landed (this wave's loads), and of its second what the first three phases of the main loop
+  // are not going to wait for: its first two halves, in the order in which a tile of an even (odd) number of K-steps needs
+  // them.  AFTER: stores that went out behind the loads.
+  auto landed = [&](int total, auto after) {
+    constexpr int AFTER = decltype(after)::value;
+    if (total & 1) wait_vmcnt<2 + AFTER>(); else wait_vmcnt<4 + AFTER>();
+  };
+  constexpr std::integral_constant<int, 0> C0{};
+  constexpr std::integral_constant<int, 1> C1{};
+  constexpr std::integral_constant<int, 2> C2{};
+  constexpr std::integral_constant<int, 3> C3{};
+  constexpr std::integral_constant<int, EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_GRAD ? 32 : 16> STORES{};   // of a wave, of a whole tile
+  landed(tl.total, C0);
+
+  // Lane's place in a fragment.  k-major: rows of 128 bytes, the second 32 k at this ^ 64.  mn-major: rows of 256 bytes (one k),
+  // block f of 16 at this ^ 32 f.
+  uint32_t lane_a, lane_b;
+  const int lane0 = threadIdx.x & 63;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(smem);
+  if constexpr (KM) {
+    const uint32_t l = (lane0 & 15) * (BK * 2) + (((lane0 >> 4) ^ ((lane0 >> 1) & 7)) << 4);
+    lane_a = l + lds0 + wave_m * TM * BK * 2;
+    lane_b = l + lds0 + 2 * HALF + wave_n * TN * BK * 2;
+  } else {
+    const int grp = lane0 >> 4, e = (lane0 >> 2) & 3, g = lane0 & 3;
+    const uint32_t l = (grp * 8 + e) * 256 + (((g >> 1) ^ (e << 2) ^ ((grp & 1) << 1)) << 4) + (g & 1) * 8;
+    lane_a = (l ^ (wave_m * 128)) + lds0;
+    lane_b = (l ^ (wave_n * 64)) + lds0 + 2 * HALF;
+  }
+  // Waves 4 to 7, the other wave of each SIMD, run one slot behind waves 0 to 3.
+  const bool behind = wave >= 4;
+  uint32_t cs = 0;   // the ring stage of the K-step: the K-steps of successive tiles form one stream through the ring
   while (true) {
-    const Tile p = tl;   // this tile; `tl` moves on to the next one during its last K-steps
-    const int m0 = tl.m0, n0 = tl.n0, total = tl.total;
-    bool early = false;
-    acc_t acc[FN][FM];
+    const Tile p = tl;
+    const int m0 = p.m0, n0 = p.n0, total = p.total;
+    f32x4 acc[FN][FM];
 #pragma unroll
     for (int i = 0; i < FN; ++i)
 #pragma unroll
-      for (int j = 0; j < FM; ++j)
+      for (int j = 0; j < FM; ++j) {
 #pragma unroll
-        for (int e = 0; e < NACC; ++e) acc[i][j][e] = 0.f;
-
-    // K-step 0 has landed in every loading wave's share (waited for before the first tile, or in the
-    // previous tile's epilogue); the barrier makes it visible to all waves
+        for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+        asm volatile("" : "+v"(acc[i][j]));   // zeroed here, not in front of the first MFMA (see mfma_quadrant)
+      }
+    // K-step 0 has landed in every wave's share; the barrier makes it visible to all waves
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    // Software-pipelined K loop: operand fragments are double-buffered in registers; the barrier that
-    // hands over to the next stage sits before the last MFMA group of the current one, so the matrix
-    // pipe stays busy while the first fragments of the next stage are fetched from LDS.
-    constexpr int KK = BK / KSTEP;
     bf16x8 fa[2][FM], fb[2][FN];
-    {
-      const char* ta = smem + par * STAGE;
-      const char* tb = ta + A_BYTES;
-#pragma unroll
-      for (int j = 0; j < FM; ++j) fa[0][j] = read_frag<BM, AK>(ta, wave_m * TM + j * MI, 0, lane);
-#pragma unroll
-      for (int i = 0; i < FN; ++i) fb[0][i] = read_frag<BN, BKM>(tb, wave_n * TN + i * MI, 0, lane);
-    }
-    if constexpr (!(AK && BKM)) wait_frags(fa[0], fb[0]);
-    for (int t = 0; t < total; ++t) {
-      // Every load of this tile is out once its last but one K-step begins.  The cursor moves on to the
-      // workgroup's next tile there, and that tile's first two K-steps go out at this tile's last two
-      // hand-overs like any other refill: by the time the epilogue runs they have had a K-step to land.
-      if (t == total - 2 && id + (int)gridDim.x < ntiles) {
-        tl = locate(id + gridDim.x);
-        early = true;
-      }
-      char* st_cur = smem + ((t + par) & 1) * STAGE;
-      const char* ta = st_cur;
-      const char* tb = ta + A_BYTES;
-      static_for<0, KK>([&](auto kk_c) {
+    // half H & 1 of the wave's A (H < 2) or B fragments
+    auto reads = [&](auto H, uint32_t st) {
+      constexpr int h = decltype(H)::value & 1;
+      constexpr bool A = decltype(H)::value < 2;
+      constexpr int F = A ? FM : FN;
+      auto& a = fa;
+      auto& b = fb;
+      const uint32_t at = (A ? lane_a : lane_b) + st;
+      static_for<0, 2>([&](auto kk_c) {
         constexpr int kk = decltype(kk_c)::value;
-        constexpr int cb = kk & 1, nb = cb ^ 1;
-        if constexpr (AK && BKM) {
-          if (kk + 1 < KK) {
-#pragma unroll
-            for (int j = 0; j < FM; ++j) fa[nb][j] = read_frag<BM, AK>(ta, wave_m * TM + j * MI, kk + 1, lane);
-#pragma unroll
-            for (int i = 0; i < FN; ++i) fb[nb][i] = read_frag<BN, BKM>(tb, wave_n * TN + i * MI, kk + 1, lane);
-          } else {
-            // all of this wave's reads of stage t are in registers; stage t+1 must have landed
-            wait_vmcnt<0>();   // the only loads in flight are those of stage t+1, issued one K-step ago
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            // every wave now holds its last fragments of stage t in registers: refill that stage with
-            // step t+2 right away, so the loads get a whole K-step to land (about 2800 cycles at 1.9 GHz
-            // under sustained load; cycle counters put the wait for the slowest of them, those that
-            // miss the L2, at some 300 cycles per K-step on top of that)
-            if (loader) cur.issue_next(one, st_cur, wave, tl.m0, tl.n0, lane);
-            // the reads go out unconditionally (after the last K-step they fetch stale bytes nobody
-            // uses), which keeps them in one block with this group's MFMAs so that the scheduler
-            // interleaves them (+2 %)
-            const char* na = smem + ((t + 1 + par) & 1) * STAGE;
-            const char* nbp = na + A_BYTES;
-#pragma unroll
-            for (int j = 0; j < FM; ++j) fa[nb][j] = read_frag<BM, AK>(na, wave_m * TM + j * MI, 0, lane);
-#pragma unroll
-            for (int i = 0; i < FN; ++i) fb[nb][i] = read_frag<BN, BKM>(nbp, wave_n * TN + i * MI, 0, lane);
-          }
-#pragma unroll
-          for (int i = 0; i < FN; ++i)
-#pragma unroll
-            for (int j = 0; j < FM; ++j)
-              acc[i][j] = mfma(fb[cb][i], fa[cb][j], acc[i][j]);
-#pragma unroll
-          for (int q = 0; q < FM + FN; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, (FM * FN) / (FM + FN), 0);  // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                      // DS read
-          }
-        } else {
-          // With a transposed operand the fragment reads are inline assembly (see read_frag), which the
-          // scheduler neither counts nor places, so the order is fixed by hand: the group's FN rows of
-          // MFMAs, each preceded by its share of the next fragments.  In the last group of a K-step the
-          // first row runs before the hand-over (it only needs registers), so the matrix pipe has
-          // work while the wave sits at the barrier.
-          constexpr bool last = kk + 1 == KK;
-          // the refill of the drained stage is spread over the rows after the hand-over: a wave is held
-          // for some 27 cycles per load instruction, which its own queued MFMAs then cover (-0.15 ms)
-          constexpr bool GEMM_SPREAD_LOADS = true;
-          constexpr int NF = FM + FN;                       // fragments to fetch: A 0..FM-1, then B
-          constexpr int NCH = last ? FN - 1 : FN;           // chunks they are spread over
-          const char* ra_ = last ? smem + ((t + 1 + par) & 1) * STAGE : ta;
-          const char* rb_ = ra_ + A_BYTES;
-          const bool do_reads = !last || t + 1 < total;
-          static_for<0, FN>([&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            if (last && i == 1) {
-              wait_vmcnt<0>();   // stage t+1 has landed (loads issued one K-step ago)
-              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-              __builtin_amdgcn_s_barrier();
-              asm volatile("" ::: "memory");
-              if (!GEMM_SPREAD_LOADS && loader) cur.issue_next(one, st_cur, wave, tl.m0, tl.n0, lane);   // step t+2 into the drained stage
-            }
-            if constexpr (GEMM_SPREAD_LOADS && last && i >= 1) {
-              if (loader) cur.template issue_piece<i - 1, FN - 1>(one, st_cur, wave, tl.m0, tl.n0, lane);
-            }
-              const int ch = last ? i - 1 : i;
-            if (ch >= 0 && do_reads) {
-#pragma unroll
-              for (int f = ch * NF / NCH; f < (ch + 1) * NF / NCH; ++f) {
-                if (f < FM) fa[nb][f] = read_frag<BM, AK>(ra_, wave_m * TM + f * MI, last ? 0 : kk + 1, lane);
-                else fb[nb][f - FM] = read_frag<BN, BKM>(rb_, wave_n * TN + (f - FM) * MI, last ? 0 : kk + 1, lane);
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < FM; ++j) acc[i][j] = mfma(fb[cb][i], fa[cb][j], acc[i][j]);
-            __builtin_amdgcn_sched_barrier(0);
-          });
-          // the fragments fetched above are complete once this wait has passed; the next group's MFMAs
-          // depend on it
-          wait_frags(fa[nb], fb[nb]);
-        }
+        static_for<0, F / 2>([&](auto f_c) {
+          constexpr int f = decltype(f_c)::value;
+          bf16x8& v = A ? a[kk][(h * F / 2 + f) % FM] : b[kk][(h * F / 2 + f) % FN];
+          if constexpr (KM) lds_read<(h * F / 2 + f) * MI * BK * 2>(v, kk ? at ^ 64 : at);
+          else lds_read_tr<h * HALF + kk * 8192>(v, at ^ (f * 32));
+        });
       });
-    }
-    // Next tile.  Normally its cursor was opened and its first two K-steps sent during the last two
-    // K-steps above; a tile of a single K-step sends them here (the last hand-over waited for every
-    // load and passed a barrier after every wave's last LDS read: the whole ring is free).
-    id += gridDim.x;
-    const bool more = id < ntiles;
-    par = (par + total) & 1;
-    if (more && !early) {
-      tl = locate(id);
-      if (loader) {
-        cur.issue_next(one, smem + par * STAGE, wave, tl.m0, tl.n0, lane);
-        cur.issue_next(one, smem + (par ^ 1) * STAGE, wave, tl.m0, tl.n0, lane);
+    };
+    auto tie = [&](auto H) {
+      constexpr int h = decltype(H)::value & 1;
+      constexpr bool A = decltype(H)::value < 2;
+      constexpr int F = A ? FM : FN;
+      auto& a = fa;
+      auto& b = fb;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int f = h * F / 2; f < (h + 1) * F / 2; ++f) {
+          bf16x8& v = A ? a[kk][f % FM] : b[kk][f % FN];
+          asm volatile("" : "+v"(v));
+        }
+    };
+    // waits for this wave's LDS reads and makes the half's fragments depend on it
+    auto arrived = [&](auto H) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      tie(H);
+    };
+    // One K-step in four phases, one quadrant of the wave's tile each: A0 Bq, A0 Bq', A1 Bq', A1 Bq (q' = 1 - q).  A phase is a
+    // slot of memory work (fragments for the next phase, one half of the K-step after next) and a slot of MFMAs; the wave
+    // groups are a slot apart, so one feeds the matrix pipes while the other reads and loads.  Q = 1 for the last K-step
+    // and every other before it, so that the next K-step's first B half can be read before this one's last is done with.
+    auto kstep = [&](auto Q, int t) {
+      constexpr int q = decltype(Q)::value;
+      if (q == 0 && t == total - 2) {   // every load of this tile is out: on to the next one's
+        if (more) cur.begin(start, next.total, wave); else cur.close();
       }
+      static_for<0, 4>([&](auto P) {
+        constexpr int ph = decltype(P)::value;
+        constexpr int h = ph == 0 ? 3 - q : ph == 1 ? 1 : ph == 2 ? 0 : 3 - q;
+        constexpr std::integral_constant<int, h> H{};
+        reads(H, ph < 2 ? cs : STAGE - cs);
+        // the half of this stage that every wave has read since two phases
+        if constexpr (ph == 0) cur.template issue<true, 0>(smem + cs + pa);
+        if constexpr (ph == 1) cur.template issue<false, q>(smem + cs + pb);
+        if constexpr (ph == 2) cur.template issue<false, 1 - q>(smem + cs + pb);
+        if constexpr (ph == 3) cur.template issue<true, 1>(smem + cs + pa);
+        // The half that the next phase reads went out six phases ago, five halves are younger.  (What the first three
+        // phases read has landed; waiting there would be for the last tile's stores.)
+        if (ph == 3 || t > 0) wait_vmcnt<10>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr int i = (ph == 0 || ph == 3 ? q : 1 - q) * FN / 2, j = ph < 2 ? 0 : FM / 2;
+        mfma_quadrant(acc[i][j], acc[i + 1][j], acc[i][j + 1], acc[i + 1][j + 1], acc[i][j + 2], acc[i + 1][j + 2], acc[i][j + 3],
+                      acc[i + 1][j + 3], fb[0][i], fb[0][i + 1], fb[1][i], fb[1][i + 1], fa[0][j], fa[0][j + 1], fa[0][j + 2], fa[0][j + 3],
+                      fa[1][j], fa[1][j + 1], fa[1][j + 2], fa[1][j + 3]);
+        __builtin_amdgcn_sched_barrier(0);
+        arrived(H);
+        __builtin_amdgcn_s_barrier();
+        if constexpr (ph == 3) cur.advance(one, wave);
+        asm volatile("" ::: "memory");
+      });
+      cs = STAGE - cs;
+    };
+    const bool odd = total & 1;
+    reads(C0, cs);
+    if (odd) reads(C3, cs); else reads(C2, cs);
+    arrived(C0);
+    tie(C2);
+    tie(C3);
+    __builtin_amdgcn_s_barrier();   // before the first load into this stage
+    if (behind) __builtin_amdgcn_s_barrier();
+    if (odd) kstep(C1, 0);
+    for (int t = odd; t < total; t += 2) {
+      kstep(C0, t);
+      kstep(C1, t + 1);
     }
+    if (!behind) __builtin_amdgcn_s_barrier();
+    mfma_drain();
 
+    // Waiting for the next tile's loads behind the epilogue's stores takes a known number of them: where the tile lies inside C.
+    const bool inside = m0 + PM <= p.M && n0 + PN <= p.N;
     // Epilogue through LDS (a region behind the ring): each wave owns a [TM/4][64] bf16 staging area
     // (128 bytes per row, chunk c of row m stored at c ^ ((m >> 1) & 7)), filled from the accumulator
     // layout (8 bytes per lane) and drained row-contiguously (16 bytes per lane, 8 lanes per row); a
     // wave's tile goes through it in 4 * TN/64 pieces.
     constexpr int HM = TM / 4, HF = FM / 4;
     char* stg = smem + NS * STAGE + wave * (HM * 128);
+    const int lane = lane_anew();
     const int lm = lane & (MI - 1), lq = lane / MI;
     const int rrow = lane >> 3, rpc = lane & 7;
     constexpr int TPB = 64 / MI;      // MFMA blocks per 64 staged columns
-    constexpr int NG = NACC / 4;      // 4-column groups a lane holds per MFMA block
-    // column (within the 64 staged ones) of group g of block i for this lane; jj: block row in the half
-    auto stg_off = [&](int jj, int i, int g) {
+    // this lane's 4 columns of block i (within the 64 staged ones); jj: block row in the quarter
+    auto stg_off = [&](int jj, int i) {
       const int row = jj * MI + lm;
-      const int n = i * MI + (MI == 32 ? g * 8 + lq * 4 : lq * 4);
+      const int n = i * MI + lq * 4;
       return row * 128 + ((((n >> 3) ^ ((row >> 1) & 7)) << 4) | ((n & 4) << 1));
     };
     if constexpr (EPI == EPI_SWIGLU_GRAD) {
@@ -350,11 +526,11 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
         for (int t = 0; t < NT; ++t) *reinterpret_cast<bf16x8*>(stg + (t * 8 + rrow) * 128 + (rpc << 4)) = v8[t];
 #pragma unroll
-        for (int i = 0; i < TPB; ++i) q[i] = *reinterpret_cast<const bf16x4*>(stg + stg_off(0, i, 0));
+        for (int i = 0; i < TPB; ++i) q[i] = *reinterpret_cast<const bf16x4*>(stg + stg_off(0, i));
       };
       auto drain = [&](int s, const bf16x4 (&q)[TPB], bf16_t* dst) {
 #pragma unroll
-        for (int i = 0; i < TPB; ++i) *reinterpret_cast<bf16x4*>(stg + stg_off(0, i, 0)) = q[i];
+        for (int i = 0; i < TPB; ++i) *reinterpret_cast<bf16x4*>(stg + stg_off(0, i)) = q[i];
         const int mbase = m0 + wave_m * TM + s * MI;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -385,9 +561,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
             gq[i][e] = (bf16_t)(d * (float)uq[i][e] * sg * (1.0f + z * (1.0f - sg)));
             uq[i][e] = (bf16_t)(d * z * sg);
           }
-        if (s == 0 && more) {
-          if (tl.total >= 2) wait_vmcnt<LPW>(); else wait_vmcnt<0>();
-        }
+        if (s == 0 && more && !inside) landed(next.total, C0);
         drain(s, gq, p.c);
         drain(s, uq, one.c2);
       });
@@ -404,11 +578,9 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
             bf16x4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = (bf16_t)acc[i][hf * HF + jj][e];
-            *reinterpret_cast<bf16x4*>(stg + stg_off(jj, i, 0)) = o;
+            *reinterpret_cast<bf16x4*>(stg + stg_off(jj, i)) = o;
           }
-        if (hf == 0 && more) {
-          if (tl.total >= 2) wait_vmcnt<LPW>(); else wait_vmcnt<0>();
-        }
+        if (hf == 0 && more && !inside) landed(next.total, C0);
 #pragma unroll
         for (int t = 0; t < HM / 8; ++t) {
           const int row = t * 8 + rrow;
@@ -429,7 +601,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
               const float z = acc[i][hf * HF + jj][e];
               o[e] = (bf16_t)(z * logistic(z) * acc[i + 2][hf * HF + jj][e]);
             }
-            *reinterpret_cast<bf16x4*>(stg + stg_off(jj, i, 0)) = o;
+            *reinterpret_cast<bf16x4*>(stg + stg_off(jj, i)) = o;
           }
 #pragma unroll
         for (int t = 0; t < HM / 8; ++t) {
@@ -442,9 +614,14 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
         }
       }
     } else {
-#pragma unroll
-    for (int nb = 0; nb < TN / 64; ++nb) {
-      const int nbase = n0 + wave_n * TN + nb * 64;
+      const int nbase = n0 + wave_n * TN;
+      // Column of C of staged column cl.  Partner-order tiles: staged columns 0..31 are features (wave_n & 1) * 32 + .. of head wave_n / 2
+      // of the tile, 32..63 the same features 64 further on.  mn-major B: the wave's 32 columns of either half of the tile.
+      auto column = [&](int cl) {
+        if constexpr (PERM) return n0 + (wave_n >> 1) * 128 + (wave_n & 1) * 32 + (cl & 31) + ((cl >> 5) << 6);
+        else if constexpr (!KM) return n0 + wave_n * 32 + (cl & 31) + ((cl >> 5) << 7);
+        else return nbase + cl;
+      };
 #pragma unroll
       for (int hf = 0; hf < 4; ++hf) {
         const int mbase = m0 + wave_m * TM + hf * HM;
@@ -454,7 +631,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
           for (int t = 0; t < HM / 8; ++t) {
             const int row = t * 8 + rrow;
             const int m = mbase + row;
-            const int n = nbase + ((rpc ^ ((row >> 1) & 7)) << 3);
+            const int n = column((rpc ^ ((row >> 1) & 7)) << 3);
             bf16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
             if (m < p.M && n < p.N) v = *reinterpret_cast<const bf16x8*>(src + (int64_t)m * p.ldc + n);
             *reinterpret_cast<bf16x8*>(stg + row * 128 + (rpc << 4)) = v;
@@ -462,13 +639,11 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
           for (int jj = 0; jj < HF; ++jj)
 #pragma unroll
-            for (int i = 0; i < TPB; ++i)
+            for (int i = 0; i < TPB; ++i) {
+              const bf16x4 v = *reinterpret_cast<const bf16x4*>(stg + stg_off(jj, i));
 #pragma unroll
-              for (int g = 0; g < NG; ++g) {
-                const bf16x4 v = *reinterpret_cast<const bf16x4*>(stg + stg_off(jj, i, g));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[nb * TPB + i][hf * HF + jj][g * 4 + e] += (float)v[e];
-              }
+              for (int e = 0; e < 4; ++e) acc[i][hf * HF + jj][e] += (float)v[e];
+            }
         }
         if constexpr (EPI == EPI_ROPE) {
           if (p.rope) {
@@ -487,7 +662,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
                   const int idx = narrow ? lq * 4 : (PERM ? (wave_n & 1) * 32 : 0) + t * 16 + lq * 4;
                   const f32x4 c4 = *reinterpret_cast<const f32x4*>(cr + idx);
                   const f32x4 s4 = *reinterpret_cast<const f32x4*>(sr + idx);
-                  auto rot = [&](acc_t& a, acc_t& b) {
+                  auto rot = [&](f32x4& a, f32x4& b) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                       const float fa = a[e], fb = b[e];
@@ -518,56 +693,45 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 #pragma unroll
         for (int jj = 0; jj < HF; ++jj)
 #pragma unroll
-          for (int i = 0; i < TPB; ++i)
+          for (int i = 0; i < TPB; ++i) {
+            bf16x4 o;
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-              bf16x4 o;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o[e] = (bf16_t)acc[nb * TPB + i][hf * HF + jj][g * 4 + e];
-              *reinterpret_cast<bf16x4*>(stg + stg_off(jj, i, g)) = o;
-            }
-        // Before this tile's first store: the next tile's K-step 0 must have landed, and waiting for
-        // it here (nothing younger than K-step 1 is in flight) keeps the stores out of that wait, so
-        // they complete under the next main loop.
-        if (nb == 0 && hf == 0 && more) {
-          if (tl.total >= 2) wait_vmcnt<LPW>(); else wait_vmcnt<0>();
-        }
+            for (int e = 0; e < 4; ++e) o[e] = (bf16_t)acc[i][hf * HF + jj][e];
+            *reinterpret_cast<bf16x4*>(stg + stg_off(jj, i)) = o;
+          }
+        if (hf == 0 && more && !inside) landed(next.total, C0);
 #pragma unroll
         for (int t = 0; t < HM / 8; ++t) {
           const int row = t * 8 + rrow;
           const int m = mbase + row;
-          const int cl = (rpc ^ ((row >> 1) & 7)) << 3;   // column among the wave's 64
-          // partner-order tiles: staged columns 0..31 are features (wave_n & 1) * 32 + .. of head wave_n / 2 of
-          // the tile, columns 32..63 the same features 64 further on
-          const int n = PERM ? n0 + (wave_n >> 1) * 128 + (wave_n & 1) * 32 + (cl & 31) + ((cl >> 5) << 6) : nbase + cl;
+          const int n = column((rpc ^ ((row >> 1) & 7)) << 3);
           const bf16x8 v = *reinterpret_cast<const bf16x8*>(stg + row * 128 + (rpc << 4));
           if (m < p.M && n < p.N) *reinterpret_cast<bf16x8*>(p.c + (int64_t)m * p.ldc + n) = v;
         }
       }
     }
-    }
     if (!more) break;
+    tl = next;
+    id += step;
+    more = id + step < ntiles;
+    if (more) next = locate(id + step, start);   // while the stores and the loads behind them are on their way
+    if (inside) landed(tl.total, STORES);
   }
+  wait_vmcnt<0>();   // a closed stream's loads still write to LDS
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_kernel(const GemmKArgs p) {
-  gemm_persistent<false, BM, BN, WM, WN, AK, BKM>(GemmGroupKArgs{}, p);
-}
+template <bool KM>
+__global__ __launch_bounds__(512) void gemm_kernel(const GemmKArgs p) { gemm_persistent<false, KM>(GemmGroupKArgs{}, p); }
 
-template <int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_swiglu_kernel(const GemmKArgs p) {
-  gemm_persistent<false, BM, BN, WM, WN, true, true, EPI>(GemmGroupKArgs{}, p);
-}
+template <int EPI>
+__global__ __launch_bounds__(512) void gemm_swiglu_kernel(const GemmKArgs p) { gemm_persistent<false, true, EPI>(GemmGroupKArgs{}, p); }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_group_kernel(const GemmGroupKArgs g) {
-  gemm_persistent<true, BM, BN, WM, WN, AK, BKM>(g, g.prob[0]);
-}
+template <bool KM>
+__global__ __launch_bounds__(512) void gemm_group_kernel(const GemmGroupKArgs g) { gemm_persistent<true, KM>(g, g.prob[0]); }
 
-template <int BM, int BN, int WM, int WN, bool PERM>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_group_rope_kernel(const GemmGroupKArgs g) {
-  gemm_persistent<true, BM, BN, WM, WN, true, true, EPI_ROPE, PERM>(g, g.prob[0]);
+template <bool PERM>
+__global__ __launch_bounds__(512) void gemm_group_rope_kernel(const GemmGroupKArgs g) {
+  gemm_persistent<true, true, EPI_ROPE, PERM>(g, g.prob[0]);
 }
 
 // Tile rows per band of the tile sequence.  An XCD runs some 32 consecutive tiles at a time: 8 rows x 4
@@ -600,8 +764,7 @@ static int persistent_grid(int ntiles) {
   return ntiles < cus ? ntiles : cus;
 }
 
-constexpr int PM = 256, PN = 256, PWM = 2, PWN = 4;   // the persistent kernels' tile and waves
-constexpr size_t kPersistentLds = (size_t)NS * (PM + PN) * BK * 2 + (size_t)PWM * PWN * (PM / PWM / 4) * 128;
+constexpr size_t kPersistentLds = (size_t)NS * STAGE + (size_t)PWM * PWN * (PM / PWM / 4) * 128;
 
 static int64_t k_total(const GemmKArgs& k) {
   int64_t t = 0;
@@ -612,6 +775,9 @@ static GemmKArgs persistent_tiling(GemmKArgs k, bool both_kmajor, bool epilogue_
   k.tiles_m = (k.M + PM - 1) / PM;
   k.tiles_n = (k.N + PN - 1) / PN;
   k.band_rows = band_rows_for(both_kmajor, k_total(k), epilogue_reads_tiles);
+  k.band_tiles = k.band_rows * k.tiles_n;
+  k.band_recip = (uint32_t)((((uint64_t)1 << 32) + k.band_tiles - 1) / k.band_tiles);
+  k.ksteps = (int)(k_total(k) / BK);
   return k;
 }
 
@@ -620,7 +786,7 @@ static GemmKArgs persistent_tiling(GemmKArgs k, bool both_kmajor, bool epilogue_
     auto kern_ = KERN;                                                                                          \
     static std::atomic<unsigned long long> lds_done{0};                                                         \
     if (int rc_ = reserve_lds(kern_, kPersistentLds, lds_done, WHAT)) return rc_;                               \
-    hipLaunchKernelGGL(kern_, dim3((unsigned)persistent_grid(NTILES)), dim3(PWM * PWN * 64), kPersistentLds, st, ARGS); \
+    hipLaunchKernelGGL(kern_, dim3((unsigned)persistent_grid(NTILES)), dim3(512), kPersistentLds, st, ARGS); \
     return check_launch(WHAT);                                                                                  \
   } while (0)
 
@@ -636,21 +802,21 @@ static int launch_persistent_group(const GemmKArgs* ks, int n, bool ak, bool bk,
     g.rope_seq = rope->seq; g.rope_dh = rope->head_dim; g.rope_layout = rope->layout;
     for (int i = 0; i < n; ++i) g.prob[i].rope = ks[i].rope;
     if (rope->layout == 0 && rope->head_dim == 128)
-      GEMM_LAUNCH((gemm_group_rope_kernel<PM, PN, PWM, PWN, true>), g.tile_start[n], g, "gemm group (rotary epilogue)");
-    GEMM_LAUNCH((gemm_group_rope_kernel<PM, PN, PWM, PWN, false>), g.tile_start[n], g, "gemm group (rotary epilogue)");
+      GEMM_LAUNCH((gemm_group_rope_kernel<true>), g.tile_start[n], g, "gemm group (rotary epilogue)");
+    GEMM_LAUNCH((gemm_group_rope_kernel<false>), g.tile_start[n], g, "gemm group (rotary epilogue)");
   }
   // only the layout in use is instantiated: the weight-gradient products (both operands mn-major)
-  if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<PM, PN, PWM, PWN, false, false>), g.tile_start[n], g, "gemm group");
+  if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<false>), g.tile_start[n], g, "gemm group");
   return fail(-1, "gemm group: operand layout not built");
 }
 
 static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue epi, hipStream_t st) {
   const GemmKArgs a = persistent_tiling(k, ak && bk, epi == TileEpilogue::SWIGLU_GRAD);
   const int ntiles = a.tiles_m * a.tiles_n;
-  if (epi == TileEpilogue::SWIGLU) GEMM_LAUNCH((gemm_swiglu_kernel<PM, PN, PWM, PWN, EPI_SWIGLU>), ntiles, a, "gemm swiglu");
-  if (epi == TileEpilogue::SWIGLU_GRAD) GEMM_LAUNCH((gemm_swiglu_kernel<PM, PN, PWM, PWN, EPI_SWIGLU_GRAD>), ntiles, a, "gemm swiglu grad");
-  if (ak && bk) GEMM_LAUNCH((gemm_kernel<PM, PN, PWM, PWN, true, true>), ntiles, a, "gemm");
-  if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<PM, PN, PWM, PWN, false, false>), ntiles, a, "gemm");
+  if (epi == TileEpilogue::SWIGLU) GEMM_LAUNCH((gemm_swiglu_kernel<EPI_SWIGLU>), ntiles, a, "gemm swiglu");
+  if (epi == TileEpilogue::SWIGLU_GRAD) GEMM_LAUNCH((gemm_swiglu_kernel<EPI_SWIGLU_GRAD>), ntiles, a, "gemm swiglu grad");
+  if (ak && bk) GEMM_LAUNCH((gemm_kernel<true>), ntiles, a, "gemm");
+  if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<false>), ntiles, a, "gemm");
   return fail(-1, "gemm: operand layout not built");
 }
 #undef GEMM_LAUNCH

@@ -8,19 +8,9 @@
 
 namespace dl {
 
-// Measured on MI355X (M=16384, K=4096, N=14336, normal data): 2 stages of 64 k-values beat 3, 4 and 5
-// stages of 32 (the K-step is not latency-bound, a deeper ring only adds barriers); 16x16x32 MFMA
-// blocks beat 32x32x16 by 3 % on y = x W^T and 11 % on dx = dy W (half the accumulator traffic per
-// flop); 8 waves of 128x64 beat 4 waves of 128x128 under the compiler's schedule.
 constexpr int BK = 64;   // k-values per pipeline stage
-constexpr int NS = 2;    // ring stages
-constexpr int MI = 16;               // MFMA block edge: 32 (32x32x16) or 16 (16x16x32)
-constexpr int KSTEP = MI == 32 ? 16 : 32;  // k per MFMA
-constexpr int NACC = MI * MI / 64;       // accumulator registers per MFMA block
-typedef float acc_t __attribute__((ext_vector_type(NACC)));
-__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
+constexpr int MI = 16;               // MFMA block edge: 16x16x32 holds 2.2 PFLOP/s under the power limit, 32x32x16 1.95
+constexpr int KSTEP = 32;            // k per MFMA
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -39,6 +29,10 @@ struct GemmKArgs {
   int accumulate;
   int tiles_m, tiles_n;
   int band_rows;   // tile rows per band of the tile sequence (see band_rows_for)
+  // persistent kernels: tiles of a band, 2^32 / that rounded up, K-steps of all segments
+  int band_tiles;
+  uint32_t band_recip;
+  int ksteps;
   // gated-pair products only (see gemm_swiglu_kernel): second weight, second and third output
   const bf16_t* b2;
   bf16_t *c2, *c3;
@@ -114,24 +108,6 @@ struct TileLoader {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(lds_tile + j * 1024), 16, vo, soff, 0, 0);
     }
   }
-  // Tile of a k-major matrix whose rows are heads of 128 features, loaded so that a wave whose MFMA
-  // tile spans 64 tile rows holds 32 features of a head's first half and, 32 tile rows further, their
-  // rotary partners 64 features on: tile row r <- matrix row
-  // 128 * (r / 128) + 32 * ((r / 64) & 1) + r % 32 + 64 * ((r / 32) & 1).
-  static __device__ __forceinline__ int perm_row(int r) {
-    return ((r >> 7) << 7) + (((r >> 6) & 1) << 5) + (r & 31) + (((r >> 5) & 1) << 6);
-  }
-  template <int I0, int I1>
-  __device__ __forceinline__ void issue_perm_range(__amdgpu_buffer_rsrc_t rs, char* lds_tile, int wave, int64_t ld,
-                                                   int k0) const {
-    static_assert(KMAJOR && 32 % RPI == 0, "an instruction's rows must lie in one run of 32");
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-      const int j = wave * PER_WAVE + i;
-      const uint32_t soff = (uint32_t)(((int64_t)perm_row(j * RPI) * ld + k0) * 2);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_PTR(void))(lds_tile + j * 1024), 16, voff[i % NVAR], soff, 0, 0);
-    }
-  }
   // Tile of a PAIR of k-major matrices: of every 64 tile rows the first 32 are rows of the first
   // matrix and the next 32 the SAME rows of the second (tile row r <- matrix (r / 32) & 1, row
   // (r / 64) * 32 + r % 32), so that a wave whose MFMA tile spans 64 of these rows holds both values
@@ -151,37 +127,6 @@ struct TileLoader {
     }
   }
 };
-
-// MFMA operand fragment for MI rows starting at row0 (tile-local M/N index), k-substep kk (KSTEP k).
-template <int R, bool KMAJOR>
-__device__ __forceinline__ bf16x8 read_frag(const char* tile, int row0, int kk, int lane) {
-  if constexpr (KMAJOR) {
-    constexpr int CPRK = BK / 8, RPW = 16 / CPRK;
-    const int row = row0 + (lane & (MI - 1));
-    const int c = (kk * (KSTEP / 8) + lane / MI) ^ ((row / RPW) & (CPRK - 1));
-    return *reinterpret_cast<const bf16x8*>(tile + row * (BK * 2) + (c << 4));
-  } else {
-    constexpr int CPR = R / 8;
-    const int grp = lane >> 4, s = lane & 15, e = s >> 2, g = s & 3;
-    const int col = MI == 32 ? row0 + ((grp & 1) << 4) + (g << 2) : row0 + (g << 2);
-    const int krow = MI == 32 ? kk * 16 + ((grp >> 1) << 3) + e : kk * 32 + (grp << 3) + e;
-    const int f = (((krow & 3) << 2) | (((krow >> 3) & 1) << 1)) & (CPR - 1);  // same for krow and krow + 4
-    const char* p0 = tile + krow * (R * 2) + ((((col >> 3) ^ f) << 4) | ((col & 7) << 1));
-    // Issued as inline assembly: for the builtin the compiler cannot tell that the read does not
-    // touch the stage the asynchronous global -> LDS loads are filling and puts an s_waitcnt vmcnt(0)
-    // in front of it, which stalls the loading waves for the whole load latency every K-step.  The
-    // price: the compiler does not count these reads in lgkmcnt either, so every consumer must sit
-    // behind wait_frags().
-    bf16x8 v;
-    bf16x4 lo, hi;
-    const uint32_t a0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(p0);
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(a0));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(a0), "n"(4 * R * 2));
-    v.lo = lo;
-    v.hi = hi;
-    return v;
-  }
-}
 
 // Rotation of the pair (a, b) by the angle with cosine c and sine s.  The fused operations are written out: left to the
 // compiler, every kernel rounds another one of the two products, and a head has other bits on another tile.
@@ -210,19 +155,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 // same bits in whatever launch it is computed.
 __device__ __forceinline__ int k_start(int m0, int total) { return (((m0 >> 11) & 7) * total) >> 3; }
 
-// Waits for every LDS read of this wave and makes the fragments depend on that wait, so that no
-// consumer of a fragment fetched by the inline-assembly transposed read can be scheduled before it.
-__device__ __forceinline__ void wait_frags(bf16x8 (&fa)[8], bf16x8 (&fb)[4]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fa[4]), "+v"(fa[5]), "+v"(fa[6]), "+v"(fa[7]),
-                 "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]), "+v"(fb[3]));
-}
-
 // Position of the next tile pair to fetch: segment, k offset, and that segment's descriptors.
 // PAIR: the B tile interleaves two weight matrices (TileLoader::issue_pair_range); n0 and N then
 // count columns of the interleaved product, twice the rows of either matrix.
-// PERM: the B tile takes its rows in the rotary-partner order of TileLoader::issue_perm_range.
-template <int BM, int BN, int NW, bool AK, bool BKM, bool PAIR = false, bool PERM = false>
+template <int BM, int BN, int NW, bool AK, bool BKM, bool PAIR = false>
 struct LoadCursor {
   TileLoader<BM, AK, NW> la;
   TileLoader<BN, BKM, NW> lb;
@@ -265,8 +201,6 @@ struct LoadCursor {
       la.template issue_range<C * PA / NC, (C + 1) * PA / NC>(ra, stage, wave, lda, k);
       if constexpr (PAIR)
         lb.template issue_pair_range<C * PB / NC, (C + 1) * PB / NC>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
-      else if constexpr (PERM)
-        lb.template issue_perm_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
       else
         lb.template issue_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
       if constexpr (C + 1 == NC) advance(segs, m0, n0, lane);
@@ -278,8 +212,6 @@ struct LoadCursor {
       la.issue(ra, stage, wave, lda, k);
       if constexpr (PAIR)
         lb.template issue_pair_range<0, TileLoader<BN, BKM, NW>::PER_WAVE>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
-      else if constexpr (PERM)
-        lb.template issue_perm_range<0, TileLoader<BN, BKM, NW>::PER_WAVE>(rb, stage + BM * BK * 2, wave, ldb, k);
       else
         lb.issue(rb, stage + BM * BK * 2, wave, ldb, k);
       advance(segs, m0, n0, lane);

@@ -19,7 +19,8 @@
 namespace dl {
 
 // Operand fragments of one wave from an LDS tile: F blocks of 16 rows (the M/N index) from row0 on, k-substep kk.
-// The reads are inline assembly, see read_frag; consumers sit behind wait_reads().
+// The reads are assembly (for the builtins the compiler waits for the loads in flight, which it cannot tell from what is read)
+// and not counted by the compiler: consumers sit behind wait_reads().
 template <int R, bool KMAJOR, int F>
 struct FragReader {
   uint32_t at[KMAJOR ? 2 : F];

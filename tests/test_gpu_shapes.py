@@ -294,6 +294,21 @@ def test_input_gradient_with_and_without_the_transposed_weights(K, rows, Kd, N, 
         assert torch.equal(dx.view(torch.int16), first[:T].view(torch.int16)), T
 
 
+def test_layer_with_short_segments_on_full_tiles(K):
+    """The fused input gradients on 256 x 256 tiles with segments of one and of three K-steps: walks that start in any segment
+    (a row group of 2048 starts its eighth of the way further on), odd and even, over more than one round of tiles."""
+    cfg = si.CONFIGS["tiny"].with_(batch=8, seq=2048, d_model=2112, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ff=192)
+    for steps in (3 * 64, 2 * 192):
+        assert K.gemm_route(0, 0, [16384], [2112], [steps], compute_units=256)[0] == PERSISTENT
+    inp = si.make_layer_inputs(cfg, seed=3)
+    f, r = _oracle(cfg, inp)
+    g = GpuLayer(K, cfg, inp)
+    g.forward()
+    g.backward()
+    torch.cuda.synchronize()
+    _check_layer(g, f, r, "short segments")
+
+
 # batch, seq, width, query heads, KV heads, head width, layout (0 split pairs, 1 adjacent)
 ROTARY = [
     ((1, 128, 64, 2, 1, 64, 0), (T64, -1)),           # a head per tile
