@@ -65,42 +65,6 @@ enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_GRAD = 2, EPI_ROPE = 3 };
 constexpr int PM = 256, PN = 256, PWM = 2, PWN = 4;   // tile and waves
 constexpr int STAGE = (PM + PN) * BK * 2, HALF = STAGE / 4, NS = 2;
 
-// acc[i][j] += A[i] B[j] over two k-substeps, for 2 x 4 blocks: cIJ is block (i, j), aKI and bKJ the operands of substep K.
-// As assembly, in place: left to itself the compiler lets accumulators wander from one set of registers to another and
-// runs out of them.  The B operand stays for two MFMAs and the blocks are taken four at a time: the fewer operand bits
-// change from one MFMA to the next, the less power it draws (16384 x 4096 x 14336: A held for four MFMAs while B changes
-// 1288 us, this order 1268; B held for four gains no more).  The s_nop covers a VALU write of an operand right in front; the
-// accumulators may not be read otherwise before mfma_drain().
-__device__ __forceinline__ void mfma_quadrant(f32x4& c00, f32x4& c10, f32x4& c01, f32x4& c11, f32x4& c02, f32x4& c12, f32x4& c03, f32x4& c13,
-                                              bf16x8 a00, bf16x8 a01, bf16x8 a10, bf16x8 a11, bf16x8 b00, bf16x8 b01, bf16x8 b02, bf16x8 b03,
-                                              bf16x8 b10, bf16x8 b11, bf16x8 b12, bf16x8 b13) {
-#define MFMA(C, A, B) "v_mfma_f32_16x16x32_bf16 %" #C ", %" #A ", %" #B ", %" #C "\n\t"
-  asm volatile("s_nop 1\n\t"
-               MFMA(0, 8, 12) MFMA(1, 9, 12) MFMA(2, 8, 13) MFMA(3, 9, 13) MFMA(0, 10, 16) MFMA(1, 11, 16) MFMA(2, 10, 17) MFMA(3, 11, 17)
-               MFMA(4, 8, 14) MFMA(5, 9, 14) MFMA(6, 8, 15) MFMA(7, 9, 15) MFMA(4, 10, 18) MFMA(5, 11, 18) MFMA(6, 10, 19) MFMA(7, 11, 19)
-               : "+v"(c00), "+v"(c10), "+v"(c01), "+v"(c11), "+v"(c02), "+v"(c12), "+v"(c03), "+v"(c13)
-               : "v"(a00), "v"(a01), "v"(a10), "v"(a11), "v"(b00), "v"(b01), "v"(b02), "v"(b03), "v"(b10), "v"(b11), "v"(b12), "v"(b13));
-#undef MFMA
-}
-// waits until the last MFMA has written its block
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 3" ::: "memory"); }
-
-// 16 bytes per lane from LDS address `at` + OFF, or the transposed 2 x 8 of k-rows r and r + 4 of a 256-byte row tile.  As
-// assembly: for the builtins the compiler cannot tell that a read stays clear of the stage the asynchronous loads are filling
-// and waits for those in front of it.  It does not count these reads either, so every fragment passes through arrived().
-template <int OFF>
-__device__ __forceinline__ void lds_read(bf16x8& v, uint32_t at) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(at), "n"(OFF));
-}
-template <int OFF>
-__device__ __forceinline__ void lds_read_tr(bf16x8& v, uint32_t at) {
-  bf16x4 lo, hi;
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(at), "n"(OFF));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(at), "n"(OFF + 1024));
-  v.lo = lo;
-  v.hi = hi;
-}
-
 // The lane number, anew.  What the compiler computes from one that it knows is lifted out of the tile loop and spilled across the
 // main loop, and its reload (counted in order behind the next tile's loads) then waits for all of those.
 __device__ __forceinline__ int lane_anew() {
@@ -349,7 +313,8 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
   constexpr std::integral_constant<int, 2> C2{};
   constexpr std::integral_constant<int, 3> C3{};
   constexpr std::integral_constant<int, EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_GRAD ? 32 : 16> STORES{};   // of a wave, of a whole tile
-  landed(tl.total, C0);
+  wait_vmcnt<10>();   // first tile: A half 0 and the B halves of K-step 0
+  int waits_from = 0;   // K-step from which on the first three phases of a K-step wait for loads
 
   // Lane's place in a fragment.  k-major: rows of 128 bytes, the second 32 k at this ^ 64.  mn-major: rows of 256 bytes (one k),
   // block f of 16 at this ^ 32 f.
@@ -400,7 +365,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
           constexpr int f = decltype(f_c)::value;
           bf16x8& v = A ? a[kk][(h * F / 2 + f) % FM] : b[kk][(h * F / 2 + f) % FN];
           if constexpr (KM) lds_read<(h * F / 2 + f) * MI * BK * 2>(v, kk ? at ^ 64 : at);
-          else lds_read_tr<h * HALF + kk * 8192>(v, at ^ (f * 32));
+          else lds_read_tr<h * HALF + kk * 8192, 1024>(v, at ^ (f * 32));
         });
       });
     };
@@ -442,9 +407,9 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
         if constexpr (ph == 1) cur.template issue<false, q>(smem + cs + pb);
         if constexpr (ph == 2) cur.template issue<false, 1 - q>(smem + cs + pb);
         if constexpr (ph == 3) cur.template issue<true, 1>(smem + cs + pa);
-        // The half that the next phase reads went out six phases ago, five halves are younger.  (What the first three
-        // phases read has landed; waiting there would be for the last tile's stores.)
-        if (ph == 3 || t > 0) wait_vmcnt<10>();
+        // The half that the next phase reads went out six phases ago, five halves are younger.  (In a workgroup's later
+        // tiles what the first three phases read has landed; waiting there would be for the last tile's stores.)
+        if (ph == 3 || t >= waits_from) wait_vmcnt<10>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         constexpr int i = (ph == 0 || ph == 3 ? q : 1 - q) * FN / 2, j = ph < 2 ? 0 : FM / 2;
@@ -711,6 +676,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
       }
     }
     if (!more) break;
+    waits_from = 1;
     tl = next;
     id += step;
     more = id + step < ntiles;

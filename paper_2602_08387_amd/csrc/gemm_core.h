@@ -155,6 +155,42 @@ __device__ __forceinline__ void wait_vmcnt() {
 // same bits in whatever launch it is computed.
 __device__ __forceinline__ int k_start(int m0, int total) { return (((m0 >> 11) & 7) * total) >> 3; }
 
+// acc[i][j] += A[i] B[j] over two k-substeps, for 2 x 4 blocks: cIJ is block (i, j), aKI and bKJ the operands of substep K.
+// As assembly, in place: left to itself the compiler lets accumulators wander from one set of registers to another and
+// runs out of them.  The B operand stays for two MFMAs and the blocks are taken four at a time: the fewer operand bits
+// change from one MFMA to the next, the less power it draws (16384 x 4096 x 14336: A held for four MFMAs while B changes
+// 1288 us, this order 1268; B held for four gains no more).  The s_nop covers a VALU write of an operand right in front; the
+// accumulators may not be read otherwise before mfma_drain().
+__device__ __forceinline__ void mfma_quadrant(f32x4& c00, f32x4& c10, f32x4& c01, f32x4& c11, f32x4& c02, f32x4& c12, f32x4& c03, f32x4& c13,
+                                              bf16x8 a00, bf16x8 a01, bf16x8 a10, bf16x8 a11, bf16x8 b00, bf16x8 b01, bf16x8 b02, bf16x8 b03,
+                                              bf16x8 b10, bf16x8 b11, bf16x8 b12, bf16x8 b13) {
+#define MFMA(C, A, B) "v_mfma_f32_16x16x32_bf16 %" #C ", %" #A ", %" #B ", %" #C "\n\t"
+  asm volatile("s_nop 1\n\t"
+               MFMA(0, 8, 12) MFMA(1, 9, 12) MFMA(2, 8, 13) MFMA(3, 9, 13) MFMA(0, 10, 16) MFMA(1, 11, 16) MFMA(2, 10, 17) MFMA(3, 11, 17)
+               MFMA(4, 8, 14) MFMA(5, 9, 14) MFMA(6, 8, 15) MFMA(7, 9, 15) MFMA(4, 10, 18) MFMA(5, 11, 18) MFMA(6, 10, 19) MFMA(7, 11, 19)
+               : "+v"(c00), "+v"(c10), "+v"(c01), "+v"(c11), "+v"(c02), "+v"(c12), "+v"(c03), "+v"(c13)
+               : "v"(a00), "v"(a01), "v"(a10), "v"(a11), "v"(b00), "v"(b01), "v"(b02), "v"(b03), "v"(b10), "v"(b11), "v"(b12), "v"(b13));
+#undef MFMA
+}
+// waits until the last MFMA has written its block
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 3" ::: "memory"); }
+
+// 16 bytes per lane from LDS address `at` + OFF, or transposed 2 x 8 of k-rows r and r + 4, HI bytes apart.  As
+// assembly: for the builtins the compiler cannot tell that a read stays clear of the stage the asynchronous loads are filling
+// and waits for those in front of it.  It does not count these reads either, so every fragment passes through a wait that names it.
+template <int OFF>
+__device__ __forceinline__ void lds_read(bf16x8& v, uint32_t at) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(at), "n"(OFF));
+}
+template <int OFF, int HI>
+__device__ __forceinline__ void lds_read_tr(bf16x8& v, uint32_t at) {
+  bf16x4 lo, hi;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(at), "n"(OFF));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(at), "n"(OFF + HI));
+  v.lo = lo;
+  v.hi = hi;
+}
+
 // Position of the next tile pair to fetch: segment, k offset, and that segment's descriptors.
 // PAIR: the B tile interleaves two weight matrices (TileLoader::issue_pair_range); n0 and N then
 // count columns of the interleaved product, twice the rows of either matrix.
