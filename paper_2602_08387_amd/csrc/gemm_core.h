@@ -228,20 +228,6 @@ struct LoadCursor {
   __device__ __forceinline__ void open(const GemmKArgs& p, int s, int m0, int n0, int lane) {
     open_raw(p.a[s], p.b[s], p.lda[s], p.ldb[s], p.K[s], p.M, p.N, m0, n0, lane);
   }
-  // The same in NC pieces (piece C of the A loads and of the B loads), so that a wave can spread its
-  // loads between MFMAs; the cursor moves on with the last piece.
-  template <int C, int NC>
-  __device__ __forceinline__ void issue_piece(const GemmKArgs& segs, char* stage, int wave, int m0, int n0, int lane) {
-    constexpr int PA = TileLoader<BM, AK, NW>::PER_WAVE, PB = TileLoader<BN, BKM, NW>::PER_WAVE;
-    if (left > 0) {
-      la.template issue_range<C * PA / NC, (C + 1) * PA / NC>(ra, stage, wave, lda, k);
-      if constexpr (PAIR)
-        lb.template issue_pair_range<C * PB / NC, (C + 1) * PB / NC>(rb, rb2, stage + BM * BK * 2, wave, ldb, k);
-      else
-        lb.template issue_range<C * PB / NC, (C + 1) * PB / NC>(rb, stage + BM * BK * 2, wave, ldb, k);
-      if constexpr (C + 1 == NC) advance(segs, m0, n0, lane);
-    }
-  }
   // `segs`: the problem whose further K-segments follow (only read when nseg > 1)
   __device__ __forceinline__ void issue_next(const GemmKArgs& segs, char* stage, int wave, int m0, int n0, int lane) {
     if (left > 0) {

@@ -3,15 +3,17 @@
 // product has the same bits on either.
 //
 // What bounds it: the smaller the tile, the more bytes per flop have to reach a CU, and some 100 GB/s per CU is what the
-// global -> LDS loads bring (64 x 64 tiles, two per CU, 97 GB/s; 128 x 128 86; 128 x 256 75, next to its fragment reads: without
-// either of the two it runs at the MFMAs' rate).  With four waves, a two-stage ring and its loads and fragment reads in bunches
-// around the barrier a 128 x 128 tile paid 0.77 us per K-step of 64 (T = 1920, K = 6272, N = 1152: 68 us), of which its MFMAs are
-// 0.21 us and its loads, 16 cycles each at the address unit, 0.22.  Measured on the way: a four-stage ring alone changes nothing;
-// eight waves of 64 x 32 0.48; reads and loads between the rows of MFMAs, half a K-step ahead, 0.40 (44 us); tiles through
-// registers and ds_write instead of straight to LDS 0.55; the two-group loop of the 128 x 256 tile 0.41.  A 64 x 64 tile takes
-// 0.25 us, four times the tiles to fill the chip with (T = 1000, K = 2048, N = 1024: 25 -> 9 us).  The 128 x 256 tile (T = 8192,
-// N = 768, K = 2048 / 4096) as the smaller two 31.6 / 53.5 us, with its waves in two groups 29.5 / 49.7.  Full rounds of 256 x 256
-// tiles stay on the persistent kernel: a quarter fewer loads per flop, and its epilogue under the next tile's main loop.
+// global -> LDS loads bring (128 x 128: 92, 64 x 64: 100, one tile per CU; T = 8192, N = 768 on 128 x 256 tiles 75, next to its
+// fragment reads: without either of the two it runs at the MFMAs' rate).  And a wave that loads stands still: the address unit
+// takes 16 cycles per wave-wide load, of all waves in turn.  So four waves of a workgroup do nothing but load, and the others
+// never wait for the address unit.  Microseconds per K-step of 64 (K from 2048 to 4096 or 3136 to 6272), all waves loading
+// and now: 64 x 64 (T = 1000, N = 1024: 256 tiles) 0.25, 0.16; 128 x 128 (T = 1920, N = 1152: 135 tiles) 0.39, 0.35; 128 x 256 (192
+// tiles) 0.66, 0.61.  Whole products: T 1000, K 2048, N 1024 10.9 -> 9.0 us; T 1920, K 6272, N 1152 42.7 -> 38.8; T 8192, K 4096, N 768
+// 54 -> 49.5; weight gradient 1024 x 1024 of 2048 tokens 12.4 -> 9.8.  Measured on the way: deeper rings (five stages, eight)
+// change nothing; fragments requested a whole K-step ahead: 128 x 128 10 % slower; tiles through registers and ds_write instead of
+// straight to LDS 20 to 50 % slower; two wave groups a slot apart, as in the persistent kernel, on the 128 x 256 tile as fast as this.
+// Full rounds of 256 x 256 tiles stay on the persistent kernel: a quarter fewer loads per flop, its epilogue under the next
+// tile's main loop, and accumulators that leave no registers for a third wave per SIMD.
 //
 // The epilogue passes the fp32 sums through LDS (the ring is free by then), so every fused epilogue is an
 // element-wise function of rows: residual or accumulation, rotary embedding (both members of a pair lie in the
@@ -121,8 +123,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
   // different banks), then 8 consecutive columns per thread along rows.
   constexpr int SP = BN + 4;
   constexpr int OC = PAIR ? BN / 2 : BN;               // output columns of the tile
-  constexpr int VPR = OC / 8, NV = BM * VPR / NT;      // 8-column vectors per row and per thread
-  static_assert(BM * VPR % NT == 0, "vectors deal evenly");
+  constexpr int VPR = OC / 8, NV = (BM * VPR + NT - 1) / NT;   // 8-column vectors per row and per thread
   float* stg = reinterpret_cast<float*>(smem);
   const int M = t.M, N = t.N, m0 = t.m0, n0 = t.n0, accumulate = t.accumulate;
   const int64_t ldc = t.ldc;
@@ -138,7 +139,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
         const int id = v * NT + (int)threadIdx.x, m = m0 + id / VPR, n = on0 + id % VPR * 8;
         const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
         pre[v] = zero;
-        if (m < M && n < ON) pre[v] = *reinterpret_cast<const bf16x8*>(src + (int64_t)m * ldc + n);
+        if ((BM * VPR % NT == 0 || id < BM * VPR) && m < M && n < ON) pre[v] = *reinterpret_cast<const bf16x8*>(src + (int64_t)m * ldc + n);
       }
     }
   }
@@ -156,7 +157,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
   for (int v = 0; v < NV; ++v) {
     const int id = v * NT + (int)threadIdx.x, row = id / VPR, col = id % VPR * 8;
     const int m = m0 + row, n = on0 + col;
-    if (m >= M || n >= ON) continue;
+    if ((BM * VPR % NT != 0 && id >= BM * VPR) || m >= M || n >= ON) continue;
     if constexpr (EPI == TILE_SWIGLU) {
       // of every 64 tile columns the first 32 are g, the next 32 u (LoadCursor PAIR)
       float g[8], u[8], a[8];
@@ -217,10 +218,13 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
   }
 }
 
+constexpr int LOADERS = 4;   // waves that load; two are slower (T 512, K = N = 2048 input gradient 9.1 -> 10.2 us)
+constexpr int tile_threads(int bm) { return ((bm == 64 ? 4 : 8) + LOADERS) * 64; }
+
 // NST: ring stages.  EPI as the persistent kernel's epilogues.
-template <bool GROUPED, int BM, int BN, int WM, int WN, bool AK, bool BKM, int NST, int EPI>
+template <bool GROUPED, int BM, int BN, bool AK, bool BKM, int NST, int EPI>
 __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmKArgs& one) {
-  constexpr int NW = WM * WN, NT = NW * 64;
+  constexpr int WM = 2, WN = BM == 64 ? 2 : 4, NW = WM * WN, NL = LOADERS, NT = tile_threads(BM);   // waves that multiply, waves that load
   constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
   constexpr int A_BYTES = BM * BK * 2, STAGE = A_BYTES + BN * BK * 2;
   constexpr bool PAIR = EPI == TILE_SWIGLU;
@@ -232,9 +236,11 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
 
   const TileOf t = find_tile<GROUPED, BM, BN>(grp, one);
   const int M = t.M, N = t.N, m0 = t.m0, n0 = t.n0, total = t.total;
-  LoadCursor<BM, BN, NW, AK, BKM, PAIR> cur;
-  constexpr int LPW = TileLoader<BM, AK, NW>::PER_WAVE + TileLoader<BN, BKM, NW>::PER_WAVE;
-  {
+  constexpr int LPW = TileLoader<BM, AK, NL>::PER_WAVE + TileLoader<BN, BKM, NL>::PER_WAVE;
+  f32x4 acc[FN][FM];
+  if (wave >= NW) {
+    LoadCursor<BM, BN, NL, AK, BKM, PAIR> cur;
+    const int lwave = wave - NW;
     cur.nseg = GROUPED ? 1 : one.nseg;
     cur.left = total;
     int first = k_start(m0 + t.m_base, total);
@@ -250,89 +256,87 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
     } else {
       cur.open(one, cur.seg, m0, n0, lane);
     }
-  }
-
-  FragReader<BM, AK, FM> ra;
-  FragReader<BN, BKM, FN> rb;
-  ra.init(smem, wave_m * TM, lane);
-  rb.init(smem + A_BYTES, wave_n * TN, lane);
-  f32x4 acc[FN][FM];
 #pragma unroll
-  for (int i = 0; i < FN; ++i)
-#pragma unroll
-    for (int j = 0; j < FM; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-
-#pragma unroll
-  for (int s = 0; s < NST; ++s) cur.issue_next(one, smem + s * STAGE, wave, m0, n0, lane);
-  if (total >= NST) wait_vmcnt<(NST - 1) * LPW>(); else wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  // Fragments run half a K-step ahead of the MFMAs.  The MFMAs of a k-substep go out in rows (one fragment of the side
-  // with more of them against all of the other side); the reads of the next substep go between its first rows and
-  // half of a K-step's loads behind one of them.  In a bunch in front of the MFMAs the reads of all waves, and still
-  // more the loads (16 cycles each at the address unit), queue with every wave's MFMAs behind them.
-  constexpr int NF = FM + FN, ROWS = FM > FN ? FM : FN;
-  bf16x8 fa[2][FM], fb[2][FN];
-  auto read_one = [&](auto KS, auto F, uint32_t stage) {
-    constexpr int ks = decltype(KS)::value, f = decltype(F)::value;
-    if constexpr (f < FM) ra.template read<ks, f>(fa[ks], stage);
-    else rb.template read<ks, f - FM>(fb[ks], stage);
-  };
-  auto mfma_row = [&](auto KS, auto RW) {
-    constexpr int ks = decltype(KS)::value, r = decltype(RW)::value;
-    if constexpr (FM > FN) {
-#pragma unroll
-      for (int i = 0; i < FN; ++i) acc[i][r] = mfma(fb[ks][i], fa[ks][r], acc[i][r]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < FM; ++j) acc[r][j] = mfma(fb[ks][r], fa[ks][j], acc[r][j]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  constexpr std::integral_constant<int, 0> S0{};
-  constexpr std::integral_constant<int, 1> S1{};
-  static_for<0, NF>([&](auto f) { read_one(S0, f, 0u); });
-  wait_reads(fa[0], fb[0]);
-  uint32_t st = 0, prev = 0;             // byte offsets of the stages of K-steps k and k - 1
-  for (int k = 0; k < total; ++k) {
-    constexpr int RD0 = ROWS >= 4 ? 2 : 1;              // rows the reads are spread over
-    static_for<0, ROWS>([&](auto r) {
-      constexpr int i = decltype(r)::value;
-      if constexpr (i < RD0) static_for<i * NF / RD0, (i + 1) * NF / RD0>([&](auto f) { read_one(S1, f, st); });
-      mfma_row(S0, r);
-      if constexpr (i == ROWS / 2 - 1) {
-        if (k > 0) cur.template issue_piece<1, 2>(one, smem + prev, wave, m0, n0, lane);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    });
-    wait_reads(fa[1], fb[1]);
-    const uint32_t nx = st + STAGE == NST * STAGE ? 0 : st + STAGE;
-    mfma_row(S1, S0);
-    if (k + 1 < total) {
+    for (int s = 0; s < NST; ++s) cur.issue_next(one, smem + s * STAGE, lwave, m0, n0, lane);
+    if (total >= NST) wait_vmcnt<(NST - 1) * LPW>(); else wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    uint32_t st = 0;
+    for (int k = 0; k + 1 < total; ++k) {
       // K-step k + 1 has landed once at most the NST - 2 younger ones are in flight; past the barrier every wave has its
       // last fragments of K-step k in registers, and its stage takes K-step k + NST
       if (k + NST <= total) wait_vmcnt<(NST - 2) * LPW>(); else wait_vmcnt<0>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
+      cur.issue_next(one, smem + st, lwave, m0, n0, lane);
+      st = st + STAGE == NST * STAGE ? 0 : st + STAGE;
     }
-    // the reads go out after the last K-step too (of a stage nobody fills any more; nobody uses them)
-    constexpr int RD1 = ROWS >= 4 ? 2 : 1;
-    static_for<1, ROWS>([&](auto r) {
-      constexpr int i = decltype(r)::value;
-      if constexpr (i <= RD1) static_for<(i - 1) * NF / RD1, i * NF / RD1>([&](auto f) { read_one(S0, f, nx); });
-      mfma_row(S1, r);
-      if constexpr (i == (ROWS > 2 ? ROWS - 2 : 1)) {
-        if (k + 1 < total) cur.template issue_piece<0, 2>(one, smem + st, wave, m0, n0, lane);
-        __builtin_amdgcn_sched_barrier(0);
+  } else {
+    FragReader<BM, AK, FM> ra;
+    FragReader<BN, BKM, FN> rb;
+    ra.init(smem, wave_m * TM, lane);
+    rb.init(smem + A_BYTES, wave_n * TN, lane);
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+      for (int j = 0; j < FM; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // Fragments run half a K-step ahead of the MFMAs.  The MFMAs of a k-substep go out in rows (one fragment of the side
+    // with more of them against all of the other side); the reads of the next substep go between its first rows: in a bunch in
+    // front of the MFMAs the reads of all waves queue with every wave's MFMAs behind them.
+    constexpr int NF = FM + FN, ROWS = FM > FN ? FM : FN;
+    bf16x8 fa[2][FM], fb[2][FN];
+    auto read_one = [&](auto KS, auto F, uint32_t stage) {
+      constexpr int ks = decltype(KS)::value, f = decltype(F)::value;
+      if constexpr (f < FM) ra.template read<ks, f>(fa[ks], stage);
+      else rb.template read<ks, f - FM>(fb[ks], stage);
+    };
+    auto mfma_row = [&](auto KS, auto RW) {
+      constexpr int ks = decltype(KS)::value, r = decltype(RW)::value;
+      if constexpr (FM >= FN) {   // the B operand stays (see mfma_quadrant)
+#pragma unroll
+        for (int i = 0; i < FN; ++i) acc[i][r] = mfma(fb[ks][i], fa[ks][r], acc[i][r]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < FM; ++j) acc[r][j] = mfma(fb[ks][r], fa[ks][j], acc[r][j]);
       }
-    });
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr std::integral_constant<int, 0> S0{};
+    constexpr std::integral_constant<int, 1> S1{};
+    static_for<0, NF>([&](auto f) { read_one(S0, f, 0u); });
     wait_reads(fa[0], fb[0]);
-    prev = st;
-    st = nx;
+    uint32_t st = 0;                       // byte offset of the stage
+    for (int k = 0; k < total; ++k) {
+      constexpr int RD0 = ROWS >= 4 ? 2 : 1;              // rows the reads are spread over
+      static_for<0, ROWS>([&](auto r) {
+        constexpr int i = decltype(r)::value;
+        if constexpr (i < RD0) static_for<i * NF / RD0, (i + 1) * NF / RD0>([&](auto f) { read_one(S1, f, st); });
+        mfma_row(S0, r);
+      });
+      wait_reads(fa[1], fb[1]);
+      const uint32_t nx = st + STAGE == NST * STAGE ? 0 : st + STAGE;
+      mfma_row(S1, S0);
+      if (k + 1 < total) {   // K-step k + 1 has landed, see above
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      // the reads go out after the last K-step too (of a stage nobody fills any more; nobody uses them)
+      constexpr int RD1 = ROWS >= 4 ? 2 : 1;
+      static_for<1, ROWS>([&](auto r) {
+        constexpr int i = decltype(r)::value;
+        if constexpr (i <= RD1) static_for<(i - 1) * NF / RD1, i * NF / RD1>([&](auto f) { read_one(S0, f, nx); });
+        mfma_row(S1, r);
+      });
+      wait_reads(fa[0], fb[0]);
+      st = nx;
+    }
   }
   tile_epilogue<BM, BN, NT, EPI>(grp, one, t, smem, [&](float* stg) {
+    if (wave >= NW) return;
 #pragma unroll
     for (int i = 0; i < FN; ++i)
 #pragma unroll
@@ -341,267 +345,13 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
   });
 }
 
-// Load cursor of the 128 x 256 tile (eight waves).  A K-step lies in LDS as two A parts of 64 rows (8 KiB, a load per wave) and two B
-// parts of 128 columns (16 KiB, two loads per wave).  A wave owns 32 rows of either A part and 32 columns of either B part.  Parts of k-major operands are [rows][64 k], of mn-major ones [64 k][64 or 128], swizzled as in gemm.hip
-// (64 wide: 128-byte rows, two share a bank window, rows k, k + 2 are told apart by bit 2).
-template <bool AK, bool BKM, bool PAIR>
-struct PartStream {
-  __amdgpu_buffer_rsrc_t ra, rb, rb2;
-  uint32_t va, vb, sa, sb, sa0, sb0, lda2, ldb2;
-  int k, kend, seg, nseg, left;
-
-  __device__ __forceinline__ void open(const bf16_t* a, const bf16_t* b, const bf16_t* b2, int64_t lda, int64_t ldb, int K, int M, int N, int m0,
-                                       int n0, int wave, int lane) {
-    kend = K;
-    lda2 = (uint32_t)(lda * 2);
-    ldb2 = (uint32_t)(ldb * 2);
-    if constexpr (PAIR) { N /= 2; n0 /= 2; }
-    const uint32_t b_bytes = BKM ? (uint32_t)(N - n0 - 1) * ldb2 + K * 2 : (uint32_t)(K - 1) * ldb2 + (N - n0) * 2;
-    ra = make_rsrc(AK ? a + (int64_t)m0 * lda : a + m0, AK ? (uint32_t)(M - m0 - 1) * lda2 + K * 2 : (uint32_t)(K - 1) * lda2 + (M - m0) * 2);
-    rb = make_rsrc(BKM ? b + (int64_t)n0 * ldb : b + n0, b_bytes);
-    if constexpr (PAIR) rb2 = make_rsrc(b2 + (int64_t)n0 * ldb, b_bytes);
-    const int kmaj = ((lane & 7) ^ (((wave & 1) * 4 + (lane >> 4)) & 7)) << 4;   // eight rows of 64 k
-    va = AK ? (lane >> 3) * lda2 + kmaj : (lane >> 3) * lda2 + (((lane & 7) ^ ((((lane >> 4) & 1) << 2) | ((wave & 1) << 1))) << 4);
-    vb = BKM ? (lane >> 3) * ldb2 + kmaj : (lane >> 4) * ldb2 + (((lane & 15) ^ (((lane >> 4) << 2) | (((wave >> 1) & 1) << 1))) << 4);
-    sa0 = wave * 8 * lda2;
-    // PAIR: tile row r is row 32 (r / 64) + r % 32 of matrix (r / 32) & 1
-    sb0 = (BKM ? (PAIR ? (wave & 3) * 8 : wave * 8) : wave * 4) * ldb2;
-    sa = sa0 + (AK ? k * 2 : k * lda2);
-    sb = sb0 + (BKM ? k * 2 : k * ldb2);
-  }
-  __device__ __forceinline__ void open(const GemmKArgs& p, int s, int m0, int n0, int wave, int lane) {
-    open(p.a[s], p.b[s], nullptr, p.lda[s], p.ldb[s], p.K[s], p.M, p.N, m0, n0, wave, lane);
-  }
-  template <int H>
-  __device__ __forceinline__ void issue_a(char* dst) const {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LDS_PTR(void))(dst + H * 8192), 16, va, AK ? sa + H * 64 * lda2 : sa + H * 128, 0, 0);
-  }
-  template <int H>
-  __device__ __forceinline__ void issue_b(char* dst, int wave) const {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint32_t so = !BKM ? sb + H * 256 + i * 32 * ldb2 : PAIR ? sb + (H * 64 + i * 32) * ldb2 : sb + (H * 128 + i * 64) * ldb2;
-      if (PAIR && wave >= 4)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb2, (LDS_PTR(void))(dst + H * 16384 + i * 8192), 16, vb, so, 0, 0);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (LDS_PTR(void))(dst + H * 16384 + i * 8192), 16, vb, so, 0, 0);
-    }
-  }
-  // one K-step on, as LoadCursor::advance
-  template <bool SEGS>
-  __device__ __forceinline__ void advance(const GemmKArgs& p, int m0, int n0, int wave, int lane) {
-    --left;
-    k += BK;
-    sa += AK ? BK * 2 : BK * lda2;
-    sb += BKM ? BK * 2 : BK * ldb2;
-    if (k == kend) {
-      k = 0;
-      sa = sa0;
-      sb = sb0;
-      if (SEGS && nseg > 1 && left > 0) {
-        seg = seg + 1 == nseg ? 0 : seg + 1;
-        open(p, seg, m0, n0, wave, lane);
-      }
-    }
-  }
-};
-
-// 128 x 256 tile, eight waves in two groups a slot apart, as in the persistent kernel: a phase is a slot of fragment reads (for the
-// next phase) and loads and a slot of sixteen MFMAs, a K-step is two phases, the ring has three stages.
-template <bool GROUPED, bool AK, bool BKM, int EPI>
-__device__ __forceinline__ void gemm_pingpong(const GemmGroupKArgs& grp, const GemmKArgs& one) {
-  constexpr int BM = 128, BN = 256, NST = 3, FM = 4, FN = 4, A_BYTES = BM * BK * 2, STAGE = A_BYTES + BN * BK * 2;
-  constexpr bool PAIR = EPI == TILE_SWIGLU, SEGS = !GROUPED && EPI == TILE_PLAIN;
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wave_m = wave & 1, wave_n = wave >> 1;
-  const TileOf t = find_tile<GROUPED, BM, BN>(grp, one);
-  PartStream<AK, BKM, PAIR> cur;
-  cur.nseg = SEGS ? one.nseg : 1;
-  cur.left = t.total;
-  {
-    int first = k_start(t.m0 + t.m_base, t.total);
-    cur.seg = 0;
-    if constexpr (SEGS) {
-      for (int s = 0; s + 1 < one.nseg; ++s)
-        if (cur.seg == s && first >= one.K[s] / BK) { first -= one.K[s] / BK; cur.seg = s + 1; }
-    }
-    cur.k = first * BK;
-    if (!SEGS || cur.seg == 0) cur.open(t.a0, t.b0, PAIR ? one.b2 : nullptr, t.lda0, t.ldb0, t.K0, t.M, t.N, t.m0, t.n0, wave, lane);
-    else cur.open(one, cur.seg, t.m0, t.n0, wave, lane);
-  }
-  auto step = [&] { cur.template advance<SEGS>(one, t.m0, t.n0, wave, lane); };
-  char* const pa = smem + wave * 1024;
-  char* const pb = pa + A_BYTES;
-
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(smem);
-  uint32_t lane_a, lane_b;   // lane's place in a part's fragments: the second 32 k (k-major), block 1 (mn-major) by exclusive or
-  {
-    const int g4 = lane >> 4, e = (lane >> 2) & 3, g = lane & 3;
-    const uint32_t km = (lane & 15) * 128 + ((g4 ^ ((lane >> 1) & 7)) << 4);
-    if constexpr (AK) lane_a = lds0 + km + wave_m * 4096;
-    else lane_a = lds0 + (((g4 * 8 + e) * 128 + (((g >> 1) ^ (((e >> 1) & 1) << 2) ^ ((g4 & 1) << 1)) << 4) + (g & 1) * 8) ^ (wave_m * 64));
-    if constexpr (BKM) lane_b = lds0 + A_BYTES + km + wave_n * 4096;
-    else lane_b = lds0 + A_BYTES + (((g4 * 8 + e) * 256 + (((g >> 1) ^ (e << 2) ^ ((g4 & 1) << 1)) << 4) + (g & 1) * 8) ^ (wave_n * 64));
-  }
-  f32x4 acc[FN][FM];
-#pragma unroll
-  for (int i = 0; i < FN; ++i)
-#pragma unroll
-    for (int j = 0; j < FM; ++j) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-      asm volatile("" : "+v"(acc[i][j]));   // zeroed here, not in front of the first MFMA (see mfma_quadrant)
-    }
-  // A fragments of two K-steps by turns, B fragments of the two parts
-  bf16x8 fa[2][2][FM], fb[2][2][2];   // [turn or part][k-substep][block]
-  auto read_a = [&](auto Q, auto H, uint32_t st) {
-    constexpr int q = decltype(Q)::value, h = decltype(H)::value;
-    const uint32_t at = lane_a + st;
-    auto& v = fa;
-    static_for<0, 4>([&](auto n_c) {
-      constexpr int n = decltype(n_c)::value, kk = n >> 1, f = n & 1;
-      if constexpr (AK) lds_read<h * 8192 + f * 2048>(v[q][kk][2 * h + f], kk ? at ^ 64 : at);
-      else lds_read_tr<h * 8192 + kk * 4096, 512>(v[q][kk][2 * h + f], at ^ (f * 32));
-    });
-  };
-  auto read_b = [&](auto H, uint32_t st) {
-    constexpr int h = decltype(H)::value;
-    const uint32_t at = lane_b + st;
-    auto& v = fb;
-    static_for<0, 4>([&](auto n_c) {
-      constexpr int n = decltype(n_c)::value, kk = n >> 1, f = n & 1;
-      if constexpr (BKM) lds_read<h * 16384 + f * 2048>(v[h][kk][f], kk ? at ^ 64 : at);
-      else lds_read_tr<h * 16384 + kk * 8192, 1024>(v[h][kk][f], at ^ (f * 32));
-    });
-  };
-  // waits for this wave's LDS reads and makes the fragments named depend on it: A blocks J0 .. J1 - 1 of turn QA, B part QB
-  auto arrived = [&](auto QA, auto J0, auto J1, auto QB) {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    auto& a = fa;
-    auto& b = fb;
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-      for (int j = decltype(J0)::value; j < decltype(J1)::value; ++j) asm volatile("" : "+v"(a[decltype(QA)::value][kk][j]));
-#pragma unroll
-      for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(b[decltype(QB)::value][kk][i]));
-    }
-  };
-  constexpr std::integral_constant<int, 0> C0{};
-  constexpr std::integral_constant<int, 1> C1{};
-  constexpr std::integral_constant<int, 2> C2{};
-  constexpr std::integral_constant<int, 4> C4{};
-
-  // K-steps 0, 1 and 2 but for the second B part of the last, which goes out in the first phase
-  auto next_stage = [](uint32_t st) { return st + STAGE == (uint32_t)NST * STAGE ? 0u : st + STAGE; };
-  uint32_t st = 0, ld = 0;   // ring stages of the present K-step, and of the K-step that the cursor is at
-  const bool behind = wave >= 4;
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    if (s < t.total) {
-      cur.template issue_a<0>(pa + ld); cur.template issue_a<1>(pa + ld); cur.template issue_b<0>(pb + ld, wave);
-      if (s < 2) {
-        cur.template issue_b<1>(pb + ld, wave);
-        step();
-        ld = next_stage(ld);
-      }
-    }
-  }
-  if (t.total > 2) wait_vmcnt<12>(); else wait_vmcnt<0>();   // A and B part 0 of K-step 0
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  const bool odd = t.total & 1;
-  // the last K-step takes turn 1
-  if (odd) { read_a(C1, C0, 0u); read_a(C1, C1, 0u); } else { read_a(C0, C0, 0u); read_a(C0, C1, 0u); }
-  read_b(C0, 0u);
-  arrived(C0, C0, C4, C0);
-  arrived(C1, C0, C4, C1);
-  if (t.total > 2) wait_vmcnt<9>();   // what the first phase reads: B part 1, A part 0 of K-step 1
-  __builtin_amdgcn_s_barrier();       // before the first load into this stage
-  asm volatile("" ::: "memory");
-  if (behind) __builtin_amdgcn_s_barrier();
-
-  auto slot = [&](auto QA, auto QB, auto I0) {
-    constexpr int qa = decltype(QA)::value, qb = decltype(QB)::value, i = decltype(I0)::value;
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_quadrant(acc[i][0], acc[i + 1][0], acc[i][1], acc[i + 1][1], acc[i][2], acc[i + 1][2], acc[i][3], acc[i + 1][3], fb[qb][0][0],
-                  fb[qb][0][1], fb[qb][1][0], fb[qb][1][1], fa[qa][0][0], fa[qa][0][1], fa[qa][0][2], fa[qa][0][3], fa[qa][1][0],
-                  fa[qa][1][1], fa[qa][1][2], fa[qa][1][3]);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  // LEFT: K-steps left, this one included, where they are the last three (then there is less to fetch), or 4
-  auto kstep = [&](auto Q, auto LEFT) {
-    constexpr std::integral_constant<int, 1 - decltype(Q)::value> R{};   // the next K-step's turn
-    constexpr int left = decltype(LEFT)::value;
-    const uint32_t nx = next_stage(st);
-    // phase 0: B part 0.  Reads A part 0 of the next K-step and B part 1; sends B part 1 of K-step k + 2, A part 0 of k + 3.
-    if constexpr (left > 1) read_a(R, C0, nx);
-    read_b(C1, st);
-    if constexpr (left > 2) cur.template issue_b<1>(pb + ld, wave);
-    if constexpr (left > 3) {
-      step();
-      ld = next_stage(ld);
-      cur.template issue_a<0>(pa + ld);
-    }
-    // what the next phase reads went out four phases ago, three loads a phase
-    if constexpr (left > 1) wait_vmcnt<(left > 3 ? 9 : left == 3 ? 8 : 2)>();
-    slot(Q, C0, C0);
-    arrived(R, C0, C2, C1);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    // phase 1: B part 1.  Reads A part 1 and B part 0 of the next K-step; sends A part 1 and B part 0 of K-step k + 3.
-    if constexpr (left > 1) {
-      read_a(R, C1, nx);
-      read_b(C0, nx);
-    }
-    if constexpr (left > 3) {
-      cur.template issue_a<1>(pa + ld);
-      cur.template issue_b<0>(pb + ld, wave);
-    }
-    if constexpr (left > 1) wait_vmcnt<(left > 3 ? 9 : left == 3 ? 5 : 0)>();
-    slot(Q, C1, C2);
-    arrived(R, C2, C4, C0);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    st = nx;
-  };
-  constexpr std::integral_constant<int, 3> C3{};
-  int k = t.total - 3;
-  if (!odd && k > 0) {
-    kstep(C0, C4);
-    --k;
-  }
-  for (; k > 0; k -= 2) {
-    kstep(C1, C4);
-    kstep(C0, C4);
-  }
-  if (t.total > 2) kstep(C1, C3);
-  if (t.total > 1) kstep(C0, C2);
-  kstep(C1, C1);
-  if (!behind) __builtin_amdgcn_s_barrier();
-  mfma_drain();
-  tile_epilogue<BM, BN, 512, EPI>(grp, one, t, smem, [&](float* stg) {
-#pragma unroll
-    for (int i = 0; i < FN; ++i)
-#pragma unroll
-      for (int j = 0; j < FM; ++j)
-        *reinterpret_cast<f32x4*>(stg + ((j >> 1) * 64 + wave_m * 32 + (j & 1) * 16 + (lane & 15)) * (BN + 4) + (i >> 1) * 128 + wave_n * 32 +
-                                  (i & 1) * 16 + (lane >> 4) * 4) = acc[i][j];
-  });
-}
-
 template <int BM, int BN, bool AK, bool BKM, int NST, int EPI>
-__global__ __launch_bounds__(BM == 64 ? 256 : 512) void gemm_tile_kernel(const GemmKArgs p) {
-  if constexpr (BN == 256) gemm_pingpong<false, AK, BKM, EPI>(GemmGroupKArgs{}, p);
-  else gemm_tile<false, BM, BN, 2, BM == 64 ? 2 : 4, AK, BKM, NST, EPI>(GemmGroupKArgs{}, p);
+__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_kernel(const GemmKArgs p) {
+  gemm_tile<false, BM, BN, AK, BKM, NST, EPI>(GemmGroupKArgs{}, p);
 }
 template <int BM, int BN, bool AK, bool BKM, int NST, int EPI>
-__global__ __launch_bounds__(BM == 64 ? 256 : 512) void gemm_tile_group_kernel(const GemmGroupKArgs g) {
-  if constexpr (BN == 256) gemm_pingpong<true, AK, BKM, EPI>(g, g.prob[0]);
-  else gemm_tile<true, BM, BN, 2, BM == 64 ? 2 : 4, AK, BKM, NST, EPI>(g, g.prob[0]);
+__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_group_kernel(const GemmGroupKArgs g) {
+  gemm_tile<true, BM, BN, AK, BKM, NST, EPI>(g, g.prob[0]);
 }
 
 template <int BM, int BN, int NST, bool AK, bool BKM, int EPI>
@@ -614,7 +364,7 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hi
     k.band_rows = 8;
     return k;
   };
-  const dim3 block(BM == 64 ? 256 : 512);
+  const dim3 block(tile_threads(BM));
   static std::atomic<unsigned long long> lds_done{0};
   if constexpr (EPI != TILE_ROPE) {
     if (n == 1) {
@@ -646,7 +396,7 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hi
   return fail(-1, "gemm tile: no grouped launch of this kind");
 }
 
-// T128x256: 144 KB of LDS, T128: 96 KB, one workgroup of eight waves per CU; T64: 64 KB, two of four waves.
+// T128x256: 144 KB of LDS, T128: 96 KB, one workgroup of eight waves and four that load per CU; T64: 64 KB, two of four and four.
 template <bool AK, bool BKM, int EPI>
 static int launch_size(TileSize size, const GemmKArgs* ks, int n, const RopeEpilogue* rope, hipStream_t st) {
   switch (size) {
