@@ -171,14 +171,18 @@ static int gemm_nt(const void* x, int64_t ldx, const void* w, const void* res, i
 
 // dx[T,K] = sum_s dy_s[T,N_s] W_s[N_s,K] with W_s as stored, or (transposed) through the copies W_s^T [K,N_s]; ld: leading
 // dimension of every dy_s, and of the copies, where it is not N_s; lddx: that of dx
-static int gemm_dgrad(int nseg, const void* const* dy, const void* const* w, const int64_t* Ns, int64_t ld, bool transposed,
-                      int64_t T, int64_t K, void* dx, int64_t lddx, hipStream_t st) {
+static GemmArgs dgrad_args(int nseg, const void* const* dy, const void* const* w, const int64_t* Ns, int64_t ld, bool transposed,
+                           int64_t T, int64_t K, void* dx, int64_t lddx) {
   GemmArgs g{};
   g.nseg = nseg;
   for (int s = 0; s < nseg; ++s) g.seg[s] = {dy[s], w[s], ld ? ld : Ns[s], !transposed ? K : ld ? ld : Ns[s], (int)Ns[s]};
   g.M = (int)T; g.N = (int)K; g.c = dx; g.ldc = lddx; g.r = nullptr; g.accumulate = 0;
   g.a_kmajor = true; g.b_kmajor = transposed;
-  return launch_gemm(g, st);
+  return g;
+}
+static int gemm_dgrad(int nseg, const void* const* dy, const void* const* w, const int64_t* Ns, int64_t ld, bool transposed,
+                      int64_t T, int64_t K, void* dx, int64_t lddx, hipStream_t st) {
+  return launch_gemm(dgrad_args(nseg, dy, w, Ns, ld, transposed, T, K, dx, lddx), st);
 }
 
 // Whether the input gradient [T, K] of a product reads its weights as they are stored, not through a transposed copy.
@@ -305,13 +309,15 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
   }
   TRY(launch_rmsnorm_bwd_rows(s.y1, w->g_mlp, s.rstd2, k.dh2, dy, T, D, k.dy1, k.rms_ws2, st));
   // y1 = x + o Wo^T
+  bool stats_done = false;
   {
     const void* dys[1] = {k.dy1}; const void* ws[1] = {direct ? w->wo : k.woT}; const int64_t ns[1] = {D};
-    TRY(gemm_dgrad(1, dys, ws, ns, 0, !direct, T, QD, k.d_o, QD, st));
+    const DeltaEpilogue stats = {s.o, s.lse, attention_bwd_delta(k.attn_ws), attention_bwd_lse2(k.attn_ws, B, S, Hq), (int)S, (int)Hq, (int)dh};
+    TRY(launch_gemm_delta(dgrad_args(1, dys, ws, ns, 0, !direct, T, QD, k.d_o, QD), stats, &stats_done, st));
   }
   // dq and dk come back as gradients of the unrotated q and k (inverse rotation inside the kernels' stores)
   TRY(launch_attention_bwd_rope(s.q, s.k, s.v, s.o, k.d_o, s.lse, B, S, Hq, Hkv, dh, k.dq, k.dk, k.dv, k.attn_ws,
-                                s.rope_cos, s.rope_sin, cfg->rope_layout, st));
+                                s.rope_cos, s.rope_sin, cfg->rope_layout, stats_done, st));
   {
     const void* dys[3] = {k.dq, k.dk, k.dv};
     const void* ws[3] = {direct ? w->wq : k.wqT, direct ? w->wk : k.wkT, direct ? w->wv : k.wvT};
@@ -319,7 +325,6 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
     TRY(gemm_dgrad(3, dys, ws, ns, 0, !direct, T, D, k.dh1, D, st));
   }
   TRY(launch_rmsnorm_bwd_rows(x, w->g_attn, s.rstd1, k.dh1, k.dy1, T, D, dx, k.rms_ws1, st));
-  TRY(launch_rmsnorm_bwd_gain(k.rms_ws1, dw->g_attn, k.rms_ws2, dw->g_mlp, T, D, acc, st));
   // Recomputing configurations: the normalised activations and the SwiGLU output are only operands of
   // the weight gradients; they are rebuilt here from x, y1 (with the saved statistics) and from g, u.
   if (!s.h1) {
@@ -338,7 +343,7 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
       wgrad_args(k.du, Fp, s.h2, D, T, F, D, dw->w_up, acc),     wgrad_args(k.dy1, D, s.o, QD, T, D, QD, dw->wo, acc),
       wgrad_args(k.dq, QD, s.h1, D, T, QD, D, dw->wq, acc),      wgrad_args(k.dk, KD, s.h1, D, T, KD, D, dw->wk, acc),
       wgrad_args(k.dv, KD, s.h1, D, T, KD, D, dw->wv, acc)};
-  TRY(launch_gemm_group(wg, 7, st));
+  TRY(launch_gemm_group_gains(wg, 7, rmsnorm_bwd_gain_sums(k.rms_ws1, dw->g_attn, k.rms_ws2, dw->g_mlp, T, D, acc), st));
   return DLAYER_OK;
 }
 

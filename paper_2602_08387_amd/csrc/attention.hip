@@ -24,7 +24,6 @@
 
 namespace dl {
 
-constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 // v_exp_f32: 2^x without the denormal-range fix-up (results below 2^-126 flush to zero, which is
@@ -1012,9 +1011,8 @@ template <int DH>
 static int bwd_dh(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                   const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv, void* dq, void* dk,
                   void* dv, void* workspace, const float* rope_cos, const float* rope_sin, int rope_layout,
-                  hipStream_t st) {
-  float* delta = (float*)workspace;
-  float* lse2 = delta + B * Hq * S;
+                  bool stats_done, hipStream_t st) {
+  float *delta = attention_bwd_delta(workspace), *lse2 = attention_bwd_lse2(workspace, B, S, Hq);
   char* after_stats = reinterpret_cast<char*>(workspace) + bwd_stats_bytes(B, S, Hq);
   AttnBwdArgs a{};
   a.q = (const bf16_t*)q; a.k = (const bf16_t*)k; a.v = (const bf16_t*)v; a.d_o = (const bf16_t*)d_o;
@@ -1027,10 +1025,12 @@ static int bwd_dh(const void* q, const void* k, const void* v, const void* o, co
   a.scale = (float)(1.0 / sqrt((double)DH));
   a.rope_cos = rope_cos; a.rope_sin = rope_sin; a.rope_layout = rope_layout;
   const int64_t rows = B * S * Hq;
-  const int64_t nthreads = rows * (DH / 8);
-  hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, st,
-                     (const bf16_t*)o, (const bf16_t*)d_o, lse, delta, lse2, rows, (int)S, (int)Hq);
-  if (int rc = check_launch("attention_backward(delta)")) return rc;
+  if (!stats_done) {
+    const int64_t nthreads = rows * (DH / 8);
+    hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, st,
+                       (const bf16_t*)o, (const bf16_t*)d_o, lse, delta, lse2, rows, (int)S, (int)Hq);
+    if (int rc = check_launch("attention_backward(delta)")) return rc;
+  }
   const unsigned kv_blocks = (unsigned)(S / 128 * Hkv * B * a.ns), q_blocks = (unsigned)(S / 128 * Hq * B);
   const size_t lds_kv = 2 * (2 * (size_t)(32 * DH * 2) + 512) + (size_t)RowTile<128, DH, 4>::BYTES;
   if constexpr (DH == 128) {
@@ -1078,16 +1078,16 @@ static int bwd_dh(const void* q, const void* k, const void* v, const void* o, co
 int launch_attention_bwd(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                          const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh,
                          void* dq, void* dk, void* dv, void* workspace, hipStream_t st) {
-  return launch_attention_bwd_rope(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dh, dq, dk, dv, workspace, nullptr, nullptr, 0, st);
+  return launch_attention_bwd_rope(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dh, dq, dk, dv, workspace, nullptr, nullptr, 0, false, st);
 }
 
 int launch_attention_bwd_rope(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                               const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh,
                               void* dq, void* dk, void* dv, void* workspace, const float* rope_cos,
-                              const float* rope_sin, int rope_layout, hipStream_t st) {
-  if (dh == 128) return bwd_dh<128>(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dq, dk, dv, workspace, rope_cos, rope_sin, rope_layout, st);
-  if (dh == 64) return bwd_dh<64>(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dq, dk, dv, workspace, rope_cos, rope_sin, rope_layout, st);
-  return bwd_dh<32>(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dq, dk, dv, workspace, rope_cos, rope_sin, rope_layout, st);
+                              const float* rope_sin, int rope_layout, bool stats_done, hipStream_t st) {
+  if (dh == 128) return bwd_dh<128>(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dq, dk, dv, workspace, rope_cos, rope_sin, rope_layout, stats_done, st);
+  if (dh == 64) return bwd_dh<64>(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dq, dk, dv, workspace, rope_cos, rope_sin, rope_layout, stats_done, st);
+  return bwd_dh<32>(q, k, v, o, d_o, lse, B, S, Hq, Hkv, dq, dk, dv, workspace, rope_cos, rope_sin, rope_layout, stats_done, st);
 }
 
 }  // namespace dl

@@ -17,6 +17,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int kWave = 64;
+constexpr float kLog2e = 1.4426950408889634f;
 
 // Sum / max across the 64 lanes of a wavefront; every lane receives the result.
 __device__ __forceinline__ float wave_sum(float v) {

@@ -4,6 +4,7 @@
 // consecutive addresses, keep a row in registers between the reduction and the write, and
 // reduce with wavefront shuffles.
 #include "common.h"
+#include "gain_sums.h"
 #include "kernels.h"
 
 namespace dl {
@@ -235,36 +236,9 @@ __global__ __launch_bounds__(TPR * RG) void rmsnorm_bwd_kernel(
   }
 }
 
-// Column sums of the per-block partial rows, of one or two norms (blockIdx.y): 1024 threads = 32 columns x 32 row
-// groups, folded through LDS.  Four loads in flight per thread and 32 groups: the kernel is a chain of load latencies
-// (512 rows: 7 us with 8 groups, 5 us with 32).
-__global__ __launch_bounds__(1024) void colsum_partials_kernel(const float* __restrict__ pa, const float* __restrict__ pb, int nrows,
-                                                               int D, bf16_t* outa, bf16_t* outb, int accumulate) {
-  __shared__ float red[32][33];
-  const float* partial = blockIdx.y ? pb : pa;
-  bf16_t* out = blockIdx.y ? outb : outa;
-  const int cl = threadIdx.x & 31, rg = threadIdx.x >> 5;
-  const int c = blockIdx.x * 32 + cl;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  if (c < D) {
-    int r = rg;
-    for (; r + 96 < nrows; r += 128) {
-      s0 += partial[(int64_t)r * D + c];
-      s1 += partial[(int64_t)(r + 32) * D + c];
-      s2 += partial[(int64_t)(r + 64) * D + c];
-      s3 += partial[(int64_t)(r + 96) * D + c];
-    }
-    for (; r < nrows; r += 32) s0 += partial[(int64_t)r * D + c];
-  }
-  red[rg][cl] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  if (rg == 0 && c < D) {
-    float t = 0.f;
-#pragma unroll
-    for (int g = 0; g < 32; ++g) t += red[g][cl];
-    if (accumulate) t += (float)out[c];
-    out[c] = (bf16_t)t;
-  }
+__global__ __launch_bounds__(1024) void colsum_partials_kernel(const GainSums s) {
+  __shared__ float red[32 * 33];
+  gain_sums<1024>(s, (int)blockIdx.x, red);
 }
 
 // Workgroups, i.e. partial rows: one per eight rows and at most 512, which is what the size query asks room for.
@@ -296,11 +270,16 @@ int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd,
   return check_launch("rmsnorm_backward");
 }
 
+GainSums rmsnorm_bwd_gain_sums(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D, int accumulate) {
+  return {(const float*)ws_a, (const float*)ws_b, dgamma_a, dgamma_b, rms_bwd_blocks(T), (int)D, accumulate};
+}
+int launch_gain_sums(const GainSums& s, hipStream_t st) {
+  hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)gain_sum_blocks(s)), dim3(1024), 0, st, s);
+  return check_launch("rmsnorm_backward(dgamma)");
+}
 int launch_rmsnorm_bwd_gain(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D,
                             int accumulate, hipStream_t st) {
-  hipLaunchKernelGGL(colsum_partials_kernel, dim3((unsigned)((D + 31) / 32), dgamma_b ? 2 : 1), dim3(1024), 0, st, (const float*)ws_a,
-                     (const float*)ws_b, rms_bwd_blocks(T), (int)D, (bf16_t*)dgamma_a, (bf16_t*)dgamma_b, accumulate);
-  return check_launch("rmsnorm_backward(dgamma)");
+  return launch_gain_sums(rmsnorm_bwd_gain_sums(ws_a, dgamma_a, ws_b, dgamma_b, T, D, accumulate), st);
 }
 
 int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,

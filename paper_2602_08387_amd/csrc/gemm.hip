@@ -901,10 +901,13 @@ static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk,
   p.first = whole_us <= tile_us ? kPersistent : tile;
 }
 
-static int run_gemm(const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, hipStream_t st) {
+static int run_gemm(const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, hipStream_t st,
+                    const GainSums* gains = nullptr) {
   GemmPlan p;
   plan_gemm(p, ks, n, ak, bk, epi, rope, compute_units());
-  if (p.first != kPersistent) return launch_gemm_tile((TileSize)p.first, p.head, p.nh, ak, bk, epi, rope, st);
+  if (p.first != kPersistent) return launch_gemm_tile((TileSize)p.first, p.head, p.nh, ak, bk, epi, rope, st, gains);
+  if (gains)
+    if (int rc = launch_gain_sums(*gains, st)) return rc;
   const int rc = p.nh > 1 || rope ? launch_persistent_group(p.head, p.nh, ak, bk, rope, st) : launch_persistent(p.head[0], ak, bk, epi, st);
   if (rc || p.second < 0) return rc;
   return launch_gemm_tile((TileSize)p.second, p.tail, p.nt, ak, bk, epi, rope, st);
@@ -960,6 +963,17 @@ int launch_gemm(const GemmArgs& g, hipStream_t st) {
   return run_gemm(&k, 1, g.a_kmajor, g.b_kmajor, TileEpilogue::PLAIN, nullptr, st);
 }
 
+int launch_gemm_delta(const GemmArgs& g, const DeltaEpilogue& d, bool* done, hipStream_t st) {
+  const GemmKArgs k = kernel_args(g);
+  GemmPlan p;
+  plan_gemm(p, &k, 1, g.a_kmajor, g.b_kmajor, TileEpilogue::PLAIN, nullptr, compute_units());
+  // a launch of its own costs 2 to 9 us; on the persistent kernel a wave holds half of a 128-wide head, and the
+  // statistics are a hundredth of the attention backward that follows
+  *done = p.first != kPersistent && g.a_kmajor && !(p.first == (int)TileSize::T64 && d.head_dim == 128);
+  return *done ? launch_gemm_tile_delta((TileSize)p.first, k, g.b_kmajor, d, st)
+               : run_gemm(&k, 1, g.a_kmajor, g.b_kmajor, TileEpilogue::PLAIN, nullptr, st);
+}
+
 int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* wu, int64_t ldw, int64_t T, int64_t K,
                        int64_t F, void* g, void* u, int64_t ldgu, void* a, int64_t lda, hipStream_t st) {
   GemmKArgs k{};
@@ -1001,9 +1015,7 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_
   return run_gemm(&k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, st);
 }
 
-int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st) { return launch_gemm_group_rope(gs, n, nullptr, st); }
-
-int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, hipStream_t st) {
+static int run_group(const GemmArgs* gs, int n, const RopeEpilogue* rope, const GainSums* gains, hipStream_t st) {
   if (n < 1 || n > MAX_GROUP) return fail(-1, "gemm group: 1..%d problems, got %d", MAX_GROUP, n);
   GemmKArgs ks[MAX_GROUP];
   for (int i = 0; i < n; ++i) {
@@ -1020,7 +1032,10 @@ int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, 
       if (gs[i].r || gs[i].accumulate || gs[i].N % rope->head_dim || gs[i].ldc % 8)
         return fail(-1, "gemm group: rotary epilogue on a product with residual, accumulation or partial heads");
   }
-  return run_gemm(ks, n, gs[0].a_kmajor, gs[0].b_kmajor, TileEpilogue::PLAIN, rope, st);
+  return run_gemm(ks, n, gs[0].a_kmajor, gs[0].b_kmajor, TileEpilogue::PLAIN, rope, st, gains);
 }
+int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st) { return run_group(gs, n, nullptr, nullptr, st); }
+int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, hipStream_t st) { return run_group(gs, n, rope, nullptr, st); }
+int launch_gemm_group_gains(const GemmArgs* gs, int n, const GainSums& gains, hipStream_t st) { return run_group(gs, n, nullptr, &gains, st); }
 
 }  // namespace dl

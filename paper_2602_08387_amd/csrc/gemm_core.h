@@ -271,7 +271,7 @@ struct GemmGroupKArgs {
   const float *rope_cos, *rope_sin;
   int rope_seq, rope_dh, rope_layout;
 };
-// Problem i of a grouped launch, whose GemmGroupKArgs is the kernel's only argument: a reference into the constant
+// Problem i of a grouped launch, whose GemmGroupKArgs is the kernel's first argument: a reference into the constant
 // kernel-argument segment, so that a wave-uniform run-time index becomes scalar loads of the one problem (selecting
 // among all of them by compile-time index held eight problems in scalar registers and spilled two hundred).
 typedef const __attribute__((address_space(4))) GemmGroupKArgs ConstGroupKArgs;
@@ -283,7 +283,10 @@ __device__ __forceinline__ const __attribute__((address_space(4))) GemmKArgs& gr
 // Kernels of gemm_tile.hip: one tile per workgroup.
 enum class TileSize { T128x256, T128, T64 };
 enum class TileEpilogue { PLAIN, SWIGLU, SWIGLU_GRAD };
+// one product with the row statistics of the attention backward in its epilogue; the tile holds whole heads
+int launch_gemm_tile_delta(TileSize size, const GemmKArgs& k, bool b_kmajor, const DeltaEpilogue& d, hipStream_t st);
+// gains: weight gradients only, summed by further workgroups of the launch
 int launch_gemm_tile(TileSize size, const GemmKArgs* ks, int n, bool a_kmajor, bool b_kmajor, TileEpilogue epi, const RopeEpilogue* rope,
-                     hipStream_t st);
+                     hipStream_t st, const GainSums* gains = nullptr);
 
 }  // namespace dl

@@ -18,6 +18,7 @@
 // The epilogue passes the fp32 sums through LDS (the ring is free by then), so every fused epilogue is an
 // element-wise function of rows: residual or accumulation, rotary embedding (both members of a pair lie in the
 // tile), gated pair, activation gradient.
+#include "gain_sums.h"
 #include "gemm_core.h"
 
 namespace dl {
@@ -68,7 +69,9 @@ __device__ __forceinline__ void wait_reads(bf16x8 (&a)[FA], bf16x8 (&b)[FB]) {
   for (int j = 0; j < FB; ++j) asm volatile("" : "+v"(b[j]));
 }
 
-enum { TILE_PLAIN = 0, TILE_SWIGLU = 1, TILE_SWIGLU_GRAD = 2, TILE_ROPE = 3 };
+// TILE_DELTA: plain, and of every head's columns -rowsum(dO * O) of the values stored, and lse * log2(e), as
+// attn_delta_kernel writes them (same order of summation).
+enum { TILE_PLAIN = 0, TILE_SWIGLU = 1, TILE_SWIGLU_GRAD = 2, TILE_ROPE = 3, TILE_DELTA = 4 };
 
 // A workgroup's tile: its problem's fields and where it lies.
 struct TileOf {
@@ -117,7 +120,7 @@ __device__ __forceinline__ TileOf find_tile(const GemmGroupKArgs& grp, const Gem
 // The tile's results: `to_staging` writes a wave's fp32 sums to [BM][BN + 4] floats in LDS (the ring is free by then), from where
 // every fused epilogue is an element-wise function of rows.
 template <int BM, int BN, int NT, int EPI, typename F>
-__device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const GemmKArgs& one, const TileOf& t, char* smem, F&& to_staging) {
+__device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const GemmKArgs& one, const DeltaEpilogue& da, const TileOf& t, char* smem, F&& to_staging) {
   constexpr bool PAIR = EPI == TILE_SWIGLU;
   // Epilogue.  fp32 sums to LDS, rows of BN + 4 floats (the 16 bytes more put the 16 rows a store instruction touches in
   // different banks), then 8 consecutive columns per thread along rows.
@@ -209,11 +212,25 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
             }
           }
         }
-      } else if (res || accumulate) {
+      } else if (EPI == TILE_PLAIN && (res || accumulate)) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] += (float)pre[v][e];
       }
-      *reinterpret_cast<bf16x8*>(cmat + (int64_t)m * ldc + n) = pack8(f);
+      const bf16x8 out = pack8(f);
+      *reinterpret_cast<bf16x8*>(cmat + (int64_t)m * ldc + n) = out;
+      if constexpr (EPI == TILE_DELTA) {
+        const bf16x8 o = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(da.o) + (int64_t)m * ldc + n);
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += (float)o[e] * (float)out[e];
+        for (int off = da.head_dim >> 4; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (n % da.head_dim == 0) {
+          const int b = m / da.seq;
+          const int64_t at = ((int64_t)b * da.heads + n / da.head_dim) * da.seq + (m - b * da.seq);
+          da.delta[at] = -s;
+          da.lse2[at] = da.lse[at] * kLog2e;
+        }
+      }
     }
   }
 }
@@ -223,7 +240,7 @@ constexpr int tile_threads(int bm) { return ((bm == 64 ? 4 : 8) + LOADERS) * 64;
 
 // NST: ring stages.  EPI as the persistent kernel's epilogues.
 template <bool GROUPED, int BM, int BN, bool AK, bool BKM, int NST, int EPI>
-__device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmKArgs& one) {
+__device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmKArgs& one, const DeltaEpilogue& da) {
   constexpr int WM = 2, WN = BM == 64 ? 2 : 4, NW = WM * WN, NL = LOADERS, NT = tile_threads(BM);   // waves that multiply, waves that load
   constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
   constexpr int A_BYTES = BM * BK * 2, STAGE = A_BYTES + BN * BK * 2;
@@ -335,7 +352,7 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
       st = nx;
     }
   }
-  tile_epilogue<BM, BN, NT, EPI>(grp, one, t, smem, [&](float* stg) {
+  tile_epilogue<BM, BN, NT, EPI>(grp, one, da, t, smem, [&](float* stg) {
     if (wave >= NW) return;
 #pragma unroll
     for (int i = 0; i < FN; ++i)
@@ -347,15 +364,28 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
 
 template <int BM, int BN, bool AK, bool BKM, int NST, int EPI>
 __global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_kernel(const GemmKArgs p) {
-  gemm_tile<false, BM, BN, AK, BKM, NST, EPI>(GemmGroupKArgs{}, p);
+  gemm_tile<false, BM, BN, AK, BKM, NST, EPI>(GemmGroupKArgs{}, p, DeltaEpilogue{});
 }
 template <int BM, int BN, bool AK, bool BKM, int NST, int EPI>
-__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_group_kernel(const GemmGroupKArgs g) {
-  gemm_tile<true, BM, BN, AK, BKM, NST, EPI>(g, g.prob[0]);
+__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_group_kernel(const GemmGroupKArgs g, const GainSums gains, int first_gain) {
+  // Weight gradients of a layer: the gain sums of its norms ride behind the tiles (a launch of their own takes 2.5 to 5 us)
+  if constexpr (EPI == TILE_PLAIN) {
+    if ((int)blockIdx.x >= first_gain) {
+      extern __shared__ __attribute__((aligned(1024))) char smem[];
+      gain_sums<tile_threads(BM)>(gains, (int)blockIdx.x - first_gain, reinterpret_cast<float*>(smem));
+      return;
+    }
+  }
+  gemm_tile<true, BM, BN, AK, BKM, NST, EPI>(g, g.prob[0], DeltaEpilogue{});
+}
+
+template <int BM, int BN, bool BKM, int NST>
+__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_delta_kernel(const GemmKArgs p, const DeltaEpilogue d) {
+  gemm_tile<false, BM, BN, true, BKM, NST, TILE_DELTA>(GemmGroupKArgs{}, p, d);
 }
 
 template <int BM, int BN, int NST, bool AK, bool BKM, int EPI>
-static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hipStream_t st) {
+static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, const DeltaEpilogue* delta, const GainSums* gains, hipStream_t st) {
   constexpr size_t ring = (size_t)NST * (BM + BN) * BK * 2, staging = (size_t)BM * (BN + 4) * sizeof(float);
   constexpr size_t lds = ring > staging ? ring : staging;
   auto tiled = [](GemmKArgs k) {
@@ -366,8 +396,14 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hi
   };
   const dim3 block(tile_threads(BM));
   static std::atomic<unsigned long long> lds_done{0};
-  if constexpr (EPI != TILE_ROPE) {
-    if (n == 1) {
+  if constexpr (EPI == TILE_DELTA) {
+    auto kern = gemm_tile_delta_kernel<BM, BN, BKM, NST>;
+    if (int rc = reserve_lds(kern, lds, lds_done, "gemm tile (row statistics)")) return rc;
+    const GemmKArgs k = tiled(ks[0]);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(k.tiles_m * k.tiles_n)), block, lds, st, k, *delta);
+    return check_launch("gemm tile (row statistics)");
+  } else if constexpr (EPI != TILE_ROPE) {
+    if (n == 1 && !gains) {
       auto kern = gemm_tile_kernel<BM, BN, AK, BKM, NST, EPI>;
       if (int rc = reserve_lds(kern, lds, lds_done, "gemm tile")) return rc;
       const GemmKArgs k = tiled(ks[0]);
@@ -390,7 +426,8 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hi
       g.rope_cos = rope->cos; g.rope_sin = rope->sin;
       g.rope_seq = rope->seq; g.rope_dh = rope->head_dim; g.rope_layout = rope->layout;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)g.tile_start[n]), block, lds, st, g);
+    const int tiles = g.tile_start[n];
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles + (gains ? gain_sum_blocks(*gains) : 0))), block, lds, st, g, gains ? *gains : GainSums{}, tiles);
     return check_launch("gemm tile group");
   }
   return fail(-1, "gemm tile: no grouped launch of this kind");
@@ -398,23 +435,28 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, hi
 
 // T128x256: 144 KB of LDS, T128: 96 KB, one workgroup of eight waves and four that load per CU; T64: 64 KB, two of four and four.
 template <bool AK, bool BKM, int EPI>
-static int launch_size(TileSize size, const GemmKArgs* ks, int n, const RopeEpilogue* rope, hipStream_t st) {
+static int launch_size(TileSize size, const GemmKArgs* ks, int n, const RopeEpilogue* rope, hipStream_t st, const DeltaEpilogue* delta = nullptr,
+                       const GainSums* gains = nullptr) {
   switch (size) {
-    case TileSize::T128x256: return launch_tiles<128, 256, 3, AK, BKM, EPI>(ks, n, rope, st);
-    case TileSize::T128: return launch_tiles<128, 128, 3, AK, BKM, EPI>(ks, n, rope, st);
-    case TileSize::T64: return launch_tiles<64, 64, 4, AK, BKM, EPI>(ks, n, rope, st);
+    case TileSize::T128x256: return launch_tiles<128, 256, 3, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
+    case TileSize::T128: return launch_tiles<128, 128, 3, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
+    case TileSize::T64: return launch_tiles<64, 64, 4, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
   }
   return fail(-1, "gemm tile: unknown size");
 }
 
+int launch_gemm_tile_delta(TileSize size, const GemmKArgs& k, bool bk, const DeltaEpilogue& d, hipStream_t st) {
+  return bk ? launch_size<true, true, TILE_DELTA>(size, &k, 1, nullptr, st, &d) : launch_size<true, false, TILE_DELTA>(size, &k, 1, nullptr, st, &d);
+}
+
 int launch_gemm_tile(TileSize size, const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope,
-                     hipStream_t st) {
+                     hipStream_t st, const GainSums* gains) {
   if (rope) return launch_size<true, true, TILE_ROPE>(size, ks, n, rope, st);
   if (epi == TileEpilogue::SWIGLU) return launch_size<true, true, TILE_SWIGLU>(size, ks, n, nullptr, st);
   if (epi == TileEpilogue::SWIGLU_GRAD)
     return bk ? launch_size<true, true, TILE_SWIGLU_GRAD>(size, ks, n, nullptr, st) : launch_size<true, false, TILE_SWIGLU_GRAD>(size, ks, n, nullptr, st);
   if (ak && bk) return launch_size<true, true, TILE_PLAIN>(size, ks, n, nullptr, st);
-  if (!ak && !bk) return launch_size<false, false, TILE_PLAIN>(size, ks, n, nullptr, st);
+  if (!ak && !bk) return launch_size<false, false, TILE_PLAIN>(size, ks, n, nullptr, st, nullptr, gains);
   if (ak && !bk) return launch_size<true, false, TILE_PLAIN>(size, ks, n, nullptr, st);
   return fail(-1, "gemm tile: operand layout not built");
 }

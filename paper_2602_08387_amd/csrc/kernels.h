@@ -22,6 +22,11 @@ size_t rmsnorm_bwd_workspace(int64_t T, int64_t D);
 // (ws_b, dgamma_b not null) two of the same shape
 int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd, const void* dh,
                             const void* dres, int64_t T, int64_t D, void* dx, void* workspace, hipStream_t st);
+// The second half as an argument for a launch that has room for it: column sums of nrows partial rows of D, one norm or (b not
+// null) two
+struct GainSums { const float *pa, *pb; void *outa, *outb; int nrows, D, accumulate; };
+GainSums rmsnorm_bwd_gain_sums(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D, int accumulate);
+int launch_gain_sums(const GainSums& s, hipStream_t st);
 int launch_rmsnorm_bwd_gain(const void* ws_a, void* dgamma_a, const void* ws_b, void* dgamma_b, int64_t T, int64_t D,
                             int accumulate, hipStream_t st);
 int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,
@@ -75,8 +80,15 @@ struct GemmArgs {
   bool a_kmajor, b_kmajor;
 };
 int launch_gemm(const GemmArgs& g, hipStream_t st);
+// The product is dO [tokens][heads][head_dim] for a coming attention backward: where it runs on one-tile kernels that hold
+// whole heads, their epilogue writes what attn_delta_kernel would (the same bits), and *done is set.  o: as c; lse, delta, lse2:
+// [batch][heads][seq].
+struct DeltaEpilogue { const void* o; const float* lse; float *delta, *lse2; int seq, heads, head_dim; };
+int launch_gemm_delta(const GemmArgs& g, const DeltaEpilogue& d, bool* done, hipStream_t st);
 // Up to 8 independent problems in one launch, both operands mn-major (the weight-gradient products).
 int launch_gemm_group(const GemmArgs* gs, int n, hipStream_t st);
+// the same, and the gain sums of a layer's norms: in the same launch where that is of one-tile kernels, before it otherwise
+int launch_gemm_group_gains(const GemmArgs* gs, int n, const GainSums& gains, hipStream_t st);
 // The same for k-major products whose outputs are [tokens][heads][head_dim], with the rotary embedding
 // applied in the epilogue (on the fp32 accumulators) to the problems whose bit is set in rotate_mask.
 // cos, sin: [seq][head_dim / 2] fp32 (launch_rope_table); position of a row = row % seq.
@@ -104,17 +116,21 @@ int attention_bwd_pieces(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t 
 int launch_attention_fwd(const void* q, const void* k, const void* v, int64_t B, int64_t S,
                          int64_t Hq, int64_t Hkv, int64_t dh, void* o, float* lse, hipStream_t st);
 size_t attention_bwd_workspace(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh);
+// the row statistics of the backward lie at the start of its workspace: delta, then lse2, [B, Hq, S] each
+inline float* attention_bwd_delta(void* workspace) { return static_cast<float*>(workspace); }
+inline float* attention_bwd_lse2(void* workspace, int64_t B, int64_t S, int64_t Hq) { return attention_bwd_delta(workspace) + B * Hq * S; }
 int launch_attention_bwd(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                          const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh,
                          void* dq, void* dk, void* dv, void* workspace, hipStream_t st);
 
 // The same for q and k that were rotated (rotary embedding) after their projections: dq and dk are
 // the gradients of the UNROTATED q and k, the inverse rotation being applied to the fp32 sums before
-// they are rounded.  rope_cos, rope_sin: [S][dh / 2] fp32 (launch_rope_table), or null for no rotation.
+// they are rounded.  rope_cos, rope_sin: [S][dh / 2] fp32 (launch_rope_table), or null for no rotation.  stats_done: the row
+// statistics are in the workspace already (launch_gemm_delta).
 int launch_attention_bwd_rope(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                               const float* lse, int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int64_t dh,
                               void* dq, void* dk, void* dv, void* workspace, const float* rope_cos,
-                              const float* rope_sin, int rope_layout, hipStream_t st);
+                              const float* rope_sin, int rope_layout, bool stats_done, hipStream_t st);
 
 // ---- ce.hip
 size_t ce_workspace(int64_t T, int64_t V);

@@ -294,6 +294,36 @@ def test_input_gradient_with_and_without_the_transposed_weights(K, rows, Kd, N, 
         assert torch.equal(dx.view(torch.int16), first[:T].view(torch.int16)), T
 
 
+# batch, seq, width, query heads, KV heads, head width, d_ff; weights as stored; tile of the o projection's input gradient
+STATISTICS = [
+    ((1, 256, 128, 4, 2, 32, 192), True, T64),        # two heads per tile
+    ((1, 256, 128, 2, 1, 64, 192), True, T64),
+    ((1, 256, 128, 2, 1, 128, 192), True, T64),       # a head spans two tiles: statistics in a launch of their own
+    ((3, 640, 192, 9, 3, 128, 320), False, T128),
+    ((3, 640, 192, 18, 6, 64, 320), False, T128),
+    ((8, 1024, 320, 6, 2, 128, 320), False, T128X256),
+    ((8, 1024, 320, 24, 8, 32, 320), False, T128X256),
+]
+
+
+@pytest.mark.parametrize("shape,stored,tile", STATISTICS)
+def test_layer_with_row_statistics_in_the_epilogue(K, shape, stored, tile):
+    """The attention backward's row statistics come out of the product that makes dO, the norms' gain sums out of the weight
+    gradients' launch."""
+    B, S, D, Hq, Hkv, dh, F = shape
+    T, QD = B * S, Hq * dh
+    assert stored == (D * max(F, QD) <= 65536 and T <= 4096)
+    assert K.gemm_route(1 if stored else 0, 0, [T], [QD], [D], compute_units=256)[:2] == (tile, -1)
+    cfg = si.CONFIGS["tiny"].with_(batch=B, seq=S, d_model=D, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=F)
+    inp = si.make_layer_inputs(cfg, seed=5)
+    f, r = _oracle(cfg, inp)
+    g = GpuLayer(K, cfg, inp)
+    g.forward()
+    g.backward()
+    torch.cuda.synchronize()
+    _check_layer(g, f, r, "statistics")
+
+
 def test_layer_with_short_segments_on_full_tiles(K):
     """The fused input gradients on 256 x 256 tiles with segments of one and of three K-steps: walks that start in any segment
     (a row group of 2048 starts its eighth of the way further on), odd and even, over more than one round of tiles."""
