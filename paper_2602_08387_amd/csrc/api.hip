@@ -301,13 +301,13 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
     TRY(launch_transpose_group(jobs, 7, st));
   }
   // y = y1 + a Wd^T
-  TRY(launch_gemm_swiglu_grad(dy, D, direct ? w->w_down : k.wdT, !direct, direct ? F : D, T, D, F, s.g, s.u, F, k.da_dg, k.du, Fp, st));
+  TRY(launch_gemm_swiglu_grad(dy, D, direct ? w->w_down : k.wdT, !direct, direct ? F : D, T, D, F, s.g, s.u, F, k.da_dg, k.du, Fp, s.a ? nullptr : k.a, st));
   {
     const void* dys[2] = {k.da_dg, k.du}; const void* ws[2] = {direct ? w->w_gate : k.wgT, direct ? w->w_up : k.wuT};
     const int64_t ns[2] = {F, F};
     TRY(gemm_dgrad(2, dys, ws, ns, Fp, !direct, T, D, k.dh2, D, st));
   }
-  TRY(launch_rmsnorm_bwd_rows(s.y1, w->g_mlp, s.rstd2, k.dh2, dy, T, D, k.dy1, k.rms_ws2, st));
+  TRY(launch_rmsnorm_bwd_rows(s.y1, w->g_mlp, s.rstd2, k.dh2, dy, T, D, k.dy1, k.h2, k.rms_ws2, st));
   // y1 = x + o Wo^T
   bool stats_done = false;
   {
@@ -324,17 +324,11 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
     const int64_t ns[3] = {QD, KD, KD};
     TRY(gemm_dgrad(3, dys, ws, ns, 0, !direct, T, D, k.dh1, D, st));
   }
-  TRY(launch_rmsnorm_bwd_rows(x, w->g_attn, s.rstd1, k.dh1, k.dy1, T, D, dx, k.rms_ws1, st));
-  // Recomputing configurations: the normalised activations and the SwiGLU output are only operands of
-  // the weight gradients; they are rebuilt here from x, y1 (with the saved statistics) and from g, u.
-  if (!s.h1) {
-    s.h1 = k.h1; s.h2 = k.h2;
-    TRY(launch_rmsnorm_fwd_pair(x, w->g_attn, s.h1, s.rstd1, s.y1, w->g_mlp, s.h2, s.rstd2, T, D, cfg->rms_eps, st));
-  }
-  if (!s.a) {
-    s.a = k.a;
-    TRY(launch_swiglu_fwd_rows(s.g, s.u, T, F, F, s.a, Fp, st));
-  }
+  TRY(launch_rmsnorm_bwd_rows(x, w->g_attn, s.rstd1, k.dh1, k.dy1, T, D, dx, k.h1, k.rms_ws1, st));
+  // Recomputing configurations: the normalised activations and the SwiGLU output are only operands of the weight gradients;
+  // the launches above that read x and y1 (with the saved statistics), and g and u, have rebuilt them in passing.
+  if (!s.h1) { s.h1 = k.h1; s.h2 = k.h2; }
+  if (!s.a) s.a = k.a;
   // All seven weight gradients in one grid: every operand (saved activations, the gradient buffers
   // of the workspace, dy) is still alive here, and one launch fills the chip evenly where the
   // separate products leave partly filled rounds (and two of them are too small to fill it at all).
@@ -543,9 +537,9 @@ int linear_swiglu_backward(const void* dy, const void* w_down, const void* g, co
   REQUIRE_PTR(workspace);
   TRY(check_device());
   hipStream_t st = (hipStream_t)stream;
-  if (weights_as_stored(T, F, D * F)) return launch_gemm_swiglu_grad(dy, D, w_down, false, F, T, D, F, g, u, F, dg, du, F, st);
+  if (weights_as_stored(T, F, D * F)) return launch_gemm_swiglu_grad(dy, D, w_down, false, F, T, D, F, g, u, F, dg, du, F, nullptr, st);
   TRY(launch_transpose(w_down, workspace, D, F, D, st));
-  return launch_gemm_swiglu_grad(dy, D, workspace, true, D, T, D, F, g, u, F, dg, du, F, st);
+  return launch_gemm_swiglu_grad(dy, D, workspace, true, D, T, D, F, g, u, F, dg, du, F, nullptr, st);
 }
 
 int linear_wgrad_group(int32_t n, const void* const* dy, const void* const* x, const int64_t* N, const int64_t* K,

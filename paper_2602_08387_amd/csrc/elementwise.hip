@@ -10,12 +10,11 @@
 namespace dl {
 
 // ------------------------------------------------------------------------------------------
-// RMSNorm forward: one wavefront per token row, the row stays in registers.  A launch takes one or two norms of the
-// same shape, and may carry the rotary table (the angles as cos and sin for the kernels that rotate inside another
-// pass, the q/k projection epilogue and the attention backward stores) on workgroups of its own behind them: for
-// small layers a launch costs more than its work (5 us each for the table and for the second norm at T = 1920).
+// RMSNorm forward: one wavefront per token row, the row stays in registers.  A launch may carry the rotary table (the
+// angles as cos and sin for the kernels that rotate inside another pass, the q/k projection epilogue and the attention
+// backward stores) on workgroups of its own behind the rows: for small layers a launch costs more than its work (5 us
+// for the table at T = 1920).
 // ------------------------------------------------------------------------------------------
-struct RmsFwdJob { const bf16_t *x, *gamma; bf16_t* h; float* rstd; };
 struct RopeTableJob { float *cs, *sn; int seq, half; double log2_base; };
 
 // angle p * base^(-i / half) of (position p, pair i) in fp64, stored as fp32 [seq][half]
@@ -30,21 +29,15 @@ __device__ __forceinline__ void rope_table_entry(const RopeTableJob& r, int idx)
 }
 
 template <int NV, bool ROPE>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const RmsFwdJob ja, const RmsFwdJob jb, int blocks, int norms, int64_t T,
-                                                          int D, float eps, const RopeTableJob rope) {
-  int b = blockIdx.x;
+__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16_t* x, const bf16_t* gamma, bf16_t* h, float* rstd,
+                                                          int blocks, int64_t T, int D, float eps, const RopeTableJob rope) {
+  const int b = blockIdx.x;
   if constexpr (ROPE) {
-    if (b >= blocks * norms) {
-      rope_table_entry(rope, (b - blocks * norms) * 256 + (int)threadIdx.x);
+    if (b >= blocks) {
+      rope_table_entry(rope, (b - blocks) * 256 + (int)threadIdx.x);
       return;
     }
   }
-  const bool second = b >= blocks;
-  if (second) b -= blocks;
-  const bf16_t* x = second ? jb.x : ja.x;
-  const bf16_t* gamma = second ? jb.gamma : ja.gamma;
-  bf16_t* h = second ? jb.h : ja.h;
-  float* rstd = second ? jb.rstd : ja.rstd;
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)b * 4 + (threadIdx.x >> 6);
   if (row >= T) return;
@@ -79,12 +72,14 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const RmsFwdJob ja, co
 }
 
 template <bool ROPE>
-static int launch_rms_jobs(const RmsFwdJob& ja, const RmsFwdJob& jb, int norms, int64_t T, int64_t D, float eps,
-                           const RopeTableJob& rope, hipStream_t st) {
+static int launch_rms_fwd(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h, float* rstd,
+                          const RopeTableJob& rope, hipStream_t st) {
   const int nv = (int)((D / 8 + 63) / 64);
   const int64_t blocks = (T + 3) / 4, table = ROPE ? ((int64_t)rope.seq * rope.half + 255) / 256 : 0;
-  dim3 grid((unsigned)(blocks * norms + table)), block(256);
-#define RMS_FWD(NV) hipLaunchKernelGGL((rmsnorm_fwd_kernel<NV, ROPE>), grid, block, 0, st, ja, jb, (int)blocks, norms, T, (int)D, eps, rope)
+  dim3 grid((unsigned)(blocks + table)), block(256);
+#define RMS_FWD(NV)                                                                                               \
+  hipLaunchKernelGGL((rmsnorm_fwd_kernel<NV, ROPE>), grid, block, 0, st, (const bf16_t*)x, (const bf16_t*)gamma, \
+                     (bf16_t*)h, rstd, (int)blocks, T, (int)D, eps, rope)
   if (nv <= 1) RMS_FWD(1);
   else if (nv <= 2) RMS_FWD(2);
   else if (nv <= 4) RMS_FWD(4);
@@ -97,18 +92,11 @@ static int launch_rms_jobs(const RmsFwdJob& ja, const RmsFwdJob& jb, int norms, 
 
 int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h,
                        float* rstd, hipStream_t st) {
-  const RmsFwdJob j{(const bf16_t*)x, (const bf16_t*)gamma, (bf16_t*)h, rstd};
-  return launch_rms_jobs<false>(j, j, 1, T, D, eps, RopeTableJob{}, st);
-}
-int launch_rmsnorm_fwd_pair(const void* xa, const void* ga, void* ha, float* ra, const void* xb, const void* gb, void* hb, float* rb,
-                            int64_t T, int64_t D, float eps, hipStream_t st) {
-  const RmsFwdJob ja{(const bf16_t*)xa, (const bf16_t*)ga, (bf16_t*)ha, ra}, jb{(const bf16_t*)xb, (const bf16_t*)gb, (bf16_t*)hb, rb};
-  return launch_rms_jobs<false>(ja, jb, 2, T, D, eps, RopeTableJob{}, st);
+  return launch_rms_fwd<false>(x, gamma, T, D, eps, h, rstd, RopeTableJob{}, st);
 }
 int launch_rmsnorm_fwd_rope_table(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h, float* rstd, float* cos,
                                   float* sin, int64_t seq, int64_t head_dim, float base, hipStream_t st) {
-  const RmsFwdJob j{(const bf16_t*)x, (const bf16_t*)gamma, (bf16_t*)h, rstd};
-  return launch_rms_jobs<true>(j, j, 1, T, D, eps, RopeTableJob{cos, sin, (int)seq, (int)(head_dim / 2), log2((double)base)}, st);
+  return launch_rms_fwd<true>(x, gamma, T, D, eps, h, rstd, RopeTableJob{cos, sin, (int)seq, (int)(head_dim / 2), log2((double)base)}, st);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -117,12 +105,15 @@ int launch_rmsnorm_fwd_rope_table(const void* x, const void* gamma, int64_t T, i
 // registers, folds its groups through LDS and writes one fp32 partial row; a second kernel sums the partial
 // rows.  Bound by HBM (8 bytes per element with the residual gradient).  A thread holds one vector of a row where a wave
 // held the whole row, in 100 to 128 registers for its two rows, and the residual row is asked for together with the
-// others; rows of any width are read once.
+// others; rows of any width are read once.  h, if asked for, is the forward's output again (the same bits: the same three
+// factors in the same order), at the cost of its stores, where a pass of its own reads x again (5.8 us and a launch for the
+// two norms of 1920 x 1152).
 // ------------------------------------------------------------------------------------------
 template <int TPR, int NV, int RG>
 __global__ __launch_bounds__(TPR * RG) void rmsnorm_bwd_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma, const float* __restrict__ rstd,
-    const bf16_t* __restrict__ dh, const bf16_t* dres, bf16_t* dx, float* __restrict__ partial, int64_t T, int D) {
+    const bf16_t* __restrict__ dh, const bf16_t* dres, bf16_t* dx, bf16_t* __restrict__ h, float* __restrict__ partial,
+    int64_t T, int D) {
   constexpr int WPR = TPR / 64, U = NV == 1 ? 2 : 1;
   __shared__ float red[2][RG][U][WPR];
   __shared__ float fold[RG > 1 ? RG * TPR * NV * 8 : 1];
@@ -207,6 +198,11 @@ __global__ __launch_bounds__(TPR * RG) void rmsnorm_bwd_kernel(
             o[e] = (bf16_t)(r[u] * ((float)dv[u][i][e] * gv[i][e] - xh * mean) + (float)rv[u][i][e]);
           }
           reinterpret_cast<bf16x8*>(dx + row * D)[c] = o;
+          if (h) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)xv[u][i][e] * r[u] * gv[i][e]);
+            reinterpret_cast<bf16x8*>(h + row * D)[c] = o;
+          }
         }
       }
     }
@@ -253,12 +249,12 @@ size_t rmsnorm_bwd_workspace(int64_t T, int64_t D) { return (size_t)rms_bwd_bloc
 // threads: T 2048 17.7 / 16.2, T 4096 25.3 / 27.6).  With 256 threads and up to 1024 partial rows: D 2048 T 8192 27.7
 // against 24.8, D 768 T 8192 14.3 against 13.0.
 int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd, const void* dh,
-                            const void* dres, int64_t T, int64_t D, void* dx, void* workspace, hipStream_t st) {
+                            const void* dres, int64_t T, int64_t D, void* dx, void* h, void* workspace, hipStream_t st) {
   const int nb = rms_bwd_blocks(T);
   float* partial = (float*)workspace;
 #define RMS_BWD(TPR, NV, RG)                                                                                   \
   hipLaunchKernelGGL((rmsnorm_bwd_kernel<TPR, NV, RG>), dim3(nb), dim3(TPR * RG), 0, st, (const bf16_t*)x,      \
-                     (const bf16_t*)gamma, rstd, (const bf16_t*)dh, (const bf16_t*)dres, (bf16_t*)dx, partial, T, (int)D)
+                     (const bf16_t*)gamma, rstd, (const bf16_t*)dh, (const bf16_t*)dres, (bf16_t*)dx, (bf16_t*)h, partial, T, (int)D)
   if (D <= 512) RMS_BWD(64, 1, 8);
   else if (D <= 1024) RMS_BWD(128, 1, 4);
   else if (D <= 2048) RMS_BWD(256, 1, 2);
@@ -285,7 +281,7 @@ int launch_rmsnorm_bwd_gain(const void* ws_a, void* dgamma_a, const void* ws_b, 
 int launch_rmsnorm_bwd(const void* x, const void* gamma, const float* rstd, const void* dh,
                        const void* dres, int64_t T, int64_t D, void* dx, void* dgamma,
                        int accumulate, void* workspace, hipStream_t st) {
-  if (int rc = launch_rmsnorm_bwd_rows(x, gamma, rstd, dh, dres, T, D, dx, workspace, st)) return rc;
+  if (int rc = launch_rmsnorm_bwd_rows(x, gamma, rstd, dh, dres, T, D, dx, nullptr, workspace, st)) return rc;
   return launch_rmsnorm_bwd_gain(workspace, dgamma, nullptr, nullptr, T, D, accumulate, st);
 }
 

@@ -996,7 +996,7 @@ int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* w
 
 int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_kmajor, int64_t ldw, int64_t T, int64_t K, int64_t F,
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
-                            hipStream_t st) {
+                            void* a, hipStream_t st) {
   GemmKArgs k{};
   k.nseg = 1;
   k.a[0] = (const bf16_t*)dy;
@@ -1012,6 +1012,18 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_
   k.e1 = (const bf16_t*)g;
   k.e2 = (const bf16_t*)u;
   k.lde = ldgu;
+  if (!a) return run_gemm(&k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, st);
+  GemmPlan p;
+  plan_gemm(p, &k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, compute_units());
+  // The one-tile kernels' epilogue has g and u at hand and writes a as well; with the norms' outputs from their backward
+  // that takes a layer of 1920 tokens, D 1152, F 3136, two micro-batches, from 664 to 641 us.  On the persistent kernel a
+  // third run of stores would go out behind the next tile's loads, more than the wait counter can tell apart (63), and a
+  // launch of its own is a hundredth of the step.
+  if (p.first != kPersistent) {
+    k.c3 = (bf16_t*)a;
+    return launch_gemm_tile((TileSize)p.first, &k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, st);
+  }
+  if (int rc = launch_swiglu_fwd_rows(g, u, T, F, ldgu, a, ldd, st)) return rc;
   return run_gemm(&k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, st);
 }
 

@@ -37,7 +37,7 @@ struct GemmKArgs {
   const bf16_t* b2;
   bf16_t *c2, *c3;
   int64_t ldc3;
-  // activation-gradient epilogue only (see EPI_SWIGLU_GRAD)
+  // activation-gradient epilogue only (see EPI_SWIGLU_GRAD); the one-tile kernels write silu(e1) * e2 to c3 unless it is null
   const bf16_t *e1, *e2;
   int64_t lde;
   // rotary epilogue only (see EPI_ROPE): rotate this problem's output

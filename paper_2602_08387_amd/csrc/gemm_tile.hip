@@ -179,10 +179,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
       unpack8(*reinterpret_cast<const bf16x8*>(one.e2 + (int64_t)m * one.lde + n), u);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float sg = logistic(z[e]), dz = d[e] * u[e] * sg * (1.0f + z[e] * (1.0f - sg));
+        const float sg = logistic(z[e]), dz = d[e] * u[e] * sg * (1.0f + z[e] * (1.0f - sg)), a = z[e] * sg * u[e];
         u[e] = d[e] * z[e] * sg;
         d[e] = dz;
+        z[e] = a;
       }
+      if (one.c3) *reinterpret_cast<bf16x8*>(one.c3 + (int64_t)m * ldc + n) = pack8(z);
       *reinterpret_cast<bf16x8*>(cmat + (int64_t)m * ldc + n) = pack8(d);
       *reinterpret_cast<bf16x8*>(one.c2 + (int64_t)m * ldc + n) = pack8(u);
     } else {

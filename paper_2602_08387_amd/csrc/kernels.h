@@ -11,17 +11,14 @@ namespace dl {
 // ---- elementwise.hip
 int launch_rmsnorm_fwd(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h,
                        float* rstd, hipStream_t st);
-// two norms of one shape in one launch
-int launch_rmsnorm_fwd_pair(const void* xa, const void* ga, void* ha, float* ra, const void* xb, const void* gb, void* hb, float* rb,
-                            int64_t T, int64_t D, float eps, hipStream_t st);
 // a norm and the rotary table (launch_rope_table) in one launch
 int launch_rmsnorm_fwd_rope_table(const void* x, const void* gamma, int64_t T, int64_t D, float eps, void* h, float* rstd, float* cos,
                                   float* sin, int64_t seq, int64_t head_dim, float base, hipStream_t st);
 size_t rmsnorm_bwd_workspace(int64_t T, int64_t D);
 // the two halves of launch_rmsnorm_bwd: dx and the partial rows in `workspace`; then dgamma from them, of one norm or
-// (ws_b, dgamma_b not null) two of the same shape
+// (ws_b, dgamma_b not null) two of the same shape.  h (or null): the forward's output, written again from x and rstd
 int launch_rmsnorm_bwd_rows(const void* x, const void* gamma, const float* rstd, const void* dh,
-                            const void* dres, int64_t T, int64_t D, void* dx, void* workspace, hipStream_t st);
+                            const void* dres, int64_t T, int64_t D, void* dx, void* h, void* workspace, hipStream_t st);
 // The second half as an argument for a launch that has room for it: column sums of nrows partial rows of D, one norm or (b not
 // null) two
 struct GainSums { const float *pa, *pb; void *outa, *outb; int nrows, D, accumulate; };
@@ -99,10 +96,11 @@ int launch_gemm_group_rope(const GemmArgs* gs, int n, const RopeEpilogue* rope, 
 int launch_gemm_swiglu(const void* x, int64_t ldx, const void* wg, const void* wu, int64_t ldw, int64_t T, int64_t K,
                        int64_t F, void* g, void* u, int64_t ldgu, void* a, int64_t lda, hipStream_t st);
 // da = dy W^T for dy [T, K] (lddy) and W stored [F, K] (w_kmajor) or [K, F] with ldw, then (dg, du) = gradient of silu(g) * u for
-// the fp32 da, which is never stored.  g, u with ldgu; dg, du with ldd.
+// the fp32 da, which is never stored.  g, u with ldgu; dg, du with ldd.  a (or null): silu(g) * u, written again, with ldd, as
+// launch_swiglu_fwd_rows does.
 int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_kmajor, int64_t ldw, int64_t T, int64_t K, int64_t F,
                             const void* g, const void* u, int64_t ldgu, void* dg, void* du, int64_t ldd,
-                            hipStream_t st);
+                            void* a, hipStream_t st);
 
 // Which kernels a product, or a group, of these sizes runs on: see gemm_route in dlayer.h.  Nothing is launched.
 enum { GEMM_ROUTE_K_K = 0, GEMM_ROUTE_K_MN = 1, GEMM_ROUTE_MN_MN = 2 };

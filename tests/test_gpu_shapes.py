@@ -324,6 +324,40 @@ def test_layer_with_row_statistics_in_the_epilogue(K, shape, stored, tile):
     _check_layer(g, f, r, "statistics")
 
 
+# batch, seq, width, query heads, KV heads, head width, d_ff; weights as stored; kernel of the gated gradient
+REBUILT = [
+    ((1, 128, 192, 2, 1, 64, 320), True, T64),         # a wave per row of the norm
+    ((1, 256, 576, 2, 1, 64, 192), False, T64),
+    ((5, 384, 1088, 1, 1, 64, 1216), False, T128),     # ragged tiles, two waves share a row's end
+    ((8, 1024, 320, 2, 1, 128, 832), False, T128X256),
+    ((1, 2176, 2112, 1, 1, 64, 64), False, T64),       # more rows than one per compute unit at a time
+    ((1, 256, 2112, 1, 1, 64, 64), False, T64),        # two rows to a workgroup
+    ((1, 128, 4160, 1, 1, 64, 64), False, T64),
+    ((1, 128, 8256, 1, 1, 64, 64), False, T64),        # two vectors of a row per thread
+    ((8, 2048, 128, 2, 1, 64, 1024), False, PERSISTENT),   # a in a launch of its own
+]
+
+
+@pytest.mark.parametrize("shape,stored,kernel", REBUILT)
+def test_activations_rebuilt_in_passing(K, shape, stored, kernel):
+    """recompute: the norms' backward writes h1 and h2 again (same bits), the gated gradient's epilogue a."""
+    B, S, D, Hq, Hkv, dh, F = shape
+    T = B * S
+    assert stored == (D * max(F, Hq * dh) <= 65536 and T <= 4096)
+    assert K.gemm_route(1 if stored else 0, 2, [T], [F], [D], compute_units=256)[0] == kernel
+    cfg = si.CONFIGS["tiny"].with_(batch=B, seq=S, d_model=D, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=F)
+    inp = si.make_layer_inputs(cfg, seed=7)
+    f, r = _oracle(cfg, inp)
+    a, b = GpuLayer(K, cfg, inp), GpuLayer(K, cfg.with_(recompute=3), inp)
+    for g in (a, b):
+        g.forward()
+        g.backward()
+    torch.cuda.synchronize()
+    _check_layer(b, f, r, "rebuilt")
+    for n, p, q in [("dx", a.dx, b.dx)] + [(n, a.dw[n], b.dw[n]) for n in si.WEIGHT_NAMES if n != "w_down"]:
+        assert torch.equal(p.view(torch.int16), q.view(torch.int16)), f"{n} differs between keeping and rebuilding"
+
+
 def test_layer_with_short_segments_on_full_tiles(K):
     """The fused input gradients on 256 x 256 tiles with segments of one and of three K-steps: walks that start in any segment
     (a row group of 2048 starts its eighth of the way further on), odd and even, over more than one round of tiles."""
