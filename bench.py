@@ -26,7 +26,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
 # run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
 # counters were taken on: reported as null when gemm.hip or gemm_core.h has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "9b93a098540b4ccc283c30b15dec481e0665133d8fc405a228b4868ed656ced2",
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "1cb38a1c63556cd07cf5229c4a2aa5602529e8454866eacc6f489151ed831334",
                 "fetch_bytes": 1.496e+09, "write_bytes": 2.013e+08}
 
 
@@ -464,7 +464,7 @@ def main():
     torch.cuda.synchronize()
     total_ms = sum(a.elapsed_time(b) for a, b in dur_ms)
     achieved = gemm_flops / (total_ms * 1e-3) / 1e12
-    roofline = {"bound": "mfma", "kernel": "gemm_kernel<256,256,2,4,k-major,k-major> (the layer's 7 projection shapes)",
+    roofline = {"bound": "mfma", "kernel": "gemm_kernel<true> (both operands k-major; the layer's 7 projection shapes)",
                 "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                 "avg_launch_ms": total_ms / len(dur_ms), "launches_timed": len(dur_ms),
                 "traffic": _gemm_traffic(args.config), "traffic_unit": "HBM bytes per launch (fetched + written)",

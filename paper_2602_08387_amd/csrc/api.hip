@@ -188,9 +188,10 @@ static int gemm_dgrad(int nseg, const void* const* dy, const void* const* w, con
 // Whether the input gradient [T, K] of a product reads its weights as they are stored, not through a transposed copy.
 // The copy costs a launch and a read and a write of the weights; reading W[N, K] across its rows costs the product 5 to
 // 10 % (transposing LDS reads), which grows with T.  The whole call with the copy and without, us, measured for
-// (T, K, N): linear_backward (2048,1024,1024) 13.8 / 9.9, (512,2048,2048) 18.0 / 12.5, (2048,4096,14336) 258 / 182,
-// (4096,2048,2048) 37.0 / 31.2, (2048,14336,4096) 208 / 211, (4096,4096,4096) 103 / 108, (4160,4416,4288) 137 / 156;
-// lm_head_ce_fwd_bwd (448,2176,33088) 443 / 365, (4096,1024,64000) 1816 / 1778, (4096,4096,128256) 10260 / 10397.
+// (T, K, N): linear_backward (512,2048,2048) 15.7 / 10.0, (2048,4096,14336) 233 / 173, (4096,4096,4096) 102 / 107, and,
+// before the tile kernels had loading waves, (2048,1024,1024) 13.8 / 9.9, (4096,2048,2048) 37.0 / 31.2,
+// (2048,14336,4096) 208 / 211, (4160,4416,4288) 137 / 156; lm_head_ce_fwd_bwd (448,2176,33088) 443 / 365,
+// (4096,1024,64000) 1816 / 1778, (4096,4096,128256) 10260 / 10397.
 // The weights are one buffer of a workgroup's loads, whose offsets have 32 bits: at most 2 GiB.
 static bool weights_as_stored(int64_t T, int64_t K, int64_t weight_numel) {
   return T <= 4096 && T * K <= (int64_t)4096 * 2048 && weight_numel <= ((int64_t)1 << 30);
@@ -290,8 +291,8 @@ int dlayer_backward(const dlayer_cfg* cfg, const void* x, const dlayer_weights* 
   const int64_t Fp = padded_ff(cfg);
   // A call that reuses the copies pays for none, and which call will follow is not known here; one that reads the
   // weights as stored is as fast as such a call only where the products are all launch latency.  The call with copies,
-  // reusing them, and without, us: D 128, F 384, 128 tokens 50.9 / 46.9 / 47.3; D 256, F 704, 256 tokens 59.0 / 54.4 /
-  // 55.3; D 2048, F 5632, 2048 tokens 620 / 589 / 616; D 4096, F 14336, 256 tokens 816 / 639 / 678.
+  // reusing them, and without, us: D 128, F 384, 128 tokens 41.9 / 38.1 / 38.1; D 256, F 704, 256 tokens 51.5 / 46.9 /
+  // 47.3; D 2048, F 5632, 2048 tokens 590 / 558 / 590; D 4096, F 14336, 256 tokens 759 / 568 / 611.
   const int64_t widest = D * (F > QD ? F : QD);
   const bool direct = widest <= 65536 && weights_as_stored(T, D, widest);
   if (!direct && !(flags & DLAYER_REUSE_TRANSPOSED_WEIGHTS)) {
@@ -370,8 +371,8 @@ static int64_t lm_head_chunk(int64_t T, int64_t D, int64_t V, int64_t chunk_rows
   if (c <= 0) {
     // About 1 GiB of logits.  2 GiB where the input gradient of such a chunk [c, D] has fewer than 256 tiles of
     // 256 x 256, one per compute unit: every chunk also re-reads and re-rounds the weight gradient.  T = 8192,
-    // V = 128256, chunks of 4096 / 8192 rows, ms: D = 1024 7.0 / 6.2, 2048 11.4 / 10.7, 3072 17.4 / 16.2; at D = 4096,
-    // where the tiles of 4096 rows are all there, 20.6 / 20.2 and half the scratch.
+    // V = 128256, chunks of 4096 / 8192 rows, ms: D = 1024 6.6 / 5.9, 2048 10.7 / 9.8, 3072 15.1 / 15.4 (17.4 / 16.2 when
+    // the line was drawn); at D = 4096, where the tiles of 4096 rows are all there, 18.9 / 18.6 and half the scratch.
     const int64_t gib1 = ((int64_t)1 << 30) / (V * 2) / 256 * 256, gib2 = ((int64_t)1 << 31) / (V * 2) / 256 * 256;
     c = gib1 * D < (int64_t)256 * 256 * 256 ? gib2 : gib1;
     if (c < 256) c = 256;

@@ -703,10 +703,9 @@ __global__ __launch_bounds__(512) void gemm_group_rope_kernel(const GemmGroupKAr
 // Tile rows per band of the tile sequence.  An XCD runs some 32 consecutive tiles at a time: 8 rows x 4
 // columns of tiles with bands of 8, 4 x 8 with bands of 4 - twelve operand panels either way, but the
 // wider arrangement touches longer runs of every C row (and of the g, u rows the activation-gradient
-// epilogue reads).  Measured at the 8B shape, per launch: bands of 8 are 1-2.5 % faster for k-major
-// products with K <= 4096 (q/k/v, o, gate/up forward, o input gradient), bands of 4 are 1-4 % faster for
-// the long contractions (down projection, fused input gradients: +6-8 % at K = 8192), the
-// activation-gradient epilogue and the weight gradients; bands of 2 or 16 lose everywhere.
+// epilogue reads).  us, bands of 8 / 4, T = 16384: K = 4096, N = 14336 1280 / 1289, N = 4096 381 / 383, gated pair 2652 / 2663;
+// K = 14336, N = 4096 1316 / 1280, K = 28672 2729 / 2661; activation gradient 1590 / 1577; weight gradient 14336 x 4096
+// 1427 / 1398, of T = 8192 128256 x 2048 3240 / 3147.  (On an earlier loop bands of 2 or 16 lost everywhere.)
 static int band_rows_for(bool both_kmajor, int64_t k_total, bool epilogue_reads_tiles) {
   return both_kmajor && !epilogue_reads_tiles && k_total <= 4096 ? 8 : 4;
 }
@@ -794,8 +793,10 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
 // (a CU runs faster while others idle: clock, L2) - and the cheapest runs: the persistent kernel, one of the three
 // tile sizes of gemm_tile.hip, or the persistent kernel for its full rounds and a smaller tile, in a second
 // launch, for the rows left over.  All give the same bits.  Microseconds, from sweeps on MI355X
-// (both operands k-major / an operand mn-major); per_cu: tiles of a compute unit in flight.  The estimates are within 10 % of
-// the measured launches from 15 us up (256 compute units).
+// (both operands k-major / an operand mn-major); per_cu: tiles of a compute unit in flight.  The constants, and the launches
+// beside them, were taken before the wave groups and the loading waves; now the kernels are up to 25 % quicker, all of them,
+// and over 115 products (256 compute units) the choice is on average 0.5 % (k-major), 1.4 % (mn-major) and 0.4 % (mixed) behind
+// the best kernel.
 // ------------------------------------------------------------------------------------------
 struct KernelCost { int bm, bn, per_cu; double lo, hi, tile; };
 constexpr int kPersistent = 3;
