@@ -29,6 +29,7 @@
 // the tile through LDS so that global stores (and residual loads) are 16 bytes per lane along
 // rows of C.
 #include "gemm_core.h"
+#include "gemm_schedule.h"
 
 namespace dl {
 
@@ -64,6 +65,7 @@ enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_GRAD = 2, EPI_ROPE = 3 };
 
 constexpr int PM = 256, PN = 256, PWM = 2, PWN = 4;   // tile and waves
 constexpr int STAGE = (PM + PN) * BK * 2, HALF = STAGE / 4, NS = 2;
+static_assert(HALF == LOADS_PER_HALF * PWM * PWN * 1024, "a half tile is sent by all waves, 1 KiB per load");
 
 // The lane number, anew.  What the compiler computes from one that it knows is lifted out of the tile loop and spilled across the
 // main loop, and its reload (counted in order behind the next tile's loads) then waits for all of those.
@@ -290,31 +292,25 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
   Tile tl = locate(id, start), next = tl;
   cur.begin(start, tl.total, wave);
   const int pa = Stream::a_part(wave), pb = Stream::b_part(wave);
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    cur.template issue<true, 0>(smem + t * STAGE + pa);
-    cur.template issue<false, 0>(smem + t * STAGE + pb);
-    cur.template issue<false, 1>(smem + t * STAGE + pb);
-    cur.template issue<true, 1>(smem + t * STAGE + pa);
-    cur.advance(one, wave);
-  }
+  first_loads(
+      tl.total & 1,
+      [&](auto T, auto H) {
+        constexpr int h = decltype(H)::value;
+        cur.template issue<(h < HALF_B0), h & 1>(smem + decltype(T)::value * STAGE + (h < HALF_B0 ? pa : pb));
+      },
+      [&] { cur.advance(one, wave); });
   bool more = id + step < ntiles;
   if (more) next = locate(id + step, start);
 
-  // The tile's first K-step has landed (this wave's loads), and of its second what the first three phases of the main loop
-  // are not going to wait for: its first two halves, in the order in which a tile of an even (odd) number of K-steps needs
-  // them.  AFTER: stores that went out behind the loads.
+  // Wait for the next tile's first loads (in_flight_landed).  AFTER: stores that went out behind them.
   auto landed = [&](int total, auto after) {
     constexpr int AFTER = decltype(after)::value;
-    if (total & 1) wait_vmcnt<2 + AFTER>(); else wait_vmcnt<4 + AFTER>();
+    if (total & 1) wait_vmcnt<in_flight_landed(true) + AFTER>(); else wait_vmcnt<in_flight_landed(false) + AFTER>();
   };
-  constexpr std::integral_constant<int, 0> C0{};
-  constexpr std::integral_constant<int, 1> C1{};
-  constexpr std::integral_constant<int, 2> C2{};
-  constexpr std::integral_constant<int, 3> C3{};
-  constexpr std::integral_constant<int, EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_GRAD ? 32 : 16> STORES{};   // of a wave, of a whole tile
-  wait_vmcnt<10>();   // first tile: A half 0 and the B halves of K-step 0
-  int waits_from = 0;   // K-step from which on the first three phases of a K-step wait for loads
+  constexpr Int<0> C0{};
+  constexpr Int<EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_GRAD ? 32 : 16> STORES{};   // of a wave, of a whole tile
+  wait_vmcnt<IN_FLIGHT_FIRST>();
+  int waits_from = 0;   // see tile_k_steps
 
   // Lane's place in a fragment.  k-major: rows of 128 bytes, the second 32 k at this ^ 64.  mn-major: rows of 256 bytes (one k),
   // block f of 16 at this ^ 32 f.
@@ -346,19 +342,15 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
         for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
         asm volatile("" : "+v"(acc[i][j]));   // zeroed here, not in front of the first MFMA (see mfma_quadrant)
       }
-    // K-step 0 has landed in every wave's share; the barrier makes it visible to all waves
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-
     bf16x8 fa[2][FM], fb[2][FN];
-    // half H & 1 of the wave's A (H < 2) or B fragments
-    auto reads = [&](auto H, uint32_t st) {
+    // the wave's A or B fragments of half H
+    auto read = [&](auto H, auto NEXT) {
       constexpr int h = decltype(H)::value & 1;
-      constexpr bool A = decltype(H)::value < 2;
+      constexpr bool A = decltype(H)::value < HALF_B0;
       constexpr int F = A ? FM : FN;
       auto& a = fa;
       auto& b = fb;
-      const uint32_t at = (A ? lane_a : lane_b) + st;
+      const uint32_t at = (A ? lane_a : lane_b) + (decltype(NEXT)::value ? STAGE - cs : cs);
       static_for<0, 2>([&](auto kk_c) {
         constexpr int kk = decltype(kk_c)::value;
         static_for<0, F / 2>([&](auto f_c) {
@@ -369,9 +361,11 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
         });
       });
     };
-    auto tie = [&](auto H) {
+    // waits for this wave's LDS reads and makes the half's fragments depend on it
+    auto arrived = [&](auto H) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       constexpr int h = decltype(H)::value & 1;
-      constexpr bool A = decltype(H)::value < 2;
+      constexpr bool A = decltype(H)::value < HALF_B0;
       constexpr int F = A ? FM : FN;
       auto& a = fa;
       auto& b = fb;
@@ -383,61 +377,28 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
           asm volatile("" : "+v"(v));
         }
     };
-    // waits for this wave's LDS reads and makes the half's fragments depend on it
-    auto arrived = [&](auto H) {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      tie(H);
+    auto send = [&](auto H) {
+      constexpr int h = decltype(H)::value;
+      cur.template issue<(h < HALF_B0), h & 1>(smem + cs + (h < HALF_B0 ? pa : pb));
     };
-    // One K-step in four phases, one quadrant of the wave's tile each: A0 Bq, A0 Bq', A1 Bq', A1 Bq (q' = 1 - q).  A phase is a
-    // slot of memory work (fragments for the next phase, one half of the K-step after next) and a slot of MFMAs; the wave
-    // groups are a slot apart, so one feeds the matrix pipes while the other reads and loads.  Q = 1 for the last K-step
-    // and every other before it, so that the next K-step's first B half can be read before this one's last is done with.
-    auto kstep = [&](auto Q, int t) {
-      constexpr int q = decltype(Q)::value;
-      if (q == 0 && t == total - 2) {   // every load of this tile is out: on to the next one's
-        if (more) cur.begin(start, next.total, wave); else cur.close();
-      }
-      static_for<0, 4>([&](auto P) {
-        constexpr int ph = decltype(P)::value;
-        constexpr int h = ph == 0 ? 3 - q : ph == 1 ? 1 : ph == 2 ? 0 : 3 - q;
-        constexpr std::integral_constant<int, h> H{};
-        reads(H, ph < 2 ? cs : STAGE - cs);
-        // the half of this stage that every wave has read since two phases
-        if constexpr (ph == 0) cur.template issue<true, 0>(smem + cs + pa);
-        if constexpr (ph == 1) cur.template issue<false, q>(smem + cs + pb);
-        if constexpr (ph == 2) cur.template issue<false, 1 - q>(smem + cs + pb);
-        if constexpr (ph == 3) cur.template issue<true, 1>(smem + cs + pa);
-        // The half that the next phase reads went out six phases ago, five halves are younger.  (In a workgroup's later
-        // tiles what the first three phases read has landed; waiting there would be for the last tile's stores.)
-        if (ph == 3 || t >= waits_from) wait_vmcnt<10>();
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        constexpr int i = (ph == 0 || ph == 3 ? q : 1 - q) * FN / 2, j = ph < 2 ? 0 : FM / 2;
-        mfma_quadrant(acc[i][j], acc[i + 1][j], acc[i][j + 1], acc[i + 1][j + 1], acc[i][j + 2], acc[i + 1][j + 2], acc[i][j + 3],
-                      acc[i + 1][j + 3], fb[0][i], fb[0][i + 1], fb[1][i], fb[1][i + 1], fa[0][j], fa[0][j + 1], fa[0][j + 2], fa[0][j + 3],
-                      fa[1][j], fa[1][j + 1], fa[1][j + 2], fa[1][j + 3]);
-        __builtin_amdgcn_sched_barrier(0);
-        arrived(H);
-        __builtin_amdgcn_s_barrier();
-        if constexpr (ph == 3) cur.advance(one, wave);
-        asm volatile("" ::: "memory");
-      });
-      cs = STAGE - cs;
+    auto barrier = [&] {
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
     };
-    const bool odd = total & 1;
-    reads(C0, cs);
-    if (odd) reads(C3, cs); else reads(C2, cs);
-    arrived(C0);
-    tie(C2);
-    tie(C3);
-    __builtin_amdgcn_s_barrier();   // before the first load into this stage
-    if (behind) __builtin_amdgcn_s_barrier();
-    if (odd) kstep(C1, 0);
-    for (int t = odd; t < total; t += 2) {
-      kstep(C0, t);
-      kstep(C1, t + 1);
-    }
-    if (!behind) __builtin_amdgcn_s_barrier();
+    auto multiply = [&](auto Q, auto PHASE) {
+      constexpr int q = decltype(Q)::value, ph = decltype(PHASE)::value;
+      constexpr int i = (ph == 0 || ph == 3 ? q : 1 - q) * FN / 2, j = ph < 2 ? 0 : FM / 2;
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_quadrant(acc[i][j], acc[i + 1][j], acc[i][j + 1], acc[i + 1][j + 1], acc[i][j + 2], acc[i + 1][j + 2], acc[i][j + 3],
+                    acc[i + 1][j + 3], fb[0][i], fb[0][i + 1], fb[1][i], fb[1][i + 1], fa[0][j], fa[0][j + 1], fa[0][j + 2], fa[0][j + 3],
+                    fa[1][j], fa[1][j + 1], fa[1][j + 2], fa[1][j + 3]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // One wave group feeds the matrix pipes while the other, a slot apart, reads and loads.
+    auto ops = wave_ops(read, arrived, send, [&] { wait_vmcnt<IN_FLIGHT_PHASE>(); }, barrier, multiply,
+                        [&] { if (more) cur.begin(start, next.total, wave); else cur.close(); },
+                        [&] { cur.advance(one, wave); }, [&] { cs = STAGE - cs; });
+    tile_k_steps(ops, total, behind, waits_from);
     mfma_drain();
 
     // Waiting for the next tile's loads behind the epilogue's stores takes a known number of them: where the tile lies inside C.
