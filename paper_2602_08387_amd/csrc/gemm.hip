@@ -131,7 +131,7 @@ struct LoadStream {
   __device__ __forceinline__ void close() {
     ra = rb = make_rsrc(nullptr, 0);
     if constexpr (PAIR) rb2 = ra;
-    left = 1 << 30;
+    left = LEFT_CLOSED;
     pad = false;
   }
   static __device__ __forceinline__ int a_part(int wave) { return KM ? (wave >> 2) * 16384 + (wave & 3) * 1024 : wave * 1024; }
@@ -165,7 +165,7 @@ struct LoadStream {
       sa = sa0;
       sb = sb0;
       if constexpr (SEGS) {
-        if (p.nseg > 1 && left > 0) {
+        if (p.nseg > 1 && opens_segment(left)) {
           StreamStart s;
           s.seg = seg + 1 == p.nseg ? 0 : seg + 1;
           open_segment(s, p, m0, n0);

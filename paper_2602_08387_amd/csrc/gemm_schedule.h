@@ -35,6 +35,11 @@ constexpr int IN_FLIGHT_FIRST = 5 * LOADS_PER_HALF;
 // halves (three where K-step 0 has q = 1).
 constexpr int in_flight_landed(bool odd) { return (odd ? 1 : 2) * LOADS_PER_HALF; }
 
+// K-steps that a stream of loads has left.  Past the end of a K-segment it opens the next one, but not behind the workgroup's last tile, where
+// loads go on and bring zeros so that the main loop counts them as ever.
+constexpr int LEFT_CLOSED = 0;
+constexpr bool opens_segment(int left) { return left > 0; }
+
 // What one wave does in the main loop.  read(H, NEXT): the fragments of half H from this K-step's stage of the ring or the next
 // one's; arrived(H): waits for them; send(H): half H into this stage; wait(): until at most IN_FLIGHT_PHASE loads are in flight; barrier():
 // all waves; multiply(Q, PHASE); next_tile(): the loads go on with the workgroup's next tile; next_k(): they go on to the

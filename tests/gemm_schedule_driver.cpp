@@ -114,8 +114,21 @@ static int check(const std::vector<Tile>& tiles, int store_count, int edge_store
   return bad;
 }
 
+// A closed stream opens no segment during the two K-steps of loads that a workgroup's last tile still sends; an open one does until its
+// last K-step is out.
+static int check_close() {
+  int left = LEFT_CLOSED, bad = 0;
+  for (int i = 0; i < 2; ++i)
+    if (opens_segment(--left)) ++bad, std::printf("a closed stream opens a segment\n");
+  for (left = 3; left > 0;) {
+    --left;
+    if (opens_segment(left) != (left != 0)) ++bad, std::printf("an open stream, %d K-steps left\n", left);
+  }
+  return bad;
+}
+
 int main() {
-  int bad = 0, runs = 0;
+  int bad = check_close(), runs = 0;
   for (int stores : {16, 32})
     for (int edge_stores : {0, 5, stores})
       for (int a = 2; a <= 7; ++a)
