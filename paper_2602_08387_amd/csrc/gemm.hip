@@ -399,7 +399,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
                         [&] { if (more) cur.begin(start, next.total, wave); else cur.close(); },
                         [&] { cur.advance(one, wave); }, [&] { cs = STAGE - cs; });
     tile_k_steps(ops, total, behind, waits_from);
-    mfma_drain();
+    mfma_drain(acc);
 
     // Waiting for the next tile's loads behind the epilogue's stores takes a known number of them: where the tile lies inside C.
     const bool inside = m0 + PM <= p.M && n0 + PN <= p.N;

@@ -172,8 +172,16 @@ __device__ __forceinline__ void mfma_quadrant(f32x4& c00, f32x4& c10, f32x4& c01
                : "v"(a00), "v"(a01), "v"(a10), "v"(a11), "v"(b00), "v"(b01), "v"(b02), "v"(b03), "v"(b10), "v"(b11), "v"(b12), "v"(b13));
 #undef MFMA
 }
-// waits until the last MFMA has written its block
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 3" ::: "memory"); }
+// Waits until the last MFMA has written its block, and makes the accumulators depend on the wait: the compiler, which sees no
+// MFMA and no hazard, may otherwise put a read of them in front of it.
+template <int N, int M>
+__device__ __forceinline__ void mfma_drain(f32x4 (&acc)[N][M]) {
+  asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < M; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
 
 // 16 bytes per lane from LDS address `at` + OFF, or transposed 2 x 8 of k-rows r and r + 4, HI bytes apart.  As
 // assembly: for the builtins the compiler cannot tell that a read stays clear of the stage the asynchronous loads are filling

@@ -1,0 +1,48 @@
+"""What the compiler makes of the GEMM's assembly blocks (compiled for gfx950 here, nothing is run)."""
+import os
+import re
+import shutil
+import subprocess
+
+from paper_2602_08387_amd import build as b
+
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+# one block of MFMAs, and its results rounded and stored: the conversions need nothing but the accumulators
+DRAIN = """
+#include "gemm_core.h"
+using namespace dl;
+__global__ __launch_bounds__(512) void drained(const bf16x8* in, bf16_t* out, int n) {
+  f32x4 acc[2][4];
+  for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+  const int l = threadIdx.x;
+  for (int k = 0; k < n; ++k) {
+    const bf16x8* p = in + (size_t)k * 512 * 12 + l;
+    mfma_quadrant(acc[0][0], acc[1][0], acc[0][1], acc[1][1], acc[0][2], acc[1][2], acc[0][3], acc[1][3], p[0], p[512], p[1024], p[1536],
+                  p[2048], p[2560], p[3072], p[3584], p[4096], p[4608], p[5120], p[5632]);
+  }
+  mfma_drain(acc);
+  for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 4; ++j)
+      for (int e = 0; e < 4; ++e) out[((i * 4 + j) * 4 + e) * 512 + l] = (bf16_t)acc[i][j][e];
+}
+"""
+
+
+def _compile(tmp_path, *args):
+    r = subprocess.run([HIPCC, *b.FLAGS, "-I", b.CSRC, "--offload-device-only", *args], capture_output=True, text=True, cwd=tmp_path)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return r.stderr
+
+
+def test_no_accumulator_is_read_before_the_last_mfma_has_written_it(tmp_path):
+    """The MFMAs are assembly, so the compiler knows of no hazard: only the dependence on mfma_drain() keeps it from converting an
+    accumulator right behind them."""
+    (tmp_path / "drain.hip").write_text(DRAIN)
+    _compile(tmp_path, "-S", "drain.hip", "-o", "drain.s")
+    ops = [m[1] for m in re.finditer(r"^\s+([vs]_\w+)(?: 15\b)?", (tmp_path / "drain.s").read_text(), re.M)
+           if m[1].startswith(("v_mfma", "v_cvt")) or m[0].rstrip().endswith("s_nop 15")]
+    last_mfma = max(i for i, op in enumerate(ops) if op.startswith("v_mfma"))
+    behind = ops[last_mfma + 1:]
+    assert behind[0] == "s_nop" and sum(op.startswith("v_cvt") for op in behind) >= 16, behind
