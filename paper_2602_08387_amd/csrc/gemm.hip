@@ -312,21 +312,6 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
   wait_vmcnt<IN_FLIGHT_FIRST>();
   int waits_from = 0;   // see tile_k_steps
 
-  // Lane's place in a fragment.  k-major: rows of 128 bytes, the second 32 k at this ^ 64.  mn-major: rows of 256 bytes (one k),
-  // block f of 16 at this ^ 32 f.
-  uint32_t lane_a, lane_b;
-  const int lane0 = threadIdx.x & 63;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(smem);
-  if constexpr (KM) {
-    const uint32_t l = (lane0 & 15) * (BK * 2) + (((lane0 >> 4) ^ ((lane0 >> 1) & 7)) << 4);
-    lane_a = l + lds0 + wave_m * TM * BK * 2;
-    lane_b = l + lds0 + 2 * HALF + wave_n * TN * BK * 2;
-  } else {
-    const int grp = lane0 >> 4, e = (lane0 >> 2) & 3, g = lane0 & 3;
-    const uint32_t l = (grp * 8 + e) * 256 + (((g >> 1) ^ (e << 2) ^ ((grp & 1) << 1)) << 4) + (g & 1) * 8;
-    lane_a = (l ^ (wave_m * 128)) + lds0;
-    lane_b = (l ^ (wave_n * 64)) + lds0 + 2 * HALF;
-  }
   // Waves 4 to 7, the other wave of each SIMD, run one slot behind waves 0 to 3.
   const bool behind = wave >= 4;
   uint32_t cs = 0;   // the ring stage of the K-step: the K-steps of successive tiles form one stream through the ring
@@ -342,6 +327,21 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
         for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
         asm volatile("" : "+v"(acc[i][j]));   // zeroed here, not in front of the first MFMA (see mfma_quadrant)
       }
+    // Lane's place in a fragment.  k-major: rows of 128 bytes, the second 32 k at this ^ 64.  mn-major: rows of 256 bytes (one k),
+    // block f of 16 at this ^ 32 f.
+    uint32_t lane_a, lane_b;
+    const int lane0 = lane_anew();
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_PTR(char))(smem);
+    if constexpr (KM) {
+      const uint32_t l = (lane0 & 15) * (BK * 2) + (((lane0 >> 4) ^ ((lane0 >> 1) & 7)) << 4);
+      lane_a = l + lds0 + wave_m * TM * BK * 2;
+      lane_b = l + lds0 + 2 * HALF + wave_n * TN * BK * 2;
+    } else {
+      const int grp = lane0 >> 4, e = (lane0 >> 2) & 3, g = lane0 & 3;
+      const uint32_t l = (grp * 8 + e) * 256 + (((g >> 1) ^ (e << 2) ^ ((grp & 1) << 1)) << 4) + (g & 1) * 8;
+      lane_a = (l ^ (wave_m * 128)) + lds0;
+      lane_b = (l ^ (wave_n * 64)) + lds0 + 2 * HALF;
+    }
     bf16x8 fa[2][FM], fb[2][FN];
     // the wave's A or B fragments of half H
     auto read = [&](auto H, auto NEXT) {

@@ -46,3 +46,17 @@ def test_no_accumulator_is_read_before_the_last_mfma_has_written_it(tmp_path):
     last_mfma = max(i for i, op in enumerate(ops) if op.startswith("v_mfma"))
     behind = ops[last_mfma + 1:]
     assert behind[0] == "s_nop" and sum(op.startswith("v_cvt") for op in behind) >= 16, behind
+
+
+def test_the_persistent_kernels_spill_no_vector_register(tmp_path):
+    """The reload of a spilled register is counted in order behind the next tile's loads and the last tile's stores: whatever
+    waits for it waits for all of those."""
+    out = _compile(tmp_path, "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(b.CSRC, "gemm.hip"), "-o", "gemm.o")
+    spills = {}
+    for m in re.finditer(r"(Function Name|VGPRs Spill|ScratchSize \[bytes/lane\]): (\S+)", out):
+        if m[1] == "Function Name":
+            name = m[2]
+        else:
+            spills[name] = spills.get(name, 0) + int(m[2])
+    assert len(spills) == 7 and all("gemm" in n for n in spills), spills
+    assert not any(spills.values()), spills
