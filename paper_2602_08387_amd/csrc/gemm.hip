@@ -45,6 +45,9 @@ namespace dl {
 // would make the compiler copy the whole block to scratch memory and read it back through vector loads.  A
 // grouped launch reads its problem through group_problem().
 //
+// SINGLE: every tile has one K-step.  A path of its own in the common kernel costs that 130 to 260 spilled registers, a branch in its
+// loop 1 to 2 % of short contractions.
+//
 // EPI_SWIGLU: the gated pair of the MLP in one pass.  B interleaves the rows of two weight matrices
 // (LoadStream PAIR) so that every wave holds g = x Wg^T and u = x Wu^T for the same 32 columns; the
 // epilogue stores g to c, u to c2 and silu(g) * u, taken from the fp32 sums, to c3.  M x N is the interleaved
@@ -199,7 +202,7 @@ struct LoadStream {
   }
 };
 
-template <bool GROUPED, bool KM, int EPI = EPI_PLAIN, bool PERM = false>
+template <bool GROUPED, bool KM, int EPI = EPI_PLAIN, bool PERM = false, bool SINGLE = false>
 __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const GemmKArgs& one) {
   constexpr int TM = PM / PWM, TN = PN / PWN, FM = TM / MI, FN = TN / MI;
   constexpr bool SWIGLU = EPI == EPI_SWIGLU;
@@ -222,7 +225,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
 
   // What the epilogue needs of a tile's problem, by value.
   struct Tile { int m0, n0, total, M, N, accumulate, rope; bf16_t* c; const bf16_t* r; int64_t ldc; };
-  constexpr bool SEGS = KM && !GROUPED && EPI == EPI_PLAIN;   // fused input gradients: several K-segments
+  constexpr bool SEGS = KM && !GROUPED && EPI == EPI_PLAIN && !SINGLE;   // fused input gradients: several K-segments
   using Stream = LoadStream<KM, SWIGLU, PERM, SEGS>;
   Stream cur;
 
@@ -398,7 +401,8 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
     auto ops = wave_ops(read, arrived, send, [&] { wait_vmcnt<IN_FLIGHT_PHASE>(); }, barrier, multiply,
                         [&] { if (more) cur.begin(start, next.total, wave); else cur.close(); },
                         [&] { cur.advance(one, wave); }, [&] { cs = STAGE - cs; });
-    tile_k_steps(ops, total, behind, waits_from);
+    if constexpr (SINGLE) tile_of_one_k_step(ops, behind, waits_from);
+    else tile_k_steps(ops, total, behind, waits_from);
     mfma_drain(acc);
 
     // Waiting for the next tile's loads behind the epilogue's stores takes a known number of them: where the tile lies inside C.
@@ -647,8 +651,10 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
   wait_vmcnt<0>();   // a closed stream's loads still write to LDS
 }
 
-template <bool KM>
-__global__ __launch_bounds__(512) void gemm_kernel(const GemmKArgs p) { gemm_persistent<false, KM>(GemmGroupKArgs{}, p); }
+template <bool KM, bool SINGLE>
+__global__ __launch_bounds__(512) void gemm_kernel(const GemmKArgs p) {
+  gemm_persistent<false, KM, EPI_PLAIN, false, SINGLE>(GemmGroupKArgs{}, p);
+}
 
 template <int EPI>
 __global__ __launch_bounds__(512) void gemm_swiglu_kernel(const GemmKArgs p) { gemm_persistent<false, true, EPI>(GemmGroupKArgs{}, p); }
@@ -741,8 +747,11 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
   const int ntiles = a.tiles_m * a.tiles_n;
   if (epi == TileEpilogue::SWIGLU) GEMM_LAUNCH((gemm_swiglu_kernel<EPI_SWIGLU>), ntiles, a, "gemm swiglu");
   if (epi == TileEpilogue::SWIGLU_GRAD) GEMM_LAUNCH((gemm_swiglu_kernel<EPI_SWIGLU_GRAD>), ntiles, a, "gemm swiglu grad");
-  if (ak && bk) GEMM_LAUNCH((gemm_kernel<true>), ntiles, a, "gemm");
-  if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<false>), ntiles, a, "gemm");
+  // One K-step: walked as two, as the common loop does with every short tile, 4096 x 64 -> 4096 took 12.9 us, now 11.3; 16384 x 64 -> 4096
+  // 31.5, now 29.3.
+  if (ak && bk && a.ksteps == 1) GEMM_LAUNCH((gemm_kernel<true, true>), ntiles, a, "gemm");
+  if (ak && bk) GEMM_LAUNCH((gemm_kernel<true, false>), ntiles, a, "gemm");
+  if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<false, false>), ntiles, a, "gemm");
   return fail(-1, "gemm: operand layout not built");
 }
 #undef GEMM_LAUNCH

@@ -90,12 +90,9 @@ DL_SCHEDULE void k_step_from(W& w, bool waits) {
   }
 }
 
-// The K-steps of one tile, at least two.  `behind`: the wave belongs to the group that runs one slot behind the other.  waits_from: K-step from
-// which on the first three phases wait for loads; 1 in a workgroup's later tiles, where what they read in K-step 0 has landed
-// (waiting there would be for the last tile's stores).
+// A tile's first fragments; `odd`: an odd number of K-steps.
 template <class W>
-DL_SCHEDULE void tile_k_steps(W& w, int total, bool behind, int waits_from) {
-  const bool odd = total & 1;
+DL_SCHEDULE void open_tile(W& w, bool odd, bool behind) {
   w.barrier();   // K-step 0 has landed in every wave's share: visible to all waves
   w.read(Int<HALF_A0>{}, Int<0>{});
   if (odd) w.read(Int<HALF_B1>{}, Int<0>{}); else w.read(Int<HALF_B0>{}, Int<0>{});
@@ -104,6 +101,15 @@ DL_SCHEDULE void tile_k_steps(W& w, int total, bool behind, int waits_from) {
   w.arrived(Int<HALF_B1>{});
   w.barrier();   // before the first load into this stage
   if (behind) w.barrier();
+}
+
+// The K-steps of one tile, at least two.  `behind`: the wave belongs to the group that runs one slot behind the other.  waits_from: K-step from
+// which on the first three phases wait for loads; 1 in a workgroup's later tiles, where what they read in K-step 0 has landed
+// (waiting there would be for the last tile's stores).
+template <class W>
+DL_SCHEDULE void tile_k_steps(W& w, int total, bool behind, int waits_from) {
+  const bool odd = total & 1;
+  open_tile(w, odd, behind);
   if (odd) {
     k_step_from<1, 0>(w, waits_from == 0);
     w.next_stage();
@@ -115,6 +121,23 @@ DL_SCHEDULE void tile_k_steps(W& w, int total, bool behind, int waits_from) {
     k_step_from<1, 0>(w, t + 1 >= waits_from);
     w.next_stage();
   }
+  if (!behind) w.barrier();
+}
+
+// A tile of one K-step, where all tiles are such: loaded as two, of which the second brings zeros that nothing reads; its place
+// takes the second of the next tile, in the order in which phases would send it.
+template <class W>
+DL_SCHEDULE void tile_of_one_k_step(W& w, bool behind, int waits_from) {
+  open_tile(w, false, behind);
+  w.next_tile();
+  k_step_from<0, 0>(w, waits_from == 0);
+  w.next_stage();
+  w.send(Int<half_sent(1, 0)>{});
+  w.send(Int<half_sent(1, 1)>{});
+  w.send(Int<half_sent(1, 2)>{});
+  w.send(Int<half_sent(1, 3)>{});
+  w.next_k();
+  w.next_stage();
   if (!behind) w.barrier();
 }
 

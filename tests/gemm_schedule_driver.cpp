@@ -25,8 +25,9 @@ struct Wave {
   std::vector<Send> sends;
   std::vector<Read> reads;
   std::vector<int> in_flight;                  // in order: index of a send, or -1 for a store
+  bool single;                                 // products of one K-step
 
-  explicit Wave(const std::vector<Tile>& t) : tiles(t) {}
+  Wave(const std::vector<Tile>& t, bool s) : tiles(t), single(s) {}
 
   void send_to(int stage, int half) {
     sends.push_back({to_tile, to_step, stage, half, epoch, NEVER});
@@ -47,7 +48,7 @@ struct Wave {
   void read(H, Next) {
     const int next = Next::value;
     // behind a tile's last K-step the next tile's first is read once more, by its own first reads
-    const bool over = step + next >= tiles[tile].total;
+    const bool over = step + next >= (single ? 1 : tiles[tile].total);
     if (!over) reads.push_back({tile, step + next, next ? 1 - cs : cs, H::value, epoch, NEVER});
   }
   template <class H>
@@ -67,15 +68,17 @@ struct Wave {
   void next_stage() { cs = 1 - cs; ++step; }
 };
 
-static Wave run(const std::vector<Tile>& tiles, bool behind, int store_count, int edge_stores) {
-  Wave w(tiles);
+// `single`: the loop of products of one K-step, whose tiles are loaded as two
+static Wave run(const std::vector<Tile>& tiles, bool single, bool behind, int store_count, int edge_stores) {
+  Wave w(tiles, single);
   first_loads(
       tiles[0].total & 1, [&](auto stage, auto half) { w.send_to(decltype(stage)::value, decltype(half)::value); }, [&] { w.next_k(); });
   w.wait_for(IN_FLIGHT_FIRST);
   int waits_from = 0;
   for (w.tile = 0; w.tile < (int)tiles.size(); ++w.tile) {
     w.step = 0;
-    tile_k_steps(w, tiles[w.tile].total, behind, waits_from);
+    if (single) tile_of_one_k_step(w, behind, waits_from);
+    else tile_k_steps(w, tiles[w.tile].total, behind, waits_from);
     const bool more = w.tile + 1 < (int)tiles.size();
     const int landed = more ? in_flight_landed(tiles[w.tile + 1].total & 1) : 0;
     if (more && !tiles[w.tile].inside) w.wait_for(landed);
@@ -87,8 +90,8 @@ static Wave run(const std::vector<Tile>& tiles, bool behind, int store_count, in
   return w;
 }
 
-static int check(const std::vector<Tile>& tiles, int store_count, int edge_stores) {
-  const Wave waves[2] = {run(tiles, false, store_count, edge_stores), run(tiles, true, store_count, edge_stores)};
+static int check(const std::vector<Tile>& tiles, int store_count, int edge_stores, bool single = false) {
+  const Wave waves[2] = {run(tiles, single, false, store_count, edge_stores), run(tiles, single, true, store_count, edge_stores)};
   int bad = 0;
   auto complain = [&](const Read& r, int reader, const char* what) {
     ++bad;
@@ -135,6 +138,9 @@ int main() {
         for (int b = 2; b <= 7; ++b)
           for (int c = 2; c <= 7; ++c)
             for (int in = 0; in < 4; ++in, ++runs) bad += check({{a, (in & 1) != 0}, {b, (in & 2) != 0}, {c, true}}, stores, edge_stores);
+  for (int edge_stores : {0, 5, 16})
+    for (int in = 0; in < 4; ++in, ++runs) bad += check({{2, (in & 1) != 0}, {2, (in & 2) != 0}, {2, true}}, 16, edge_stores, true);
+  bad += check({{2, true}}, 16, 0, true), ++runs;
   for (int total : {2, 3, 64, 65}) bad += check({{total, true}}, 16, 0), ++runs;
   std::printf("%d runs, %d reads not covered\n", runs, bad);
   return bad != 0;

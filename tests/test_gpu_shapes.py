@@ -172,6 +172,25 @@ def test_linear_forward_on_every_tile_size(K, shape, res, route):
             _same_bits(part(T, cols), y[:, :cols], f"{cols} columns")
 
 
+@pytest.mark.parametrize("shape,res", [((4096, 4096), False), ((4160, 4288), True), ((20520, 2056), True)])
+def test_linear_forward_over_one_k_step_on_full_tiles(K, shape, res):
+    """K = 64 on the persistent kernel: one tile to a workgroup, two, and three with ragged rows and columns."""
+    T, N = shape
+    assert K.gemm_route(0, 0, [T], [N], [64]) == (PERSISTENT, -1, T)
+    rng = np.random.default_rng(T)
+    xb, wb, rb = _rand_bits(rng, (T, 64)), _rand_bits(rng, (N, 64), 0.1), _rand_bits(rng, (T, N))
+    xd, wd, rd = map(dev_bf16, (xb, wb, rb))
+    y = torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    K.linear_forward(xd, wd, rd if res else None, T, 64, N, y)
+    x, w, r = (si.bf16_bits_to_f32(b) for b in (xb, wb, rb))
+    assert _norm_err(y, x @ w.T + (r if res else 0.0)) <= ONE_ROUNDING
+    for c0 in (0, N - 136):   # the same bits on another kernel, in the first and the last columns
+        assert K.gemm_route(0, 0, [T], [136], [64])[0] != PERSISTENT
+        part = torch.full((T, 136), float("nan"), dtype=torch.bfloat16, device="cuda")
+        K.linear_forward(xd, wd[c0:c0 + 136].contiguous(), rd[:, c0:c0 + 136].contiguous() if res else None, T, 64, 136, part)
+        _same_bits(part, y[:, c0:c0 + 136], f"columns from {c0}")
+
+
 WEIGHT_GRADIENTS = [
     (64, [(64, 64)], (T64, -1)),                                                  # one tile, one K-step
     (320, [(64, 192), (320, 64), (128, 128)], (T64, -1)),
