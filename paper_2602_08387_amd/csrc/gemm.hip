@@ -659,8 +659,10 @@ __global__ __launch_bounds__(512) void gemm_kernel(const GemmKArgs p) {
 template <int EPI>
 __global__ __launch_bounds__(512) void gemm_swiglu_kernel(const GemmKArgs p) { gemm_persistent<false, true, EPI>(GemmGroupKArgs{}, p); }
 
-template <bool KM>
-__global__ __launch_bounds__(512) void gemm_group_kernel(const GemmGroupKArgs g) { gemm_persistent<true, KM>(g, g.prob[0]); }
+template <bool KM, bool SINGLE>
+__global__ __launch_bounds__(512) void gemm_group_kernel(const GemmGroupKArgs g) {
+  gemm_persistent<true, KM, EPI_PLAIN, false, SINGLE>(g, g.prob[0]);
+}
 
 template <bool PERM>
 __global__ __launch_bounds__(512) void gemm_group_rope_kernel(const GemmGroupKArgs g) {
@@ -738,7 +740,10 @@ static int launch_persistent_group(const GemmKArgs* ks, int n, bool ak, bool bk,
     GEMM_LAUNCH((gemm_group_rope_kernel<false>), g.tile_start[n], g, "gemm group (rotary epilogue)");
   }
   // only the layout in use is instantiated: the weight-gradient products (both operands mn-major)
-  if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<false>), g.tile_start[n], g, "gemm group");
+  bool single = true;
+  for (int i = 0; i < n; ++i) single = single && g.prob[i].ksteps == 1;
+  if (!ak && !bk && single) GEMM_LAUNCH((gemm_group_kernel<false, true>), g.tile_start[n], g, "gemm group");
+  if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<false, false>), g.tile_start[n], g, "gemm group");
   return fail(-1, "gemm group: operand layout not built");
 }
 
@@ -751,6 +756,7 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
   // 31.5, now 29.3.
   if (ak && bk && a.ksteps == 1) GEMM_LAUNCH((gemm_kernel<true, true>), ntiles, a, "gemm");
   if (ak && bk) GEMM_LAUNCH((gemm_kernel<true, false>), ntiles, a, "gemm");
+  if (!ak && !bk && a.ksteps == 1) GEMM_LAUNCH((gemm_kernel<false, true>), ntiles, a, "gemm");
   if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<false, false>), ntiles, a, "gemm");
   return fail(-1, "gemm: operand layout not built");
 }
@@ -759,7 +765,8 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
 // ------------------------------------------------------------------------------------------
 // Which kernel a product runs on.  A 256 x 256 tile has the cheapest K-step per flop, but a launch costs whole rounds
 // of 256 tiles: 289 tiles take two.  So the time of every candidate is estimated from its rounds -
-//   time = launch + rounds x (K-steps x step + tile), a last round that is filled to f taking step lo + f (hi - lo)
+//   time = launch + rounds x (K-steps x step) + tile + (rounds - 1) x again, a last round that is filled to f taking step
+//   lo + f (hi - lo)
 // (a CU runs faster while others idle: clock, L2) - and the cheapest runs: the persistent kernel, one of the three
 // tile sizes of gemm_tile.hip, or the persistent kernel for its full rounds and a smaller tile, in a second
 // launch, for the rows left over.  All give the same bits.  Microseconds, from sweeps on MI355X
@@ -768,23 +775,28 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
 // and over 115 products (256 compute units) the choice is on average 0.5 % (k-major), 1.4 % (mn-major) and 0.4 % (mixed) behind
 // the best kernel.
 // ------------------------------------------------------------------------------------------
-struct KernelCost { int bm, bn, per_cu; double lo, hi, tile; };
+struct KernelCost { int bm, bn, per_cu; double lo, hi, tile, again; };   // again: fixed part of a workgroup's later tiles
 constexpr int kPersistent = 3;
 static const KernelCost kCostKK[4] = {
-    {128, 256, 1, 0.62, 0.75, 4.0},   // T = 8192, K = 4096, N = 768 (192 tiles): 50 us against 71 on 96 tiles of 256 x 256
-    {128, 128, 1, 0.38, 0.48, 3.0},   // T = 1920, K = 6272, N = 1152 (135 tiles): 44 us; 67 as 75 tiles of 128 x 256
-    {64, 64, 2, 0.25, 0.33, 2.0},     // T = 2048, K = 2816, N = 1024 (512 tiles): 20 us; 23 as 128 tiles of 128 x 128
-    {256, 256, 1, 0.98, 1.39, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
+    {128, 256, 1, 0.62, 0.75, 4.0, 4.0},   // T = 8192, K = 4096, N = 768 (192 tiles): 50 us against 71 on 96 tiles of 256 x 256
+    {128, 128, 1, 0.38, 0.48, 3.0, 3.0},   // T = 1920, K = 6272, N = 1152 (135 tiles): 44 us; 67 as 75 tiles of 128 x 256
+    {64, 64, 2, 0.25, 0.33, 2.0, 2.0},     // T = 2048, K = 2816, N = 1024 (512 tiles): 20 us; 23 as 128 tiles of 128 x 128
+    {256, 256, 1, 0.98, 1.39, 5.0, 5.0}};  // T = 8192, K = 5632, N = 2048 (256 tiles): 132 us
 // The fixed part per tile counts where the contraction is short (a weight gradient over few tokens), and there the 256 x 256
 // tile's is large: its two-stage ring starts and its accumulators drain with nothing beside them.  Less so since its wave
 // groups run a slot apart: with 8.0 for 8.5 weight gradients over 128 to 384 tokens go to it, us, 128 x 256 or 128 x 128 tiles
 // before: 128 tokens, 8192 x 8192 47.7, now 33.7; 192, 4096 x 4096 16.9, now 14.1; 320, 4096 x 3072 17.5, now 14.5; 512,
 // 14336 x 4096 (in two launches) 79, now 69.5.  Thirty-six of 170 that changed were measured: 8 to 30 % faster, all of them.
+// A workgroup's later tiles cost less, their fill and drain lie beside other tiles' K-steps, and so does a product of one K-step, which
+// has its own kernel.  128 x 256 tiles before the wave groups, with them, and now: 64 tokens, 4096 x 4096 13.5, 14.1, 11.7;
+// 14336 x 4096 34.2, 36.1, 26.5; 128 tokens, 14336 x 4096 41.8, 43.9, 30.9; 192 tokens 46.0, 47.6, 35.3; 256 tokens 52, 52.4,
+// 40.7.  Of a grid of 6800 sizes and groups the 222 that changed were measured: 6 to 58 % faster, all of them.
 static const KernelCost kCostMN[4] = {
-    {128, 256, 1, 0.70, 0.85, 3.8},   // 4096 x 4096, K = 64 (512 tiles): 13.2 us; 768 x 768, K = 8192 (18 tiles): 94 us
-    {128, 128, 1, 0.48, 0.56, 2.2},   // the first as 1024 tiles: 14.8 us; the second as 36: 63 us
-    {64, 64, 2, 0.28, 0.39, 1.3},     // as 4096 tiles: 17.2 us; as 144: 39 us
-    {256, 256, 1, 1.20, 1.45, 8.0}};  // as 256 tiles: 15.6 us; as 9: 157 us
+    {128, 256, 1, 0.70, 0.85, 3.8, 3.8},   // 4096 x 4096, K = 64 (512 tiles): 13.2 us; 768 x 768, K = 8192 (18 tiles): 94 us
+    {128, 128, 1, 0.48, 0.56, 2.2, 2.2},   // the first as 1024 tiles: 14.8 us; the second as 36: 63 us
+    {64, 64, 2, 0.28, 0.39, 1.3, 1.3},     // as 4096 tiles: 17.2 us; as 144: 39 us
+    {256, 256, 1, 1.20, 1.45, 8.0, 5.0}};  // as 9 tiles: 157 us
+static const KernelCost kCostOneStep = {256, 256, 1, 1.20, 1.45, 5.5, 4.5};   // a mn-major product of one K-step: the first as 256 tiles: 11.7 us
 constexpr double kLaunchUs = 3.5;
 
 static double kernel_us(const KernelCost& c, int cus, const GemmKArgs* ks, int n) {
@@ -795,8 +807,8 @@ static double kernel_us(const KernelCost& c, int cus, const GemmKArgs* ks, int n
     steps = s > steps ? s : steps;
   }
   const int64_t slots = (int64_t)c.per_cu * cus, full = tiles / slots, rem = tiles % slots;
-  double us = kLaunchUs + full * (steps * c.hi + c.tile);
-  if (rem) us += steps * (c.lo + (c.hi - c.lo) * rem / slots) + c.tile;
+  double us = kLaunchUs + full * steps * c.hi + c.tile + (full + (rem ? 1 : 0) - 1) * c.again;
+  if (rem) us += steps * (c.lo + (c.hi - c.lo) * rem / slots);
   return us;
 }
 
@@ -824,6 +836,9 @@ struct GemmPlan {
 
 static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, int cus) {
   const KernelCost* cost = ak && bk ? kCostKK : kCostMN;
+  bool one_step = !ak && !bk;
+  for (int i = 0; i < n; ++i) one_step = one_step && k_total(ks[i]) == BK;
+  const KernelCost& full_tile = one_step ? kCostOneStep : cost[kPersistent];
   // a 64-column tile does not hold both members of a split pair of a 128-wide head; the persistent kernels are not built
   // for one k-major and one mn-major operand
   const bool no64 = rope && rope->layout == 0 && rope->head_dim == 128, persistent = ak == bk;
@@ -838,7 +853,7 @@ static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk,
   };
   double tile_us;
   const int tile = best_tile(ks, n, tile_us);
-  const double whole_us = persistent ? kernel_us(cost[kPersistent], cus, ks, n) : 1e30;
+  const double whole_us = persistent ? kernel_us(full_tile, cus, ks, n) : 1e30;
   // full rounds of the persistent kernel, the rows behind them on a smaller tile
   int64_t tiles = 0;
   for (int i = 0; i < n; ++i) tiles += (int64_t)((ks[i].M + PM - 1) / PM) * ((ks[i].N + PN - 1) / PN);
@@ -857,12 +872,16 @@ static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk,
     if (p.nh > 0 && p.nt > 0) {
       double tail_us;
       const int tail_tile = best_tile(p.tail, p.nt, tail_us);
-      const double split_us = kernel_us(cost[kPersistent], cus, p.head, p.nh) + tail_us;
+      // The cut is judged with the whole fixed part for every tile: with the lower one 24 products of mn-major operands went back to
+      // one launch, between 5 % faster and 1.5 % slower (1024 tokens, 10240 x 10240: 182.1 us in two launches, 184.9 in one).
+      KernelCost every_tile = full_tile;
+      every_tile.again = every_tile.tile;
+      const double split_us = kernel_us(every_tile, cus, p.head, p.nh) + tail_us;
       // The second launch drains the chip once more, which the estimate of a launch leaves out: 3 %, and 10 % for the gated
       // pair, whose three outputs the persistent kernel stores under its next main loop (T = 2048, K = 4096,
       // F = 14336: 413 us in two launches, 406 in one, 7 % apart the other way in the estimate).
       const double margin = epi == TileEpilogue::SWIGLU ? 0.9 : 0.97;
-      if (split_us < margin * whole_us && split_us < tile_us) {
+      if (split_us < margin * kernel_us(every_tile, cus, ks, n) && split_us < tile_us) {
         p.first = kPersistent;
         p.second = tail_tile;
         return;

@@ -221,6 +221,34 @@ def test_weight_gradients_on_every_tile_size(K, T, shapes, route):
         _same_bits(narrow, dws[i][:, :64], f"dw[{i}] of 64 columns")
 
 
+ONE_STEP_GRADIENTS = [
+    [(4096, 4096)],                                   # one tile to a workgroup
+    [(7232, 4160)],                                   # two, ragged in both directions
+    [(8192, 2112), (4160, 1088), (8256, 448)],        # a group of nearly two, its products ragged
+]
+
+
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("shapes", ONE_STEP_GRADIENTS)
+def test_weight_gradients_over_one_k_step_on_full_tiles(K, shapes, accumulate):
+    """64 tokens on the persistent kernels."""
+    Ns, Ks = [n for n, _ in shapes], [k for _, k in shapes]
+    assert K.gemm_route(2, 0, Ns, Ks, [64] * len(shapes))[:2] == (PERSISTENT, -1)
+    rng = np.random.default_rng(len(shapes))
+    dyb, xb, wb = ([_rand_bits(rng, s) for s in sizes] for sizes in ([(64, n) for n in Ns], [(64, k) for k in Ks], shapes))
+    dyd, xd, dws = ([dev_bf16(b) for b in bits] for bits in (dyb, xb, wb))
+    first = [w.clone() for w in dws]
+    K.linear_wgrad_group(dyd, xd, Ns, Ks, 64, dws, accumulate)
+    for i, (n, k) in enumerate(shapes):
+        dy, x, w = (si.bf16_bits_to_f32(b[i]) for b in (dyb, xb, wb))
+        assert _norm_err(dws[i], dy.T @ x + (w if accumulate else 0.0)) <= ONE_ROUNDING, i
+        for c0 in (0, k - 64):   # the same bits on a smaller tile, in the first and the last columns
+            assert K.gemm_route(2, 0, [n], [64], [64])[0] != PERSISTENT
+            part = first[i][:, c0:c0 + 64].contiguous()
+            K.linear_backward(xd[i][:, c0:c0 + 64].contiguous(), xd[i], dyd[i], 64, 64, n, None, part, accumulate, None)
+            _same_bits(part, dws[i][:, c0:c0 + 64], f"dw[{i}], columns from {c0}")
+
+
 GATED_PAIRS = [
     ((64, 64, 64), (T64, -1)),
     ((200, 192, 104), (T64, -1)),

@@ -28,6 +28,15 @@ def test_weight_gradients_over_few_tokens_take_a_smaller_tile(K, T, Kd, N):
     assert K.gemm_route(2, 0, [N], [Kd], [T], compute_units=256)[0] in (T128, T128X256, T64)
 
 
+def test_full_tiles_over_few_tokens(K):
+    """A workgroup's further tiles cost less than its first, and a product of one K-step less than others: full 256 x 256 tiles from
+    a round of them on, and smaller tiles for half a round."""
+    for T in (64, 128, 192, 256, 512):
+        assert K.gemm_route(2, 0, [14336], [4096], [T], compute_units=256)[0] == PERSISTENT
+    assert K.gemm_route(2, 0, [4096], [4096], [64], compute_units=256) == (PERSISTENT, -1, 4096)
+    assert K.gemm_route(2, 0, [2048], [4096], [64], compute_units=256)[0] != PERSISTENT
+
+
 def test_key_blocks_are_split_for_the_compute_units_there_are(K):
     shape = (2, 2944, 16, 4, 64)
     assert K.attention_backward_pieces(*shape, compute_units=256) > 1
