@@ -656,17 +656,19 @@ __global__ __launch_bounds__(512) void gemm_kernel(const GemmKArgs p) {
   gemm_persistent<false, KM, EPI_PLAIN, false, SINGLE>(GemmGroupKArgs{}, p);
 }
 
-template <int EPI>
-__global__ __launch_bounds__(512) void gemm_swiglu_kernel(const GemmKArgs p) { gemm_persistent<false, true, EPI>(GemmGroupKArgs{}, p); }
+template <int EPI, bool SINGLE>
+__global__ __launch_bounds__(512) void gemm_swiglu_kernel(const GemmKArgs p) {
+  gemm_persistent<false, true, EPI, false, SINGLE>(GemmGroupKArgs{}, p);
+}
 
 template <bool KM, bool SINGLE>
 __global__ __launch_bounds__(512) void gemm_group_kernel(const GemmGroupKArgs g) {
   gemm_persistent<true, KM, EPI_PLAIN, false, SINGLE>(g, g.prob[0]);
 }
 
-template <bool PERM>
+template <bool PERM, bool SINGLE>
 __global__ __launch_bounds__(512) void gemm_group_rope_kernel(const GemmGroupKArgs g) {
-  gemm_persistent<true, true, EPI_ROPE, PERM>(g, g.prob[0]);
+  gemm_persistent<true, true, EPI_ROPE, PERM, SINGLE>(g, g.prob[0]);
 }
 
 // Tile rows per band of the tile sequence.  An XCD runs some 32 consecutive tiles at a time: 8 rows x 4
@@ -723,43 +725,47 @@ static GemmKArgs persistent_tiling(GemmKArgs k, bool both_kmajor, bool epilogue_
     hipLaunchKernelGGL(kern_, dim3((unsigned)persistent_grid(NTILES)), dim3(512), kPersistentLds, st, ARGS); \
     return check_launch(WHAT);                                                                                  \
   } while (0)
+// The instance for products of one K-step, or the common one.  us, common (walked as two K-steps) and own instance: 4096 x 64 -> 4096 12.9,
+// 11.3; 16384 x 64 -> 4096 31.0, 29.2; weight gradient 14336 x 4096 of 64 tokens 31.3, 26.5.
+#define GEMM_LAUNCH_STEPS(SINGLE, NTILES, ARGS, WHAT, KERN, ...)                        \
+  do {                                                                                  \
+    if (SINGLE) GEMM_LAUNCH((KERN<__VA_ARGS__, true>), NTILES, ARGS, WHAT);             \
+    GEMM_LAUNCH((KERN<__VA_ARGS__, false>), NTILES, ARGS, WHAT);                        \
+  } while (0)
 
 static int launch_persistent_group(const GemmKArgs* ks, int n, bool ak, bool bk, const RopeEpilogue* rope, hipStream_t st) {
   GemmGroupKArgs g{};
   g.n = n;
+  bool single = true;
   for (int i = 0; i < n; ++i) {
     g.prob[i] = persistent_tiling(ks[i], ak && bk, false);
     g.tile_start[i + 1] = g.tile_start[i] + g.prob[i].tiles_m * g.prob[i].tiles_n;
+    single = single && g.prob[i].ksteps == 1;
   }
   if (rope) {
     g.rope_cos = rope->cos; g.rope_sin = rope->sin;
     g.rope_seq = rope->seq; g.rope_dh = rope->head_dim; g.rope_layout = rope->layout;
     for (int i = 0; i < n; ++i) g.prob[i].rope = ks[i].rope;
     if (rope->layout == 0 && rope->head_dim == 128)
-      GEMM_LAUNCH((gemm_group_rope_kernel<true>), g.tile_start[n], g, "gemm group (rotary epilogue)");
-    GEMM_LAUNCH((gemm_group_rope_kernel<false>), g.tile_start[n], g, "gemm group (rotary epilogue)");
+      GEMM_LAUNCH_STEPS(single, g.tile_start[n], g, "gemm group (rotary epilogue)", gemm_group_rope_kernel, true);
+    GEMM_LAUNCH_STEPS(single, g.tile_start[n], g, "gemm group (rotary epilogue)", gemm_group_rope_kernel, false);
   }
   // only the layout in use is instantiated: the weight-gradient products (both operands mn-major)
-  bool single = true;
-  for (int i = 0; i < n; ++i) single = single && g.prob[i].ksteps == 1;
-  if (!ak && !bk && single) GEMM_LAUNCH((gemm_group_kernel<false, true>), g.tile_start[n], g, "gemm group");
-  if (!ak && !bk) GEMM_LAUNCH((gemm_group_kernel<false, false>), g.tile_start[n], g, "gemm group");
+  if (!ak && !bk) GEMM_LAUNCH_STEPS(single, g.tile_start[n], g, "gemm group", gemm_group_kernel, false);
   return fail(-1, "gemm group: operand layout not built");
 }
 
 static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue epi, hipStream_t st) {
   const GemmKArgs a = persistent_tiling(k, ak && bk, epi == TileEpilogue::SWIGLU_GRAD);
   const int ntiles = a.tiles_m * a.tiles_n;
-  if (epi == TileEpilogue::SWIGLU) GEMM_LAUNCH((gemm_swiglu_kernel<EPI_SWIGLU>), ntiles, a, "gemm swiglu");
-  if (epi == TileEpilogue::SWIGLU_GRAD) GEMM_LAUNCH((gemm_swiglu_kernel<EPI_SWIGLU_GRAD>), ntiles, a, "gemm swiglu grad");
-  // One K-step: walked as two, as the common loop does with every short tile, 4096 x 64 -> 4096 took 12.9 us, now 11.3; 16384 x 64 -> 4096
-  // 31.5, now 29.3.
-  if (ak && bk && a.ksteps == 1) GEMM_LAUNCH((gemm_kernel<true, true>), ntiles, a, "gemm");
-  if (ak && bk) GEMM_LAUNCH((gemm_kernel<true, false>), ntiles, a, "gemm");
-  if (!ak && !bk && a.ksteps == 1) GEMM_LAUNCH((gemm_kernel<false, true>), ntiles, a, "gemm");
-  if (!ak && !bk) GEMM_LAUNCH((gemm_kernel<false, false>), ntiles, a, "gemm");
+  const bool single = a.ksteps == 1;
+  if (epi == TileEpilogue::SWIGLU) GEMM_LAUNCH_STEPS(single, ntiles, a, "gemm swiglu", gemm_swiglu_kernel, EPI_SWIGLU);
+  if (epi == TileEpilogue::SWIGLU_GRAD) GEMM_LAUNCH_STEPS(single, ntiles, a, "gemm swiglu grad", gemm_swiglu_kernel, EPI_SWIGLU_GRAD);
+  if (ak && bk) GEMM_LAUNCH_STEPS(single, ntiles, a, "gemm", gemm_kernel, true);
+  if (!ak && !bk) GEMM_LAUNCH_STEPS(single, ntiles, a, "gemm", gemm_kernel, false);
   return fail(-1, "gemm: operand layout not built");
 }
+#undef GEMM_LAUNCH_STEPS
 #undef GEMM_LAUNCH
 
 // ------------------------------------------------------------------------------------------

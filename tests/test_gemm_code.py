@@ -58,5 +58,5 @@ def test_the_persistent_kernels_spill_no_vector_register(tmp_path):
             name = m[2]
         else:
             spills[name] = spills.get(name, 0) + int(m[2])
-    assert len(spills) == 10 and all("gemm" in n for n in spills), spills
+    assert len(spills) == 14 and all("gemm" in n for n in spills), spills
     assert not any(spills.values()), spills

@@ -256,6 +256,7 @@ GATED_PAIRS = [
     ((1000, 64, 1608), (T128, -1)),
     ((1920, 1152, 1096), (T128X256, -1)),
     ((4160, 192, 2176), (PERSISTENT, -1)),
+    ((4160, 64, 4288), (PERSISTENT, -1)),             # one K-step
     ((4160, 1024, 2176), (PERSISTENT, T64)),
     ((2048, 512, 4224), (PERSISTENT, T128)),
 ]
@@ -429,6 +430,7 @@ ROTARY = [
     ((1, 1216, 64, 9, 9, 64, 1), (T128, -1)),
     ((5, 384, 192, 9, 9, 128, 0), (T128X256, -1)),
     ((3, 2816, 64, 12, 12, 64, 0), (PERSISTENT, -1)), # more than one round, in one launch
+    ((5, 1024, 64, 31, 8, 128, 0), (PERSISTENT, -1)), # one K-step, weight tiles in partner order
     ((5, 1728, 256, 30, 2, 64, 0), (PERSISTENT, T128)),     # cut in q, in the middle of a sequence: positions go on across it
     ((5, 1664, 256, 15, 1, 128, 0), (PERSISTENT, T128)),    # the same, weight tiles of the full rounds in partner order
     ((5, 1664, 256, 15, 1, 128, 1), (PERSISTENT, T128)),
