@@ -38,8 +38,10 @@ namespace dl {
 // tiles the first two K-steps of the next tile are already on their way into the LDS ring while the
 // epilogue of the current one drains the accumulators through a staging region of its own, and the
 // C stores of a tile complete under the next tile's main loop.  Vector memory operations complete in order, so
-// nothing between two tiles may wait for a load of its own (a spilled register, a table) behind the tile's loads:
-// the gated pair took 346 us instead of 296 with twenty registers spilled around its epilogue.
+// nothing between two tiles should wait for a load of its own (a spilled register, a table) behind the tile's loads:
+// the gated pair took 346 us instead of 296 with twenty registers spilled around its epilogue.  The epilogues that read
+// (residual, accumulation, rotary table, g and u) do wait: for the next tile's loads, and since their range checks are branches,
+// behind which the compiler counts no store, each part of one for the stores of the part before.
 //
 // The kernel arguments are only read with compile-time offsets: a run-time index into the argument block
 // would make the compiler copy the whole block to scratch memory and read it back through vector loads.  A
@@ -47,6 +49,11 @@ namespace dl {
 //
 // SINGLE: every tile has one K-step.  A path of its own in the common kernel costs that 130 to 260 spilled registers, a branch in its
 // loop 1 to 2 % of short contractions.
+//
+// Short contractions: the two wave groups take 1 to 4 thousand cycles more for a tile's fill and drain than waves in step did and
+// 80 fewer for each K-step, and a short launch is not at the power limit.  us, in step / now: 4096 x K -> 4096, K = 128
+// 12.4 / 12.8, 256 14.4 / 15.1, 512 19.6 / 20.2, 1024 30.2 / 30.3, 4096 95.3 / 93.8.  Not in the stores of the last tile (counted
+// in the waits behind them: no change), nor in the loads of zeros behind the last one (left out: no change).
 //
 // EPI_SWIGLU: the gated pair of the MLP in one pass.  B interleaves the rows of two weight matrices
 // (LoadStream PAIR) so that every wave holds g = x Wg^T and u = x Wu^T for the same 32 columns; the
@@ -480,7 +487,7 @@ __device__ __forceinline__ void gemm_persistent(const GemmGroupKArgs& grp, const
         bf16x4 gq[TPB], uq[TPB];
         to_acc_layout(gv[s % (PF + 1)], gq);
         to_acc_layout(uv[s % (PF + 1)], uq);
-        // each fetch is issued before this row's stores, so waiting for it does not wait for the stores
+        // issued before this row's stores; those sit behind branches, so the compiler's wait for it is one for them too
         if constexpr (s + PF < FM) fetch(s + PF, gv[(s + PF) % (PF + 1)], uv[(s + PF) % (PF + 1)]);
 #pragma unroll
         for (int i = 0; i < TPB; ++i)
@@ -777,9 +784,9 @@ static int launch_persistent(const GemmKArgs& k, bool ak, bool bk, TileEpilogue 
 // tile sizes of gemm_tile.hip, or the persistent kernel for its full rounds and a smaller tile, in a second
 // launch, for the rows left over.  All give the same bits.  Microseconds, from sweeps on MI355X
 // (both operands k-major / an operand mn-major); per_cu: tiles of a compute unit in flight.  The constants, and the launches
-// beside them, were taken before the wave groups and the loading waves; now the kernels are up to 25 % quicker, all of them,
-// and over 115 products (256 compute units) the choice is on average 0.5 % (k-major), 1.4 % (mn-major) and 0.4 % (mixed) behind
-// the best kernel.
+// beside them, were taken before the wave groups and the loading waves, but for the fixed parts of full mn-major tiles; now
+// most launches are up to 25 % quicker.  Over 115 products (256 compute units) the choice was on average 0.5 % (k-major) and 0.4 %
+// (mixed) behind the best kernel, and 1.4 % (mn-major) before those fixed parts were taken again.
 // ------------------------------------------------------------------------------------------
 struct KernelCost { int bm, bn, per_cu; double lo, hi, tile, again; };   // again: fixed part of a workgroup's later tiles
 constexpr int kPersistent = 3;
@@ -1015,9 +1022,9 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_
   GemmPlan p;
   plan_gemm(p, &k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, compute_units());
   // The one-tile kernels' epilogue has g and u at hand and writes a as well; with the norms' outputs from their backward
-  // that takes a layer of 1920 tokens, D 1152, F 3136, two micro-batches, from 664 to 641 us.  On the persistent kernel a
-  // third run of stores would go out behind the next tile's loads, more than the wait counter can tell apart (63), and a
-  // launch of its own is a hundredth of the step.
+  // that takes a layer of 1920 tokens, D 1152, F 3136, two micro-batches, from 664 to 641 us.  On the persistent kernel
+  // (not tried) a third run of stores would lie in an epilogue that waits for each of them, and a launch of its own is a hundredth of
+  // the step.
   if (p.first != kPersistent) {
     k.c3 = (bf16_t*)a;
     return launch_gemm_tile((TileSize)p.first, &k, 1, true, w_kmajor, TileEpilogue::SWIGLU_GRAD, nullptr, st);

@@ -48,10 +48,11 @@ def test_no_accumulator_is_read_before_the_last_mfma_has_written_it(tmp_path):
     assert behind[0] == "s_nop" and sum(op.startswith("v_cvt") for op in behind) >= 16, behind
 
 
-def test_the_persistent_kernels_spill_no_vector_register(tmp_path):
+def test_the_persistent_kernels_spill_no_vector_register_and_store_what_their_waits_count(tmp_path):
     """The reload of a spilled register is counted in order behind the next tile's loads and the last tile's stores: whatever
-    waits for it waits for all of those."""
-    out = _compile(tmp_path, "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(b.CSRC, "gemm.hip"), "-o", "gemm.o")
+    waits for it waits for all of those.  And the wait for the next tile's loads counts a wave's stores of a tile inside C, 16 or, with
+    two or three outputs, 32: fewer would leave loads unwaited for."""
+    out = _compile(tmp_path, "-Rpass-analysis=kernel-resource-usage", "-S", os.path.join(b.CSRC, "gemm.hip"), "-o", "gemm.s")
     spills = {}
     for m in re.finditer(r"(Function Name|VGPRs Spill|ScratchSize \[bytes/lane\]): (\S+)", out):
         if m[1] == "Function Name":
@@ -60,3 +61,8 @@ def test_the_persistent_kernels_spill_no_vector_register(tmp_path):
             spills[name] = spills.get(name, 0) + int(m[2])
     assert len(spills) == 14 and all("gemm" in n for n in spills), spills
     assert not any(spills.values()), spills
+    text = (tmp_path / "gemm.s").read_text()
+    for name in spills:
+        code = text[text.index(f"\n{name}:"):]
+        stores = len(re.findall(r"^\s+(?:global|flat|buffer)_store", code[:code.index(".Lfunc_end")], re.M))
+        assert stores == (32 if "swiglu" in name else 16), (name, stores)

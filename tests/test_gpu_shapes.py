@@ -372,6 +372,34 @@ def test_layer_with_row_statistics_in_the_epilogue(K, shape, stored, tile):
     _check_layer(g, f, r, "statistics")
 
 
+# query heads, KV heads, head width; batches whose o projection's input gradient runs on a tile kernel, and which
+STATISTICS_BITS = [(32, 16, 32, ((16, T64), (32, T128), (48, T128X256))), (16, 8, 64, ((16, T64), (32, T128), (48, T128X256))),
+                   (8, 4, 128, ((32, T128), (48, T128X256)))]
+
+
+@pytest.mark.parametrize("Hq,Hkv,dh,fewer", STATISTICS_BITS)
+def test_row_statistics_have_the_same_bits_in_the_epilogue_and_in_a_launch_of_their_own(K, Hq, Hkv, dh, fewer):
+    """A batch's input gradient depends on its own rows only, and every product has the same bits on every kernel: what is left between
+    128 batches, whose o projection's input gradient runs on the persistent kernel, and fewer of them, which take the
+    statistics from its epilogue, are the statistics."""
+    S, D, F, many = 128, 192, 192, 128
+    assert K.gemm_route(0, 0, [many * S], [Hq * dh], [D])[0] == PERSISTENT and D * Hq * dh > 65536
+    cfg = si.CONFIGS["tiny"].with_(batch=many, seq=S, d_model=D, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=F)
+    inp = si.make_layer_inputs(cfg, seed=11)
+    g = GpuLayer(K, cfg, inp)
+    g.forward()
+    g.backward()
+    for batch, tile in fewer:
+        assert K.gemm_route(0, 0, [batch * S], [Hq * dh], [D])[:2] == (tile, -1)
+        assert K.attention_backward_pieces(batch, S, Hq, Hkv, dh) == K.attention_backward_pieces(many, S, Hq, Hkv, dh)
+        one = GpuLayer(K, cfg.with_(batch=batch), {n: v[:batch] if n in ("x", "dy") else v for n, v in inp.items()})
+        one.forward()
+        one.backward()
+        rows = one.dx.reshape(-1, D).shape[0]
+        assert rows == batch * S
+        _same_bits(one.dx.reshape(-1, D), g.dx.reshape(-1, D)[:rows], f"{batch} batches")
+
+
 # batch, seq, width, query heads, KV heads, head width, d_ff; weights as stored; kernel of the gated gradient
 REBUILT = [
     ((1, 128, 192, 2, 1, 64, 320), True, T64),         # a wave per row of the norm
