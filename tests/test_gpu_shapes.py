@@ -379,25 +379,29 @@ STATISTICS_BITS = [(32, 16, 32, ((16, T64), (32, T128), (48, T128X256))), (16, 8
 
 @pytest.mark.parametrize("Hq,Hkv,dh,fewer", STATISTICS_BITS)
 def test_row_statistics_have_the_same_bits_in_the_epilogue_and_in_a_launch_of_their_own(K, Hq, Hkv, dh, fewer):
-    """A batch's input gradient depends on its own rows only, and every product has the same bits on every kernel: what is left between
-    128 batches, whose o projection's input gradient runs on the persistent kernel, and fewer of them, which take the
-    statistics from its epilogue, are the statistics."""
+    """Layers of 128 batches take them from a launch of their own (the o projection's input gradient runs on the persistent kernel), of
+    fewer from its epilogue.  Where dy is zero for the batches beyond those, everything else is the same bit for bit.  All
+    tokens of a sequence are the same, so that dP - rowsum(dO * O), and with it dq and dk, is nothing but the order of sums."""
     S, D, F, many = 128, 192, 192, 128
     assert K.gemm_route(0, 0, [many * S], [Hq * dh], [D])[0] == PERSISTENT and D * Hq * dh > 65536
     cfg = si.CONFIGS["tiny"].with_(batch=many, seq=S, d_model=D, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh, d_ff=F)
     inp = si.make_layer_inputs(cfg, seed=11)
-    g = GpuLayer(K, cfg, inp)
-    g.forward()
-    g.backward()
+    inp["x"] = np.repeat(inp["x"][:, :1], S, axis=1)
     for batch, tile in fewer:
         assert K.gemm_route(0, 0, [batch * S], [Hq * dh], [D])[:2] == (tile, -1)
         assert K.attention_backward_pieces(batch, S, Hq, Hkv, dh) == K.attention_backward_pieces(many, S, Hq, Hkv, dh)
-        one = GpuLayer(K, cfg.with_(batch=batch), {n: v[:batch] if n in ("x", "dy") else v for n, v in inp.items()})
-        one.forward()
-        one.backward()
-        rows = one.dx.reshape(-1, D).shape[0]
-        assert rows == batch * S
-        _same_bits(one.dx.reshape(-1, D), g.dx.reshape(-1, D)[:rows], f"{batch} batches")
+        dy = inp["dy"].copy()
+        dy[batch:] = 0
+        layers = [GpuLayer(K, cfg, dict(inp, dy=dy)), GpuLayer(K, cfg.with_(batch=batch), dict(inp, x=inp["x"][:batch], dy=dy[:batch]))]
+        for g in layers:
+            g.forward()
+            g.backward()
+        own, epilogue = layers
+        rows = batch * S
+        _same_bits(epilogue.dx.reshape(rows, D), own.dx.reshape(-1, D)[:rows], f"{batch} batches: dx")
+        for n in si.WEIGHT_NAMES:
+            if not n.startswith("g_"):   # the gains' partial sums go by the number of rows
+                _same_bits(epilogue.dw[n], own.dw[n], f"{batch} batches: d{n}")
 
 
 # batch, seq, width, query heads, KV heads, head width, d_ff; weights as stored; kernel of the gated gradient
