@@ -25,17 +25,17 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 # HBM bytes per launch of the dominant kernel (mean over the replayed launches of the seven projection
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
 # run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
-# counters were taken on: reported as null when gemm.hip or gemm_core.h has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "f877b52e273c1086edd54a1645713642dc571cad39a8c17c464ca22488f02cef",
-                "fetch_bytes": 1.496e+09, "write_bytes": 2.013e+08}
+# counters were taken on: reported as null when gemm.hip, gemm_core.h or gemm_schedule.h has changed since.
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "8c88089d30c4c8a1bdba47a7f0368bbf0b1cc248a81718bb4da336b3cf963131",
+                "fetch_bytes": 1.497e+09, "write_bytes": 2.013e+08}
 
 
 def _gemm_traffic(config_name):
     import hashlib
     src = os.path.join(ROOT, "paper_2602_08387_amd", "csrc")
     try:
-        both = b"".join(open(os.path.join(src, n), "rb").read() for n in ("gemm.hip", "gemm_core.h"))
-        same = hashlib.sha256(both).hexdigest() == GEMM_TRAFFIC["gemm_sha256"]
+        text = b"".join(open(os.path.join(src, n), "rb").read() for n in ("gemm.hip", "gemm_core.h", "gemm_schedule.h"))
+        same = hashlib.sha256(text).hexdigest() == GEMM_TRAFFIC["gemm_sha256"]
     except OSError:
         same = False
     if not same or config_name != GEMM_TRAFFIC["config"]:
@@ -164,10 +164,10 @@ def time_components(torch, K, si, cfg, x, w, reps):
          lambda: K.qkv_rope_forward(h, w["wq"], w["wk"], w["wv"], B, S, D, Hq, Hkv, dh, cfg.rope_base, cfg.rope_layout, q, k, v, ws_rope)),
         ("attention forward", "attn_fwd_kernel", attn, lambda: K.attention_forward(q, k, v, B, S, Hq, Hkv, dh, o, lse)),
         ("o projection + residual", "gemm_kernel<k,k>", 2.0 * T * QD * D, lambda: K.linear_forward(o, w["wo"], x, T, QD, D, y)),
-        ("gate/up projections + SwiGLU", "gemm_swiglu_kernel<1>", 4.0 * T * D * F,
+        ("gate/up projections + SwiGLU", "gemm_swiglu_kernel<1, false>", 4.0 * T * D * F,
          lambda: K.linear_swiglu_forward(h, w["w_gate"], w["w_up"], T, D, F, g, u, a)),
         ("down projection + residual", "gemm_kernel<k,k>", 2.0 * T * F * D, lambda: K.linear_forward(a, w["w_down"], x, T, F, D, y)),
-        ("down input gradient + SwiGLU gradient (+ W_down transpose)", "gemm_swiglu_kernel<2>", 2.0 * T * D * F,
+        ("down input gradient + SwiGLU gradient (+ W_down transpose)", "gemm_swiglu_kernel<2, false>", 2.0 * T * D * F,
          lambda: K.linear_swiglu_backward(x, w["w_down"], g, u, T, D, F, dg, du, ws_sw)),
         ("gate input gradient (+ W_gate transpose)", "gemm_kernel<k,k>", 2.0 * T * D * F,
          lambda: K.linear_backward(h, w["w_gate"], dg, T, D, F, dx, None, 0, ws_lin)),
@@ -464,7 +464,7 @@ def main():
     torch.cuda.synchronize()
     total_ms = sum(a.elapsed_time(b) for a, b in dur_ms)
     achieved = gemm_flops / (total_ms * 1e-3) / 1e12
-    roofline = {"bound": "mfma", "kernel": "gemm_kernel<true> (both operands k-major; the layer's 7 projection shapes)",
+    roofline = {"bound": "mfma", "kernel": "gemm_kernel<true, false> (both operands k-major; the layer's 7 projection shapes)",
                 "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                 "avg_launch_ms": total_ms / len(dur_ms), "launches_timed": len(dur_ms),
                 "traffic": _gemm_traffic(args.config), "traffic_unit": "HBM bytes per launch (fetched + written)",
