@@ -241,12 +241,14 @@ __device__ __forceinline__ void tile_epilogue(const GemmGroupKArgs& grp, const G
 }
 
 constexpr int LOADERS = 4;   // waves that load; two are slower (T 512, K = N = 2048 input gradient 9.1 -> 10.2 us)
-constexpr int tile_threads(int bm) { return ((bm == 64 ? 4 : 8) + LOADERS) * 64; }
+constexpr int FEW = 2;       // ring stages of the kernels for contractions of at most as many K-steps
+constexpr int tile_threads(int bm, int nst) { return ((bm == 64 ? 4 : 8) + (nst == FEW ? 0 : LOADERS)) * 64; }
 
-// NST: ring stages.  EPI as the persistent kernel's epilogues.
+// NST: ring stages.  FEW: nothing is left to load in the loop, so all K-steps go out at the start, by the waves that multiply, and are waited
+// for together.  EPI as the persistent kernel's epilogues.
 template <bool GROUPED, int BM, int BN, bool AK, bool BKM, int NST, int EPI>
 __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmKArgs& one, const DeltaEpilogue& da) {
-  constexpr int WM = 2, WN = BM == 64 ? 2 : 4, NW = WM * WN, NL = LOADERS, NT = tile_threads(BM);   // waves that multiply, waves that load
+  constexpr int WM = 2, WN = BM == 64 ? 2 : 4, NW = WM * WN, NL = NST == FEW ? NW : LOADERS, NT = tile_threads(BM, NST);   // waves that multiply, load
   constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
   constexpr int A_BYTES = BM * BK * 2, STAGE = A_BYTES + BN * BK * 2;
   constexpr bool PAIR = EPI == TILE_SWIGLU;
@@ -260,9 +262,9 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
   const int M = t.M, N = t.N, m0 = t.m0, n0 = t.n0, total = t.total;
   constexpr int LPW = TileLoader<BM, AK, NL>::PER_WAVE + TileLoader<BN, BKM, NL>::PER_WAVE;
   f32x4 acc[FN][FM];
-  if (wave >= NW) {
-    LoadCursor<BM, BN, NL, AK, BKM, PAIR> cur;
-    const int lwave = wave - NW;
+  LoadCursor<BM, BN, NL, AK, BKM, PAIR> cur;
+  const int lwave = NST == FEW ? wave : wave - NW;
+  auto first_loads = [&] {
     cur.nseg = GROUPED ? 1 : one.nseg;
     cur.left = total;
     int first = k_start(m0 + t.m_base, total);
@@ -280,6 +282,9 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
     }
 #pragma unroll
     for (int s = 0; s < NST; ++s) cur.issue_next(one, smem + s * STAGE, lwave, m0, n0, lane);
+  };
+  if (NST != FEW && wave >= NW) {
+    first_loads();
     if (total >= NST) wait_vmcnt<(NST - 1) * LPW>(); else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     uint32_t st = 0;
@@ -293,6 +298,7 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
       st = st + STAGE == NST * STAGE ? 0 : st + STAGE;
     }
   } else {
+    if constexpr (NST == FEW) first_loads();
     FragReader<BM, AK, FM> ra;
     FragReader<BN, BKM, FN> rb;
     ra.init(smem, wave_m * TM, lane);
@@ -304,6 +310,7 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
+    if constexpr (NST == FEW) wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     // Fragments run half a K-step ahead of the MFMAs.  The MFMAs of a k-substep go out in rows (one fragment of the side
@@ -342,7 +349,7 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
       wait_reads(fa[1], fb[1]);
       const uint32_t nx = st + STAGE == NST * STAGE ? 0 : st + STAGE;
       mfma_row(S1, S0);
-      if (k + 1 < total) {   // K-step k + 1 has landed, see above
+      if (NST != FEW && k + 1 < total) {   // K-step k + 1 has landed, see above
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
       }
@@ -358,7 +365,7 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
     }
   }
   tile_epilogue<BM, BN, NT, EPI>(grp, one, da, t, smem, [&](float* stg) {
-    if (wave >= NW) return;
+    if (NST != FEW && wave >= NW) return;
 #pragma unroll
     for (int i = 0; i < FN; ++i)
 #pragma unroll
@@ -368,16 +375,16 @@ __device__ __forceinline__ void gemm_tile(const GemmGroupKArgs& grp, const GemmK
 }
 
 template <int BM, int BN, bool AK, bool BKM, int NST, int EPI>
-__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_kernel(const GemmKArgs p) {
+__global__ __launch_bounds__(tile_threads(BM, NST)) void gemm_tile_kernel(const GemmKArgs p) {
   gemm_tile<false, BM, BN, AK, BKM, NST, EPI>(GemmGroupKArgs{}, p, DeltaEpilogue{});
 }
 template <int BM, int BN, bool AK, bool BKM, int NST, int EPI>
-__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_group_kernel(const GemmGroupKArgs g, const GainSums gains, int first_gain) {
+__global__ __launch_bounds__(tile_threads(BM, NST)) void gemm_tile_group_kernel(const GemmGroupKArgs g, const GainSums gains, int first_gain) {
   // Weight gradients of a layer: the gain sums of its norms ride behind the tiles (a launch of their own takes 2.5 to 5 us)
   if constexpr (EPI == TILE_PLAIN) {
     if ((int)blockIdx.x >= first_gain) {
       extern __shared__ __attribute__((aligned(1024))) char smem[];
-      gain_sums<tile_threads(BM)>(gains, (int)blockIdx.x - first_gain, reinterpret_cast<float*>(smem));
+      gain_sums<tile_threads(BM, NST)>(gains, (int)blockIdx.x - first_gain, reinterpret_cast<float*>(smem));
       return;
     }
   }
@@ -385,7 +392,7 @@ __global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_group_kernel(const
 }
 
 template <int BM, int BN, bool BKM, int NST>
-__global__ __launch_bounds__(tile_threads(BM)) void gemm_tile_delta_kernel(const GemmKArgs p, const DeltaEpilogue d) {
+__global__ __launch_bounds__(tile_threads(BM, NST)) void gemm_tile_delta_kernel(const GemmKArgs p, const DeltaEpilogue d) {
   gemm_tile<false, BM, BN, true, BKM, NST, TILE_DELTA>(GemmGroupKArgs{}, p, d);
 }
 
@@ -399,7 +406,7 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, co
     k.band_rows = 8;
     return k;
   };
-  const dim3 block(tile_threads(BM));
+  const dim3 block(tile_threads(BM, NST));
   static std::atomic<unsigned long long> lds_done{0};
   if constexpr (EPI == TILE_DELTA) {
     auto kern = gemm_tile_delta_kernel<BM, BN, BKM, NST>;
@@ -439,9 +446,25 @@ static int launch_tiles(const GemmKArgs* ks, int n, const RopeEpilogue* rope, co
 }
 
 // T128x256: 144 KB of LDS, T128: 96 KB, one workgroup of eight waves and four that load per CU; T64: 64 KB, two of four and four.
+// FEW: 133, 67 and 32 KB.
 template <bool AK, bool BKM, int EPI>
 static int launch_size(TileSize size, const GemmKArgs* ks, int n, const RopeEpilogue* rope, hipStream_t st, const DeltaEpilogue* delta = nullptr,
                        const GainSums* gains = nullptr) {
+  // One or two K-steps: four waves fewer to start, for which such a launch waits longer than for its loads.  us, with loading waves / without:
+  // T 1792, K 64, N 960 4.5 / 4.2; gated pair T 768, K 64, F 832 4.7 / 4.3; T 11520, K 128, N 512 8.2 / 7.8.  Over 162 products 1.026 (K 64)
+  // and 1.016 (K 128), with residual 1.015 and 1.014, gated pairs 1.035 and 1.025; three K-steps 0.998, four 0.97; the activation's
+  // gradient 0.97, head projections and weight gradients no faster.
+  if constexpr (AK && BKM && (EPI == TILE_PLAIN || EPI == TILE_SWIGLU)) {
+    int64_t k = 0;
+    for (int s = 0; s < ks[0].nseg; ++s) k += ks[0].K[s];
+    if (n == 1 && k <= FEW * BK) {
+      switch (size) {
+        case TileSize::T128x256: return launch_tiles<128, 256, FEW, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
+        case TileSize::T128: return launch_tiles<128, 128, FEW, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
+        case TileSize::T64: return launch_tiles<64, 64, FEW, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
+      }
+    }
+  }
   switch (size) {
     case TileSize::T128x256: return launch_tiles<128, 256, 3, AK, BKM, EPI>(ks, n, rope, delta, gains, st);
     case TileSize::T128: return launch_tiles<128, 128, 3, AK, BKM, EPI>(ks, n, rope, delta, gains, st);

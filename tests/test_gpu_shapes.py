@@ -172,6 +172,62 @@ def test_linear_forward_on_every_tile_size(K, shape, res, route):
             _same_bits(part(T, cols), y[:, :cols], f"{cols} columns")
 
 
+# rows, contraction, columns, gated pair, tile: one and two K-steps, all of them loaded at the start; ragged rows and columns
+FEW_STEPS = [
+    ((65, 128, 136), False, T64),
+    ((1600, 64, 1160), False, T64),
+    ((2000, 128, 1160), False, T128),
+    ((2000, 64, 1864), False, T128),
+    ((1088, 128, 6792), False, T128X256),
+    ((1000, 64, 7000), False, T128X256),
+    ((65, 128, 72), True, T64),
+    ((900, 64, 1800), True, T128),
+    ((600, 128, 3400), True, T128X256),
+]
+
+
+@pytest.mark.parametrize("shape,gated,tile", FEW_STEPS)
+def test_one_and_two_k_steps_on_small_tiles(K, shape, gated, tile):
+    """The same bits as the contraction with 128 zeros behind it, which runs with waves that only load (and within 2048 rows adds
+    the same terms in the same order)."""
+    T, Kd, N = shape
+    for k in (Kd, Kd + 128):
+        assert K.gemm_route(0, int(gated), [T], [N], [k], compute_units=256) == (tile, -1, T)
+    rng = np.random.default_rng(T)
+    xb, wb, vb, rb = _rand_bits(rng, (T, Kd)), _rand_bits(rng, (N, Kd), 0.1), _rand_bits(rng, (N, Kd), 0.1), _rand_bits(rng, (T, N))
+    x, w, v, r = map(si.bf16_bits_to_f32, (xb, wb, vb, rb))
+    xd, wd, vd, rd = map(dev_bf16, (xb, wb, vb, rb))
+
+    def run(res, pad):
+        a, b, c = (torch.nn.functional.pad(t, (0, pad)) for t in (xd, wd, vd))
+        out = [torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3 if gated else 1)]
+        if gated:
+            K.linear_swiglu_forward(a, b, c, T, Kd + pad, N, *out)
+        else:
+            K.linear_forward(a, b, rd if res else None, T, Kd + pad, N, *out)
+        return out
+
+    for res in (False,) if gated else (False, True):
+        got, padded = run(res, 0), run(res, 128)
+        g, u = x @ w.T, x @ v.T
+        for i, ref in enumerate((g, u, odl.swiglu_fwd(g, u)) if gated else (g + (r if res else 0.0),)):
+            assert _norm_err(got[i], ref) <= ONE_ROUNDING, i
+            _same_bits(got[i], padded[i], f"output {i}, residual {res}")
+
+
+def test_layer_with_two_segments_of_one_k_step(K):
+    """d_ff 64: the fused input gradient of gate and up is two segments of one K-step each."""
+    cfg = si.CONFIGS["tiny"].with_(batch=1, seq=640, d_model=2112, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ff=64)
+    assert K.gemm_route(0, 0, [640], [2112], [128], compute_units=256)[0] != PERSISTENT
+    inp = si.make_layer_inputs(cfg, seed=4)
+    f, r = _oracle(cfg, inp)
+    g = GpuLayer(K, cfg, inp)
+    g.forward()
+    g.backward()
+    torch.cuda.synchronize()
+    _check_layer(g, f, r, "two segments of one K-step")
+
+
 @pytest.mark.parametrize("shape,res", [((4096, 4096), False), ((4160, 4288), True), ((20520, 2056), True)])
 def test_linear_forward_over_one_k_step_on_full_tiles(K, shape, res):
     """K = 64 on the persistent kernel: one tile to a workgroup, two, and three with ragged rows and columns."""
