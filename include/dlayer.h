@@ -351,7 +351,7 @@ int issue_rate_probe(int family, int variant, int waves_per_simd, double* result
  * projections).
  *   operands  0 both stored along K (y = x W^T), 1 the second along N (dx = dy W, W as stored),
  *             2 both along M or N (dW = dy^T x)
- *   epilogue  0 none, residual or accumulation, 1 gated pair (N = columns of each half), 2 its gradient,
+ *   epilogue  0 none or residual, 5 weight gradients that accumulate, 1 gated pair (N = columns of each half), 2 its gradient,
  *             3 rotary embedding with split pairs, 4 with adjacent pairs (head_dim: else ignored)
  * route (3 ints): tile of the first launch (0 128x256, 1 128x128, 2 64x64, one tile per workgroup;
  * 3 256x256, persistent workgroups), tile of the second launch or -1, rows (of all n together) in the first.

@@ -696,10 +696,11 @@ int embed_backward(const void* dx0, const int64_t* ids, int64_t T, int64_t V, in
 
 int gemm_route(int32_t operands, int32_t epilogue, int32_t head_dim, int32_t compute_units, int32_t n, const int64_t* M,
                const int64_t* N, const int64_t* K, int32_t* route) {
-  REQUIRE(operands >= GEMM_ROUTE_K_K && operands <= GEMM_ROUTE_MN_MN && epilogue >= GEMM_ROUTE_PLAIN && epilogue <= GEMM_ROUTE_ROTARY_ADJACENT,
-          "gemm_route: operands 0..2, epilogue 0..4");
-  const bool rotary = epilogue >= GEMM_ROUTE_ROTARY_SPLIT;
-  REQUIRE(epilogue == GEMM_ROUTE_PLAIN || operands == GEMM_ROUTE_K_K || (epilogue == GEMM_ROUTE_GATED_GRADIENT && operands == GEMM_ROUTE_K_MN),
+  REQUIRE(operands >= GEMM_ROUTE_K_K && operands <= GEMM_ROUTE_MN_MN && epilogue >= GEMM_ROUTE_PLAIN && epilogue <= GEMM_ROUTE_ACCUMULATE,
+          "gemm_route: operands 0..2, epilogue 0..5");
+  const bool rotary = epilogue == GEMM_ROUTE_ROTARY_SPLIT || epilogue == GEMM_ROUTE_ROTARY_ADJACENT;
+  REQUIRE(epilogue == GEMM_ROUTE_ACCUMULATE ? operands == GEMM_ROUTE_MN_MN :
+          epilogue == GEMM_ROUTE_PLAIN || operands == GEMM_ROUTE_K_K || (epilogue == GEMM_ROUTE_GATED_GRADIENT && operands == GEMM_ROUTE_K_MN),
           "gemm_route: no product has this epilogue with these operands");
   REQUIRE(!rotary || head_dim == 32 || head_dim == 64 || head_dim == 128, "gemm_route: head_dim must be 32, 64 or 128");
   REQUIRE(n >= 1 && n <= 8 && (n == 1 || rotary || operands == GEMM_ROUTE_MN_MN), "gemm_route: 1 product, or up to 8 weight gradients or rotary projections");

@@ -810,6 +810,12 @@ static const KernelCost kCostMN[4] = {
     {64, 64, 2, 0.28, 0.39, 1.3, 1.3},     // as 4096 tiles: 17.2 us; as 144: 39 us
     {256, 256, 1, 1.20, 1.45, 8.0, 5.0}};  // as 9 tiles: 157 us
 static const KernelCost kCostOneStep = {256, 256, 1, 1.20, 1.45, 5.5, 4.5};   // a mn-major product of one K-step: the first as 256 tiles: 11.7 us
+// The persistent kernels' epilogue fetches the old value of a weight gradient 16 bytes at a time and waits for each, 5 to 6 us per tile
+// where the contraction is short; the one-tile kernels ask for all of it at once.  Without this constant accumulation over few tokens ran
+// on full tiles; us, 128 x 256 tiles / full ones: 64 tokens, 4160 x 5120 20.3 / 27.7; 128, 1344 x 9216 14.6 / 17.5; 192, 3584 x 10304
+// 40.6 / 46.6; 256, 4160 x 13568 59.8 / 66.0; 512, 5440 x 1792 21.1 (128 x 128) / 23.8.  Not above 512 tokens, where the constants overrate the
+// full tile by as much (1024, 2560 x 6400 and the like 0 to 8 % slower with it).
+constexpr double kOldValueUs = 4.0;
 constexpr double kLaunchUs = 3.5;
 
 static double kernel_us(const KernelCost& c, int cus, const GemmKArgs* ks, int n) {
@@ -849,9 +855,14 @@ struct GemmPlan {
 
 static void plan_gemm(GemmPlan& p, const GemmKArgs* ks, int n, bool ak, bool bk, TileEpilogue epi, const RopeEpilogue* rope, int cus) {
   const KernelCost* cost = ak && bk ? kCostKK : kCostMN;
-  bool one_step = !ak && !bk;
-  for (int i = 0; i < n; ++i) one_step = one_step && k_total(ks[i]) == BK;
-  const KernelCost& full_tile = one_step ? kCostOneStep : cost[kPersistent];
+  int64_t longest = 0;
+  for (int i = 0; i < n; ++i) longest = k_total(ks[i]) > longest ? k_total(ks[i]) : longest;
+  const bool one_step = !ak && !bk && longest == BK;
+  KernelCost full_tile = one_step ? kCostOneStep : cost[kPersistent];
+  if (!ak && !bk && ks[0].accumulate && longest <= 512) {
+    full_tile.tile += kOldValueUs;
+    full_tile.again += kOldValueUs;
+  }
   // a 64-column tile does not hold both members of a split pair of a 128-wide head; the persistent kernels are not built
   // for one k-major and one mn-major operand
   const bool no64 = rope && rope->layout == 0 && rope->head_dim == 128, persistent = ak == bk;
@@ -927,6 +938,7 @@ void query_gemm_route(int operands, int epilogue, int head_dim, int cus, int n, 
     ks[i].M = (int)M[i];
     ks[i].N = (int)(epilogue == GEMM_ROUTE_GATED_PAIR ? 2 * N[i] : N[i]);
     ks[i].K[0] = (int)K[i];
+    ks[i].accumulate = epilogue == GEMM_ROUTE_ACCUMULATE;
   }
   RopeEpilogue rope{};
   rope.head_dim = head_dim;

@@ -104,7 +104,8 @@ int launch_gemm_swiglu_grad(const void* dy, int64_t lddy, const void* w, bool w_
 
 // Which kernels a product, or a group, of these sizes runs on: see gemm_route in dlayer.h.  Nothing is launched.
 enum { GEMM_ROUTE_K_K = 0, GEMM_ROUTE_K_MN = 1, GEMM_ROUTE_MN_MN = 2 };
-enum { GEMM_ROUTE_PLAIN = 0, GEMM_ROUTE_GATED_PAIR = 1, GEMM_ROUTE_GATED_GRADIENT = 2, GEMM_ROUTE_ROTARY_SPLIT = 3, GEMM_ROUTE_ROTARY_ADJACENT = 4 };
+enum { GEMM_ROUTE_PLAIN = 0, GEMM_ROUTE_GATED_PAIR = 1, GEMM_ROUTE_GATED_GRADIENT = 2, GEMM_ROUTE_ROTARY_SPLIT = 3, GEMM_ROUTE_ROTARY_ADJACENT = 4,
+       GEMM_ROUTE_ACCUMULATE = 5 };
 void query_gemm_route(int operands, int epilogue, int head_dim, int cus, int n, const int64_t* M, const int64_t* N, const int64_t* K,
                       int32_t* route);
 

@@ -287,9 +287,10 @@ ONE_STEP_GRADIENTS = [
 @pytest.mark.parametrize("accumulate", [0, 1])
 @pytest.mark.parametrize("shapes", ONE_STEP_GRADIENTS)
 def test_weight_gradients_over_one_k_step_on_full_tiles(K, shapes, accumulate):
-    """64 tokens on the persistent kernels."""
+    """64 tokens on the persistent kernels, and, accumulating, on the tiles that those take."""
     Ns, Ks = [n for n, _ in shapes], [k for _, k in shapes]
-    assert K.gemm_route(2, 0, Ns, Ks, [64] * len(shapes))[:2] == (PERSISTENT, -1)
+    first, second, _ = K.gemm_route(2, 5 if accumulate else 0, Ns, Ks, [64] * len(shapes))
+    assert (first != PERSISTENT if accumulate else first == PERSISTENT) and second == -1
     rng = np.random.default_rng(len(shapes))
     dyb, xb, wb = ([_rand_bits(rng, s) for s in sizes] for sizes in ([(64, n) for n in Ns], [(64, k) for k in Ks], shapes))
     dyd, xd, dws = ([dev_bf16(b) for b in bits] for bits in (dyb, xb, wb))
@@ -303,6 +304,32 @@ def test_weight_gradients_over_one_k_step_on_full_tiles(K, shapes, accumulate):
             part = first[i][:, c0:c0 + 64].contiguous()
             K.linear_backward(xd[i][:, c0:c0 + 64].contiguous(), xd[i], dyd[i], 64, 64, n, None, part, accumulate, None)
             _same_bits(part, dws[i][:, c0:c0 + 64], f"dw[{i}], columns from {c0}")
+
+
+# tokens, products that accumulate, route: either side of the line at 512 tokens
+OLD_VALUES = [
+    (512, [(5440, 1792), (448, 192)], (T128, -1)),
+    (576, [(5440, 1792), (448, 192)], (PERSISTENT, -1)),
+    (576, [(4160, 4288), (448, 192)], (PERSISTENT, T64)),
+]
+
+
+@pytest.mark.parametrize("T,shapes,route", OLD_VALUES)
+def test_weight_gradients_that_accumulate(K, T, shapes, route):
+    """One rounding of product and old value, and the same bits whatever kernel."""
+    Ns, Ks = [n for n, _ in shapes], [k for _, k in shapes]
+    assert K.gemm_route(2, 5, Ns, Ks, [T] * len(shapes))[:2] == route
+    rng = np.random.default_rng(T)
+    dyb, xb, wb = ([_rand_bits(rng, s) for s in sizes] for sizes in ([(T, n) for n in Ns], [(T, k) for k in Ks], shapes))
+    dyd, xd, dws = ([dev_bf16(b) for b in bits] for bits in (dyb, xb, wb))
+    first = [w.clone() for w in dws]
+    K.linear_wgrad_group(dyd, xd, Ns, Ks, T, dws, 1)
+    for i, (n, k) in enumerate(shapes):
+        dy, x, w = (si.bf16_bits_to_f32(b[i]) for b in (dyb, xb, wb))
+        assert _norm_err(dws[i], dy.T @ x + w) <= ONE_ROUNDING, i
+        part = first[i][:, k - 64:].contiguous()
+        K.linear_backward(xd[i][:, k - 64:].contiguous(), xd[i], dyd[i], T, 64, n, None, part, 1, None)
+        _same_bits(part, dws[i][:, k - 64:], f"last columns of dw[{i}]")
 
 
 GATED_PAIRS = [

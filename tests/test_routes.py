@@ -37,6 +37,14 @@ def test_full_tiles_over_few_tokens(K):
     assert K.gemm_route(2, 0, [2048], [4096], [64], compute_units=256)[0] != PERSISTENT
 
 
+@pytest.mark.parametrize("T,N,Kd", [(64, 4160, 5120), (128, 1344, 9216), (192, 3584, 10304), (256, 4160, 13568), (512, 5440, 1792)])
+def test_weight_gradients_over_few_tokens_that_accumulate(K, T, N, Kd):
+    """The full tile waits for each part of the old value: another tile, though without accumulation the full one is faster."""
+    assert K.gemm_route(2, 0, [N], [Kd], [T], compute_units=256)[0] == PERSISTENT
+    assert K.gemm_route(2, 5, [N], [Kd], [T], compute_units=256)[0] != PERSISTENT
+    assert K.gemm_route(2, 5, [N], [Kd], [2048], compute_units=256) == K.gemm_route(2, 0, [N], [Kd], [2048], compute_units=256)
+
+
 def test_key_blocks_are_split_for_the_compute_units_there_are(K):
     shape = (2, 2944, 16, 4, 64)
     assert K.attention_backward_pieces(*shape, compute_units=256) > 1
@@ -45,7 +53,7 @@ def test_key_blocks_are_split_for_the_compute_units_there_are(K):
 
 
 def test_route_query_rejects_what_no_call_runs(K):
-    for bad in ((3, 0, [64], [64], [64]), (0, 5, [64], [64], [64]), (2, 1, [64], [64], [64]), (1, 3, [64], [64], [64]),
+    for bad in ((3, 0, [64], [64], [64]), (0, 5, [64], [64], [64]), (1, 5, [64], [64], [64]), (2, 6, [64], [64], [64]), (2, 1, [64], [64], [64]), (1, 3, [64], [64], [64]),
                 (0, 3, [64], [64], [64]), (0, 0, [64, 64], [64, 64], [64, 64]), (0, 0, [0], [64], [64]), (0, 0, [64], [64], [65])):
         with pytest.raises(K.DLayerError):
             K.gemm_route(*bad)
@@ -59,6 +67,9 @@ def test_the_shapes_of_the_gpu_tests_reach_the_paths_they_name(K):
     for T, products, route in shapes.WEIGHT_GRADIENTS:
         assert K.gemm_route(2, 0, [n for n, _ in products], [k for _, k in products], [T] * len(products),
                             compute_units=256)[:2] == route, ("weight gradients", T, products)
+    for T, products, route in shapes.OLD_VALUES:
+        assert K.gemm_route(2, 5, [n for n, _ in products], [k for _, k in products], [T] * len(products),
+                            compute_units=256)[:2] == route, ("accumulation", T, products)
     for (T, Kd, F), route in shapes.GATED_PAIRS:
         assert K.gemm_route(0, 1, [T], [F], [Kd], compute_units=256)[:2] == route, ("gated pair", T, Kd, F)
     for (T, D, F), stored, route in shapes.ACTIVATION_GRADIENTS:
