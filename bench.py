@@ -24,9 +24,10 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/
 
 # HBM bytes per launch of the dominant kernel (mean over the replayed launches of the seven projection
 # shapes of the 8B-shaped layer), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain 1 GiB copy in the same
-# run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the GEMM source the
-# counters were taken on: reported as null when gemm.hip, gemm_core.h or gemm_schedule.h has changed since.
-GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "8c88089d30c4c8a1bdba47a7f0368bbf0b1cc248a81718bb4da336b3cf963131",
+# run (factors 2.0 and 1.0; profiles/layer_8b_hbm_traffic.txt).  Only valid for the kernels and launches the
+# counters were taken on: reported as null when gemm_core.h, gemm_schedule.h or what stands in gemm.hip before the choice between
+# kernels has changed since.
+GEMM_TRAFFIC = {"config": "8b", "gemm_sha256": "cc40ec4753a4a6326bd3d7fa336342a20942d671f9c39351b8d59ca0d7548c4f",
                 "fetch_bytes": 1.497e+09, "write_bytes": 2.013e+08}
 
 
@@ -34,7 +35,8 @@ def _gemm_traffic(config_name):
     import hashlib
     src = os.path.join(ROOT, "paper_2602_08387_amd", "csrc")
     try:
-        text = b"".join(open(os.path.join(src, n), "rb").read() for n in ("gemm.hip", "gemm_core.h", "gemm_schedule.h"))
+        text = b"".join(open(os.path.join(src, n), "rb").read().split(b"// Which kernel a product runs on.")[0]
+                        for n in ("gemm.hip", "gemm_core.h", "gemm_schedule.h"))
         same = hashlib.sha256(text).hexdigest() == GEMM_TRAFFIC["gemm_sha256"]
     except OSError:
         same = False
